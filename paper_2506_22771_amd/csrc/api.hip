@@ -18,7 +18,7 @@ struct Dims {
     int kind;
     int64_t B, M, K, N, rps;   // M rows per pass (dense: B; conv: B*Ho*Wo), rps rows per sample
     int64_t in_rows, in_cols;  // 2-D view of the layer input: dense [B, K]; conv [B*H*W, C_in]
-    bool implicit;             // conv whose forward runs as an implicit GEMM (C_in % 16 == 0)
+    bool implicit;             // conv whose forward runs as an implicit GEMM (C_in % 4 == 0, more than a handful of channels)
     bool pointwise;            // 1x1 stride-1 convolution: its transposed patch matrix is the transposed input itself
     ConvGeom g;                // conv only
     int n_chunks;              // weight-gradient accumulators per pass
@@ -70,7 +70,7 @@ static ff_status layer_dims(const ff_layer_desc* L, Dims* d)
         d->N = L->C_out;
         d->in_rows = d->B * L->H * L->W;
         d->in_cols = L->C_in;
-        d->implicit = L->kind == FF_CONV2D && (L->C_in & 15) == 0;
+        d->implicit = L->kind == FF_CONV2D && (L->C_in & 3) == 0 && L->C_in > 4;
         d->pointwise = L->kind == FF_CONV2D && L->ksize == 1 && L->stride == 1;
         if (d->in_rows * g.cpitch >= (int64_t(1) << 31) || d->M >= (int64_t(1) << 31)) return FF_ERR_UNSUPPORTED;
     } else {
@@ -116,18 +116,42 @@ static int32_t goodness_shift(int64_t K, int64_t terms)
 // Scratch one layer needs per pass beyond FF_WS_MIN_BYTES.
 // `col`: the row-major patch matrix of an explicit-im2col forward or the transposed patch matrix of one
 // weight-gradient chunk (conv only).  `part`: partial accumulators of a split weight-gradient reduction.
-// have_aqt: the caller keeps a transposed copy of a pointwise layer's input, which serves as its patch matrix.
-static size_t layer_col_bytes(const Dims& d, bool have_aqt = false)
+// These sizes are what the entry points ask their callers for (ff_layer_workspace_bytes); they cover every route below.
+static size_t layer_col_bytes(const Dims& d)
 {
     if (d.kind != FF_CONV2D) return 0;   // dense and depthwise layers need no patch matrix
-    const size_t fwd = d.implicit || d.pointwise ? 0 : (size_t)(d.M * pitch8(d.K));
-    const size_t bwd = have_aqt && d.pointwise ? 0 : (size_t)(d.K * pitch8(d.chunk_b * d.rps));
+    const size_t fwd = (d.g.Cin & 15) == 0 || d.pointwise ? 0 : (size_t)(d.M * pitch8(d.K));
+    const size_t bwd = (size_t)(d.K * pitch8(d.chunk_b * d.rps));
     return align_up(fwd > bwd ? fwd : bwd, 256);
 }
 static size_t layer_part_bytes(const Dims& d, int nb)
 {
     if (d.kind == FF_DWCONV2D) return 0;
     const GemmPlan p = gemm_plan(d.N, d.K, min(d.M, d.chunk_b * d.rps), nb, true);
+    if (p.splits <= 1) return 0;
+    return align_up((size_t)p.splits * (size_t)(d.N * pitch32(d.K)) * sizeof(int32_t), 256);
+}
+// Convolutions whose forward pass materialises the row-major patch matrix (1x1 stride-1 ones never do).
+static bool explicit_patches(const Dims& d) { return d.kind == FF_CONV2D && !d.implicit && !d.pointwise; }
+// ... and whose weight gradient reads it again, reduction-major: up to four channels, where the NHWC input is mostly pad
+// channels (9 * 16 columns for 27).  Other layers' weight gradients read the NHWC input itself.  (The contraction
+// addresses the operand of one weight-gradient chunk with 32-bit offsets; layer_dims keeps the NHWC input below 2^31 bytes.)
+static bool wgrad_from_patches(const Dims& d)
+{
+    return explicit_patches(d) && d.g.Cin <= 4 && min(d.M, d.chunk_b * d.rps) * pitch8(d.K) < (int64_t(1) << 31);
+}
+// Columns of the weight-gradient contraction: operands read reduction-major are worked on in whole 16-byte chunks
+// (GemmArgs::conv == 2).
+static int64_t wgrad_cols(const Dims& d, bool have_aqt)
+{
+    if (d.kind != FF_CONV2D || (have_aqt && d.pointwise)) return d.K;
+    if (wgrad_from_patches(d)) return (d.K + 15) & ~int64_t(15);
+    return (int64_t)d.g.ks * d.g.ks * ((d.g.Cin + 15) & ~15);
+}
+static size_t wgrad_part_bytes(const Dims& d, int nb, bool have_aqt)
+{
+    if (d.kind == FF_DWCONV2D) return 0;
+    const GemmPlan p = gemm_plan(d.N, wgrad_cols(d, have_aqt), min(d.M, d.chunk_b * d.rps), nb, true);
     if (p.splits <= 1) return 0;
     return align_up((size_t)p.splits * (size_t)(d.N * pitch32(d.K)) * sizeof(int32_t), 256);
 }
@@ -147,7 +171,7 @@ struct WsLayout {
     size_t zero_bytes;     // the region [0, zero_bytes) is cleared at the start of a step
     size_t off_scales;     // fp32: s_a[k][2], s_g[k][2]
     // Scratch of one layer's update chain (local gradient -> weight gradient -> update -> requantise), `lanes` copies
-    // `lane_stride` bytes apart: off_wbmax, off_gy, off_dw, off_col and off_part below are those of lane 0.  The chains
+    // `lane_stride` bytes apart: off_wbmax, off_gy, off_dw and off_part below are those of lane 0.  The chains
     // of different layers are independent of each other (layer-local learning), so a step may run them on several
     // streams at once, each with a scratch of its own.
     int lanes;
@@ -156,7 +180,7 @@ struct WsLayout {
     size_t off_c, off_ct;  // fp32 [k][2][B]
     size_t off_gy, st_gy;  // int8 scratch [2][st_gy]: transposed quantised local gradient
     size_t off_dw, st_dw, dw_bytes;  // int32 scratch [2][MAX_CHUNKS][dw_bytes]; st_dw = pass stride (bytes)
-    size_t off_col, st_col;          // int8 scratch [2][st_col]: patch matrices of conv layers
+    size_t off_col[MAX_LAYERS], st_col[MAX_LAYERS];   // explicit patch matrices [2][st] (see explicit_patches), retained
     size_t off_part, st_part;        // int32 scratch [2][st_part] (bytes): partial sums of split weight gradients
     size_t off_aq[MAX_LAYERS], st_aq[MAX_LAYERS];    // quantised layer input [2][st]: dense layers share one scratch
     size_t off_aqt[MAX_LAYERS], st_aqt[MAX_LAYERS];  // dense and 1x1 stride-1 conv: transposed quantised input [2][st], retained
@@ -258,14 +282,13 @@ static ff_status make_layout(const ff_net_desc* net, WsLayout* w)
     off = align_up(off + sizeof(float) * k * 2 * B, A);
     w->off_ct = off;
     off = align_up(off + sizeof(float) * k * 2 * B, A);
-    size_t aq_dense = 0, gy = 0, dw = 0, col = 0, part = 0;
+    size_t aq_dense = 0, gy = 0, dw = 0, part = 0;
     for (int i = 0; i < w->k; ++i) {
         const Dims& d = w->d[i];
         if (d.kind == FF_DENSE) aq_dense = max(aq_dense, (size_t)(d.in_rows * pitch8(d.in_cols)));
         gy = max(gy, d.kind == FF_DWCONV2D ? (size_t)(d.M * pitch8(d.N)) : (size_t)(d.N * pitch8(d.M)));
         dw = max(dw, (size_t)(d.N * pitch32(d.K)) * sizeof(int32_t));
-        col = max(col, layer_col_bytes(d, true));
-        part = max(part, layer_part_bytes(d, 2));
+        part = max(part, wgrad_part_bytes(d, 2, true));
     }
     aq_dense = align_up(aq_dense, A);
     const size_t off_aq_dense = off;
@@ -323,9 +346,6 @@ static ff_status make_layout(const ff_net_desc* net, WsLayout* w)
     w->st_dw = MAX_CHUNKS * w->dw_bytes;
     w->off_dw = off;
     off += 2 * w->st_dw;
-    w->st_col = col;
-    w->off_col = off;
-    off += 2 * w->st_col;
     w->st_part = part;
     w->off_part = off;
     off += 2 * w->st_part;
@@ -347,6 +367,9 @@ static ff_status make_layout(const ff_net_desc* net, WsLayout* w)
             w->off_aqt[i] = d.pointwise ? off : 0;
             off += 2 * w->st_aqt[i];
         }
+        w->st_col[i] = explicit_patches(d) ? align_up((size_t)(d.M * pitch8(d.K)), A) : 0;
+        w->off_col[i] = off;
+        off += 2 * w->st_col[i];
         w->st_acc[i] = align_up((size_t)(d.M * pitch32(d.N)) * sizeof(int32_t), A);
         w->off_acc[i] = off;
         off += 2 * w->st_acc[i];
@@ -444,6 +467,22 @@ struct Timed {
     }
 };
 
+static Im2colArgs im2col_args(const Dims& d, const int8_t* aq, int64_t st_aq, int8_t* col, int64_t st_col, int nb)
+{
+    Im2colArgs ic;
+    memset(&ic, 0, sizeof(ic));
+    ic.a = aq;
+    ic.st_a = st_aq;
+    ic.out = col;
+    ic.st_out = st_col;
+    ic.g = d.g;
+    ic.K = (int32_t)d.K;
+    ic.B = (int32_t)d.B;
+    ic.ld_out = pitch8(d.K);
+    ic.nb = nb;
+    return ic;
+}
+
 // ---- the two contractions of a layer, for nb passes at once ------------------------------------------
 // Forward: acc[z] = A_q[z] x W_q^T (+ per-sample sums).  `aq` is the quantised layer input (dense: [M, pitch(K)];
 // conv: NHWC), `col` scratch for an explicit patch matrix (3x3 or strided conv with C_in % 16 != 0).
@@ -500,23 +539,12 @@ static ff_status run_forward(const Dims& d, int relu, const int8_t* aq, int64_t 
         g.st_p = st_aq;
         g.ldp = 16;  // unused by the implicit loader
         g.conv = 1;
-        g.H = d.g.H; g.W = d.g.W; g.Cin = d.g.Cin; g.cpitch = d.g.cpitch; g.ks = d.g.ks;
+        g.R = d.g.ks * d.g.ks * ((d.g.Cin + 15) & ~15);
+        g.H = d.g.H; g.W = d.g.W; g.Cin = (d.g.Cin + 15) & ~15; g.cin_out = d.g.Cin; g.cpitch = d.g.cpitch; g.ks = d.g.ks;
         g.stride = d.g.stride; g.pad = d.g.pad; g.Ho = d.g.Ho; g.Wo = d.g.Wo;
         g.p_bytes = d.in_rows * d.g.cpitch;
     } else {
-        Im2colArgs ic;
-        memset(&ic, 0, sizeof(ic));
-        ic.a = aq;
-        ic.st_a = st_aq;
-        ic.out = col;
-        ic.st_out = st_col;
-        ic.g = d.g;
-        ic.K = (int32_t)d.K;
-        ic.b0 = 0;
-        ic.b1 = (int32_t)d.B;
-        ic.ld_out = pitch8(d.K);
-        ic.nb = nb;
-        HIPCHK_T(FF_K_IM2COL, launch_im2col(ic, false, s));
+        HIPCHK_T(FF_K_IM2COL, launch_im2col(im2col_args(d, aq, st_aq, col, st_col, nb), s));
         g.P = col;
         g.st_p = st_col;
         g.ldp = pitch8(d.K);
@@ -526,21 +554,14 @@ static ff_status run_forward(const Dims& d, int relu, const int8_t* aq, int64_t 
     return FF_OK;
 }
 
-// Convolutions whose weight gradient reads column-shifted planes of the input instead of the full transposed
-// patch matrix (see GemmArgs::conv == 2).
-static bool wgrad_uses_planes(const Dims& d, int64_t nbatch, int nb)
-{
-    if (d.kind != FF_CONV2D || d.g.ks != 3 || (d.g.Wo & 15) != 0) return false;
-    const int64_t bytes = (int64_t)d.g.ks * d.g.Cin * pitch8(nbatch * d.g.H * d.g.Wo);
-    return bytes < (int64_t(1) << 31) && im2col_planes_ok(d.g, nbatch * nb);
-}
-
 // Weight gradient: dw[z][c] = gy_q_t[z][:, chunk c] x (patches of chunk c)^T for every chunk c.
 // `aqt` is the transposed quantised input (dense; also a 1x1 stride-1 convolution when aqt_transposed is set) or the
-// NHWC quantised input (conv; patches are materialised chunk by chunk into `colT`).  dw accumulators of one pass are dw_elems apart.
+// NHWC quantised input (conv), which the contraction reads reduction-major as it is -- or the row-major patch matrix
+// [M, pitch(K)] (wgrad_from_patches).  dw accumulators of one pass are
+// dw_elems apart.  `part`: st_part elements per pass for the partial sums of a split reduction.
 static ff_status run_wgrad(const Dims& d, const int8_t* gy_t, int64_t st_gy, const int8_t* aqt, int64_t st_aqt,
-                           int8_t* colT, int64_t st_colT, int32_t* part, int64_t st_part, int32_t* dw, int64_t st_dw,
-                           int64_t dw_elems, int nb, hipStream_t s, bool aqt_transposed = false)
+                           int32_t* part, int64_t st_part, int32_t* dw, int64_t st_dw, int64_t dw_elems, int nb,
+                           hipStream_t s, bool aqt_transposed = false)
 {
     // depthwise accumulators are added to with atomics and must start at zero: one fill over all passes and chunks when
     // that span is small (it usually is: C x 12 words per accumulator), else one per accumulator
@@ -589,39 +610,29 @@ static ff_status run_wgrad(const Dims& d, const int8_t* gy_t, int64_t st_gy, con
             g.st_q = st_aqt;
             g.ldq = pitch8(d.M);
         } else {
-            Im2colArgs ic;
-            memset(&ic, 0, sizeof(ic));
-            ic.a = aqt;
-            ic.st_a = st_aqt;
-            ic.out = colT;
-            ic.st_out = st_colT;
-            ic.g = d.g;
-            ic.b0 = (int32_t)b0;
-            ic.b1 = (int32_t)b1;
-            ic.nb = nb;
-            g.Q = colT;
-            g.st_q = st_colT;
-            if (wgrad_uses_planes(d, b1 - b0, nb)) {
-                // 3x3 convolution on rows of whole 16-pixel chunks: only the three column-shifted planes of the input
-                // are written (a third of the patch matrix); the contraction applies the row offsets itself
-                const int64_t ld3 = pitch8((b1 - b0) * d.g.H * d.g.Wo);
-                ic.K = (int32_t)(d.g.ks * d.g.Cin);
-                ic.ld_out = ld3;
-                ic.wtaps_only = 1;
-                HIPCHK_T(FF_K_IM2COL, launch_im2col(ic, true, s));
-                g.ldq = ld3;
-                g.conv = 2;
-                g.H = d.g.H; g.W = d.g.W; g.Cin = d.g.Cin; g.cpitch = d.g.cpitch; g.ks = d.g.ks;
-                g.stride = d.g.stride; g.pad = d.g.pad; g.Ho = d.g.Ho; g.Wo = d.g.Wo;
-                g.p_bytes = (int64_t)ic.K * ld3;
-            } else {
-                ic.K = (int32_t)d.K;
-                ic.ld_out = pitch8(mc);
-                HIPCHK_T(FF_K_IM2COL, launch_im2col(ic, true, s));
-                g.ldq = pitch8(mc);
+            // the operand as it lies in memory, read reduction-major: the NHWC input, or the patch matrix, which is the
+            // NHWC input of a 1x1 convolution with K channels
+            ConvGeom q = d.g;
+            if (wgrad_from_patches(d)) {
+                q.H = q.Ho;
+                q.W = q.Wo;
+                q.Cin = (int32_t)d.K;
+                q.cpitch = (int32_t)pitch8(d.K);
+                q.ks = q.stride = 1;
+                q.pad = 0;
             }
+            g.Q = aqt + b0 * q.H * q.W * q.cpitch;
+            g.st_q = st_aqt;
+            g.ldq = 16;   // unused by this loader
+            g.conv = 2;
+            g.J = (int32_t)wgrad_cols(d, false);
+            g.H = q.H; g.W = q.W; g.Cin = (q.Cin + 15) & ~15; g.cin_out = q.Cin; g.cpitch = q.cpitch; g.ks = q.ks;
+            g.stride = q.stride; g.pad = q.pad; g.Ho = q.Ho; g.Wo = q.Wo;
+            g.p_bytes = (b1 - b0) * q.H * q.W * q.cpitch;
         }
         g.splits = gemm_plan(g.I, g.J, g.R, nb, true).splits;
+        const int64_t fit = st_part / (d.N * pitch32(d.K));   // partial results the scratch holds
+        if (g.splits > fit) g.splits = split_evenly(g.R, fit < 1 ? 1 : fit);
         g.clk = g_clock_probe;
         if (g.splits > 1) {
             int32_t* out = g.C;
@@ -740,7 +751,7 @@ ff_status ff_layer_forward(const ff_layer_desc* layer, const int8_t* a_q, const 
     if (!aligned16(a_q) || !aligned16(w_q) || !aligned16(acc) || (((uintptr_t)gsum_int) & 7) || !aligned4(vmax))
         return FF_ERR_ALIGN;
     if (d.K > INT32_SAFE_LEN) return FF_ERR_OVERFLOW_BOUND;
-    const bool need_col = d.kind == FF_CONV2D && !d.implicit;
+    const bool need_col = d.kind == FF_CONV2D && (d.g.Cin & 15) != 0;   // the layers that are asked for scratch
     if (need_col) {
         if (!ws) return FF_ERR_INVALID_ARG;
         if (!aligned16(ws)) return FF_ERR_ALIGN;
@@ -894,8 +905,18 @@ ff_status ff_layer_backward_local(const ff_layer_desc* layer, const int32_t* acc
     a.nb = 1;
     HIPCHK_T(FF_K_QUANT_GRAD, launch_quantize(QSRC_GRAD, a, s));
     const int64_t dw_elems = d.N * pitch32(d.K);
-    int8_t* colT = (int8_t*)ws + FF_WS_MIN_BYTES;
-    return run_wgrad(d, gy_q_t, 0, a_q_t, 0, colT, 0, (int32_t*)(colT + layer_col_bytes(d)), 0, dw_acc, 0, dw_elems, 1, s);
+    // scratch: [row-major patch matrix (wgrad_from_patches) | partial sums of a split reduction]
+    char* scratch = (char*)ws + FF_WS_MIN_BYTES;
+    size_t room = layer_scratch_bytes(d);
+    const int8_t* operand = a_q_t;
+    if (wgrad_from_patches(d)) {
+        Im2colArgs ic = im2col_args(d, a_q_t, 0, (int8_t*)scratch, 0, 1);
+        HIPCHK_T(FF_K_IM2COL, launch_im2col(ic, s));
+        operand = (const int8_t*)scratch;
+        scratch += layer_col_bytes(d);
+        room -= layer_col_bytes(d);
+    }
+    return run_wgrad(d, gy_q_t, 0, operand, 0, (int32_t*)scratch, (int64_t)(room / sizeof(int32_t)), dw_acc, 0, dw_elems, 1, s);
 }
 
 // ---- the entry point that allocates nothing: its scratch is a fixed array in the library's own device image ----
@@ -1298,7 +1319,7 @@ static ff_status train_step_impl(const ff_net_desc* net, const ff_net_state* sta
             return run_forward(d, L.relu ? 1 : 0, (const int8_t*)(base + w.off_aq[i]), (int64_t)w.st_aq[i], state->w_q[i],
                                (int32_t*)(base + w.off_acc[i]), (int64_t)(w.st_acc[i] / sizeof(int32_t)),
                                plain ? gsum + (int64_t)i * 2 * B : nullptr, vmax + (int64_t)i * 2 * B, B,
-                               (int8_t*)(base + w.off_col), (int64_t)w.st_col, 2, s);
+                               (int8_t*)(base + w.off_col[i]), (int64_t)w.st_col[i], 2, s);
         }();
         if (side) {   // (whatever happened on the second stream, it is joined back)
             if (hipEventRecord(pool->join[0], s) != hipSuccess) fs = fs != FF_OK ? fs : FF_ERR_HIP;
@@ -1460,14 +1481,15 @@ static ff_status train_step_impl(const ff_net_desc* net, const ff_net_state* sta
         const Dims& d = w.d[t];
         const int lane = lane_of[gl];
         hipStream_t s = lane_stream[lane];                        // (shadows the caller's stream inside the chain)
-        char* base = (char*)ws + (size_t)lane * w.lane_stride;   // lane-scoped scratch: gy, dw, col, part, wbmax
+        char* base = (char*)ws + (size_t)lane * w.lane_stride;   // lane-scoped scratch: gy, dw, part, wbmax
         char* const base0 = (char*)ws;                            // what lives outside the lanes
         const bool dense = d.kind == FF_DENSE || d.pointwise;   // layers that keep a transposed copy of their input
         const int64_t dw_elems = (int64_t)(w.dw_bytes / sizeof(int32_t));
+        const bool patches = wgrad_from_patches(d);
+        const size_t off_q = dense ? w.off_aqt[t] : (patches ? w.off_col[t] : w.off_aq[t]);
+        const size_t st_q = dense ? w.st_aqt[t] : (patches ? w.st_col[t] : w.st_aq[t]);
         const ff_status ws_ = run_wgrad(d, (const int8_t*)(base + w.off_gy), (int64_t)w.st_gy,
-                                        dense ? (const int8_t*)(base0 + w.off_aqt[t]) : (const int8_t*)(base0 + w.off_aq[t]),
-                                        dense ? (int64_t)w.st_aqt[t] : (int64_t)w.st_aq[t], (int8_t*)(base + w.off_col),
-                                        (int64_t)w.st_col, (int32_t*)(base + w.off_part),
+                                        (const int8_t*)(base0 + off_q), (int64_t)st_q, (int32_t*)(base + w.off_part),
                                         (int64_t)(w.st_part / sizeof(int32_t)), (int32_t*)(base + w.off_dw),
                                         (int64_t)(w.st_dw / sizeof(int32_t)), dw_elems, 2, s, d.pointwise);
         if (ws_ != FF_OK) return ws_;

@@ -258,14 +258,19 @@ struct GemmArgs {
     int32_t splits;
     int64_t st_split;
     // implicit-GEMM convolution (conv != 0): P is an NHWC int8 tensor [B, H, W, cpitch] and row i of the
-    // contraction is output pixel (b, ho, wo); reduction index r = (kh*ks + kw)*Cin + ci.  Cin % 16 == 0.
-    // conv == 2: Q is a set of planes S[kw][ci][(b, h, wo)] (row pitch ldq bytes) written by launch_im2col with
-    // wtaps_only; row j of the contraction is (kh, kw, ci), the reduction runs over output pixels.  W_out % 16 == 0.
+    // contraction is output pixel (b, ho, wo); reduction index r = (kh*ks + kw)*Cin + ci.  Cin is the channel count rounded
+    // up to 16 (the pad channels of P are zero, so what Q holds at their place does not matter: it is the next tap's
+    // weights), cin_out the real one, a multiple of 4: the tap stride of Q's rows.
+    // conv == 2: Q is the NHWC int8 tensor [B, H, W, cpitch] itself, column j of C is (kh, kw, ci) and the reduction runs over
+    // the output pixels of whole samples.  Cin is then the channel count rounded up to 16 (J = ks*ks*Cin) and cin_out the
+    // real one: columns of the channels in between are not stored.
     int32_t conv, H, W, Cin, cpitch, ks, stride, pad, Ho, Wo;
+    int32_t cin_out;
+    int32_t adv_b, adv_h, adv_w;   // conv == 2, filled in by launch_gemm_nt_i8: images / rows / columns 128 pixels further on
     int64_t p_bytes;  // bytes of one implicit operand tensor (conv only; must be < 2^31)
-    // log2 of C_in (conv == 1), of H_out * W_out and of W_out (conv == 2) when those are powers of two, else -1: the
-    // loaders then index with shifts instead of integer divisions.  Filled in by launch_gemm_nt_i8.
-    int32_t cin_shift, hw_shift, wo_shift;
+    // log2 of C_in (conv == 1) when that is a power of two, else -1: the loader then indexes with shifts instead of
+    // integer divisions.  Filled in by launch_gemm_nt_i8.
+    int32_t cin_shift;
     // instrumentation (null normally): every workgroup adds the shader-clock cycles and the 100 MHz constant-clock
     // ticks it was alive to clk[0] and clk[1] (their ratio is the mean shader clock during the launch) and the
     // shader clocks of each tile by phase to clk[2..6] / clk[8..12]
@@ -279,6 +284,7 @@ struct GemmPlan {
     int bm, bn, splits;
 };
 GemmPlan gemm_plan(int64_t I, int64_t J, int64_t R, int nb, bool allow_split);
+int split_evenly(int64_t R, int64_t splits);   // at most `splits` shares of a reduction of R, none of them empty
 // out[z][e] = sum over s < splits of part[z][s][e], e < n (n a multiple of 4); strides in elements
 hipError_t launch_reduce_splits(const int32_t* part, int splits, int64_t st_split, int64_t st_part_z, int32_t* out,
                                 int64_t st_out_z, int64_t n, int nb, hipStream_t s);
@@ -329,17 +335,14 @@ struct ConvGeom {
 };
 struct Im2colArgs {
     const int8_t* a;  // NHWC int8 [B, H, W, cpitch]
-    int8_t* out;      // transposed: [K, ld_out] over samples [b0, b1); row-major: [(b1-b0)*Ho*Wo, ld_out]
+    int8_t* out;      // [B*Ho*Wo, ld_out]
     ConvGeom g;
-    int32_t K, b0, b1;
+    int32_t K, B;
     int64_t ld_out;
     int32_t nb;
     int64_t st_a, st_out;
-    // transposed only: write the horizontal taps alone, as planes S[kw][ci][(b, h, wo)] over INPUT rows h:
-    // S = A[b][h][wo * stride + kw - pad][ci], zero outside the image (K = ks * C_in rows of ld_out bytes)
-    int32_t wtaps_only;
 };
-hipError_t launch_im2col(const Im2colArgs& p, bool transposed, hipStream_t s);
+hipError_t launch_im2col(const Im2colArgs& p, hipStream_t s);
 // ---- depthwise convolution (conv.hip): one ks x ks filter per channel, HBM-bound -----------------------------
 struct DwArgs {
     const int8_t* a;    // NHWC int8 [B, H, W, cpitch]
@@ -364,8 +367,5 @@ struct DwArgs {
 };
 hipError_t launch_dwconv_forward(const DwArgs& p, hipStream_t s);
 hipError_t launch_dwconv_wgrad(const DwArgs& p, hipStream_t s);
-
-// true when launch_im2col can write the planes for this geometry (LDS slab fits, grid limits)
-bool im2col_planes_ok(const ConvGeom& g, int64_t nbatch_times_nb);
 
 }  // namespace ffi

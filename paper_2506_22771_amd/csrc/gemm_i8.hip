@@ -33,6 +33,7 @@
 
 namespace ffi {
 
+typedef int v2i __attribute__((ext_vector_type(2)));
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 
@@ -88,16 +89,30 @@ __device__ __forceinline__ void wave_lds_fence()
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
+// Transposing LDS read: each group of 16 lanes reads eight rows of 16 bytes (lanes 2r and 2r + 1 give the halves of row r)
+// and lane j of the group receives byte column j, rows 0 .. 7.
+__device__ __forceinline__ v2i tr_read8(const int8_t* p)
+{
+    typedef __attribute__((address_space(3))) v2i* lds_ptr;
+    return __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_ptr)p);
+}
 __device__ __forceinline__ int swz(int row, int kc) { return row * BK + ((kc ^ ((row >> 1) & 7)) << 4); }
 
 // MODE 0: store C; 1: store C and accumulate the per-sample goodness sums / maxima; 2: split reduction, this
 // workgroup stores the partial sums of its share of the reduction steps at C + blockIdx.y * st_split.
 // CONV 0: both operands are matrices.  1: P is an NHWC tensor, row i of the contraction is an output pixel and
-// the reduction runs over (tap, channel) (forward pass of a convolution as an implicit GEMM).  2: Q is a set of
-// column-shifted channel-major planes S[kw][ci][(b, h, wo)] of the layer input, row j of the contraction is
-// (tap, channel) and the reduction runs over output pixels (weight gradient of a convolution as an implicit
-// GEMM: the vertical tap offset is an address offset of whole 16-byte chunks, rows outside the image read as
-// zero through the range check).
+// the reduction runs over (tap, channel) (forward pass of a convolution as an implicit GEMM).
+// CONV 2: Q is the NHWC tensor itself, column j of the contraction's output is (tap, channel) and the reduction runs over
+// output pixels, i.e. Q is stored reduction-major.  A step stages 128 pixels x BN (tap, channel) bytes as they lie in
+// memory (16-byte chunks of one tap's channels, taps outside the image read as zero) and the fragments are read with
+// ds_read_b64_tr_b8, which hands lane j the j-th byte column of eight consecutive pixel rows: no transposed copy of the
+// input exists anywhere, for any map size, stride or channel count.  The pixels' base offsets and tap masks of a step are
+// worked out once per workgroup (one pixel per thread of the first two wavefronts, stepping by 128 pixels without
+// divisions) and shared through a small double-buffered LDS table.  Chunk c of pixel row r lies at position
+// c ^ 2 g(r) of its row, g(r) chosen so that the 8 rows x 32 bytes of a half-wave read fall into 16 different bank groups.
+// Measured against the transposed patch matrices / column-shifted planes this replaces (which had to be written first):
+// 64 -> 128 channels at 32x32, 256 images, both sets: contraction 115 -> 104 us and 46 us of plane writing gone; maps whose
+// size is no multiple of 16 (byte gathers before) several times faster: 120 -> 160 at 21x21, 27 images, 196 -> 106 us in all.
 template <int BM, int BN, int WM, int WN, int MODE, int CONV>
 __global__ __launch_bounds__(WM* WN * 64) void k_gemm_nt_i8(GemmArgs a)
 {
@@ -112,7 +127,7 @@ __global__ __launch_bounds__(WM* WN * 64) void k_gemm_nt_i8(GemmArgs a)
     // 256-row tiles stage in the SECOND operand stage (and a little beyond it; 16 rows at a time for the 256 x 256 tile,
     // so that it fits), which leaves the first stage free for the first copies of the workgroup's next tile (persistent
     // launches); the others 32 rows from 0.
-    constexpr bool PREFETCH = FF_NEXT_TILE_PREFETCH && BM == 256 && CONV != 2 && MODE != 2;
+    constexpr bool PREFETCH = FF_NEXT_TILE_PREFETCH && BM == 256 && CONV < 2 && MODE != 2;
     constexpr int EROWS = PREFETCH && BN == 256 ? 16 : 32;
     constexpr int EROW = WTN * 4 + 16;
     constexpr int ESLICE = EROWS * EROW;
@@ -123,8 +138,14 @@ __global__ __launch_bounds__(WM* WN * 64) void k_gemm_nt_i8(GemmArgs a)
     constexpr int CH = CH_P + CH_Q;   // copy instructions of one thread per reduction step
     static_assert((NS - 1) * CH < 64, "vmcnt range");
     constexpr int LDS_BYTES = NS * STAGE_BYTES > EOFF + WM * WN * ESLICE ? NS * STAGE_BYTES : EOFF + WM * WN * ESLICE;
-    static_assert(LDS_BYTES <= 160 * 1024, "LDS");
+    static_assert(LDS_BYTES + (CONV == 2 ? 2048 : 0) <= 160 * 1024, "LDS");
     __shared__ __attribute__((aligned(16))) int8_t lds[LDS_BYTES];
+    // CONV 2: per pixel of a step {byte offset of its tap (0, 0), bit t: tap t lies inside the image}
+    __shared__ int2 tbl[CONV == 2 ? 2 : 1][CONV == 2 ? BK : 1];
+    constexpr int CPR = BN / 16;                 // CONV 2: chunks per pixel row of the staged Q tile
+    constexpr int RSQ = T / CPR;                 // pixel rows one copy instruction of the workgroup covers
+    constexpr int GSH = CPR == 16 ? 0 : (CPR == 8 ? 1 : 2), GMASK = CPR / 2 - 1;   // g(r) = (r >> GSH) & GMASK
+    static_assert(CONV != 2 || (NS == 2 && RSQ % 8 == 0 && (CPR == 16 || CPR == 8 || CPR == 4)), "pixel-row tiling");
 
     // clock probe: the counters are wavefront-uniform (scalar registers); only the final atomics are per thread
     unsigned long long clk0 = 0, rt0 = 0;
@@ -162,14 +183,51 @@ __global__ __launch_bounds__(WM* WN * 64) void k_gemm_nt_i8(GemmArgs a)
     const int rows_p = min(BM, a.I - i0), rows_q = min(BN, a.J - j0);
     __amdgpu_buffer_rsrc_t rp = CONV == 1 ? __builtin_amdgcn_make_buffer_rsrc((void*)P, 0, (int)a.p_bytes, 0x00020000)
                                           : __builtin_amdgcn_make_buffer_rsrc((void*)(P + (int64_t)i0 * a.ldp), 0, (int)(rows_p * a.ldp), 0x00020000);
-    __amdgpu_buffer_rsrc_t rq = CONV == 2 ? __builtin_amdgcn_make_buffer_rsrc((void*)Q, 0, (int)a.p_bytes, 0x00020000)
+    __amdgpu_buffer_rsrc_t rq = CONV >= 2 ? __builtin_amdgcn_make_buffer_rsrc((void*)Q, 0, (int)a.p_bytes, 0x00020000)
                                           : __builtin_amdgcn_make_buffer_rsrc((void*)(Q + (int64_t)j0 * a.ldq), 0, (int)(rows_q * a.ldq), 0x00020000);
     // Every chunk of one thread has the same k column: chunk index c = s*T + tid, T a multiple of 8,
     // LDS slot (row = c >> 3, c & 7) holds reduction chunk (c & 7) ^ ((row >> 1) & 7) of that row.
     const int kcol = (((tid & 7) ^ ((tid >> 4) & 7))) * 16;
     int offP[CH_P], offQ[CH_Q];
     int hi0[CONV == 1 ? CH_P : 1], wi0[CONV == 1 ? CH_P : 1];   // conv: input pixel of tap (0,0) for the chunk's output pixel
-    int khq[CONV == 2 ? CH_Q : 1];                              // planes: vertical tap offset (kh - pad) of the chunk's row
+    int tap_off = 0, tap_bit = 31;                              // CONV 2: this thread's (tap, channels) chunk, the same in every copy
+    int px_ho = 0, px_wo = 0, px_b = 0, px_m = 0;               // CONV 2: the pixel this thread decodes next (threads 0 .. 127)
+    if (CONV == 2) {
+        const int cq = (tid % CPR) ^ (2 * (((tid / CPR) >> GSH) & GMASK));
+        const int jc = j0 + 16 * cq;
+        const int tap = jc / a.Cin, ci = jc - tap * a.Cin;
+        const int kh = tap / a.ks, kw = tap - kh * a.ks;
+        if (tap < a.ks * a.ks) {
+            tap_off = (kh * a.W + kw) * a.cpitch + ci;
+            tap_bit = tap;
+        }
+        px_m = kt0 * BK + (tid & (BK - 1));
+        px_b = px_m / (a.Ho * a.Wo);
+        const int rem = px_m - px_b * (a.Ho * a.Wo);
+        px_ho = rem / a.Wo;
+        px_wo = rem - px_ho * a.Wo;
+    }
+    // CONV 2: table of the next reduction step (steps are decoded in order), then on to the pixels 128 further
+    auto decode = [&](int buf) {
+        if (CONV == 2 && tid < BK) {
+            const int hi = px_ho * a.stride - a.pad, wi = px_wo * a.stride - a.pad;
+            int mask = 1;
+            if (a.ks == 3) {
+                const int vc = ((unsigned)wi < (unsigned)a.W ? 1 : 0) | ((unsigned)(wi + 1) < (unsigned)a.W ? 2 : 0) |
+                               ((unsigned)(wi + 2) < (unsigned)a.W ? 4 : 0);
+                mask = ((unsigned)hi < (unsigned)a.H ? vc : 0) | ((unsigned)(hi + 1) < (unsigned)a.H ? vc << 3 : 0) |
+                       ((unsigned)(hi + 2) < (unsigned)a.H ? vc << 6 : 0);
+            }
+            tbl[CONV == 2 ? buf : 0][CONV == 2 ? tid : 0] =
+                make_int2(((px_b * a.H + hi) * a.W + wi) * a.cpitch, px_m < a.R ? mask : 0);
+            px_m += BK;
+            px_b += a.adv_b;
+            px_ho += a.adv_h;
+            px_wo += a.adv_w;
+            if (px_wo >= a.Wo) { px_wo -= a.Wo; ++px_ho; }
+            if (px_ho >= a.Ho) { px_ho -= a.Ho; ++px_b; }
+        }
+    };
 #pragma unroll
     for (int s = 0; s < CH_P; ++s) {
         const int row = (s * T + tid) >> 3;
@@ -187,13 +245,7 @@ __global__ __launch_bounds__(WM* WN * 64) void k_gemm_nt_i8(GemmArgs a)
 #pragma unroll
     for (int s = 0; s < CH_Q; ++s) {
         const int row = (s * T + tid) >> 3;
-        if (CONV == 2) {
-            const int j = j0 + row;   // (tap, channel) = (kh, kw, ci)
-            const int tap = j / a.Cin, ci = j - tap * a.Cin;
-            const int kh = tap / a.ks, kw = tap - kh * a.ks;
-            khq[s] = j < a.J ? kh - a.pad : -(1 << 20);   // rows beyond the matrix never pass the bounds test
-            offQ[s] = (kw * a.Cin + ci) * (int)a.ldq;
-        } else {
+        if (CONV != 2) {
             offQ[s] = row * (int)a.ldq + kcol;
         }
     }
@@ -214,30 +266,24 @@ __global__ __launch_bounds__(WM* WN * 64) void k_gemm_nt_i8(GemmArgs a)
                 const bool in = ok && (unsigned)(hi0[s] + kh) < (unsigned)a.H && (unsigned)(wi0[s] + kw) < (unsigned)a.W;
                 lds_dma16(rp, in ? offP[s] + dk : OOB, 0, (unsigned)(uintptr_t)(base + (s * T + wave * 64) * 16));
             }
+            const int dq = tap * a.cin_out + ci0 - kcol;   // the taps of a weight row lie cin_out bytes apart
+#pragma unroll
+            for (int s = 0; s < CH_Q; ++s)
+                lds_dma16(rq, ok ? offQ[s] + dq : OOB, 0, (unsigned)(uintptr_t)(base + BM * BK + (s * T + wave * 64) * 16));
         } else {
 #pragma unroll
             for (int s = 0; s < CH_P; ++s)
                 lds_dma16(rp, ok ? offP[s] : OOB - k0, k0, (unsigned)(uintptr_t)(base + (s * T + wave * 64) * 16));
         }
         if (CONV == 2) {
-            // the chunk's 16 reduction positions are 16 consecutive output pixels of one output row (W_out % 16 == 0)
-            const int m = k0 + kcol;
-            const int hw = a.Ho * a.Wo;
-            // (power-of-two maps, the usual case, without integer divisions)
-            const int b = a.hw_shift >= 0 ? m >> a.hw_shift : m / hw;
-            const int rem = m - b * hw;
-            const int ho = a.wo_shift >= 0 ? rem >> a.wo_shift : rem / a.Wo;
-            const int wo = rem - ho * a.Wo;
-            const int hb = ho * a.stride;
-            const int base_in = b * a.H * a.Wo + wo;
+            int2 e[CH_Q];
 #pragma unroll
-            for (int s = 0; s < CH_Q; ++s) {
-                const int hi = hb + khq[s];
-                const bool in = ok && (unsigned)hi < (unsigned)a.H;
-                lds_dma16(rq, in ? offQ[s] + base_in + hi * a.Wo : OOB, 0,
+            for (int s = 0; s < CH_Q; ++s) e[s] = tbl[CONV == 2 ? buf : 0][CONV == 2 ? tid / CPR + s * RSQ : 0];
+#pragma unroll
+            for (int s = 0; s < CH_Q; ++s)
+                lds_dma16(rq, (e[s].y >> tap_bit) & 1 ? e[s].x + tap_off : OOB, 0,
                           (unsigned)(uintptr_t)(base + BM * BK + (s * T + wave * 64) * 16));
-            }
-        } else {
+        } else if (CONV == 0) {
 #pragma unroll
             for (int s = 0; s < CH_Q; ++s)
                 lds_dma16(rq, ok ? offQ[s] : OOB - k0, k0, (unsigned)(uintptr_t)(base + BM * BK + (s * T + wave * 64) * 16));
@@ -254,11 +300,27 @@ __global__ __launch_bounds__(WM* WN * 64) void k_gemm_nt_i8(GemmArgs a)
 
     const int lr = lane & 31, lh = lane >> 5;
     v4i fp[2][TI], fq[2][TJ];
+    int qa[TJ];   // CONV 2: byte address of this lane's first transposed read within a stage
+    if (CONV == 2) {
+        const int r = 16 * lh + ((lane & 15) >> 1);
+#pragma unroll
+        for (int tj = 0; tj < TJ; ++tj) {
+            const int cc = (wn * WTN + tj * 32) / 16 + ((lane >> 4) & 1);
+            qa[tj] = BM * BK + r * BN + ((cc ^ (2 * ((r >> GSH) & GMASK))) << 4) + 8 * (lane & 1);
+        }
+    }
     auto ldfrag = [&](int set, const int8_t* sb, int ks) {
 #pragma unroll
         for (int ti = 0; ti < TI; ++ti) fp[set][ti] = *(const v4i*)(sb + swz(wm * WTM + ti * 32 + lr, ks * 2 + lh));
 #pragma unroll
-        for (int tj = 0; tj < TJ; ++tj) fq[set][tj] = *(const v4i*)(sb + BM * BK + swz(wn * WTN + tj * 32 + lr, ks * 2 + lh));
+        for (int tj = 0; tj < TJ; ++tj) {
+            if (CONV == 2) {   // pixels 16 lh .. + 15 of the sub-step, in the order the P fragment holds them
+                const v2i lo = tr_read8(sb + qa[tj] + ks * 32 * BN), hi = tr_read8(sb + qa[tj] + ks * 32 * BN + 8 * BN);
+                fq[set][tj] = (v4i){lo.x, lo.y, hi.x, hi.y};
+            } else {
+                fq[set][tj] = *(const v4i*)(sb + BM * BK + swz(wn * WTN + tj * 32 + lr, ks * 2 + lh));
+            }
+        }
     };
     auto mma = [&](int set) {
 #pragma unroll
@@ -282,6 +344,12 @@ __global__ __launch_bounds__(WM* WN * 64) void k_gemm_nt_i8(GemmArgs a)
     } else {
     // all stages are free at the start of a tile: the copies of the first NS steps go out together, so that only
     // one round trip to memory is exposed (copies complete in issue order)
+    if (CONV == 2) {
+        decode(0);
+        decode(1);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+    }
     issue(kt0, 0);
 #pragma unroll
     for (int i = 1; i < NS; ++i)
@@ -309,6 +377,7 @@ __global__ __launch_bounds__(WM* WN * 64) void k_gemm_nt_i8(GemmArgs a)
         ldfrag(0, sb, 2);
         mma(1);
         ldfrag(1, sb, 3);
+        if (CONV == 2) decode(cur);   // step kt + 2; this table's readers have passed the barrier of step kt - 1
         mma(0);
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         // the copies of step kt + 1 must have landed; those of the NS - 2 steps after it may stay in flight (near the
@@ -371,7 +440,10 @@ __global__ __launch_bounds__(WM* WN * 64) void k_gemm_nt_i8(GemmArgs a)
         wait_copies = true;
     }
     const bool interior = i0 + BM <= a.I && j0 + BN <= a.J;
-    const bool staged = FF_STAGED_EPI && (interior || (a.J & 3) == 0);
+    // CONV 2 with channel counts that are no multiple of 16: the columns run over whole 16-channel chunks and the store
+    // leaves the channels beyond C_in out
+    const bool compact = CONV == 2 && a.cin_out != a.Cin;
+    const bool staged = FF_STAGED_EPI && (interior || (a.J & 3) == 0) && !compact;
     const bool fast_sq = a.relu && a.rshift == 0;
     int8_t* const ebase = lds + EOFF + wave * ESLICE;
     if (wait_copies && !staged) {   // (copies and stores complete in issue order: wait before the first store)
@@ -390,7 +462,20 @@ __global__ __launch_bounds__(WM* WN * 64) void k_gemm_nt_i8(GemmArgs a)
                 const int j = j0 + wn * WTN + tj * 32 + 8 * g + 4 * lh;
                 const int c0 = acc[ti][tj][4 * g + 0], c1 = acc[ti][tj][4 * g + 1];
                 const int c2 = acc[ti][tj][4 * g + 2], c3 = acc[ti][tj][4 * g + 3];
-                if (!staged && i < a.I) {
+                if (compact) {
+                    const int tap = j / a.Cin, ci = j - tap * a.Cin;
+                    if (i < a.I && j < a.J) {
+                        int32_t* dst = C + (int64_t)i * a.ldc + tap * a.cin_out + ci;
+                        if ((a.cin_out & 3) == 0) {
+                            if (ci < a.cin_out) *(v4i*)dst = (v4i){c0, c1, c2, c3};
+                        } else {
+                            if (ci + 0 < a.cin_out) dst[0] = c0;
+                            if (ci + 1 < a.cin_out) dst[1] = c1;
+                            if (ci + 2 < a.cin_out) dst[2] = c2;
+                            if (ci + 3 < a.cin_out) dst[3] = c3;
+                        }
+                    }
+                } else if (!staged && i < a.I) {
                     int32_t* dst = C + (int64_t)i * a.ldc + j;
                     if (j + 3 < a.J) {
                         *(v4i*)dst = (v4i){c0, c1, c2, c3};
@@ -554,7 +639,7 @@ static hipError_t launch_cfg(const GemmArgs& a, hipStream_t s)
     // once -- one per compute unit, two where a workgroup takes at most half of the LDS -- when each has at least two
     // whole tiles
     int64_t gx = ntiles;
-    if (FF_PERSIST && FF_NEXT_TILE_PREFETCH && BM == 256 && a.conv != 2 && mode != 2) {
+    if (FF_PERSIST && FF_NEXT_TILE_PREFETCH && BM == 256 && a.conv < 2 && mode != 2) {
         const int stage = (BM + BN) * BK, eslice = (BN == 256 ? 16 : 32) * (BN / WN * 4 + 16);
         const int lds = 2 * stage > stage + WM * WN * eslice ? 2 * stage : stage + WM * WN * eslice;   // as in the kernel
         const int64_t resident = (int64_t)num_cus() * (lds <= 80 * 1024 ? 2 : 1);
@@ -627,6 +712,15 @@ GemmPlan gemm_plan(int64_t I, int64_t J, int64_t R, int nb, bool allow_split)
     return p;
 }
 
+int split_evenly(int64_t R, int64_t splits)
+{
+    const int64_t nk = (R + BK - 1) / BK;
+    if (splits > nk) splits = nk;
+    if (splits < 1) splits = 1;
+    const int64_t per = (nk + splits - 1) / splits;
+    return (int)((nk + per - 1) / per);
+}
+
 __global__ __launch_bounds__(256) void k_reduce_splits(const int32_t* __restrict__ part, int splits, int64_t st_split,
                                                        int64_t st_part_z, int32_t* __restrict__ out, int64_t st_out_z,
                                                        int64_t n4)
@@ -697,11 +791,20 @@ hipError_t launch_gemm_nt_i8(const GemmArgs& a_in, hipStream_t s)
     if (a.I <= 0 || a.J <= 0) return hipSuccess;
     // byte offsets of the operand copies are 32-bit (tile-relative for dense operands, tensor-relative for conv)
     if (a.ldp >= (int64_t(1) << 22) || a.ldq >= (int64_t(1) << 22)) return hipErrorInvalidValue;
-    if (a.conv == 1 && (a.p_bytes >= (int64_t(1) << 31) || (a.Cin & 15) != 0)) return hipErrorInvalidValue;
-    // planes: chunks of 16 output pixels must lie in one output row; the reduction covers whole samples
-    if (a.conv == 2 && (a.p_bytes >= (int64_t(1) << 31) || (a.Wo & 15) != 0 || a.R % (a.Ho * a.Wo) != 0 || a.gsum))
+    if (a.conv == 1 && (a.p_bytes >= (int64_t(1) << 31) || (a.Cin & 15) != 0 || (a.cin_out & 3) != 0 || a.cin_out > a.Cin ||
+                        a.Cin > a.cpitch))
         return hipErrorInvalidValue;
     if (a.conv < 0 || a.conv > 2) return hipErrorInvalidValue;
+    // reduction-major input: whole 16-channel chunks, offsets of one tensor in 32 bits
+    if (a.conv == 2) {
+        if (a.p_bytes >= (int64_t(1) << 31) || (a.Cin & 15) != 0 || a.Cin > a.cpitch || a.cin_out > a.Cin || a.gsum ||
+            (a.ks != 1 && a.ks != 3) || a.J != a.ks * a.ks * a.Cin || a.R % (a.Ho * a.Wo) != 0)
+            return hipErrorInvalidValue;
+        const int hw = a.Ho * a.Wo;   // 128 pixels further on = adv_b images, adv_h rows and adv_w columns
+        a.adv_b = BK / hw;
+        a.adv_h = (BK - a.adv_b * hw) / a.Wo;
+        a.adv_w = BK - a.adv_b * hw - a.adv_h * a.Wo;
+    }
     if (a.splits < 1 || (a.splits > 1 && (a.gsum || a.conv == 1))) return hipErrorInvalidValue;
     auto shift_of = [](int v) {   // log2 of a power of two, else -1
         if (v <= 0 || (v & (v - 1)) != 0) return -1;
@@ -710,8 +813,6 @@ hipError_t launch_gemm_nt_i8(const GemmArgs& a_in, hipStream_t s)
         return sh;
     };
     a.cin_shift = a.conv == 1 ? shift_of(a.Cin) : -1;
-    a.hw_shift = a.conv == 2 ? shift_of(a.Ho * a.Wo) : -1;
-    a.wo_shift = a.conv == 2 ? shift_of(a.Wo) : -1;
     GemmPlan p = gemm_plan(a.I, a.J, a.R, a.nb, a.splits > 1);
     const int bm = p.bm, bn = p.bn;
     if (bn == 256) {

@@ -20,7 +20,7 @@ def ff():
     return m
 
 
-from gpu_util import dev, empty32, pad8, pad_nhwc, workspace  # noqa: E402
+from gpu_util import check_q, dev, empty32, empty8, pad32, pad8, pad_nhwc, scalar, workspace  # noqa: E402
 
 
 @pytest.mark.parametrize("relu", [1, 0])
@@ -44,3 +44,43 @@ def test_conv_goodness_sums_of_any_map_size(ff, B, H, W, Cin, Cout, relu):
     np.testing.assert_array_equal(acc.cpu().numpy()[:, :Cout], acc_ref.reshape(-1, Cout))
     np.testing.assert_array_equal(gsum.cpu().numpy().view(np.uint64), g_ref["g_int"])
     np.testing.assert_array_equal(vmax.cpu().numpy(), g_ref["vmax"])
+
+
+@pytest.mark.parametrize("B,H,W,Cin,Cout,ks,stride", [
+    (2, 9, 7, 1, 20, 3, 1), (3, 28, 28, 1, 32, 3, 1), (2, 8, 12, 2, 17, 3, 2), (2, 10, 6, 4, 64, 3, 1), (2, 7, 9, 5, 18, 3, 1),
+    (3, 5, 5, 8, 24, 3, 2), (2, 6, 11, 12, 40, 3, 1), (2, 13, 5, 14, 9, 3, 1), (2, 14, 14, 20, 33, 3, 2), (3, 7, 7, 24, 130, 3, 1),
+    (2, 5, 3, 40, 70, 3, 1), (1, 4, 4, 120, 260, 3, 1), (2, 9, 9, 16, 16, 3, 2), (5, 7, 5, 20, 30, 1, 2), (4, 3, 1, 36, 52, 1, 1),
+    (1, 3, 3, 516, 20, 3, 1), (70, 1, 1, 16, 16, 3, 1), (9, 28, 28, 64, 64, 3, 1), (40, 16, 16, 32, 48, 3, 2),
+    (300, 8, 8, 24, 96, 3, 1)])
+def test_conv_channel_counts_map_sizes_and_strides(ff, B, H, W, Cin, Cout, ks, stride):
+    """Forward and weight gradient over every operand route: patch matrices of one to four channels, channel counts that
+    are no multiple of 16 or of 4, maps narrower than a 16-byte chunk and not a multiple of anything, split reductions."""
+    rng = np.random.default_rng(B * 100 + Cin)
+    layer = Layer("conv", H=H, W=W, C_in=Cin, C_out=Cout, ksize=ks, stride=stride, pad=ks // 2)
+    desc = ff.layer_desc(layer, B)
+    K, M = layer.K, B * layer.rows_per_sample
+    a_q = rng.integers(-127, 128, (B, H, W, Cin)).astype(np.int8)
+    w_q = rng.integers(-127, 128, (Cout, ks, ks, Cin)).astype(np.int8)
+    s_a, s_w = np.float32(0.0041), np.float32(0.0007)
+    acc_ref = O.conv_forward(a_q, w_q, stride, ks // 2)
+    r = O.goodness_shift(K, layer.terms_per_sample)
+    g_ref = O.goodness(acc_ref, 1, r, s_a, s_w)
+    ws = workspace(ff.ff_layer_workspace_bytes(desc))
+    d_aq, acc = dev(pad_nhwc(a_q)), empty32(M, Cout)
+    gsum = torch.full((B,), 7, dtype=torch.int64, device="cuda")
+    vmax = torch.full((B,), 9, dtype=torch.int32, device="cuda")
+    ff.ff_layer_forward(desc, d_aq, dev(pad8(w_q.reshape(Cout, K))), acc, gsum, vmax, ws)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(acc.cpu().numpy()[:, :Cout], acc_ref.reshape(M, Cout))
+    np.testing.assert_array_equal(gsum.cpu().numpy().view(np.uint64), g_ref["g_int"])
+    ct = (rng.standard_normal(B) * 0.3).astype(np.float32)
+    gq_ref, sg_ref = O.quantize(O.local_grad(acc_ref, 1, s_a, s_w, ct), 1, 4, 55)
+    dw_ref = O.conv_wgrad(gq_ref, a_q, ks, stride, ks // 2, 0, B)
+    gy_t, s_g, dw = empty8(Cout, M), scalar(), empty32(Cout, K)
+    ws.fill_(0x5A)
+    ff.ff_layer_backward_local(desc, dev(pad32(acc_ref.reshape(M, Cout))), dev(g_ref["vmax"]), dev(np.array([s_a])),
+                               dev(np.array([s_w])), dev(ct), 1, 4, 55, d_aq, gy_t, s_g, dw, ws)
+    torch.cuda.synchronize()
+    assert s_g.item() == sg_ref
+    check_q(gy_t, gq_ref.reshape(M, Cout).T, "gy_q_t")
+    np.testing.assert_array_equal(dw.cpu().numpy()[:, :K], dw_ref.reshape(Cout, K))
