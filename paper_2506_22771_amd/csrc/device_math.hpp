@@ -48,22 +48,58 @@ __device__ __forceinline__ uint32_t sr_mix(uint32_t v)
     return v;
 }
 
+// The same for four elements whose indices are base, base + 1, base + 2, base + 3 with base a multiple of four (v = base ^
+// key, h[c] = sr_mix(v ^ c)).  The four inputs differ in their two lowest bits only, so the first xor-shift is shared
+// and the first of the two quarter-rate multiplies becomes one multiply plus additions:
+// (x ^ 1) * m = x * m + (x & 1 ? -m : m), (x ^ 2) * m = x * m + (x & 2 ? -2m : 2m).
+__device__ __forceinline__ void sr_mix4(uint32_t v, uint32_t h[4])
+{
+    constexpr uint32_t M = 0x7FEB352Du;
+    const uint32_t x = v ^ (v >> 16);
+    const uint32_t s1 = (uint32_t)((int32_t)(x << 31) >> 31), s2 = (uint32_t)((int32_t)(x << 30) >> 31);   // all ones or zero
+    const uint32_t d1 = (M ^ s1) - s1, d2 = ((2u * M) ^ s2) - s2;
+    h[0] = x * M;
+    h[1] = h[0] + d1;
+    h[2] = h[0] + d2;
+    h[3] = h[1] + d2;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        uint32_t w = h[c];
+        w ^= w >> 15;
+        w *= 0x846CA68Bu;
+        h[c] = w ^ (w >> 16);
+    }
+}
+
 // STOCH: floor + Bernoulli(frac) from the counter-based word; else round-to-nearest-even.
 // `word_in` is (low 32 bits of the element index) ^ key, already adjusted for the high index half.
 template <bool STOCH>
-__device__ __forceinline__ int quant_code(float v, float inv, uint32_t word_in)
+__device__ __forceinline__ int quant_code_of_word(float v, float inv, uint32_t random_word)
 {
     const float t = v * inv;
     int code;
     if (STOCH) {
         const float f = floorf(t);
         const float frac = t - f;
-        const float u = (float)(sr_mix(word_in) >> 8) * 0x1p-24f;
+        const float u = (float)(random_word >> 8) * 0x1p-24f;
         code = (int)f + (u < frac ? 1 : 0);
     } else {
         code = (int)rintf(t);
     }
     return min(max(code, -127), 127);
+}
+template <bool STOCH>
+__device__ __forceinline__ int quant_code(float v, float inv, uint32_t word_in)
+{
+    return quant_code_of_word<STOCH>(v, inv, STOCH ? sr_mix(word_in) : 0u);
+}
+
+// v / d for v >= 0, d > 0 given y = 1 / d correctly rounded: one multiplication, the exact remainder, one correction
+// (Markstein's theorem: the result is the correctly rounded quotient as long as nothing leaves the normal range).
+__device__ __forceinline__ float div_by_reciprocal(float v, float d, float y)
+{
+    const float q = v * y;
+    return __builtin_fmaf(__builtin_fmaf(-q, d, v), y, q);
 }
 
 // exp(z) for z <= 0 with a fixed operation sequence (it feeds the gradient quantiser through the sigmoid)

@@ -141,21 +141,23 @@ template <int CB> struct QTile {
 // Each thread owns two 4x4 element blocks (rows 4*rb+j, cols 4*cb+c).  Codes are packed four columns
 // to a word for q, byte-transposed in registers for q_t and regrouped through LDS so that q_t is
 // written in 16-byte pieces.  All eight 16-byte loads of a thread are issued before any arithmetic.
-// VEC: 16-byte loads are legal (always for the int32 sources; for fp32 when cols % 4 == 0 and the base
-// is 16-byte aligned).  Tensors have fewer than 2^32 elements (checked by the entry points), so the low
-// word of the element index is the whole index.
-template <int SRC, bool STOCH, bool VEC, int CB = 16>
-__global__ __launch_bounds__(QT_THREADS) void k_quantize(QuantArgs a)
+// FORM 0: element loads (an fp32 source whose columns or base are not 16-byte friendly).  1: 16-byte loads (always legal
+// for the int32 sources).  2: 16-byte loads and cols % 4 == 0, so that four neighbours share a hash head (sr_mix4).
+// Tensors have fewer than 2^32 elements (checked by the entry points), so the low word of the element index is the
+// whole index.
+// What bounds it: for tensors of tens of megabytes HBM, below that the vector ALUs (26 issue slots an element for a local
+// gradient, of which the hash takes 14).  Hence: whole tiles take a body without bounds checks, row pointers advance by
+// additions, and the sample of a row comes from one 32-bit division per four rows (local gradient of 2 x 8192 x 4096:
+// 71 -> 64 us, 5.2 TB/s; 144 channels at 32x32, 512 images: 84 -> 72 us; 2 x 1024 x 2000: 16 -> 12 us).
+template <int SRC, bool STOCH, int FORM, int CB, bool WHOLE>
+__device__ __forceinline__ void quantize_tile(const QuantArgs& a, uint32_t* tileT)
 {
     constexpr int QT_ROWS = QTile<CB>::ROWS, QT_COLS = QTile<CB>::COLS, QT_LDW = QTile<CB>::LDW, QT_RH = QTile<CB>::RH;
+    constexpr bool F32SRC = SRC == QSRC_F32 || SRC == QSRC_F32_GRAD;   // the source is an fp32 tensor
     const int z = blockIdx.z;
-    const float* __restrict__ x = a.x ? a.x + z * a.st_x : nullptr;
-    const int32_t* __restrict__ acc = a.acc ? a.acc + z * a.st_acc : nullptr;
     const float* __restrict__ per_sample = a.per_sample ? a.per_sample + z * a.st_per_sample : nullptr;
     int8_t* __restrict__ q = a.q ? a.q + z * a.st_q : nullptr;
     int8_t* __restrict__ q_t = a.q_t ? a.q_t + z * a.st_qt : nullptr;
-    SrKey key = z ? a.key2 : a.key;
-    if (a.step_dev) key = make_sr_key(a.seed, stream_tag_of(a.step_dev[0], a.tag_layer, (uint32_t)z, a.tag_kind));
 
     // a vanishing range (absmax < 2^-100, all-zero tensor included) quantises to zero codes with scale 1
     uint32_t amax_word = a.amax_bits[z * a.st_amax];
@@ -168,109 +170,138 @@ __global__ __launch_bounds__(QT_THREADS) void k_quantize(QuantArgs a)
         __syncthreads();
         amax_word = max(max(amx[0], amx[1]), max(amx[2], amx[3]));
     }
-    const float amax = __uint_as_float(amax_word);
-    const bool live = amax >= 0x1p-100f;
-    const float inv = live ? 127.0f / amax : 0.0f;
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0)
-        a.scale[z * a.st_scale] = live ? amax / 127.0f : 1.0f;
-
-    constexpr bool F32SRC = SRC == QSRC_F32 || SRC == QSRC_F32_GRAD;   // the source is an fp32 tensor
-    float s_y = 1.0f;
-    if (!F32SRC) s_y = a.s_a[z * a.st_s_a] * a.s_w[z * a.st_s_w];
 
     const int64_t r0 = (int64_t)blockIdx.y * QT_ROWS;
     const int64_t c0 = (int64_t)blockIdx.x * QT_COLS;
     const int t = threadIdx.x;
-    const int cb = t & (CB - 1);
+    const int cb = t & (CB - 1), rg = t / CB;
     const int64_t col = c0 + 4 * cb;
-    const bool col_in = col < a.cols;
+    const int64_t rowb = r0 + 4 * rg;
+    const bool col_in = WHOLE || col < a.cols;
+    auto row_in = [&](int dr) { return WHOLE || rowb + dr < a.rows; };
 
-    __shared__ uint32_t tileT[QT_COLS * QT_LDW];
-
-    // ---- loads: 2 blocks x 4 rows x 16 bytes, raw bits.  Row (u, j) of this thread is rowb + QT_RH*u + j:
-    // all per-row offsets are (compile-time constant) x (uniform pitch), i.e. scalar-unit work.
-    const int64_t rowb = r0 + 4 * (t / CB);
-    const float* __restrict__ px0 = F32SRC ? x + rowb * a.cols + col : nullptr;
-    const int32_t* __restrict__ pa0 = !F32SRC ? acc + rowb * a.ldacc + col : nullptr;
-    int8_t* __restrict__ pq0 = q ? q + rowb * a.ldq + col : nullptr;
+    // ---- loads: 2 blocks x 4 rows x 16 bytes, raw bits.  Row (u, j) of this thread is rowb + QT_RH*u + j.
+    const int64_t ld = F32SRC ? a.cols : a.ldacc;
+    const uint32_t* __restrict__ src =
+        (F32SRC ? (const uint32_t*)(a.x + z * a.st_x) : (const uint32_t*)(a.acc + z * a.st_acc)) + rowb * ld + col;
     uint32_t raw[2][4][4];
-    float rowf[2][4];   // per-row factor (GRAD: 2*coeff; HANDOFF+l2norm: sqrt(goodness))
-    const bool ragged = (a.cols & 3) != 0;   // the int32 sources' pad columns hold junk: mask them at load
+    const bool ragged = FORM == 1 && (a.cols & 3) != 0;   // the int32 sources' pad columns hold junk: mask them at load
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
+        const uint32_t* __restrict__ ps = src + (u ? (int64_t)QT_RH * ld : 0);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const int dr = QT_RH * u + j;
-            const int64_t row = rowb + dr;
-            const bool in = row < a.rows && col_in;
             uint32_t w0 = 0, w1 = 0, w2 = 0, w3 = 0;
-            if (F32SRC) {
-                const float* px = px0 + (int64_t)dr * a.cols;
-                if (VEC) {
-                    if (in) {
-                        const uint4 f = ld_stream16(px);
-                        w0 = f.x; w1 = f.y; w2 = f.z; w3 = f.w;
+            if (row_in(QT_RH * u + j) && col_in) {
+                if (FORM != 0) {
+                    const uint4 f = ld_stream16(ps);
+                    w0 = f.x; w1 = f.y; w2 = f.z; w3 = f.w;
+                    if (ragged) {
+                        if (col + 1 >= a.cols) w1 = 0;
+                        if (col + 2 >= a.cols) w2 = 0;
+                        if (col + 3 >= a.cols) w3 = 0;
                     }
-                } else if (in) {
-                    w0 = __float_as_uint(px[0]);
-                    if (col + 1 < a.cols) w1 = __float_as_uint(px[1]);
-                    if (col + 2 < a.cols) w2 = __float_as_uint(px[2]);
-                    if (col + 3 < a.cols) w3 = __float_as_uint(px[3]);
-                }
-            } else if (in) {
-                const uint4 f = ld_stream16(pa0 + (int64_t)dr * a.ldacc);  // pitch is a multiple of 4
-                w0 = f.x; w1 = f.y; w2 = f.z; w3 = f.w;
-                if (ragged) {
-                    if (col + 1 >= a.cols) w1 = 0;
-                    if (col + 2 >= a.cols) w2 = 0;
-                    if (col + 3 >= a.cols) w3 = 0;
+                } else {
+                    w0 = ps[0];
+                    if (col + 1 < a.cols) w1 = ps[1];
+                    if (col + 2 < a.cols) w2 = ps[2];
+                    if (col + 3 < a.cols) w3 = ps[3];
                 }
             }
             raw[u][j][0] = w0; raw[u][j][1] = w1; raw[u][j][2] = w2; raw[u][j][3] = w3;
-            float rf = 1.0f;
-            if (SRC == QSRC_GRAD || SRC == QSRC_F32_GRAD || (SRC == QSRC_HANDOFF && a.l2norm)) {
-                rf = 0.0f;
-                if (in) {
-                    const int64_t smp = a.rows_per_sample == 1 ? row : row / a.rows_per_sample;
-                    rf = SRC == QSRC_HANDOFF ? sqrtf(per_sample[smp]) : 2.0f * per_sample[smp];
-                }
-            }
-            rowf[u][j] = rf;
+            ps += ld;
         }
     }
+    // ---- per-row factor (local gradients: 2*coeff; normalised hand-off: sqrt(goodness) and its reciprocal)
+    constexpr bool GRAD = SRC == QSRC_GRAD || SRC == QSRC_F32_GRAD;
+    const bool norm = SRC == QSRC_HANDOFF && a.l2norm;
+    float rowf[2][4];
+    if (GRAD || norm) {
+        const uint32_t rps = (uint32_t)a.rows_per_sample;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const uint32_t rfirst = (uint32_t)rowb + QT_RH * u;
+            uint32_t smp = rfirst, rem = 0;
+            if (rps != 1) {
+                smp = rfirst / rps;
+                rem = rfirst - smp * rps;
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                rowf[u][j] = row_in(QT_RH * u + j) ? per_sample[smp] : 0.0f;
+                if (++rem >= rps) { rem = 0; ++smp; }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) rowf[u][j] = GRAD ? 2.0f * rowf[u][j] : sqrtf(rowf[u][j]);
+    }
+
+    const float amax = __uint_as_float(amax_word);
+    const bool live = amax >= 0x1p-100f;
+    const float inv = live ? 127.0f / amax : 0.0f;
+    if (blockIdx.x == 0 && blockIdx.y == 0 && t == 0) a.scale[z * a.st_scale] = live ? amax / 127.0f : 1.0f;
+    float s_y = 1.0f;
+    if (!F32SRC) s_y = a.s_a[z * a.st_s_a] * a.s_w[z * a.st_s_w];
+    const float floor_y = a.relu ? 0.0f : -__builtin_inff();
+    SrKey key = z ? a.key2 : a.key;
+    if (a.step_dev) key = make_sr_key(a.seed, stream_tag_of(a.step_dev[0], a.tag_layer, (uint32_t)z, a.tag_kind));
+    // (the smallest nonzero activity is s_y, the largest 2^31 s_y: with these bounds every quotient and remainder is normal)
+    const bool plain_range = s_y > 0x1p-40f && s_y < 0x1p40f;
 
     // ---- quantise
-    const uint64_t idx0 = (uint64_t)rowb * (uint64_t)a.cols + (uint64_t)col;   // element index of (row rowb, col)
+    const uint32_t idx0 = (uint32_t)rowb * (uint32_t)a.cols + (uint32_t)col;   // element index of (row rowb, col)
+    int8_t* __restrict__ pq0 = q ? q + rowb * a.ldq + col : nullptr;
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
-        const int rb = (t / CB) + (QT_THREADS / CB) * u;
         uint32_t rowpack[4];
+        uint32_t idx = idx0 + (uint32_t)(QT_RH * u) * (uint32_t)a.cols;
+        int8_t* __restrict__ pq = pq0 + (u ? (int64_t)QT_RH * a.ldq : 0);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const int dr = QT_RH * u + j;
-            const int64_t row = rowb + dr;
-            const uint32_t base_lo = (uint32_t)idx0 + (uint32_t)dr * (uint32_t)a.cols;
-            uint32_t pack = 0;
+            uint32_t h[4];
+            if (STOCH) {
+                if (FORM == 2) {
+                    sr_mix4(idx ^ key.k0, h);
+                } else {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) h[c] = sr_mix((idx + (uint32_t)c) ^ key.k0);
+                }
+            }
+            float v[4];
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                float v = F32SRC ? __uint_as_float(raw[u][j][c]) : (float)(int)raw[u][j][c];
-                if (SRC == QSRC_F32_GRAD) v = rowf[u][j] * v;
-                if (!F32SRC) {
-                    v = v * s_y;
-                    if (a.relu) v = fmaxf(v, 0.0f);
-                    if (SRC == QSRC_GRAD) v = rowf[u][j] * v;
-                    else if (a.l2norm) v = rowf[u][j] > 0.0f ? v / rowf[u][j] : 0.0f;
-                }
-                // elements outside the tensor were loaded as zero and a dead range has inv == 0: in both
-                // cases t == 0, so the code is 0 in either rounding mode without any masking
-                const int code = quant_code<STOCH>(v, inv, (base_lo + (uint32_t)c) ^ key.k0);
-                pack |= ((uint32_t)code & 0xFFu) << (8 * c);
+                v[c] = F32SRC ? __uint_as_float(raw[u][j][c]) : (float)(int)raw[u][j][c];
+                if (!F32SRC) v[c] = fmaxf(v[c] * s_y, floor_y);
+                if (GRAD) v[c] = rowf[u][j] * v[c];
             }
-            rowpack[j] = pack;
-            if (q && row < a.rows && col < a.ldq) *(uint32_t*)(pq0 + (int64_t)dr * a.ldq) = pack;
+            if (norm) {   // (uniform)
+                const float d = rowf[u][j];
+                if (plain_range && d > 0x1p-40f && d < 0x1p40f && a.relu) {
+                    const float y = 1.0f / d;
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) v[c] = div_by_reciprocal(v[c], d, y);
+                } else {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) v[c] = d > 0.0f ? v[c] / d : 0.0f;
+                }
+            }
+            // elements outside the tensor were loaded as zero and a dead range has inv == 0: in both
+            // cases t == 0, so the code is 0 in either rounding mode without any masking
+            int code[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) code[c] = quant_code_of_word<STOCH>(v[c], inv, STOCH ? h[c] : 0u);
+            const uint32_t lo = __builtin_amdgcn_perm((uint32_t)code[1], (uint32_t)code[0], 0x0C0C0400u);
+            const uint32_t hi = __builtin_amdgcn_perm((uint32_t)code[3], (uint32_t)code[2], 0x04000C0Cu);
+            rowpack[j] = lo | hi;
+            if (q && row_in(QT_RH * u + j) && (WHOLE || col < a.ldq)) *(uint32_t*)pq = rowpack[j];
+            idx += (uint32_t)a.cols;
+            pq += a.ldq;
         }
         if (q_t) {
-            // 4x4 byte transpose: colpack[c] = byte c of rowpack[0..3]
+            // 4x4 byte transpose: column word c = byte c of rowpack[0..3]
+            const int rb = rg + (QT_THREADS / CB) * u;
             const uint32_t t0 = __builtin_amdgcn_perm(rowpack[1], rowpack[0], 0x05010400u);
             const uint32_t t1 = __builtin_amdgcn_perm(rowpack[1], rowpack[0], 0x07030602u);
             const uint32_t t2 = __builtin_amdgcn_perm(rowpack[3], rowpack[2], 0x05010400u);
@@ -289,40 +320,49 @@ __global__ __launch_bounds__(QT_THREADS) void k_quantize(QuantArgs a)
             const int cl = e / QTile<CB>::CHUNKS, ch = e % QTile<CB>::CHUNKS;
             const int64_t oc = c0 + cl;
             const int64_t orow = r0 + 16 * ch;
-            if (oc < a.cols && orow < a.ldqt) {
-                int4 o;
-                o.x = (int)tileT[cl * QT_LDW + 4 * ch + 0];
-                o.y = (int)tileT[cl * QT_LDW + 4 * ch + 1];
-                o.z = (int)tileT[cl * QT_LDW + 4 * ch + 2];
-                o.w = (int)tileT[cl * QT_LDW + 4 * ch + 3];
+            if ((WHOLE || oc < a.cols) && orow < a.ldqt) {
+                u32x4 o;
+                o.x = tileT[cl * QT_LDW + 4 * ch + 0];
+                o.y = tileT[cl * QT_LDW + 4 * ch + 1];
+                o.z = tileT[cl * QT_LDW + 4 * ch + 2];
+                o.w = tileT[cl * QT_LDW + 4 * ch + 3];
                 // the transposed copy of a layer input is read by the weight-gradient contraction much later
                 // (streaming store); that of a local gradient right away
-                if (a.qt_streaming) __builtin_nontemporal_store((u32x4){(uint32_t)o.x, (uint32_t)o.y, (uint32_t)o.z, (uint32_t)o.w}, (u32x4*)(q_t + oc * a.ldqt + orow));
-                else *(int4*)(q_t + oc * a.ldqt + orow) = o;
+                if (a.qt_streaming) __builtin_nontemporal_store(o, (u32x4*)(q_t + oc * a.ldqt + orow));
+                else *(u32x4*)(q_t + oc * a.ldqt + orow) = o;
             }
         }
     }
+}
+
+template <int SRC, bool STOCH, int FORM, int CB = 16>
+__global__ __launch_bounds__(QT_THREADS) void k_quantize(QuantArgs a)
+{
+    __shared__ uint32_t tileT[QTile<CB>::COLS * QTile<CB>::LDW];
+    const bool whole = (int64_t)(blockIdx.y + 1) * QTile<CB>::ROWS <= a.rows && (int64_t)(blockIdx.x + 1) * QTile<CB>::COLS <= a.cols;
+    if (whole) quantize_tile<SRC, STOCH, FORM, CB, true>(a, tileT);
+    else quantize_tile<SRC, STOCH, FORM, CB, false>(a, tileT);
 }
 
 template <int SRC, bool STOCH>
 static void launch_quantize_t(const QuantArgs& a, hipStream_t s)
 {
     const dim3 block(QT_THREADS);
-    bool vec = true;
-    if (SRC == QSRC_F32 || SRC == QSRC_F32_GRAD) {
-        vec = (a.cols & 3) == 0 && (((uintptr_t)a.x) & 15) == 0 && ((a.st_x & 3) == 0 || a.nb == 1);
-    }
+    constexpr bool F32SRC = SRC == QSRC_F32 || SRC == QSRC_F32_GRAD;
+    const bool cols4 = (a.cols & 3) == 0;
+    const bool vec = !F32SRC || (cols4 && (((uintptr_t)a.x) & 15) == 0 && ((a.st_x & 3) == 0 || a.nb == 1));
     if (a.cols <= QTile<8>::COLS && vec) {
         const dim3 grid(1, (unsigned)((a.rows + QTile<8>::ROWS - 1) / QTile<8>::ROWS), (unsigned)a.nb);
-        hipLaunchKernelGGL((k_quantize<SRC, STOCH, true, 8>), grid, block, 0, s, a);
+        if (cols4) hipLaunchKernelGGL((k_quantize<SRC, STOCH, 2, 8>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((k_quantize<SRC, STOCH, 1, 8>), grid, block, 0, s, a);
         return;
     }
     // (column tiles up to the row pitch of q, so that its pad bytes are written too: zeros)
     const int64_t span = a.q && a.ldq > a.cols ? a.ldq : a.cols;
     const dim3 grid((unsigned)((span + QTile<16>::COLS - 1) / QTile<16>::COLS),
                     (unsigned)((a.rows + QTile<16>::ROWS - 1) / QTile<16>::ROWS), (unsigned)a.nb);
-    if (vec) hipLaunchKernelGGL((k_quantize<SRC, STOCH, true>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((k_quantize<SRC, STOCH, SRC != QSRC_F32 && SRC != QSRC_F32_GRAD>), grid, block, 0, s, a);
+    if (vec && cols4) hipLaunchKernelGGL((k_quantize<SRC, STOCH, 2>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((k_quantize<SRC, STOCH, F32SRC ? 0 : 1>), grid, block, 0, s, a);
 }
 
 hipError_t launch_quantize(int src, const QuantArgs& a, hipStream_t s)

@@ -84,3 +84,30 @@ def test_conv_channel_counts_map_sizes_and_strides(ff, B, H, W, Cin, Cout, ks, s
     assert s_g.item() == sg_ref
     check_q(gy_t, gq_ref.reshape(M, Cout).T, "gy_q_t")
     np.testing.assert_array_equal(dw.cpu().numpy()[:, :K], dw_ref.reshape(Cout, K))
+
+
+@pytest.mark.parametrize("l2", [0, 1])
+@pytest.mark.parametrize("rps,N,B", [(1, 64, 128), (1, 67, 129), (2, 30, 70), (3, 132, 50), (5, 32, 60), (49, 96, 6), (130, 65, 3)])
+def test_handoff_and_local_gradient_codes_over_rows_per_sample(ff, rps, N, B, l2):
+    """Whole and partial quantiser tiles, ragged columns, rows of one, several and many per sample, against the oracle."""
+    rng = np.random.default_rng(rps * 1000 + N)
+    if rps == 1:
+        layer = Layer("dense", in_features=40, out_features=N, l2norm_out=l2)
+    else:
+        layer = Layer("conv", H=1, W=rps, C_in=16, C_out=N, ksize=3, stride=1, pad=1, l2norm_out=l2)
+    desc = ff.layer_desc(layer, B)
+    M = B * rps
+    acc = rng.integers(-200000, 200000, (M, N)).astype(np.int32)
+    acc[:rps] = np.minimum(acc[:rps], 0)            # a sample whose activities are all zero
+    s_a, s_w = np.float32(0.0041), np.float32(0.0007)
+    r = O.goodness_shift(layer.K, layer.terms_per_sample)
+    g = O.goodness(acc.reshape(B, rps * N), 1, r, s_a, s_w)
+    a = O.handoff(acc.reshape(B, rps * N), 1, l2, s_a, s_w, g["G"]).reshape(M, N)
+    q_ref, s_ref = O.quantize(a, 1, 3, 21)
+    q, q_t, s = empty8(M, N), empty8(N, M), scalar()
+    d_acc, d_sa, d_sw = dev(pad32(acc)), dev(np.array([s_a])), dev(np.array([s_w]))
+    ff.ff_layer_handoff(desc, d_acc, d_sa, d_sw, dev(g["G"]), dev(np.array([np.abs(a).max()], np.float32)), 1, 3, 21, q, q_t, s)
+    torch.cuda.synchronize()
+    assert s.item() == s_ref
+    check_q(q, q_ref, "hand-off codes")
+    check_q(q_t, q_ref.T, "transposed hand-off codes")
