@@ -127,7 +127,8 @@ static size_t layer_col_bytes(const Dims& d)
 static size_t layer_part_bytes(const Dims& d, int nb)
 {
     if (d.kind == FF_DWCONV2D) return 0;
-    const GemmPlan p = gemm_plan(d.N, d.K, min(d.M, d.chunk_b * d.rps), nb, true);
+    // (up to 512 splits of every tile but the largest, more than the contraction uses today: the published size stays)
+    const GemmPlan p = gemm_plan(d.N, d.K, min(d.M, d.chunk_b * d.rps), nb, true, -20000);
     if (p.splits <= 1) return 0;
     return align_up((size_t)p.splits * (size_t)(d.N * pitch32(d.K)) * sizeof(int32_t), 256);
 }
@@ -148,12 +149,17 @@ static int64_t wgrad_cols(const Dims& d, bool have_aqt)
     if (wgrad_from_patches(d)) return (d.K + 15) & ~int64_t(15);
     return (int64_t)d.g.ks * d.g.ks * ((d.g.Cin + 15) & ~15);
 }
+// Sample chunks of equal size go into one launch as further problems of the batch.
+static bool chunks_together(const Dims& d) { return d.n_chunks > 1 && d.B == d.n_chunks * d.chunk_b; }
+// Scratch for the partial results of a split weight gradient: [launch][pass][chunk of the launch][split][N, pitch32(K)].
 static size_t wgrad_part_bytes(const Dims& d, int nb, bool have_aqt)
 {
     if (d.kind == FF_DWCONV2D) return 0;
-    const GemmPlan p = gemm_plan(d.N, wgrad_cols(d, have_aqt), min(d.M, d.chunk_b * d.rps), nb, true);
+    const int extra = d.kind == FF_DENSE || (have_aqt && d.pointwise) ? 0 : GEMM_TABLE_BYTES;
+    const int problems = nb * (chunks_together(d) ? d.n_chunks : 1);
+    const GemmPlan p = gemm_plan(d.N, wgrad_cols(d, have_aqt), min(d.M, d.chunk_b * d.rps), problems, true, extra);
     if (p.splits <= 1) return 0;
-    return align_up((size_t)p.splits * (size_t)(d.N * pitch32(d.K)) * sizeof(int32_t), 256);
+    return align_up((size_t)(nb * d.n_chunks) * (size_t)p.splits * (size_t)(d.N * pitch32(d.K)) * sizeof(int32_t), 256);
 }
 static size_t layer_scratch_bytes(const Dims& d) { return layer_col_bytes(d) + layer_part_bytes(d, 1); }
 
@@ -181,7 +187,8 @@ struct WsLayout {
     size_t off_gy, st_gy;  // int8 scratch [2][st_gy]: transposed quantised local gradient
     size_t off_dw, st_dw, dw_bytes;  // int32 scratch [2][MAX_CHUNKS][dw_bytes]; st_dw = pass stride (bytes)
     size_t off_col[MAX_LAYERS], st_col[MAX_LAYERS];   // explicit patch matrices [2][st] (see explicit_patches), retained
-    size_t off_part, st_part;        // int32 scratch [2][st_part] (bytes): partial sums of split weight gradients
+    size_t off_part, part_bytes;     // int32 scratch: partial sums of split weight gradients (see wgrad_part_bytes)
+    size_t off_xmax;                 // uint32 [2][ABSMAX_MAX_BLOCKS]: per-workgroup absmax of the net input
     size_t off_aq[MAX_LAYERS], st_aq[MAX_LAYERS];    // quantised layer input [2][st]: dense layers share one scratch
     size_t off_aqt[MAX_LAYERS], st_aqt[MAX_LAYERS];  // dense and 1x1 stride-1 conv: transposed quantised input [2][st], retained
     size_t off_acc[MAX_LAYERS], st_acc[MAX_LAYERS];  // int32 accumulators [2][st] (bytes), retained
@@ -192,6 +199,7 @@ struct WsLayout {
     size_t off_hq, st_hq;          // int8 scratch [2][st_hq]: the gradient handed down, row-major
     size_t off_e, st_e;            // int32 scratch [2][st_e] (bytes): input-gradient accumulators
     size_t off_wqt;                // int8 scratch: transposed int8 weights of one layer
+    size_t off_cmax;               // uint32 [2][2][CHAIN_MAX_BLOCKS]: per-workgroup absmax of the two gradients
     // single-launch step of a small dense stack (all sizes 0 when the stack does not qualify)
     int fused_ok;                  // the stack qualifies for the single-launch kernel
     int fused_auto;                // ... and is small enough that FF_LAUNCH_AUTO picks it
@@ -336,8 +344,10 @@ static ff_status make_layout(const ff_net_desc* net, WsLayout* w)
         }
         w->lanes = min(lanes, w->k);
     }
+    w->off_xmax = off;
+    off = align_up(off + sizeof(uint32_t) * 2 * ABSMAX_MAX_BLOCKS, A);
     const size_t lane0 = off;
-    w->off_wbmax = off;   // per-workgroup maxima of a small weight update (UpdateArgs::block_max)
+    w->off_wbmax = off;   // per-workgroup maxima of a weight update (UpdateArgs::block_max)
     off = align_up(off + sizeof(uint32_t) * UPDATE_MAX_BLOCKS, A);
     w->st_gy = align_up(gy, A);
     w->off_gy = off;
@@ -346,9 +356,9 @@ static ff_status make_layout(const ff_net_desc* net, WsLayout* w)
     w->st_dw = MAX_CHUNKS * w->dw_bytes;
     w->off_dw = off;
     off += 2 * w->st_dw;
-    w->st_part = part;
+    w->part_bytes = part;
     w->off_part = off;
-    off += 2 * w->st_part;
+    off += w->part_bytes;
     w->lane_stride = align_up(off - lane0, A);
     off = lane0 + (size_t)w->lanes * w->lane_stride;
     for (int i = 0; i < w->k; ++i) {
@@ -379,7 +389,7 @@ static ff_status make_layout(const ff_net_desc* net, WsLayout* w)
     }
     w->chain = net->lookahead == FF_LOOKAHEAD_CHAIN;
     w->st_f = w->st_hq = w->st_e = 0;
-    w->off_hf = w->off_gf = w->off_hq = w->off_e = w->off_wqt = off;
+    w->off_hf = w->off_gf = w->off_hq = w->off_e = w->off_wqt = w->off_cmax = off;
     if (net->lookahead != FF_LOOKAHEAD_COEFF && net->lookahead != FF_LOOKAHEAD_CHAIN) return FF_ERR_INVALID_ARG;
     if (w->chain) {
         size_t f = 0, hq = 0, e = 0, wqt = 0;
@@ -409,6 +419,8 @@ static ff_status make_layout(const ff_net_desc* net, WsLayout* w)
         off += 2 * w->st_e;
         w->off_wqt = off;
         off += align_up(wqt, A);
+        w->off_cmax = off;
+        off += align_up(sizeof(uint32_t) * 4 * CHAIN_MAX_BLOCKS, A);
     }
     for (int i = 0; i < w->k; ++i) w->off_fgy[i] = w->st_fgy[i] = 0;
     if (net->launch_mode == FF_LAUNCH_FUSED && !w->fused_ok) return FF_ERR_UNSUPPORTED;
@@ -554,27 +566,42 @@ static ff_status run_forward(const Dims& d, int relu, const int8_t* aq, int64_t 
     return FF_OK;
 }
 
+// Where the accumulators of a weight gradient are: term[p][c] of pass p and sample chunk c is the sum of splits[c] partial
+// results, st_split elements apart.
+struct WgradTerms {
+    const int32_t* term[2][MAX_CHUNKS];
+    int splits[MAX_CHUNKS];
+    int64_t st_split;
+};
+
 // Weight gradient: dw[z][c] = gy_q_t[z][:, chunk c] x (patches of chunk c)^T for every chunk c.
 // `aqt` is the transposed quantised input (dense; also a 1x1 stride-1 convolution when aqt_transposed is set) or the
 // NHWC quantised input (conv), which the contraction reads reduction-major as it is -- or the row-major patch matrix
-// [M, pitch(K)] (wgrad_from_patches).  dw accumulators of one pass are
-// dw_elems apart.  `part`: st_part elements per pass for the partial sums of a split reduction.
+// [M, pitch(K)] (wgrad_from_patches).  dw accumulators of one pass are dw_elems apart.  `part`: part_elems elements for the
+// partial results of a split reduction.  terms == null: split results are added up into dw; otherwise they are left as
+// they are for the update, and *terms says where everything is.
 static ff_status run_wgrad(const Dims& d, const int8_t* gy_t, int64_t st_gy, const int8_t* aqt, int64_t st_aqt,
-                           int32_t* part, int64_t st_part, int32_t* dw, int64_t st_dw, int64_t dw_elems, int nb,
-                           hipStream_t s, bool aqt_transposed = false)
+                           int32_t* part, int64_t part_elems, int32_t* dw, int64_t st_dw, int64_t dw_elems, int nb,
+                           hipStream_t s, bool aqt_transposed, WgradTerms* terms)
 {
-    // depthwise accumulators are added to with atomics and must start at zero: one fill over all passes and chunks when
-    // that span is small (it usually is: C x 12 words per accumulator), else one per accumulator
-    const int64_t dw_span = (int64_t)(nb - 1) * st_dw + (int64_t)(d.n_chunks - 1) * dw_elems + d.N * pitch32(d.K);
-    const bool dw_one_fill = d.kind == FF_DWCONV2D && dw_span <= (int64_t(1) << 20);
-    if (dw_one_fill) HIPCHK_T(FF_K_SMALL, launch_fill_u32((uint32_t*)dw, dw_span, 0u, s));
-    for (int c = 0; c < d.n_chunks; ++c) {
-        const int64_t b0 = c * d.chunk_b, b1 = min(d.B, b0 + d.chunk_b);
-        const int64_t m0 = b0 * d.rps, mc = (b1 - b0) * d.rps;
-        if (d.kind == FF_DWCONV2D) {
+    const int64_t elems = d.N * pitch32(d.K);
+    if (terms) {
+        terms->st_split = elems;
+        for (int c = 0; c < d.n_chunks; ++c) {
+            terms->splits[c] = 1;
+            for (int z = 0; z < nb; ++z) terms->term[z][c] = dw + z * st_dw + c * dw_elems;
+        }
+    }
+    if (d.kind == FF_DWCONV2D) {
+        // depthwise accumulators are added to with atomics and must start at zero: one fill over all passes and chunks
+        // when that span is small (it usually is: C x 12 words per accumulator), else one per accumulator
+        const int64_t dw_span = (int64_t)(nb - 1) * st_dw + (int64_t)(d.n_chunks - 1) * dw_elems + elems;
+        const bool dw_one_fill = dw_span <= (int64_t(1) << 20);
+        if (dw_one_fill) HIPCHK_T(FF_K_SMALL, launch_fill_u32((uint32_t*)dw, dw_span, 0u, s));
+        for (int c = 0; c < d.n_chunks; ++c) {
             // gy_t holds the ROW-MAJOR int8 gradient [M, pitch(C)] for this layer kind
             for (int z = 0; z < nb && !dw_one_fill; ++z)
-                HIPCHK_T(FF_K_SMALL, launch_fill_u32((uint32_t*)(dw + z * st_dw + c * dw_elems), d.N * pitch32(d.K), 0u, s));
+                HIPCHK_T(FF_K_SMALL, launch_fill_u32((uint32_t*)(dw + z * st_dw + c * dw_elems), elems, 0u, s));
             DwArgs p;
             memset(&p, 0, sizeof(p));
             p.a = aqt;
@@ -586,28 +613,39 @@ static ff_status run_wgrad(const Dims& d, const int8_t* gy_t, int64_t st_gy, con
             p.st_gy = st_gy;
             p.dw = dw + c * dw_elems;
             p.st_dw = st_dw;
-            p.b0 = (int32_t)b0;
-            p.b1 = (int32_t)b1;
+            p.b0 = (int32_t)(c * d.chunk_b);
+            p.b1 = (int32_t)min(d.B, (c + 1) * d.chunk_b);
             p.nb = nb;
             HIPCHK_T(FF_K_DWCONV, launch_dwconv_wgrad(p, s));
-            continue;
         }
+        return FF_OK;
+    }
+    // one launch for all chunks, or one per chunk (chunks of different sizes)
+    const int together = chunks_together(d) ? d.n_chunks : 1;
+    const int launches = d.n_chunks / together;
+    for (int l = 0; l < launches; ++l) {
+        const int64_t b0 = l * d.chunk_b, b1 = min(d.B, b0 + d.chunk_b);
+        const int64_t m0 = b0 * d.rps, mc = (b1 - b0) * d.rps;
         GemmArgs g;
         memset(&g, 0, sizeof(g));
         g.P = gy_t + m0;
         g.st_p = st_gy;
+        g.st_p2 = mc;
         g.ldp = pitch8(d.M);
-        g.C = dw + c * dw_elems;
+        g.C = dw + l * dw_elems;
         g.st_c = st_dw;
+        g.st_c2 = dw_elems;
         g.I = (int32_t)d.N;
         g.J = (int32_t)d.K;
         g.R = (int32_t)mc;
         g.ldc = pitch32(d.K);
         g.rows_per_sample = 1;
-        g.nb = nb;
+        g.nb = nb * together;
+        g.nc = together;
         if (d.kind == FF_DENSE || aqt_transposed) {   // a 1x1 stride-1 convolution is a dense layer over its pixels
             g.Q = aqt + m0;
             g.st_q = st_aqt;
+            g.st_q2 = mc;
             g.ldq = pitch8(d.M);
         } else {
             // the operand as it lies in memory, read reduction-major: the NHWC input, or the patch matrix, which is the
@@ -623,6 +661,7 @@ static ff_status run_wgrad(const Dims& d, const int8_t* gy_t, int64_t st_gy, con
             }
             g.Q = aqt + b0 * q.H * q.W * q.cpitch;
             g.st_q = st_aqt;
+            g.st_q2 = d.chunk_b * q.H * q.W * q.cpitch;
             g.ldq = 16;   // unused by this loader
             g.conv = 2;
             g.J = (int32_t)wgrad_cols(d, false);
@@ -630,17 +669,29 @@ static ff_status run_wgrad(const Dims& d, const int8_t* gy_t, int64_t st_gy, con
             g.stride = q.stride; g.pad = q.pad; g.Ho = q.Ho; g.Wo = q.Wo;
             g.p_bytes = (b1 - b0) * q.H * q.W * q.cpitch;
         }
-        g.splits = gemm_plan(g.I, g.J, g.R, nb, true).splits;
-        const int64_t fit = st_part / (d.N * pitch32(d.K));   // partial results the scratch holds
+        g.splits = gemm_plan(g.I, g.J, g.R, g.nb, true, g.conv == 2 ? GEMM_TABLE_BYTES : 0).splits;
+        const int64_t room = part_elems / launches;            // this launch's share of the scratch
+        const int64_t fit = room / (elems * g.nb);             // partial results per accumulator it holds
         if (g.splits > fit) g.splits = split_evenly(g.R, fit < 1 ? 1 : fit);
         g.clk = g_clock_probe;
         if (g.splits > 1) {
-            int32_t* out = g.C;
-            g.C = part;
-            g.st_c = st_part;
-            g.st_split = d.N * pitch32(d.K);
+            // problem (pass z, chunk c) keeps its partial results at ((z * together + c) * splits) * elems
+            int32_t* const out = g.C;
+            int32_t* const mine = part + l * room / 4 * 4;
+            g.C = mine;
+            g.st_split = elems;
+            g.st_c2 = g.splits * elems;
+            g.st_c = together * g.st_c2;
             HIPCHK_T(FF_K_GEMM_DW, launch_gemm_nt_i8(g, s));
-            HIPCHK_T(FF_K_GEMM_DW, launch_reduce_splits(part, g.splits, g.st_split, st_part, out, st_dw, g.st_split, nb, s));
+            for (int c = 0; c < together; ++c) {
+                if (terms) {
+                    terms->splits[l + c] = g.splits;
+                    for (int z = 0; z < nb; ++z) terms->term[z][l + c] = mine + z * g.st_c + c * g.st_c2;
+                } else {
+                    HIPCHK_T(FF_K_GEMM_DW, launch_reduce_splits(mine + c * g.st_c2, g.splits, elems, g.st_c,
+                                                                out + c * dw_elems, st_dw, elems, nb, s));
+                }
+            }
         } else {
             HIPCHK_T(FF_K_GEMM_DW, launch_gemm_nt_i8(g, s));
         }
@@ -719,13 +770,14 @@ ff_status ff_quantize(const float* x, int64_t rows, int64_t cols, int32_t round_
     }
     if (!x) return FF_ERR_INVALID_ARG;
     if (!aligned4(x)) return FF_ERR_ALIGN;
+    static_assert(ABSMAX_MAX_BLOCKS * sizeof(uint32_t) <= FF_WS_MIN_BYTES, "one candidate per workgroup of the absmax");
     uint32_t* slot = (uint32_t*)ws;
-    HIPCHK_T(FF_K_SMALL, launch_fill_u32(slot, 1, 0u, s));
     HIPCHK_T(FF_K_ABSMAX, launch_absmax(x, 0, 1, rows * cols, slot, s));
     QuantArgs a;
     memset(&a, 0, sizeof(a));
     a.x = x;
     a.amax_bits = slot;
+    a.amax_n = absmax_blocks(rows * cols);
     a.round_mode = round_mode;
     a.key = make_sr_key(seed, stream_tag);
     a.rows = rows;
@@ -879,7 +931,7 @@ ff_status ff_layer_backward_local(const ff_layer_desc* layer, const int32_t* acc
         return FF_OK;
     }
     uint32_t* slot = (uint32_t*)ws;
-    HIPCHK_T(FF_K_SMALL, launch_grad_amax(coeff_total, vmax, s_a, s_w, d.B, slot, s));
+    HIPCHK_T(FF_K_SMALL, launch_grad_amax(coeff_total, vmax, s_a, s_w, d.B, 1, slot, s));
     QuantArgs a;
     memset(&a, 0, sizeof(a));
     a.acc = acc;
@@ -916,7 +968,8 @@ ff_status ff_layer_backward_local(const ff_layer_desc* layer, const int32_t* acc
         scratch += layer_col_bytes(d);
         room -= layer_col_bytes(d);
     }
-    return run_wgrad(d, gy_q_t, 0, operand, 0, (int32_t*)scratch, (int64_t)(room / sizeof(int32_t)), dw_acc, 0, dw_elems, 1, s);
+    return run_wgrad(d, gy_q_t, 0, operand, 0, (int32_t*)scratch, (int64_t)(room / sizeof(int32_t)), dw_acc, 0, dw_elems, 1, s,
+                     false, nullptr);
 }
 
 // ---- the entry point that allocates nothing: its scratch is a fixed array in the library's own device image ----
@@ -1000,6 +1053,7 @@ ff_status ff_chain_gradients(const ff_layer_desc* layer, const int32_t* acc, con
     ca.g = g;
     ca.h_amax_bits = (uint32_t*)h_amax;   // the bit pattern of a non-negative fp32 is the value itself
     ca.g_amax_bits = (uint32_t*)g_amax;
+    ca.amax_atomic = 1;
     ca.nb = 1;
     HIPCHK_T(FF_K_CHAIN, launch_chain_combine(ca, s));
     return FF_OK;
@@ -1051,7 +1105,6 @@ ff_status ff_layer_update(const ff_layer_desc* layer, float* w_master, const int
     if (d.n_chunks > MAX_CHUNKS) return FF_ERR_UNSUPPORTED;
     hipStream_t s = (hipStream_t)stream;
     uint32_t* slot = (uint32_t*)ws;
-    HIPCHK_T(FF_K_SMALL, launch_fill_u32(slot, 1, 0u, s));
     const int64_t dw_elems = d.N * pitch32(d.K);
     UpdateArgs u;
     memset(&u, 0, sizeof(u));
@@ -1070,12 +1123,15 @@ ff_status ff_layer_update(const ff_layer_desc* layer, float* w_master, const int
     }
     u.lr = lr;
     u.total_samples = total_samples;
-    u.w_amax_bits = slot;
+    for (int j = 0; j < u.n_terms; ++j) u.splits[j] = 1;
+    u.block_max = slot;
+    u.max_blocks = FF_WS_MIN_BYTES / sizeof(uint32_t);
     HIPCHK_T(FF_K_UPDATE, launch_update(u, s));
     QuantArgs a;
     memset(&a, 0, sizeof(a));
     a.x = w_master;
     a.amax_bits = slot;
+    a.amax_n = update_blocks(u);
     a.round_mode = FF_ROUND_NEAREST_EVEN;
     a.rows = d.N;
     a.cols = d.K;
@@ -1213,7 +1269,8 @@ static ff_status train_step_impl(const ff_net_desc* net, const ff_net_state* sta
         return FF_OK;
     }
     HIPCHK_T(FF_K_SMALL, launch_fill_u32((uint32_t*)base, (int64_t)(w.zero_bytes / 4), 0u, s));
-    HIPCHK_T(FF_K_ABSMAX, launch_absmax(x_pos, st_x, 2, n_in, out_amax, s));
+    uint32_t* const xmax = (uint32_t*)(base + w.off_xmax);
+    HIPCHK_T(FF_K_ABSMAX, launch_absmax(x_pos, st_x, 2, n_in, xmax, s));
 
     // ---- streams: the caller's, plus the library's own where the step runs independent work side by side
     hipStream_t lane_stream[MAX_LANES];
@@ -1283,8 +1340,9 @@ static ff_status train_step_impl(const ff_net_desc* net, const ff_net_state* sta
             a.relu = Lp.relu ? 1 : 0;
             a.l2norm = Lp.l2norm_out ? 1 : 0;
         }
-        a.amax_bits = out_amax + 2 * (d.src + 1);
-        a.st_amax = 1;
+        a.amax_bits = d.src < 0 ? xmax : out_amax + 2 * (d.src + 1);
+        a.st_amax = d.src < 0 ? ABSMAX_MAX_BLOCKS : 1;
+        a.amax_n = d.src < 0 ? absmax_blocks(n_in) : 0;
         a.round_mode = FF_ROUND_STOCHASTIC;
         a.key = make_sr_key(seed, ff_stream_tag(step, (uint32_t)i, 0, FF_KIND_ACT));
         a.key2 = make_sr_key(seed, ff_stream_tag(step, (uint32_t)i, 1, FF_KIND_ACT));
@@ -1488,10 +1546,11 @@ static ff_status train_step_impl(const ff_net_desc* net, const ff_net_state* sta
         const bool patches = wgrad_from_patches(d);
         const size_t off_q = dense ? w.off_aqt[t] : (patches ? w.off_col[t] : w.off_aq[t]);
         const size_t st_q = dense ? w.st_aqt[t] : (patches ? w.st_col[t] : w.st_aq[t]);
+        WgradTerms terms;
         const ff_status ws_ = run_wgrad(d, (const int8_t*)(base + w.off_gy), (int64_t)w.st_gy,
                                         (const int8_t*)(base0 + off_q), (int64_t)st_q, (int32_t*)(base + w.off_part),
-                                        (int64_t)(w.st_part / sizeof(int32_t)), (int32_t*)(base + w.off_dw),
-                                        (int64_t)(w.st_dw / sizeof(int32_t)), dw_elems, 2, s, d.pointwise);
+                                        (int64_t)(w.part_bytes / sizeof(int32_t)), (int32_t*)(base + w.off_dw),
+                                        (int64_t)(w.st_dw / sizeof(int32_t)), dw_elems, 2, s, d.pointwise, &terms);
         if (ws_ != FF_OK) return ws_;
 
         UpdateArgs u;
@@ -1501,28 +1560,27 @@ static ff_status train_step_impl(const ff_net_desc* net, const ff_net_state* sta
         u.K = d.K;
         u.lddw = pitch32(d.K);
         u.n_terms = 2 * d.n_chunks;
+        u.st_split = terms.st_split;
         for (int p = 0; p < 2; ++p)
             for (int cc = 0; cc < d.n_chunks; ++cc) {
                 const int tt = p * d.n_chunks + cc;
-                u.dw[tt] = (const int32_t*)(base + w.off_dw + p * w.st_dw + cc * w.dw_bytes);
+                u.dw[tt] = terms.term[p][cc];
+                u.splits[tt] = terms.splits[cc];
                 u.s_g[tt] = s_g + 2 * gl + p;
                 u.s_a[tt] = s_a + 2 * t + p;
             }
         u.lr = lr;
         u.total_samples = (int32_t)(2 * B);
-        u.w_amax_bits = w_amax + t;
-        // small tensors: one maximum per workgroup, reduced by the quantiser below, instead of atomics on one word
-        const int64_t nblk = update_blocks(d.N, d.K);
         uint32_t* wbmax = (uint32_t*)(base + w.off_wbmax);
-        const bool per_block = nblk <= UPDATE_MAX_BLOCKS;
-        if (per_block) u.block_max = wbmax;
+        u.block_max = wbmax;
+        u.max_blocks = UPDATE_MAX_BLOCKS;
         HIPCHK_T(FF_K_UPDATE, launch_update(u, s));
 
         QuantArgs qa;
         memset(&qa, 0, sizeof(qa));
         qa.x = state->w_master[t];
-        qa.amax_bits = per_block ? wbmax : w_amax + t;
-        qa.amax_n = per_block ? (int32_t)nblk : 0;
+        qa.amax_bits = wbmax;
+        qa.amax_n = update_blocks(u);
         qa.round_mode = FF_ROUND_NEAREST_EVEN;
         qa.rows = d.N;
         qa.cols = d.K;
@@ -1539,8 +1597,8 @@ static ff_status train_step_impl(const ff_net_desc* net, const ff_net_state* sta
     if (w.chain) {
         // ---- Eq. (4) as an exact derivative: from the last layer down, the int8 gradient h_i is handed through the
         // pre-step weights of layer i to the layer below (dense layers only, checked by make_layout)
-        uint32_t* h_amax = w_amax + k;        // [k][2]
-        uint32_t* wt_amax = h_amax + 2 * k;   // [k]
+        uint32_t* h_amax = (uint32_t*)(base + w.off_cmax);   // [2][CHAIN_MAX_BLOCKS] each
+        uint32_t* g_cand = h_amax + 2 * CHAIN_MAX_BLOCKS;
         float* s_h = s_g + 2 * k;             // [2]
         float* s_wt = s_h + 2;                // scale of the transposed weight copy (equals s_w of the layer)
         float* hf = (float*)(base + w.off_hf);
@@ -1577,9 +1635,8 @@ static ff_status train_step_impl(const ff_net_desc* net, const ff_net_state* sta
             ca.h = i > 0 ? hf : nullptr;
             ca.g = gf;
             ca.st_out = st_f;
-            ca.h_amax_bits = h_amax + 2 * i;
-            ca.g_amax_bits = g_amax + 2 * i;
-            ca.st_amax = 1;
+            ca.h_amax_bits = h_amax;
+            ca.g_amax_bits = g_cand;
             ca.nb = 2;
             // The last layer has nothing ahead of it: h = g = 2 c y, which the quantiser forms straight from the
             // accumulators (absmax by monotonicity, as in the default step); no fp32 tensors are written.
@@ -1588,9 +1645,8 @@ static ff_status train_step_impl(const ff_net_desc* net, const ff_net_state* sta
             QuantArgs a;
             memset(&a, 0, sizeof(a));
             if (top) {
-                for (int p = 0; p < 2; ++p)
-                    HIPCHK_T(FF_K_SMALL, launch_grad_amax(c + ((int64_t)i * 2 + p) * B, vmax + ((int64_t)i * 2 + p) * B,
-                                                          s_a + 2 * i + p, state->s_w[i], B, g_amax + 2 * i + p, s));
+                HIPCHK_T(FF_K_SMALL, launch_grad_amax(c + (int64_t)i * 2 * B, vmax + (int64_t)i * 2 * B, s_a + 2 * i,
+                                                      state->s_w[i], B, 2, g_amax + 2 * i, s));
                 qsrc = QSRC_GRAD;
                 a.acc = ca.acc;
                 a.st_acc = ca.st_acc;
@@ -1607,8 +1663,9 @@ static ff_status train_step_impl(const ff_net_desc* net, const ff_net_state* sta
                 a.st_x = st_f;
             }
             a.rows_per_sample = 1;
-            a.amax_bits = g_amax + 2 * i;
-            a.st_amax = 1;
+            a.amax_bits = top ? g_amax + 2 * i : g_cand;
+            a.st_amax = top ? 1 : CHAIN_MAX_BLOCKS;
+            a.amax_n = top ? 0 : chain_blocks(d.M, d.N);
             a.round_mode = FF_ROUND_STOCHASTIC;
             a.key = make_sr_key(seed, ff_stream_tag(step, (uint32_t)i, 0, FF_KIND_GRAD));
             a.key2 = make_sr_key(seed, ff_stream_tag(step, (uint32_t)i, 1, FF_KIND_GRAD));
@@ -1630,7 +1687,7 @@ static ff_status train_step_impl(const ff_net_desc* net, const ff_net_state* sta
                 QuantArgs hqa = a;
                 if (!top) {
                     hqa.x = hf;
-                    hqa.amax_bits = h_amax + 2 * i;
+                    hqa.amax_bits = h_amax;
                 }
                 hqa.key = make_sr_key(seed, ff_stream_tag(step, (uint32_t)i, 0, FF_KIND_CHAIN));
                 hqa.key2 = make_sr_key(seed, ff_stream_tag(step, (uint32_t)i, 1, FF_KIND_CHAIN));
@@ -1645,21 +1702,7 @@ static ff_status train_step_impl(const ff_net_desc* net, const ff_net_state* sta
                 HIPCHK_T(FF_K_CHAIN, launch_quantize(qsrc, hqa, s));
 
                 // transposed int8 copy of the pre-step weights: the same codes as w_q, [K, pitch(N)]
-                const int64_t nw = d.N * d.K;
-                HIPCHK_T(FF_K_CHAIN, launch_absmax(state->w_master[i], 0, 1, nw, wt_amax + i, s));
-                QuantArgs wa;
-                memset(&wa, 0, sizeof(wa));
-                wa.x = state->w_master[i];
-                wa.amax_bits = wt_amax + i;
-                wa.round_mode = FF_ROUND_NEAREST_EVEN;
-                wa.rows = d.N;
-                wa.cols = d.K;
-                wa.q_t = wqt;
-                wa.ldqt = pitch8(d.N);
-                wa.scale = s_wt;
-                wa.nb = 1;
-                wa.rows_per_sample = 1;
-                HIPCHK_T(FF_K_CHAIN, launch_quantize(QSRC_F32, wa, s));
+                HIPCHK_T(FF_K_CHAIN, launch_transpose_i8(state->w_q[i], wqt, d.N, d.K, state->s_w[i], s_wt, s));
 
                 GemmArgs ga;
                 memset(&ga, 0, sizeof(ga));

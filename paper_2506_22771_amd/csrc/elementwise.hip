@@ -29,6 +29,22 @@ __device__ __forceinline__ void block_atomic_max_bits(uint32_t bits, uint32_t* s
     }
 }
 
+// The same, stored: one candidate per workgroup for the kernel that follows.
+template <int THREADS>
+__device__ __forceinline__ void block_store_max_bits(uint32_t bits, uint32_t* out)
+{
+    __shared__ uint32_t red[THREADS / 64];
+    const uint32_t w = wave_max_u32(bits);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = w;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t m = red[0];
+#pragma unroll
+        for (int i = 1; i < THREADS / 64; ++i) m = max(m, red[i]);
+        *out = m;
+    }
+}
+
 // ------------------------------------------------------------------------------------------------
 // fill
 // ------------------------------------------------------------------------------------------------
@@ -60,8 +76,8 @@ hipError_t launch_advance_u64(uint64_t* counter, hipStream_t s)
 }
 
 // ------------------------------------------------------------------------------------------------
-// absmax of fp32 tensors -> bit pattern in slot[z] (HBM-bound: 4 bytes read per element).
-// blockIdx.y selects the tensor (x + z*stride); four independent 16-byte loads per thread per trip.
+// absmax of fp32 tensors (HBM-bound: 4 bytes read per element).  blockIdx.y selects the tensor (x + z*stride).  At most
+// one workgroup per compute unit and tensor, each leaving its own candidate: no word to clear first and no atomics.
 // ------------------------------------------------------------------------------------------------
 __device__ __forceinline__ uint32_t absbits4(const float4 v)
 {
@@ -77,8 +93,9 @@ __device__ __forceinline__ float4 ldf4(const float4* p)   // streaming hint: the
     return make_float4(v.x, v.y, v.z, v.w);
 }
 
-__global__ __launch_bounds__(256) void k_absmax_f32(const float* __restrict__ x0, int64_t st_x, int64_t n,
-                                                    uint32_t* __restrict__ slot)
+constexpr int ABS_THREADS = 512;
+__global__ __launch_bounds__(ABS_THREADS) void k_absmax_f32(const float* __restrict__ x0, int64_t st_x, int64_t n,
+                                                            uint32_t* __restrict__ part)
 {
     const float* __restrict__ x = x0 + (int64_t)blockIdx.y * st_x;
     // scalar head until 16-byte alignment, float4 body, scalar tail
@@ -87,30 +104,34 @@ __global__ __launch_bounds__(256) void k_absmax_f32(const float* __restrict__ x0
     if (head > n) head = n;
     const int64_t nvec = (n - head) >> 2;
     const float4* __restrict__ xv = (const float4*)(x + head);
-    const int64_t gtid = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int64_t gtid = (int64_t)blockIdx.x * ABS_THREADS + threadIdx.x;
     uint32_t m = 0;
-    // a workgroup walks contiguous 16 KB spans (measured: 6.2 TB/s against 5.5 TB/s for grid-strided loads)
-    constexpr int64_t SPAN = 4 * 256;
+    // a workgroup walks contiguous spans, four 16-byte loads per thread in flight
+    constexpr int64_t SPAN = 4 * ABS_THREADS;
     for (int64_t b = (int64_t)blockIdx.x * SPAN; b < nvec; b += (int64_t)gridDim.x * SPAN) {
         const int64_t i = b + threadIdx.x;
         const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
-        const float4 v0 = i < nvec ? ldf4(xv + i) : z, v1 = i + 256 < nvec ? ldf4(xv + i + 256) : z;
-        const float4 v2 = i + 512 < nvec ? ldf4(xv + i + 512) : z, v3 = i + 768 < nvec ? ldf4(xv + i + 768) : z;
+        const float4 v0 = i < nvec ? ldf4(xv + i) : z, v1 = i + ABS_THREADS < nvec ? ldf4(xv + i + ABS_THREADS) : z;
+        const float4 v2 = i + 2 * ABS_THREADS < nvec ? ldf4(xv + i + 2 * ABS_THREADS) : z;
+        const float4 v3 = i + 3 * ABS_THREADS < nvec ? ldf4(xv + i + 3 * ABS_THREADS) : z;
         m = max(m, max(max(absbits4(v0), absbits4(v1)), max(absbits4(v2), absbits4(v3))));
     }
     if (gtid < head) m = max(m, __float_as_uint(x[gtid]) & 0x7FFFFFFFu);
     const int64_t tail0 = head + (nvec << 2);
     if (tail0 + gtid < n) m = max(m, __float_as_uint(x[tail0 + gtid]) & 0x7FFFFFFFu);
-    block_atomic_max_bits<256>(m, slot + blockIdx.y);
+    block_store_max_bits<ABS_THREADS>(m, part + blockIdx.y * ABSMAX_MAX_BLOCKS + blockIdx.x);
 }
 
-hipError_t launch_absmax(const float* x, int64_t st_x, int nb, int64_t n, uint32_t* slot, hipStream_t s)
+int absmax_blocks(int64_t n)
+{
+    const int64_t blocks = (n + ABS_THREADS * 16 - 1) / (ABS_THREADS * 16);
+    return (int)max((int64_t)1, min((int64_t)ABSMAX_MAX_BLOCKS, blocks));
+}
+
+hipError_t launch_absmax(const float* x, int64_t st_x, int nb, int64_t n, uint32_t* part, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
-    int64_t blocks = (n + 256 * 16 - 1) / (256 * 16);
-    if (blocks > 4096) blocks = 4096;
-    if (blocks < 1) blocks = 1;
-    hipLaunchKernelGGL(k_absmax_f32, dim3((unsigned)blocks, (unsigned)nb), dim3(256), 0, s, x, st_x, n, slot);
+    hipLaunchKernelGGL(k_absmax_f32, dim3((unsigned)absmax_blocks(n), (unsigned)nb), dim3(ABS_THREADS), 0, s, x, st_x, n, part);
     return hipGetLastError();
 }
 
@@ -674,50 +695,47 @@ hipError_t launch_lookahead(const LookaheadArgs& a, hipStream_t s)
     return launch_lookahead_impl(a, a.s_w, s);
 }
 
-__global__ __launch_bounds__(1024) void k_grad_amax(const float* __restrict__ ct, const int32_t* __restrict__ vmax,
+__global__ __launch_bounds__(1024) void k_grad_amax(const float* __restrict__ ct0, const int32_t* __restrict__ vmax0,
                                                     const float* __restrict__ s_a, const float* __restrict__ s_w,
                                                     int64_t B, uint32_t* __restrict__ slot)
 {
-    const float s_y = s_a[0] * s_w[0];
+    const int z = blockIdx.x;
+    const float* ct = ct0 + z * B;
+    const int32_t* vmax = vmax0 + z * B;
+    const float s_y = s_a[z] * s_w[0];
     uint32_t bits = 0;
     for (int64_t b = threadIdx.x; b < B; b += 1024) {
         const float ymax = (float)vmax[b] * s_y;
         bits = max(bits, __float_as_uint(fabsf(2.0f * ct[b]) * ymax));
     }
-    __shared__ uint32_t red[16];
-    bits = wave_max_u32(bits);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = bits;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t m = 0;
-        for (int i = 0; i < 16; ++i) m = max(m, red[i]);
-        *slot = m;
-    }
+    block_store_max_bits<1024>(bits, slot + z);
 }
 
-hipError_t launch_grad_amax(const float* ct, const int32_t* vmax, const float* s_a, const float* s_w, int64_t B,
+hipError_t launch_grad_amax(const float* ct, const int32_t* vmax, const float* s_a, const float* s_w, int64_t B, int nb,
                             uint32_t* slot, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_grad_amax, dim3(1), dim3(1024), 0, s, ct, vmax, s_a, s_w, B, slot);
+    hipLaunchKernelGGL(k_grad_amax, dim3((unsigned)nb), dim3(1024), 0, s, ct, vmax, s_a, s_w, B, slot);
     return hipGetLastError();
 }
 
 // ------------------------------------------------------------------------------------------------
 // Exact-derivative look-ahead: the two gradients of a dense layer (see ChainArgs).  A thread owns four
-// consecutive columns of one row; HBM-bound (two int32 tensors read, two fp32 tensors written).
+// consecutive columns of one row per trip; HBM-bound (two int32 tensors read, two fp32 tensors written).  At most 1024
+// workgroups per pass, each leaving one candidate for the absmax of either tensor: with one workgroup per 1024 elements
+// the thousands of atomics on two words were most of a launch (2 x 1500 x 1500: 72 us, now 13).
 // ------------------------------------------------------------------------------------------------
 template <bool VEC>
 __global__ __launch_bounds__(256) void k_chain_combine(ChainArgs a)
 {
     const int z = blockIdx.y;
-    const int64_t ngroups = (a.N + 3) >> 2;
-    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const uint32_t ngroups = (uint32_t)((a.N + 3) >> 2);
+    const int64_t total = a.M * ngroups;
+    const float s_y = a.s_a[z * a.st_s_a] * a.s_w[0];
+    const float s_e = a.e_acc ? a.s_h[z * a.st_s_h] * a.s_w_up[0] : 0.0f;
     uint32_t mh = 0, mg = 0;
-    if (e < a.M * ngroups) {
-        const int64_t m = e / ngroups;
-        const int64_t j0 = (e - m * ngroups) << 2;
-        const float s_y = a.s_a[z * a.st_s_a] * a.s_w[0];
-        const float s_e = a.e_acc ? a.s_h[z * a.st_s_h] * a.s_w_up[0] : 0.0f;
+    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < total; e += (int64_t)gridDim.x * 256) {
+        const uint32_t m = (uint32_t)e / ngroups;   // fewer than 2^32 elements
+        const int64_t j0 = (int64_t)((uint32_t)e - m * ngroups) << 2;
         const float d = 2.0f * a.coeff[z * a.st_coeff + m];
         const uint4 av = ld_stream16(a.acc + z * a.st_acc + m * a.ldacc + j0);
         uint4 ev = make_uint4(0u, 0u, 0u, 0u);
@@ -751,20 +769,25 @@ __global__ __launch_bounds__(256) void k_chain_combine(ChainArgs a)
                 }
         }
     }
-    block_atomic_max_bits<256>(mg, a.g_amax_bits + z * a.st_amax);
+    if (a.amax_atomic) block_atomic_max_bits<256>(mg, a.g_amax_bits + z);
+    else block_store_max_bits<256>(mg, a.g_amax_bits + z * CHAIN_MAX_BLOCKS + blockIdx.x);
     if (a.h) {
         __syncthreads();   // the reduction buffer of the first call is read by thread 0 until here
-        block_atomic_max_bits<256>(mh, a.h_amax_bits + z * a.st_amax);
+        if (a.amax_atomic) block_atomic_max_bits<256>(mh, a.h_amax_bits + z);
+        else block_store_max_bits<256>(mh, a.h_amax_bits + z * CHAIN_MAX_BLOCKS + blockIdx.x);
     }
+}
+
+int chain_blocks(int64_t M, int64_t N)
+{
+    const int64_t total = M * ((N + 3) >> 2);
+    return (int)max((int64_t)1, min((int64_t)CHAIN_MAX_BLOCKS, (total + 255) / 256));
 }
 
 hipError_t launch_chain_combine(const ChainArgs& a, hipStream_t s)
 {
     if (a.M <= 0 || a.N <= 0) return hipSuccess;
-    const int64_t total = a.M * ((a.N + 3) >> 2);
-    const int64_t blocks = (total + 255) / 256;
-    if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)blocks, (unsigned)a.nb);
+    const dim3 grid((unsigned)chain_blocks(a.M, a.N), (unsigned)a.nb);
     const bool vec = (a.N & 3) == 0 && ((((uintptr_t)a.g) & 15) == 0) && (!a.h || (((uintptr_t)a.h) & 15) == 0) &&
                      (a.st_out & 3) == 0;
     if (vec) hipLaunchKernelGGL(k_chain_combine<true>, grid, dim3(256), 0, s, a);
@@ -772,115 +795,241 @@ hipError_t launch_chain_combine(const ChainArgs& a, hipStream_t s)
     return hipGetLastError();
 }
 
+// Transposed copy of an int8 matrix (the weights of a layer, for the gradient handed down the chain): 128 x 64 bytes per
+// workgroup, 4 x 4 byte transposes in registers, regrouped through LDS into 16-byte stores.
+__global__ __launch_bounds__(QT_THREADS) void k_transpose_i8(const int8_t* __restrict__ q, int8_t* __restrict__ q_t, int64_t N,
+                                                             int64_t K, int64_t ldq, int64_t ldqt,
+                                                             const float* __restrict__ s_in, float* __restrict__ s_out)
+{
+    constexpr int LDW = QTile<16>::LDW, RH = QTile<16>::RH, CHUNKS = QTile<16>::CHUNKS;
+    __shared__ uint32_t tileT[QTile<16>::COLS * LDW];
+    const int t = threadIdx.x, cb = t & 15, rg = t >> 4;
+    const int64_t r0 = (int64_t)blockIdx.y * QTile<16>::ROWS, c0 = (int64_t)blockIdx.x * QTile<16>::COLS;
+    if (blockIdx.x == 0 && blockIdx.y == 0 && t == 0) s_out[0] = s_in[0];
+    const int64_t col = c0 + 4 * cb;
+    uint32_t w[2][4];
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int64_t row = r0 + 4 * rg + RH * u + j;
+            w[u][j] = row < N && col < ldq ? *(const uint32_t*)(q + row * ldq + col) : 0u;
+        }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const int rb = rg + 16 * u;
+        const uint32_t t0 = __builtin_amdgcn_perm(w[u][1], w[u][0], 0x05010400u), t1 = __builtin_amdgcn_perm(w[u][1], w[u][0], 0x07030602u);
+        const uint32_t t2 = __builtin_amdgcn_perm(w[u][3], w[u][2], 0x05010400u), t3 = __builtin_amdgcn_perm(w[u][3], w[u][2], 0x07030602u);
+        tileT[(4 * cb + 0) * LDW + rb] = __builtin_amdgcn_perm(t2, t0, 0x05040100u);
+        tileT[(4 * cb + 1) * LDW + rb] = __builtin_amdgcn_perm(t2, t0, 0x07060302u);
+        tileT[(4 * cb + 2) * LDW + rb] = __builtin_amdgcn_perm(t3, t1, 0x05040100u);
+        tileT[(4 * cb + 3) * LDW + rb] = __builtin_amdgcn_perm(t3, t1, 0x07060302u);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const int e = t + QT_THREADS * u;
+        const int cl = e / CHUNKS, ch = e % CHUNKS;
+        const int64_t oc = c0 + cl, orow = r0 + 16 * ch;
+        if (oc < K && orow < ldqt) {
+            const uint32_t* p = tileT + cl * LDW + 4 * ch;
+            *(u32x4*)(q_t + oc * ldqt + orow) = (u32x4){p[0], p[1], p[2], p[3]};
+        }
+    }
+}
+
+hipError_t launch_transpose_i8(const int8_t* q, int8_t* q_t, int64_t N, int64_t K, const float* s_in, float* s_out, hipStream_t s)
+{
+    if (N <= 0 || K <= 0) return hipSuccess;
+    const dim3 grid((unsigned)((K + QTile<16>::COLS - 1) / QTile<16>::COLS), (unsigned)((N + QTile<16>::ROWS - 1) / QTile<16>::ROWS));
+    hipLaunchKernelGGL(k_transpose_i8, grid, dim3(QT_THREADS), 0, s, q, q_t, N, K, pitch8(K), pitch8(N), s_in, s_out);
+    return hipGetLastError();
+}
+
 // ------------------------------------------------------------------------------------------------
-// weight update (HBM-bound: 4 B x (1 + n_terms) read + 4 B written per weight) with fused absmax.
-// One workgroup per (row, 4096-column segment); a thread owns four groups of four columns, 256 groups
-// apart, and issues all of its loads before the arithmetic.
+// weight update (HBM-bound: 4 B x (1 + n_terms x splits) read + 4 B written per weight) with fused absmax.  The matrix is
+// walked as a flat sequence of four-column groups.  A split weight gradient is summed here, while its partial results are
+// still in the caches, instead of by a kernel of its own that writes the sum for this one to read.
+// LPG (lanes per group) 1: a thread owns groups; four of them, 256 apart, per trip, all loads before the arithmetic.
+// LPG 16: many splits of a small output (a thread that walked them alone would issue one load after the other): sixteen
+// lanes share the splits of a group and meet in LDS.
 // ------------------------------------------------------------------------------------------------
-constexpr int UP_SEG = 4096;
+struct UpdateScale {
+    float sc[4], lr_eff;
+};
+__device__ __forceinline__ UpdateScale update_scale(const UpdateArgs& a)
+{
+    UpdateScale u;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) u.sc[j] = j < a.n_terms ? a.s_g[j][0] * a.s_a[j][0] : 0.0f;
+    u.lr_eff = a.lr / (float)a.total_samples;
+    return u;
+}
+__device__ __forceinline__ float update_weight(const UpdateArgs& a, const UpdateScale& u, float w, int d0, int d1, int d2, int d3)
+{
+    float gr = (float)d0 * u.sc[0];
+    if (1 < a.n_terms) gr = __builtin_fmaf((float)d1, u.sc[1], gr);
+    if (2 < a.n_terms) gr = __builtin_fmaf((float)d2, u.sc[2], gr);
+    if (3 < a.n_terms) gr = __builtin_fmaf((float)d3, u.sc[3], gr);
+    return __builtin_fmaf(-u.lr_eff, gr, w);
+}
+// weights of one group: where they start, how many there are (four except at the end of a row that is no multiple of 4)
+template <bool VEC>
+__device__ __forceinline__ int update_group(const UpdateArgs& a, int64_t e, int64_t& at_w, int64_t& at_d)
+{
+    if (VEC) {   // rows of w and of the accumulators are contiguous: K % 4 == 0
+        at_w = at_d = 4 * e;
+        return 4;
+    }
+    const uint32_t kg = (uint32_t)((a.K + 3) >> 2);
+    const uint32_t n = (uint32_t)e / kg;   // (an [N, K] tensor has fewer than 2^32 elements)
+    const int64_t k = (int64_t)((uint32_t)e - n * kg) << 2;
+    at_w = n * a.K + k;
+    at_d = n * a.lddw + k;
+    return (int)min((int64_t)4, a.K - k);
+}
 
 template <bool VEC>
 __global__ __launch_bounds__(256) void k_update(UpdateArgs a)
 {
-    float sc[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) sc[j] = j < a.n_terms ? a.s_g[j][0] * a.s_a[j][0] : 0.0f;
-    const float lr_eff = a.lr / (float)a.total_samples;
-    const int64_t kbase = (int64_t)blockIdx.x * UP_SEG + 4 * threadIdx.x;
+    const UpdateScale us = update_scale(a);
+    const int64_t total = a.N * ((a.K + 3) >> 2);
     uint32_t m = 0;
-    for (int64_t n = blockIdx.y; n < a.N; n += gridDim.y) {
-        float* __restrict__ wrow = a.w + n * a.K;
+    for (int64_t e0 = (int64_t)blockIdx.x * 1024; e0 < total; e0 += (int64_t)gridDim.x * 1024) {
         float w[4][4];
         int4 d[4][4];
+        int64_t at_w[4], at_d[4];
         int cnt[4];
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-            const int64_t k = kbase + g * 1024;
-            cnt[g] = (int)max((int64_t)0, min((int64_t)4, a.K - k));
+            const int64_t e = e0 + g * 256 + threadIdx.x;
+            cnt[g] = 0;
+            at_w[g] = at_d[g] = 0;
+            if (e < total) cnt[g] = update_group<VEC>(a, e, at_w[g], at_d[g]);
             if (VEC) {
                 float4 f = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (cnt[g]) f = *(const float4*)(wrow + k);
+                if (cnt[g]) f = *(const float4*)(a.w + at_w[g]);
                 w[g][0] = f.x; w[g][1] = f.y; w[g][2] = f.z; w[g][3] = f.w;
             } else {
 #pragma unroll
-                for (int c = 0; c < 4; ++c) w[g][c] = c < cnt[g] ? wrow[k + c] : 0.0f;
+                for (int c = 0; c < 4; ++c) w[g][c] = c < cnt[g] ? a.w[at_w[g] + c] : 0.0f;
             }
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 d[g][j] = make_int4(0, 0, 0, 0);
                 if (j < a.n_terms && cnt[g]) {   // last use of the accumulators: streaming hint
-                    const uint4 v = ld_stream16(a.dw[j] + n * a.lddw + k);
+                    const uint4 v = ld_stream16(a.dw[j] + at_d[g]);
                     d[g][j] = make_int4((int)v.x, (int)v.y, (int)v.z, (int)v.w);
                 }
             }
         }
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            const int64_t k = kbase + g * 1024;
-            float gr[4];
-            gr[0] = (float)d[g][0].x * sc[0]; gr[1] = (float)d[g][0].y * sc[0];
-            gr[2] = (float)d[g][0].z * sc[0]; gr[3] = (float)d[g][0].w * sc[0];
+        for (int j = 0; j < 4; ++j) {
+            if (j >= a.n_terms) break;
+            for (int sp = 1; sp < a.splits[j]; ++sp) {
+                const int32_t* __restrict__ part = a.dw[j] + sp * a.st_split;
 #pragma unroll
-            for (int j = 1; j < 4; ++j) {
-                if (j < a.n_terms) {
-                    gr[0] = __builtin_fmaf((float)d[g][j].x, sc[j], gr[0]);
-                    gr[1] = __builtin_fmaf((float)d[g][j].y, sc[j], gr[1]);
-                    gr[2] = __builtin_fmaf((float)d[g][j].z, sc[j], gr[2]);
-                    gr[3] = __builtin_fmaf((float)d[g][j].w, sc[j], gr[3]);
-                }
-            }
-#pragma unroll
-            for (int c = 0; c < 4; ++c) w[g][c] = __builtin_fmaf(-lr_eff, gr[c], w[g][c]);
-            if (VEC) {
-                if (cnt[g]) {
-                    *(float4*)(wrow + k) = make_float4(w[g][0], w[g][1], w[g][2], w[g][3]);
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) m = max(m, __float_as_uint(w[g][c]) & 0x7FFFFFFFu);
-                }
-            } else {
-#pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    if (c < cnt[g]) {
-                        wrow[k + c] = w[g][c];
-                        m = max(m, __float_as_uint(w[g][c]) & 0x7FFFFFFFu);
+                for (int g = 0; g < 4; ++g)
+                    if (cnt[g]) {
+                        const int4 v = *(const int4*)(part + at_d[g]);
+                        d[g][j].x += v.x; d[g][j].y += v.y; d[g][j].z += v.z; d[g][j].w += v.w;
                     }
             }
         }
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            w[g][0] = update_weight(a, us, w[g][0], d[g][0].x, d[g][1].x, d[g][2].x, d[g][3].x);
+            w[g][1] = update_weight(a, us, w[g][1], d[g][0].y, d[g][1].y, d[g][2].y, d[g][3].y);
+            w[g][2] = update_weight(a, us, w[g][2], d[g][0].z, d[g][1].z, d[g][2].z, d[g][3].z);
+            w[g][3] = update_weight(a, us, w[g][3], d[g][0].w, d[g][1].w, d[g][2].w, d[g][3].w);
+            if (VEC) {
+                if (cnt[g]) *(float4*)(a.w + at_w[g]) = make_float4(w[g][0], w[g][1], w[g][2], w[g][3]);
+            }
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (c < cnt[g]) {
+                    if (!VEC) a.w[at_w[g] + c] = w[g][c];
+                    m = max(m, __float_as_uint(w[g][c]) & 0x7FFFFFFFu);
+                }
+        }
     }
-    if (a.block_max) {
-        m = wave_max_u32(m);
-        __shared__ uint32_t bm[4];
-        if ((threadIdx.x & 63) == 0) bm[threadIdx.x >> 6] = m;
+    block_store_max_bits<256>(m, a.block_max + blockIdx.x);
+}
+
+template <bool VEC>
+__global__ __launch_bounds__(256) void k_update_wide(UpdateArgs a)
+{
+    __shared__ int4 red[4][16][16];
+    const UpdateScale us = update_scale(a);
+    const int64_t total = a.N * ((a.K + 3) >> 2);
+    const int el = threadIdx.x & 15, sl = threadIdx.x >> 4;
+    uint32_t m = 0;
+    for (int64_t e0 = (int64_t)blockIdx.x * 16; e0 < total; e0 += (int64_t)gridDim.x * 16) {
+        int64_t at_w = 0, at_d = 0;
+        int cnt = 0;
+        if (e0 + el < total) cnt = update_group<VEC>(a, e0 + el, at_w, at_d);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (j >= a.n_terms) break;
+            int4 d = make_int4(0, 0, 0, 0);
+            if (cnt)
+                for (int sp = sl; sp < a.splits[j]; sp += 16) {
+                    const int4 v = *(const int4*)(a.dw[j] + sp * a.st_split + at_d);
+                    d.x += v.x; d.y += v.y; d.z += v.z; d.w += v.w;
+                }
+            red[j][sl][el] = d;
+        }
         __syncthreads();
-        if (threadIdx.x == 0) a.block_max[blockIdx.y * gridDim.x + blockIdx.x] = max(max(bm[0], bm[1]), max(bm[2], bm[3]));
-    } else {
-        block_atomic_max_bits<256>(m, a.w_amax_bits);
+        // four threads per group, one column each
+        if (threadIdx.x < 64) {
+            const int gel = threadIdx.x >> 2, c = threadIdx.x & 3;
+            int64_t gw = 0, gd = 0;
+            int gc = 0;
+            if (e0 + gel < total) gc = update_group<VEC>(a, e0 + gel, gw, gd);
+            if (c < gc) {
+                int d[4] = {0, 0, 0, 0};
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    if (j >= a.n_terms) break;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) d[j] += ((const int*)&red[j][r][gel])[c];
+                }
+                const float w = update_weight(a, us, a.w[gw + c], d[0], d[1], d[2], d[3]);
+                a.w[gw + c] = w;
+                m = max(m, __float_as_uint(w) & 0x7FFFFFFFu);
+            }
+        }
+        __syncthreads();
     }
+    block_store_max_bits<256>(m, a.block_max + blockIdx.x);
 }
 
-static dim3 update_grid(int64_t N, int64_t K)
+// sixteen lanes per group where a thread would have many splits to walk and there are too few groups to hide that
+static bool update_wide(const UpdateArgs& a)
 {
-    // Mid-sized tensors (thousands of short rows): a workgroup takes four rows in turn, so that fewer workgroups meet
-    // at the absmax word (cfg2: 21 -> 17 us per launch).  Few rows: one each, the chain of dependent loads stays short.
-    const int64_t rows_y = N >= 1024 && N * K <= (int64_t(8) << 20) ? (N + 3) / 4 : N;
-    return dim3((unsigned)((K + UP_SEG - 1) / UP_SEG), (unsigned)rows_y);
+    int most = 1;
+    for (int j = 0; j < a.n_terms; ++j) most = max(most, a.splits[j]);
+    return most >= 8 && a.N * ((a.K + 3) >> 2) <= (int64_t(1) << 17);
 }
 
-int64_t update_blocks(int64_t N, int64_t K)
+int update_blocks(const UpdateArgs& a)
 {
-    if (N <= 0 || K <= 0) return 0;
-    const dim3 g = update_grid(N, K);
-    return (int64_t)g.x * g.y;
+    const int64_t total = a.N * ((a.K + 3) >> 2), per = update_wide(a) ? 16 : 1024;
+    return (int)max((int64_t)1, min((int64_t)a.max_blocks, (total + per - 1) / per));
 }
 
 hipError_t launch_update(const UpdateArgs& a, hipStream_t s)
 {
     if (a.N <= 0 || a.K <= 0) return hipSuccess;
-    const dim3 grid = update_grid(a.N, a.K);
-    if (a.block_max && (int64_t)grid.x * grid.y > UPDATE_MAX_BLOCKS) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)update_blocks(a));
     const bool vec = (a.K & 3) == 0 && ((((uintptr_t)a.w) & 15) == 0);
-    if (vec) hipLaunchKernelGGL(k_update<true>, grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL(k_update<false>, grid, dim3(256), 0, s, a);
+    if (update_wide(a)) {
+        if (vec) hipLaunchKernelGGL(k_update_wide<true>, grid, dim3(256), 0, s, a);
+        else hipLaunchKernelGGL(k_update_wide<false>, grid, dim3(256), 0, s, a);
+    } else {
+        if (vec) hipLaunchKernelGGL(k_update<true>, grid, dim3(256), 0, s, a);
+        else hipLaunchKernelGGL(k_update<false>, grid, dim3(256), 0, s, a);
+    }
     return hipGetLastError();
 }
 

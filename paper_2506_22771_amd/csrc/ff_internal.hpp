@@ -89,9 +89,12 @@ struct QuantArgs {
 };
 hipError_t launch_quantize(int src, const QuantArgs& a, hipStream_t s);
 
-// absmax of |x| over n floats of tensor z (x + z*st_x, z < nb) into slot[z] (bit pattern, atomic max;
-// slots must be zeroed first).
-hipError_t launch_absmax(const float* x, int64_t st_x, int nb, int64_t n, uint32_t* slot, hipStream_t s);
+// absmax of |x| over n floats of tensor z (x + z*st_x, z < nb): workgroup b stores the bit pattern of its maximum at
+// part[z*ABSMAX_MAX_BLOCKS + b], b < absmax_blocks(n); the quantiser that follows takes the maximum of the array
+// (QuantArgs::amax_n).
+constexpr int ABSMAX_MAX_BLOCKS = 256;
+int absmax_blocks(int64_t n);
+hipError_t launch_absmax(const float* x, int64_t st_x, int nb, int64_t n, uint32_t* part, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t s);
 hipError_t launch_advance_u64(uint64_t* counter, hipStream_t s);   // *counter += 1, in stream order
 
@@ -208,35 +211,43 @@ struct ChainArgs {
     float* h;  // [M, N] contiguous per pass (stride st_out), may be null
     float* g;  // [M, N] contiguous per pass
     int64_t st_out;
-    uint32_t* h_amax_bits;  // [z * st_amax], zeroed; may be null with h
+    // absmax of both tensors: one candidate per workgroup at [z * CHAIN_MAX_BLOCKS + workgroup] (chain_blocks() of them), or,
+    // with amax_atomic, one zeroed word each; h_amax_bits may be null with h
+    uint32_t* h_amax_bits;
     uint32_t* g_amax_bits;
-    int32_t st_amax;
+    int32_t amax_atomic;
     int32_t nb;
 };
+constexpr int CHAIN_MAX_BLOCKS = 1024;
+int chain_blocks(int64_t M, int64_t N);
+// q_t[k][n] = q[n][k] for an int8 matrix [N, pitch8(K)] (pad bytes of q_t zero); *s_out = *s_in
+hipError_t launch_transpose_i8(const int8_t* q, int8_t* q_t, int64_t N, int64_t K, const float* s_in, float* s_out, hipStream_t s);
 hipError_t launch_chain_combine(const ChainArgs& a, hipStream_t s);
 
-// absmax of the local gradient for one layer / pass: max_b |2 c[b]| * (float(vmax[b]) * s_y) -> slot bits.
-hipError_t launch_grad_amax(const float* coeff_total, const int32_t* vmax, const float* s_a,
-                            const float* s_w, int64_t B, uint32_t* slot, hipStream_t s);
+// absmax of the local gradient of one layer: max_b |2 c[b]| * (float(vmax[b]) * s_y) -> slot[z], for nb passes (coefficients
+// and maxima B apart, s_a one apart).
+hipError_t launch_grad_amax(const float* coeff_total, const int32_t* vmax, const float* s_a, const float* s_w, int64_t B,
+                            int nb, uint32_t* slot, hipStream_t s);
 
 struct UpdateArgs {
     float* w;  // [N, K] contiguous
     int64_t N, K, lddw;
     int32_t n_terms;  // <= 4
+    // accumulators of each term: the sum of splits[j] partial results, st_split elements apart (1: the accumulator itself)
     const int32_t* dw[4];
+    int32_t splits[4];
+    int64_t st_split;
     const float* s_g[4];
     const float* s_a[4];
     float lr;
     int32_t total_samples;
-    uint32_t* w_amax_bits;  // zeroed slot
-    // Optional, for tensors of at most UPDATE_MAX_BLOCKS workgroups (update_blocks() below): every workgroup stores its
-    // maximum here instead of meeting the others at w_amax_bits (hundreds of simultaneous atomics on one word cost
-    // more than the rest of a small update); the quantiser that follows takes the maximum of the array
-    // (QuantArgs::amax_n).
+    // every workgroup stores the maximum of its new weights here (thousands of atomics on one word cost more than the rest
+    // of an update); the quantiser that follows takes the maximum of the array (QuantArgs::amax_n)
     uint32_t* block_max;
+    int32_t max_blocks;   // words at block_max
 };
 constexpr int UPDATE_MAX_BLOCKS = 1024;
-int64_t update_blocks(int64_t N, int64_t K);   // workgroups launch_update starts for an [N, K] tensor
+int update_blocks(const UpdateArgs& a);   // workgroups launch_update starts
 hipError_t launch_update(const UpdateArgs& a, hipStream_t s);
 
 // ---- int8 contraction (gemm_i8.hip):  C[i][j] = sum_r P[i][r] * Q[j][r] -----------------------
@@ -250,9 +261,11 @@ struct GemmArgs {
     unsigned long long* gsum;
     int32_t* vmax;
     int32_t rows_per_sample, relu, rshift;
-    // batching over blockIdx.z
-    int32_t nb;
+    // nb problems in one launch: problem z = p * nc + c lies p strides st_* and c strides st_*2 further on (weight gradients:
+    // pass p, sample chunk c; elsewhere nc = 1)
+    int32_t nb, nc;
     int64_t st_p, st_q, st_c, st_g;
+    int64_t st_p2, st_q2, st_c2;
     // split reduction (blockIdx.y): split s stores its partial sums at C + s*st_split; launch_reduce_splits
     // adds them up (integer sums: exact and order-free).  1 = no split.  Not combined with the fused reductions.
     int32_t splits;
@@ -283,7 +296,8 @@ hipError_t launch_mfma_ceiling(int32_t* sink, int iters, int kind, unsigned long
 struct GemmPlan {
     int bm, bn, splits;
 };
-GemmPlan gemm_plan(int64_t I, int64_t J, int64_t R, int nb, bool allow_split);
+GemmPlan gemm_plan(int64_t I, int64_t J, int64_t R, int nb, bool allow_split, int lds_extra = 0);
+constexpr int GEMM_TABLE_BYTES = 2048;   // LDS the reduction-major loader (conv == 2) takes beside the operand stages
 int split_evenly(int64_t R, int64_t splits);   // at most `splits` shares of a reduction of R, none of them empty
 // out[z][e] = sum over s < splits of part[z][s][e], e < n (n a multiple of 4); strides in elements
 hipError_t launch_reduce_splits(const int32_t* part, int splits, int64_t st_split, int64_t st_part_z, int32_t* out,

@@ -174,9 +174,10 @@ __global__ __launch_bounds__(WM* WN * 64) void k_gemm_nt_i8(GemmArgs a)
     if (a.clk) pht = clock64();
     const int z = t / tiles_z, tz = t - z * tiles_z;
     const int bi = tz % tiles_i, bj = tz / tiles_i;
-    const int8_t* __restrict__ P = a.P + z * a.st_p;
-    const int8_t* __restrict__ Q = a.Q + z * a.st_q;
-    int32_t* __restrict__ C = a.C + z * a.st_c;
+    const int zp = EPI ? z : z / a.nc, zc = EPI ? 0 : z - zp * a.nc;
+    const int8_t* __restrict__ P = a.P + zp * a.st_p + zc * a.st_p2;
+    const int8_t* __restrict__ Q = a.Q + zp * a.st_q + zc * a.st_q2;
+    int32_t* __restrict__ C = a.C + zp * a.st_c + zc * a.st_c2;
     const int i0 = bi * BM, j0 = bj * BN;
     if (MODE == 2) C += (int64_t)blockIdx.y * a.st_split;
 
@@ -418,10 +419,11 @@ __global__ __launch_bounds__(WM* WN * 64) void k_gemm_nt_i8(GemmArgs a)
     if (PREFETCH && t + (int)gridDim.x < ntiles) {
         const int tn = t + (int)gridDim.x;
         const int zn = tn / tiles_z, tzn = tn - zn * tiles_z;
+        const int znp = EPI ? zn : zn / a.nc, znc = EPI ? 0 : zn - znp * a.nc;
         const int i0n = (tzn % tiles_i) * BM, j0n = (tzn / tiles_i) * BN;
         if (CONV == 1) {
             // the pixel offsets of the current tile are not needed any more: those of the next one take their place
-            rp = __builtin_amdgcn_make_buffer_rsrc((void*)(a.P + zn * a.st_p), 0, (int)a.p_bytes, 0x00020000);
+            rp = __builtin_amdgcn_make_buffer_rsrc((void*)(a.P + znp * a.st_p), 0, (int)a.p_bytes, 0x00020000);
 #pragma unroll
             for (int s = 0; s < CH_P; ++s) {
                 const int m = i0n + ((s * T + tid) >> 3);
@@ -432,9 +434,9 @@ __global__ __launch_bounds__(WM* WN * 64) void k_gemm_nt_i8(GemmArgs a)
                 offP[s] = ((b * a.H + hi0[s]) * a.W + wi0[s]) * a.cpitch;
             }
         } else {
-            rp = __builtin_amdgcn_make_buffer_rsrc((void*)(a.P + zn * a.st_p + (int64_t)i0n * a.ldp), 0, (int)(min(BM, a.I - i0n) * a.ldp), 0x00020000);
+            rp = __builtin_amdgcn_make_buffer_rsrc((void*)(a.P + znp * a.st_p + znc * a.st_p2 + (int64_t)i0n * a.ldp), 0, (int)(min(BM, a.I - i0n) * a.ldp), 0x00020000);
         }
-        rq = __builtin_amdgcn_make_buffer_rsrc((void*)(a.Q + zn * a.st_q + (int64_t)j0n * a.ldq), 0, (int)(min(BN, a.J - j0n) * a.ldq), 0x00020000);
+        rq = __builtin_amdgcn_make_buffer_rsrc((void*)(a.Q + znp * a.st_q + znc * a.st_q2 + (int64_t)j0n * a.ldq), 0, (int)(min(BN, a.J - j0n) * a.ldq), 0x00020000);
         issue(0, 0);
         prefetched = true;
         wait_copies = true;
@@ -667,7 +669,7 @@ static hipError_t launch_cfg(const GemmArgs& a, hipStream_t s)
 //    quarters of the MFMA work) and tall only if that still leaves about two workgroups per compute unit.
 //  * allow_split (weight gradients): when the output alone has too few tiles -- a convolution's weight
 //    gradient has few output elements and a very long reduction -- a split reduction fills the chip.
-GemmPlan gemm_plan(int64_t I, int64_t J, int64_t R, int nb, bool allow_split)
+GemmPlan gemm_plan(int64_t I, int64_t J, int64_t R, int nb, bool allow_split, int lds_extra)
 {
     GemmPlan p;
     p.splits = 1;
@@ -693,9 +695,9 @@ GemmPlan gemm_plan(int64_t I, int64_t J, int64_t R, int nb, bool allow_split)
         // splitting the reduction: about two workgroups per compute unit, never more (a third partial round
         // would idle most of the chip), at least 16 reduction steps per split.
         p.bm = edge(I);
-        // (a 256 x 256 tile takes 128 KB of LDS, one workgroup per compute unit: one round of 256 workgroups, each with
-        // twice the reduction steps, writes and re-reads half the partial sums of two rounds of 512)
-        int64_t sp = (p.bm == 256 && p.bn == 256 ? FF_SPLIT_TARGET_BIG : 512) / tiles(p.bm, p.bn);
+        // (a tile whose stages take more than half of the LDS has one workgroup per compute unit: one round of 256
+        // workgroups, each with twice the reduction steps, writes and re-reads half the partial sums of two rounds of 512)
+        int64_t sp = (2 * (p.bm + p.bn) * BK + lds_extra > 80 * 1024 ? FF_SPLIT_TARGET_BIG : 512) / tiles(p.bm, p.bn);
         // ... (8 where one partial result is small, at most 256 KB: writing and adding up the partials then costs little)
         const int64_t min_steps = I * J * 4 <= (256 << 10) ? 8 : 16;
         if (sp > nk / min_steps) sp = nk / min_steps;
@@ -788,6 +790,8 @@ hipError_t launch_reduce_splits(const int32_t* part, int splits, int64_t st_spli
 hipError_t launch_gemm_nt_i8(const GemmArgs& a_in, hipStream_t s)
 {
     GemmArgs a = a_in;   // (the loaders' shift counts are filled in below)
+    if (a.nc < 1) a.nc = 1;
+    if (a.nc > 1 && (a.gsum || a.conv == 1 || a.nb % a.nc != 0)) return hipErrorInvalidValue;
     if (a.I <= 0 || a.J <= 0) return hipSuccess;
     // byte offsets of the operand copies are 32-bit (tile-relative for dense operands, tensor-relative for conv)
     if (a.ldp >= (int64_t(1) << 22) || a.ldq >= (int64_t(1) << 22)) return hipErrorInvalidValue;
@@ -813,7 +817,7 @@ hipError_t launch_gemm_nt_i8(const GemmArgs& a_in, hipStream_t s)
         return sh;
     };
     a.cin_shift = a.conv == 1 ? shift_of(a.Cin) : -1;
-    GemmPlan p = gemm_plan(a.I, a.J, a.R, a.nb, a.splits > 1);
+    const GemmPlan p = gemm_plan(a.I, a.J, a.R, a.nb, a.splits > 1, a.conv == 2 ? GEMM_TABLE_BYTES : 0);
     const int bm = p.bm, bn = p.bn;
     if (bn == 256) {
         if (bm == 256) return launch_cfg<256, 256, 4, 2>(a, s);

@@ -8,7 +8,7 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 from oracle import ff_oracle as O  # noqa: E402
-from workloads import Layer  # noqa: E402
+from workloads import Layer, Workload, conv_stack, mlp  # noqa: E402
 
 
 @pytest.fixture(scope="module")
@@ -21,6 +21,7 @@ def ff():
 
 
 from gpu_util import check_q, dev, empty32, empty8, pad32, pad8, pad_nhwc, scalar, workspace  # noqa: E402
+from test_gpu_parity import _matched_thetas, _run_steps  # noqa: E402
 
 
 @pytest.mark.parametrize("relu", [1, 0])
@@ -111,3 +112,20 @@ def test_handoff_and_local_gradient_codes_over_rows_per_sample(ff, rps, N, B, l2
     assert s.item() == s_ref
     check_q(q, q_ref, "hand-off codes")
     check_q(q_t, q_ref.T, "transposed hand-off codes")
+
+
+@pytest.mark.parametrize("channels,side,B", [
+    ([3, 16, 20], 32, 8),      # a few splits, summed by the update one thread per group
+    ([3, 16, 20], 32, 40),     # many splits of small outputs: sixteen lanes per group
+    ([3, 8, 10], 24, 256),     # two equal sample chunks in one launch, rows that are no multiple of four
+    ([1, 16, 7], 32, 140),     # two chunks of different sizes, one launch each
+    ([2, 12], 28, 11)])
+def test_step_with_split_and_chunked_weight_gradients(ff, channels, side, B):
+    wl = Workload("split", conv_stack(channels, side, side), B, "uniform_onehot", lam=0.05)
+    _run_steps(ff, wl, 1, theta_layer=_matched_thetas(wl), live=True)
+
+
+@pytest.mark.parametrize("widths,B", [([33, 37, 30, 41], 70), ([130, 257, 66], 300)])
+def test_chain_step_with_ragged_widths(ff, widths, B):
+    wl = Workload("chain", mlp(widths, False), B, "normal", lam=0.3)
+    _run_steps(ff, wl, 2, lookahead="chain", theta_layer=_matched_thetas(wl))
