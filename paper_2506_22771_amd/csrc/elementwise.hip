@@ -148,20 +148,20 @@ __device__ __forceinline__ uint4 ld_stream16(const void* p)
 }
 
 constexpr int QT_THREADS = 256;
-// Tile of one workgroup: CB column blocks of four columns, 2 x (256 / CB) row blocks of four rows: 128 x 64 elements
+// Tile of one workgroup: CB column blocks of four columns, U x (256 / CB) row blocks of four rows: 128 x 64 elements
 // for CB = 16, 256 x 32 for CB = 8 (matrices of at most 32 columns: no idle column lanes, and with a row pitch of
-// 32 columns or fewer the tile is one contiguous span of memory).
-template <int CB> struct QTile {
+// 32 columns or fewer the tile is one contiguous span of memory), both for U = 2.
+template <int CB, int U> struct QTile {
     static constexpr int COLS = 4 * CB;
-    static constexpr int RH = 4 * (QT_THREADS / CB);   // rows of one half tile (u = 0 / 1)
-    static constexpr int ROWS = 2 * RH;
+    static constexpr int RH = 4 * (QT_THREADS / CB);   // rows of one part of the tile (u < U)
+    static constexpr int ROWS = U * RH;
     static constexpr int LDW = ROWS / 4 + 1;           // words per column in the transposed LDS tile (+1: bank spread)
     static constexpr int CHUNKS = ROWS / 16;           // 16-byte pieces of one transposed column
 };
 
-// Each thread owns two 4x4 element blocks (rows 4*rb+j, cols 4*cb+c).  Codes are packed four columns
+// Each thread owns U 4x4 element blocks (rows 4*rb+j, cols 4*cb+c).  Codes are packed four columns
 // to a word for q, byte-transposed in registers for q_t and regrouped through LDS so that q_t is
-// written in 16-byte pieces.  All eight 16-byte loads of a thread are issued before any arithmetic.
+// written in 16-byte pieces.  All 4 U 16-byte loads of a thread are issued before any arithmetic.
 // FORM 0: element loads (an fp32 source whose columns or base are not 16-byte friendly).  1: 16-byte loads (always legal
 // for the int32 sources).  2: 16-byte loads and cols % 4 == 0, so that four neighbours share a hash head (sr_mix4).
 // Tensors have fewer than 2^32 elements (checked by the entry points), so the low word of the element index is the
@@ -170,10 +170,10 @@ template <int CB> struct QTile {
 // gradient, of which the hash takes 14).  Hence: whole tiles take a body without bounds checks, row pointers advance by
 // additions, and the sample of a row comes from one 32-bit division per four rows (local gradient of 2 x 8192 x 4096:
 // 71 -> 64 us, 5.2 TB/s; 144 channels at 32x32, 512 images: 84 -> 72 us; 2 x 1024 x 2000: 16 -> 12 us).
-template <int SRC, bool STOCH, int FORM, int CB, bool WHOLE>
+template <int SRC, bool STOCH, int FORM, int CB, int U, bool WHOLE>
 __device__ __forceinline__ void quantize_tile(const QuantArgs& a, uint32_t* tileT)
 {
-    constexpr int QT_ROWS = QTile<CB>::ROWS, QT_COLS = QTile<CB>::COLS, QT_LDW = QTile<CB>::LDW, QT_RH = QTile<CB>::RH;
+    constexpr int QT_ROWS = QTile<CB, U>::ROWS, QT_COLS = QTile<CB, U>::COLS, QT_LDW = QTile<CB, U>::LDW, QT_RH = QTile<CB, U>::RH;
     constexpr bool F32SRC = SRC == QSRC_F32 || SRC == QSRC_F32_GRAD;   // the source is an fp32 tensor
     const int z = blockIdx.z;
     const float* __restrict__ per_sample = a.per_sample ? a.per_sample + z * a.st_per_sample : nullptr;
@@ -201,14 +201,14 @@ __device__ __forceinline__ void quantize_tile(const QuantArgs& a, uint32_t* tile
     const bool col_in = WHOLE || col < a.cols;
     auto row_in = [&](int dr) { return WHOLE || rowb + dr < a.rows; };
 
-    // ---- loads: 2 blocks x 4 rows x 16 bytes, raw bits.  Row (u, j) of this thread is rowb + QT_RH*u + j.
+    // ---- loads: U blocks x 4 rows x 16 bytes, raw bits.  Row (u, j) of this thread is rowb + QT_RH*u + j.
     const int64_t ld = F32SRC ? a.cols : a.ldacc;
     const uint32_t* __restrict__ src =
         (F32SRC ? (const uint32_t*)(a.x + z * a.st_x) : (const uint32_t*)(a.acc + z * a.st_acc)) + rowb * ld + col;
-    uint32_t raw[2][4][4];
+    uint32_t raw[U][4][4];
     const bool ragged = FORM == 1 && (a.cols & 3) != 0;   // the int32 sources' pad columns hold junk: mask them at load
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
+    for (int u = 0; u < U; ++u) {
         const uint32_t* __restrict__ ps = src + (u ? (int64_t)QT_RH * ld : 0);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -236,11 +236,11 @@ __device__ __forceinline__ void quantize_tile(const QuantArgs& a, uint32_t* tile
     // ---- per-row factor (local gradients: 2*coeff; normalised hand-off: sqrt(goodness) and its reciprocal)
     constexpr bool GRAD = SRC == QSRC_GRAD || SRC == QSRC_F32_GRAD;
     const bool norm = SRC == QSRC_HANDOFF && a.l2norm;
-    float rowf[2][4];
+    float rowf[U][4];
     if (GRAD || norm) {
         const uint32_t rps = (uint32_t)a.rows_per_sample;
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
+        for (int u = 0; u < U; ++u) {
             const uint32_t rfirst = (uint32_t)rowb + QT_RH * u;
             uint32_t smp = rfirst, rem = 0;
             if (rps != 1) {
@@ -254,7 +254,7 @@ __device__ __forceinline__ void quantize_tile(const QuantArgs& a, uint32_t* tile
             }
         }
 #pragma unroll
-        for (int u = 0; u < 2; ++u)
+        for (int u = 0; u < U; ++u)
 #pragma unroll
             for (int j = 0; j < 4; ++j) rowf[u][j] = GRAD ? 2.0f * rowf[u][j] : sqrtf(rowf[u][j]);
     }
@@ -275,7 +275,7 @@ __device__ __forceinline__ void quantize_tile(const QuantArgs& a, uint32_t* tile
     const uint32_t idx0 = (uint32_t)rowb * (uint32_t)a.cols + (uint32_t)col;   // element index of (row rowb, col)
     int8_t* __restrict__ pq0 = q ? q + rowb * a.ldq + col : nullptr;
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
+    for (int u = 0; u < U; ++u) {
         uint32_t rowpack[4];
         uint32_t idx = idx0 + (uint32_t)(QT_RH * u) * (uint32_t)a.cols;
         int8_t* __restrict__ pq = pq0 + (u ? (int64_t)QT_RH * a.ldq : 0);
@@ -336,9 +336,9 @@ __device__ __forceinline__ void quantize_tile(const QuantArgs& a, uint32_t* tile
     if (q_t) {
         __syncthreads();
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
+        for (int u = 0; u < U; ++u) {
             const int e = t + QT_THREADS * u;
-            const int cl = e / QTile<CB>::CHUNKS, ch = e % QTile<CB>::CHUNKS;
+            const int cl = e / QTile<CB, U>::CHUNKS, ch = e % QTile<CB, U>::CHUNKS;
             const int64_t oc = c0 + cl;
             const int64_t orow = r0 + 16 * ch;
             if ((WHOLE || oc < a.cols) && orow < a.ldqt) {
@@ -356,34 +356,54 @@ __device__ __forceinline__ void quantize_tile(const QuantArgs& a, uint32_t* tile
     }
 }
 
-template <int SRC, bool STOCH, int FORM, int CB = 16>
+template <int SRC, bool STOCH, int FORM, int CB, int U>
 __global__ __launch_bounds__(QT_THREADS) void k_quantize(QuantArgs a)
 {
-    __shared__ uint32_t tileT[QTile<CB>::COLS * QTile<CB>::LDW];
-    const bool whole = (int64_t)(blockIdx.y + 1) * QTile<CB>::ROWS <= a.rows && (int64_t)(blockIdx.x + 1) * QTile<CB>::COLS <= a.cols;
-    if (whole) quantize_tile<SRC, STOCH, FORM, CB, true>(a, tileT);
-    else quantize_tile<SRC, STOCH, FORM, CB, false>(a, tileT);
+    __shared__ uint32_t tileT[QTile<CB, U>::COLS * QTile<CB, U>::LDW];
+    const bool whole = (int64_t)(blockIdx.y + 1) * QTile<CB, U>::ROWS <= a.rows &&
+                       (int64_t)(blockIdx.x + 1) * QTile<CB, U>::COLS <= a.cols;
+    if (whole) quantize_tile<SRC, STOCH, FORM, CB, U, true>(a, tileT);
+    else quantize_tile<SRC, STOCH, FORM, CB, U, false>(a, tileT);
+}
+
+template <int SRC, bool STOCH, int FORM, int CB, int U>
+static void launch_quantize_tiles(const QuantArgs& a, int64_t span, hipStream_t s)
+{
+    // (row tiles up to the row pitch of q_t, for the same reason)
+    const int64_t rspan = a.q_t && a.ldqt > a.rows ? a.ldqt : a.rows;
+    const dim3 grid((unsigned)((span + QTile<CB, U>::COLS - 1) / QTile<CB, U>::COLS),
+                    (unsigned)((rspan + QTile<CB, U>::ROWS - 1) / QTile<CB, U>::ROWS), (unsigned)a.nb);
+    hipLaunchKernelGGL((k_quantize<SRC, STOCH, FORM, CB, U>), grid, dim3(QT_THREADS), 0, s, a);
 }
 
 template <int SRC, bool STOCH>
 static void launch_quantize_t(const QuantArgs& a, hipStream_t s)
 {
-    const dim3 block(QT_THREADS);
     constexpr bool F32SRC = SRC == QSRC_F32 || SRC == QSRC_F32_GRAD;
+    constexpr int GENERAL = F32SRC ? 0 : 1;
     const bool cols4 = (a.cols & 3) == 0;
     const bool vec = !F32SRC || (cols4 && (((uintptr_t)a.x) & 15) == 0 && ((a.st_x & 3) == 0 || a.nb == 1));
-    if (a.cols <= QTile<8>::COLS && vec) {
-        const dim3 grid(1, (unsigned)((a.rows + QTile<8>::ROWS - 1) / QTile<8>::ROWS), (unsigned)a.nb);
-        if (cols4) hipLaunchKernelGGL((k_quantize<SRC, STOCH, 2, 8>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((k_quantize<SRC, STOCH, 1, 8>), grid, block, 0, s, a);
-        return;
-    }
+    const bool narrow = a.cols <= QTile<8, 2>::COLS && vec;
     // (column tiles up to the row pitch of q, so that its pad bytes are written too: zeros)
     const int64_t span = a.q && a.ldq > a.cols ? a.ldq : a.cols;
-    const dim3 grid((unsigned)((span + QTile<16>::COLS - 1) / QTile<16>::COLS),
-                    (unsigned)((a.rows + QTile<16>::ROWS - 1) / QTile<16>::ROWS), (unsigned)a.nb);
-    if (vec && cols4) hipLaunchKernelGGL((k_quantize<SRC, STOCH, 2>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((k_quantize<SRC, STOCH, F32SRC ? 0 : 1>), grid, block, 0, s, a);
+    // Tensors that would give a compute unit fewer than eight tiles of two blocks per thread are bound by the latency of one
+    // wavefront's chain (loads, hash, stores), not by HBM: half the tile, twice the wavefronts.  (Steps of 784-2000^4 at
+    // 1024 samples 302 -> 290 us, 1000-1500^2-1001 with the chain 284 -> 267 us; lines at 4 and 16 measure the same.)
+    constexpr int64_t Q_FEW = 8;
+    const int64_t tiles = narrow ? (a.rows + QTile<8, 2>::ROWS - 1) / QTile<8, 2>::ROWS
+                                 : ((span + QTile<16, 2>::COLS - 1) / QTile<16, 2>::COLS) * ((a.rows + QTile<16, 2>::ROWS - 1) / QTile<16, 2>::ROWS);
+    const bool few = tiles * a.nb < Q_FEW * num_cus() && (a.rows + 127) / QTile<16, 1>::ROWS < 65535;   // (grid.y)
+    if (narrow) {
+        if (cols4 && few) launch_quantize_tiles<SRC, STOCH, 2, 8, 1>(a, QTile<8, 1>::COLS, s);
+        else if (cols4) launch_quantize_tiles<SRC, STOCH, 2, 8, 2>(a, QTile<8, 2>::COLS, s);
+        else launch_quantize_tiles<SRC, STOCH, 1, 8, 2>(a, QTile<8, 2>::COLS, s);
+    } else if (vec && cols4) {
+        if (few) launch_quantize_tiles<SRC, STOCH, 2, 16, 1>(a, span, s);
+        else launch_quantize_tiles<SRC, STOCH, 2, 16, 2>(a, span, s);
+    } else {
+        if (few) launch_quantize_tiles<SRC, STOCH, GENERAL, 16, 1>(a, span, s);
+        else launch_quantize_tiles<SRC, STOCH, GENERAL, 16, 2>(a, span, s);
+    }
 }
 
 hipError_t launch_quantize(int src, const QuantArgs& a, hipStream_t s)
@@ -801,10 +821,10 @@ __global__ __launch_bounds__(QT_THREADS) void k_transpose_i8(const int8_t* __res
                                                              int64_t K, int64_t ldq, int64_t ldqt,
                                                              const float* __restrict__ s_in, float* __restrict__ s_out)
 {
-    constexpr int LDW = QTile<16>::LDW, RH = QTile<16>::RH, CHUNKS = QTile<16>::CHUNKS;
-    __shared__ uint32_t tileT[QTile<16>::COLS * LDW];
+    constexpr int LDW = QTile<16, 2>::LDW, RH = QTile<16, 2>::RH, CHUNKS = QTile<16, 2>::CHUNKS;
+    __shared__ uint32_t tileT[QTile<16, 2>::COLS * LDW];
     const int t = threadIdx.x, cb = t & 15, rg = t >> 4;
-    const int64_t r0 = (int64_t)blockIdx.y * QTile<16>::ROWS, c0 = (int64_t)blockIdx.x * QTile<16>::COLS;
+    const int64_t r0 = (int64_t)blockIdx.y * QTile<16, 2>::ROWS, c0 = (int64_t)blockIdx.x * QTile<16, 2>::COLS;
     if (blockIdx.x == 0 && blockIdx.y == 0 && t == 0) s_out[0] = s_in[0];
     const int64_t col = c0 + 4 * cb;
     uint32_t w[2][4];
@@ -841,7 +861,7 @@ __global__ __launch_bounds__(QT_THREADS) void k_transpose_i8(const int8_t* __res
 hipError_t launch_transpose_i8(const int8_t* q, int8_t* q_t, int64_t N, int64_t K, const float* s_in, float* s_out, hipStream_t s)
 {
     if (N <= 0 || K <= 0) return hipSuccess;
-    const dim3 grid((unsigned)((K + QTile<16>::COLS - 1) / QTile<16>::COLS), (unsigned)((N + QTile<16>::ROWS - 1) / QTile<16>::ROWS));
+    const dim3 grid((unsigned)((K + QTile<16, 2>::COLS - 1) / QTile<16, 2>::COLS), (unsigned)((N + QTile<16, 2>::ROWS - 1) / QTile<16, 2>::ROWS));
     hipLaunchKernelGGL(k_transpose_i8, grid, dim3(QT_THREADS), 0, s, q, q_t, N, K, pitch8(K), pitch8(N), s_in, s_out);
     return hipGetLastError();
 }

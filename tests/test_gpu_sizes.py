@@ -129,3 +129,18 @@ def test_step_with_split_and_chunked_weight_gradients(ff, channels, side, B):
 def test_chain_step_with_ragged_widths(ff, widths, B):
     wl = Workload("chain", mlp(widths, False), B, "normal", lam=0.3)
     _run_steps(ff, wl, 2, lookahead="chain", theta_layer=_matched_thetas(wl))
+
+
+@pytest.mark.parametrize("rows,cols", [(20000, 1001), (20001, 1000), (600001, 32), (530000, 20), (70, 24), (129, 31), (65, 68), (63, 1025)])
+@pytest.mark.parametrize("mode", [0, 1])
+def test_quantize_tile_sizes(ff, rows, cols, mode):
+    """Tensors with few and with many quantiser tiles, narrow ones among them, whole and ragged columns."""
+    rng = np.random.default_rng(rows + cols)
+    x = rng.standard_normal((rows, cols), dtype=np.float32)
+    q_ref, s_ref = O.quantize(x, mode, 5, 77)
+    q, q_t, s = empty8(rows, cols), empty8(cols, rows), scalar()
+    ff.ff_quantize(dev(x), rows, cols, mode, 5, 77, q, q_t, s, workspace())
+    torch.cuda.synchronize()
+    assert s.item() == s_ref
+    check_q(q, q_ref, "q")
+    check_q(q_t, q_ref.T, "q_t")
