@@ -811,8 +811,7 @@ ff_status ff_layer_forward(const ff_layer_desc* layer, const int8_t* a_q, const 
     }
     hipStream_t s = (hipStream_t)stream;
     if (d.B == 0) return FF_OK;
-    HIPCHK_T(FF_K_SMALL, launch_fill_u32((uint32_t*)gsum_int, 2 * d.B, 0u, s));
-    HIPCHK_T(FF_K_SMALL, launch_fill_u32((uint32_t*)vmax, d.B, 0u, s));
+    HIPCHK_T(FF_K_SMALL, launch_clear2_u32((uint32_t*)gsum_int, 2 * d.B, (uint32_t*)vmax, d.B, s));
     int8_t* col = need_col ? (int8_t*)ws + FF_WS_MIN_BYTES : nullptr;
     return run_forward(d, layer->relu ? 1 : 0, a_q, 0, w_q, acc, 0, (unsigned long long*)gsum_int, vmax, 0, col, 0, 1, s);
 }
@@ -1268,9 +1267,15 @@ static ff_status train_step_impl(const ff_net_desc* net, const ff_net_state* sta
         HIPCHK_T(FF_K_FUSED, launch_fused_dense_step(fa, w.fused_wgs, s));
         return FF_OK;
     }
-    HIPCHK_T(FF_K_SMALL, launch_fill_u32((uint32_t*)base, (int64_t)(w.zero_bytes / 4), 0u, s));
     uint32_t* const xmax = (uint32_t*)(base + w.off_xmax);
-    HIPCHK_T(FF_K_ABSMAX, launch_absmax(x_pos, st_x, 2, n_in, xmax, s));
+    HIPCHK_T(FF_K_ABSMAX, launch_absmax(x_pos, st_x, 2, n_in, xmax, s, (uint32_t*)base, (int64_t)(w.zero_bytes / 4)));
+    // Small batches: one kernel forms every layer's goodness, loss and coefficients after the forward pass, and the hand-off
+    // quantisers take their range from the per-sample maxima.  Each of their workgroups reads all samples of the pass
+    // (256 threads: a few loads each; with normalisation also a square root and a division per sample), which for larger
+    // batches costs more than the launch per layer it saves.
+    bool normalised = false;
+    for (int i = 0; i < k; ++i) normalised = normalised || net->layers[i].l2norm_out;
+    const bool goodness_last = B <= (normalised ? 1024 : 4096);
 
     // ---- streams: the caller's, plus the library's own where the step runs independent work side by side
     hipStream_t lane_stream[MAX_LANES];
@@ -1339,6 +1344,13 @@ static ff_status train_step_impl(const ff_net_desc* net, const ff_net_state* sta
             }
             a.relu = Lp.relu ? 1 : 0;
             a.l2norm = Lp.l2norm_out ? 1 : 0;
+            if (goodness_last) {
+                a.vmax = vmax + (int64_t)j * 2 * B;
+                a.gsum = gsum + (int64_t)j * 2 * B;
+                a.B = (int32_t)B;
+                a.rshift = goodness_shift(dp.K, dp.rps * dp.N);
+                a.st_b = B;
+            }
         }
         a.amax_bits = d.src < 0 ? xmax : out_amax + 2 * (d.src + 1);
         a.st_amax = d.src < 0 ? ABSMAX_MAX_BLOCKS : 1;
@@ -1366,7 +1378,7 @@ static ff_status train_step_impl(const ff_net_desc* net, const ff_net_state* sta
         a.nb = 2;
         const bool plain = d.role == FF_ROLE_LAYER && d.skip == FF_SKIP_NONE;   // goodness straight from the accumulators
         ff_status fs = [&]() -> ff_status {
-            if (d.role == FF_ROLE_PROJECTION) {
+            if (d.role == FF_ROLE_PROJECTION && !goodness_last) {
                 // no activity of its own: zero coefficients (nothing enters the look-ahead sums), zero loss / goodness rows
                 // (on the projection's own stream: nothing reads them before the look-ahead kernel)
                 HIPCHK_T(FF_K_SMALL, launch_fill_u32((uint32_t*)(c + (int64_t)i * 2 * B), 2 * B, 0u, s));
@@ -1440,6 +1452,7 @@ static ff_status train_step_impl(const ff_net_desc* net, const ff_net_state* sta
             HIPCHK_T(FF_K_RESIDUAL, launch_goodness_fx(fa, s));
         }
 
+        if (goodness_last) continue;
         GoodnessArgs ga;
         memset(&ga, 0, sizeof(ga));
         ga.gsum = gsum + (int64_t)i * 2 * B;
@@ -1468,7 +1481,31 @@ static ff_status train_step_impl(const ff_net_desc* net, const ff_net_state* sta
     if (proj_pending && hipStreamWaitEvent(s_main, pool->join[0], 0) != hipSuccess) return FF_ERR_HIP;
 
     // ---- look-ahead coefficients of every layer (Eq. (3)/(4)) and the absmax of every local gradient
-    if (!w.chain) {
+    if (goodness_last) {
+        GoodnessAllArgs ga;
+        memset(&ga, 0, sizeof(ga));
+        ga.k = k;
+        ga.B = B;
+        ga.lambda = w.chain ? 0.0f : lambda;   // (the chain combines the layers' own coefficients)
+        ga.gsum = gsum;
+        ga.vmax = vmax;
+        ga.s_a = s_a;
+        ga.out_amax = out_amax;
+        ga.goodness = goodness;
+        ga.coeff = c;
+        ga.coeff_total = ct;
+        ga.loss = loss;
+        ga.g_amax_bits = g_amax;
+        for (int i = 0; i < k; ++i) {
+            const Dims& d = w.d[i];
+            ga.L[i].s_w = state->s_w[i];
+            ga.L[i].theta = net->theta_layer ? net->theta_layer[i] : theta;
+            ga.L[i].rshift = goodness_shift(d.K, d.rps * d.N);
+            ga.L[i].fx = d.skip != FF_SKIP_NONE;
+            ga.L[i].projection = d.role == FF_ROLE_PROJECTION;
+        }
+        HIPCHK_T(FF_K_SMALL, launch_goodness_all(ga, s));
+    } else if (!w.chain) {
         LookaheadArgs la;
         memset(&la, 0, sizeof(la));
         la.coeff = c;
@@ -1645,7 +1682,8 @@ static ff_status train_step_impl(const ff_net_desc* net, const ff_net_state* sta
             QuantArgs a;
             memset(&a, 0, sizeof(a));
             if (top) {
-                HIPCHK_T(FF_K_SMALL, launch_grad_amax(c + (int64_t)i * 2 * B, vmax + (int64_t)i * 2 * B, s_a + 2 * i,
+                if (!goodness_last)
+                    HIPCHK_T(FF_K_SMALL, launch_grad_amax(c + (int64_t)i * 2 * B, vmax + (int64_t)i * 2 * B, s_a + 2 * i,
                                                       state->s_w[i], B, 2, g_amax + 2 * i, s));
                 qsrc = QSRC_GRAD;
                 a.acc = ca.acc;

@@ -102,6 +102,16 @@ __device__ __forceinline__ float div_by_reciprocal(float v, float d, float y)
     return __builtin_fmaf(__builtin_fmaf(-q, d, v), y, q);
 }
 
+// goodness of a sample from its integer sum: G = fp32(((fp64(sum) * 2^r) * s_y) * s_y)
+__device__ __forceinline__ float goodness_value(unsigned long long gs, double pow2r, double s_yd)
+{
+    double g = (double)gs;
+    g = g * pow2r;
+    g = g * s_yd;
+    g = g * s_yd;
+    return (float)g;
+}
+
 // exp(z) for z <= 0 with a fixed operation sequence (it feeds the gradient quantiser through the sigmoid)
 __device__ __forceinline__ float exp_nonpos(float z)
 {
@@ -121,5 +131,17 @@ __device__ __forceinline__ float exp_nonpos(float z)
     p = __builtin_fmaf(p, r, 1.0f);
     return ldexpf(p, (int)kf);
 }
+
+// dL/dG of one sample (Eq. (1): sign > 0, Eq. (2): sign < 0) from x = G - theta; xs: the argument of the softplus loss
+__device__ __forceinline__ float loss_derivative(float x, int sign, float& xs)
+{
+    const float e = exp_nonpos(-fabsf(x));
+    const float den = 1.0f + e;
+    const float sig_big = 1.0f / den, sig_small = e / den;
+    xs = sign > 0 ? -x : x;
+    return sign > 0 ? -(x >= 0.0f ? sig_small : sig_big) : (x >= 0.0f ? sig_big : sig_small);
+}
+// softplus; it feeds no quantiser, so any accurate exp / log1p will do
+__device__ __forceinline__ float loss_term(float xs) { return fmaxf(xs, 0.0f) + log1pf(expf(-fabsf(xs))); }
 
 }  // namespace ffi

@@ -64,6 +64,22 @@ hipError_t launch_fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t s)
     return hipGetLastError();
 }
 
+__global__ void k_clear2_u32(uint32_t* p, int64_t n, uint32_t* p2, int64_t n2)
+{
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n + n2; i += stride)
+        if (i < n) p[i] = 0u;
+        else p2[i - n] = 0u;
+}
+
+hipError_t launch_clear2_u32(uint32_t* p, int64_t n, uint32_t* p2, int64_t n2, hipStream_t s)
+{
+    if (n + n2 <= 0) return hipSuccess;
+    const int64_t blocks = min((n + n2 + 255) / 256, (int64_t)2048);
+    hipLaunchKernelGGL(k_clear2_u32, dim3((unsigned)blocks), dim3(256), 0, s, p, n, p2, n2);
+    return hipGetLastError();
+}
+
 __global__ void k_advance_u64(uint64_t* counter)
 {
     if (threadIdx.x == 0 && blockIdx.x == 0) counter[0] += 1;
@@ -95,8 +111,12 @@ __device__ __forceinline__ float4 ldf4(const float4* p)   // streaming hint: the
 
 constexpr int ABS_THREADS = 512;
 __global__ __launch_bounds__(ABS_THREADS) void k_absmax_f32(const float* __restrict__ x0, int64_t st_x, int64_t n,
-                                                            uint32_t* __restrict__ part)
+                                                            uint32_t* __restrict__ part, uint32_t* __restrict__ clear,
+                                                            int64_t clear_n)
 {
+    for (int64_t i = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * ABS_THREADS + threadIdx.x; i < clear_n;
+         i += (int64_t)gridDim.x * gridDim.y * ABS_THREADS)
+        clear[i] = 0u;
     const float* __restrict__ x = x0 + (int64_t)blockIdx.y * st_x;
     // scalar head until 16-byte alignment, float4 body, scalar tail
     const uintptr_t addr = (uintptr_t)x;
@@ -128,10 +148,12 @@ int absmax_blocks(int64_t n)
     return (int)max((int64_t)1, min((int64_t)ABSMAX_MAX_BLOCKS, blocks));
 }
 
-hipError_t launch_absmax(const float* x, int64_t st_x, int nb, int64_t n, uint32_t* part, hipStream_t s)
+hipError_t launch_absmax(const float* x, int64_t st_x, int nb, int64_t n, uint32_t* part, hipStream_t s, uint32_t* clear,
+                         int64_t clear_n)
 {
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_absmax_f32, dim3((unsigned)absmax_blocks(n), (unsigned)nb), dim3(ABS_THREADS), 0, s, x, st_x, n, part);
+    if (n <= 0) return launch_fill_u32(clear, clear_n, 0u, s);
+    hipLaunchKernelGGL(k_absmax_f32, dim3((unsigned)absmax_blocks(n), (unsigned)nb), dim3(ABS_THREADS), 0, s, x, st_x, n, part,
+                       clear, clear_n);
     return hipGetLastError();
 }
 
@@ -181,7 +203,7 @@ __device__ __forceinline__ void quantize_tile(const QuantArgs& a, uint32_t* tile
     int8_t* __restrict__ q_t = a.q_t ? a.q_t + z * a.st_qt : nullptr;
 
     // a vanishing range (absmax < 2^-100, all-zero tensor included) quantises to zero codes with scale 1
-    uint32_t amax_word = a.amax_bits[z * a.st_amax];
+    uint32_t amax_word = a.amax_bits ? a.amax_bits[z * a.st_amax] : 0u;
     if (a.amax_n > 1) {   // (uniform) the producer left one candidate per workgroup
         __shared__ uint32_t amx[QT_THREADS / 64];
         uint32_t mm = 0;
@@ -190,6 +212,27 @@ __device__ __forceinline__ void quantize_tile(const QuantArgs& a, uint32_t* tile
         if ((threadIdx.x & 63) == 0) amx[threadIdx.x >> 6] = mm;
         __syncthreads();
         amax_word = max(max(amx[0], amx[1]), max(amx[2], amx[3]));
+    }
+    float s_y = 1.0f;
+    if (!F32SRC) s_y = a.s_a[z * a.st_s_a] * a.s_w[z * a.st_s_w];
+    const double s_yd = (double)s_y, pow2r = (double)(1ull << a.rshift);
+    if (SRC == QSRC_HANDOFF && a.vmax) {   // (uniform) straight from the contraction's per-sample maxima (and sums)
+        __shared__ uint32_t smx[QT_THREADS / 64];
+        const int32_t* vm = a.vmax + z * a.st_b;
+        uint32_t mm = 0;
+        for (int i = threadIdx.x; i < a.B; i += QT_THREADS) {
+            if (!a.l2norm) {
+                mm = max(mm, (uint32_t)vm[i]);
+            } else {
+                const float nrm = sqrtf(goodness_value(a.gsum[z * a.st_b + i], pow2r, s_yd));
+                mm = max(mm, __float_as_uint(nrm > 0.0f ? ((float)vm[i] * s_y) / nrm : 0.0f));
+            }
+        }
+        mm = wave_max_u32(mm);
+        if ((threadIdx.x & 63) == 0) smx[threadIdx.x >> 6] = mm;
+        __syncthreads();
+        mm = max(max(smx[0], smx[1]), max(smx[2], smx[3]));
+        amax_word = a.l2norm ? mm : __float_as_uint((float)(int)mm * s_y);
     }
 
     const int64_t r0 = (int64_t)blockIdx.y * QT_ROWS;
@@ -249,7 +292,9 @@ __device__ __forceinline__ void quantize_tile(const QuantArgs& a, uint32_t* tile
             }
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                rowf[u][j] = row_in(QT_RH * u + j) ? per_sample[smp] : 0.0f;
+                if (!row_in(QT_RH * u + j)) rowf[u][j] = 0.0f;
+                else if (norm && a.vmax) rowf[u][j] = goodness_value(a.gsum[z * a.st_b + smp], pow2r, s_yd);
+                else rowf[u][j] = per_sample[smp];
                 if (++rem >= rps) { rem = 0; ++smp; }
             }
         }
@@ -263,8 +308,6 @@ __device__ __forceinline__ void quantize_tile(const QuantArgs& a, uint32_t* tile
     const bool live = amax >= 0x1p-100f;
     const float inv = live ? 127.0f / amax : 0.0f;
     if (blockIdx.x == 0 && blockIdx.y == 0 && t == 0) a.scale[z * a.st_scale] = live ? amax / 127.0f : 1.0f;
-    float s_y = 1.0f;
-    if (!F32SRC) s_y = a.s_a[z * a.st_s_a] * a.s_w[z * a.st_s_w];
     const float floor_y = a.relu ? 0.0f : -__builtin_inff();
     SrKey key = z ? a.key2 : a.key;
     if (a.step_dev) key = make_sr_key(a.seed, stream_tag_of(a.step_dev[0], a.tag_layer, (uint32_t)z, a.tag_kind));
@@ -454,28 +497,11 @@ __global__ __launch_bounds__(GL_THREADS) void k_goodness_loss(GoodnessArgs a)
     uint32_t amax_bits = 0;
     const int wg = blockIdx.y, nwg = gridDim.y;
     for (int64_t b = (int64_t)wg * GL_THREADS + threadIdx.x; b < a.B; b += (int64_t)nwg * GL_THREADS) {
-        double g = (double)gsum[b];
-        g = g * pow2r;
-        g = g * s_yd;
-        g = g * s_yd;
-        const float G = (fx && fx_amax < 0x1p-100f) ? 0.0f : (float)g;
+        const float G = (fx && fx_amax < 0x1p-100f) ? 0.0f : goodness_value(gsum[b], pow2r, s_yd);
         goodness[b] = G;
-        const float x = G - a.theta;
-        const float e = exp_nonpos(-fabsf(x));
-        const float den = 1.0f + e;
-        const float sig_big = 1.0f / den;
-        const float sig_small = e / den;
-        float c, xs;
-        if (sign > 0) {
-            c = -(x >= 0.0f ? sig_small : sig_big);
-            xs = -x;
-        } else {
-            c = (x >= 0.0f ? sig_big : sig_small);
-            xs = x;
-        }
-        coeff[b] = c;
-        // the reported loss (softplus) is not fed back into anything: fp32 terms, summed in fp64
-        lsum += (double)(fmaxf(xs, 0.0f) + log1pf(expf(-fabsf(xs))));
+        float xs;
+        coeff[b] = loss_derivative(G - a.theta, sign, xs);
+        lsum += (double)loss_term(xs);   // fp32 terms, summed in fp64
         if (a.next_amax_bits) {
             float ymax = (float)vmax[b] * s_y;
             if (a.l2norm) {
@@ -735,6 +761,103 @@ hipError_t launch_grad_amax(const float* ct, const int32_t* vmax, const float* s
                             uint32_t* slot, hipStream_t s)
 {
     hipLaunchKernelGGL(k_grad_amax, dim3((unsigned)nb), dim3(1024), 0, s, ct, vmax, s_a, s_w, B, slot);
+    return hipGetLastError();
+}
+
+// ------------------------------------------------------------------------------------------------
+// Goodness, loss, dL/dG, look-ahead and the absmax of the local gradients of ALL layers at once.  Nothing in the forward
+// pass needs a goodness before the look-ahead (the hand-off quantiser takes its range from the contraction's own
+// per-sample maxima), so the per-layer launches -- 4 to 6 us each between two contractions -- are folded into this one.
+// Workgroups 0 .. tiles-1 of a pass: 64 samples each, one wavefront per layer (16 layers at a time): every (layer, sample)
+// is worked out side by side, the coefficients meet in LDS and every thread forms its own suffix sum.  The workgroups
+// after them: the loss of one layer each, in a fixed order.
+// ------------------------------------------------------------------------------------------------
+constexpr int GA_WAVES = 16, GA_THREADS = 64 * GA_WAVES;
+
+__device__ __forceinline__ float goodness_of(const GoodnessAllArgs& a, const GoodnessLayer& L, int i, int p, int64_t b, float& s_y)
+{
+    const int64_t o = ((int64_t)i * 2 + p) * a.B + b;
+    if (L.fx) {
+        const float amax = __uint_as_float(a.out_amax[2 * (i + 1) + p]);
+        s_y = 1.0f;
+        return amax < 0x1p-100f ? 0.0f : goodness_value(a.gsum[o], 0x1p-40, (double)amax);
+    }
+    s_y = a.s_a[2 * i + p] * L.s_w[0];
+    return goodness_value(a.gsum[o], (double)(1ull << L.rshift), (double)s_y);
+}
+
+__global__ __launch_bounds__(GA_THREADS) void k_goodness_all(GoodnessAllArgs a)
+{
+    __shared__ float sc[32][64];
+    __shared__ double red[GA_THREADS];
+    const int p = blockIdx.y, tiles = (int)((a.B + 63) >> 6);
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int sign = p ? -1 : 1;
+    if ((int)blockIdx.x >= tiles) {   // the loss of one layer
+        const int i = (int)blockIdx.x - tiles;
+        const GoodnessLayer& L = a.L[i];
+        if (L.projection) {
+            if (threadIdx.x == 0) a.loss[2 * i + p] = 0.0f;
+            return;
+        }
+        double lsum = 0.0;
+        for (int64_t b = threadIdx.x; b < a.B; b += GA_THREADS) {
+            float s_y, xs;
+            const float G = goodness_of(a, L, i, p, b, s_y);
+            (void)loss_derivative(G - L.theta, sign, xs);
+            lsum += (double)loss_term(xs);
+        }
+        red[threadIdx.x] = lsum;
+        __syncthreads();
+        for (int s = GA_THREADS / 2; s > 0; s >>= 1) {
+            if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) a.loss[2 * i + p] = (float)(red[0] / (double)a.B);
+        return;
+    }
+    const int64_t b = (int64_t)blockIdx.x * 64 + lane;
+    const bool in = b < a.B;
+    float ym[2];   // largest activity of the thread's (up to two) layers
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        const int i = r * GA_WAVES + wv;
+        ym[r] = 0.0f;
+        if (i >= a.k) continue;
+        const GoodnessLayer& L = a.L[i];
+        float c = 0.0f;
+        if (in) {
+            const int64_t o = ((int64_t)i * 2 + p) * a.B + b;
+            float G = 0.0f;
+            if (!L.projection) {   // (a projection has no activity of its own: zero goodness, nothing enters the sums)
+                float s_y, xs;
+                G = goodness_of(a, L, i, p, b, s_y);
+                c = loss_derivative(G - L.theta, sign, xs);
+                ym[r] = L.fx ? __uint_as_float((uint32_t)a.vmax[o]) : (float)a.vmax[o] * s_y;
+            }
+            a.goodness[o] = G;
+            a.coeff[o] = c;
+        }
+        sc[i][lane] = c;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        const int i = r * GA_WAVES + wv;
+        if (i >= a.k) continue;
+        float S = 0.0f;
+        for (int j = a.k - 1; j > i; --j) S = S + sc[j][lane];
+        const float ct = __builtin_fmaf(a.lambda, S, sc[i][lane]);
+        if (in) a.coeff_total[((int64_t)i * 2 + p) * a.B + b] = ct;
+        const uint32_t bits = wave_max_u32(__float_as_uint(fabsf(2.0f * ct) * ym[r]));
+        if (lane == 0 && bits) atomicMax(a.g_amax_bits + 2 * i + p, bits);
+    }
+}
+
+hipError_t launch_goodness_all(const GoodnessAllArgs& a, hipStream_t s)
+{
+    if (a.k < 1 || a.k > 32 || a.B < 1) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_goodness_all, dim3((unsigned)((a.B + 63) / 64 + a.k), 2), dim3(GA_THREADS), 0, s, a);
     return hipGetLastError();
 }
 

@@ -63,6 +63,13 @@ struct QuantArgs {
     const float* per_sample; // HANDOFF with l2norm: goodness[B]; GRAD, F32_GRAD: coeff_total[B]
     int32_t rows_per_sample;
     int32_t relu, l2norm;
+    // HANDOFF, optional: the range (and with l2norm the goodness of a row's sample) straight from the contraction's
+    // per-sample maxima and sums of B samples per pass (st_b apart); amax_bits and per_sample are then unused.  Every
+    // workgroup reads all B of them: for batches small beside the tensor.
+    const int32_t* vmax;
+    const unsigned long long* gsum;
+    int32_t B, rshift;
+    int64_t st_b;
     // quantiser
     const uint32_t* amax_bits;  // device: bit pattern of the non-negative fp32 absmax
     int32_t amax_n;             // > 1: amax_bits is an array of that many candidates, the absmax is their maximum
@@ -94,7 +101,10 @@ hipError_t launch_quantize(int src, const QuantArgs& a, hipStream_t s);
 // (QuantArgs::amax_n).
 constexpr int ABSMAX_MAX_BLOCKS = 256;
 int absmax_blocks(int64_t n);
-hipError_t launch_absmax(const float* x, int64_t st_x, int nb, int64_t n, uint32_t* part, hipStream_t s);
+// The launch also clears clear_n words at `clear` (work of a step that would be a launch of its own).
+hipError_t launch_absmax(const float* x, int64_t st_x, int nb, int64_t n, uint32_t* part, hipStream_t s,
+                         uint32_t* clear = nullptr, int64_t clear_n = 0);
+hipError_t launch_clear2_u32(uint32_t* p, int64_t n, uint32_t* p2, int64_t n2, hipStream_t s);   // two ranges, one launch
 hipError_t launch_fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t s);
 hipError_t launch_advance_u64(uint64_t* counter, hipStream_t s);   // *counter += 1, in stream order
 
@@ -126,6 +136,31 @@ struct GoodnessArgs {
 };
 constexpr int GL_MAX_WG = 32;
 hipError_t launch_goodness_loss(const GoodnessArgs& a, hipStream_t s);
+
+// Goodness, loss, dL/dG and look-ahead of all layers of a step in one launch (two passes, [k][2][B] arrays).
+struct GoodnessLayer {
+    const float* s_w;
+    float theta;
+    int32_t rshift;
+    int32_t fx;          // residual layer: fixed-point sums, vmax holds fp32 bit patterns
+    int32_t projection;  // no activity of its own: zero goodness, loss and coefficient
+};
+struct GoodnessAllArgs {
+    int32_t k;
+    int64_t B;
+    float lambda;
+    const unsigned long long* gsum;
+    const int32_t* vmax;
+    const float* s_a;            // [k][2]
+    const uint32_t* out_amax;    // [k+1][2]: slot i + 1 the output of layer i (fx layers)
+    float* goodness;
+    float* coeff;
+    float* coeff_total;
+    float* loss;                 // [k][2]
+    uint32_t* g_amax_bits;       // [k][2], zeroed
+    GoodnessLayer L[32];
+};
+hipError_t launch_goodness_all(const GoodnessAllArgs& a, hipStream_t s);
 
 // coeff / coeff_total: [k][np][B] with strides; also (optionally) the absmax of each layer's local gradient.
 struct LookaheadArgs {
