@@ -16,10 +16,15 @@
 //
 // Barrier: one counter; every workgroup adds one and spins until the count reaches (barrier number) x (workgroups).
 // All workgroups must be resident at once, which holds because the grid is at most one workgroup per compute unit.
-// Agent-scope release / acquire fences on the two sides make the phases' global writes visible across the XCDs' L2
-// caches.  The counter lives in a small static array of the library's device image (zero when the library is loaded);
-// the workgroup that leaves the kernel last sets it back to zero, so the launch needs no clearing kernel in front of
-// it and can be replayed from a HIP graph.  Launches that overlap on one GPU would share the counter: serialise them.
+// The phases' writes lie in the L2 of the XCD that made them; an agent-scope release writes that L2 back, and it is the
+// dear part of a barrier: issued by every workgroup, the write-backs of one XCD queue up behind each other (82 workgroups:
+// 4.9 us a barrier, 2.2 us of it the releases).  So the workgroups of an XCD -- told apart by the hardware's XCC number
+// and counted at the first barrier -- meet at a counter of their own, and the last to arrive writes their L2 back once
+// and reports all of them (3.5 us with a read that checks it; the step of 784 -> 500 -> 500 at 64 samples 64.6 -> 59.8 us).
+// Every workgroup invalidates its caches on the way out (acquire).
+// The counters live in a small static array of the library's device image (zero when the library is loaded); the
+// workgroup that leaves the kernel last sets them back to zero, so the launch needs no clearing kernel in front of
+// it and can be replayed from a HIP graph.  Launches that overlap on one GPU would share the counters: serialise them.
 #include <mutex>
 
 #include "device_math.hpp"
@@ -33,8 +38,11 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 
 constexpr int FU_WAVES = FU_THREADS / 64;
 
-// [0] barrier counter, [1] set when a barrier wait ran into its bound, [2] count of workgroups that have left
-static __device__ __align__(256) unsigned g_fu_sync[64];
+// [0] barrier counter, [1] set when a barrier wait ran into its bound, [2] count of workgroups that have left; per XCD, a
+// cache line each: members and arrivals
+constexpr int FU_XCDS = 16, FU_XLINE = 32;   // (XCC numbers are four bits)
+constexpr int FU_MEMBERS = 64, FU_ARRIVED = FU_MEMBERS + FU_XCDS * FU_XLINE, FU_SYNC_WORDS = FU_ARRIVED + FU_XCDS * FU_XLINE;
+static __device__ __align__(256) unsigned g_fu_sync[FU_SYNC_WORDS];
 
 __device__ __forceinline__ unsigned long long shfl_xor_u64f(unsigned long long v, int d)
 {
@@ -46,16 +54,27 @@ struct FuCtx {
     unsigned* bar;
     unsigned long long* stamps;   // instrumentation (null normally): workgroup 0 records the 100 MHz clock after every barrier
     unsigned epoch, G;
+    unsigned xcd, members;   // this workgroup's XCD, the launch's workgroups on it (thread 0, from the first barrier on)
     int gtid, gsz;   // global thread index / thread count
 };
 
 __device__ __forceinline__ void grid_barrier(FuCtx& c)
 {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();   // every wavefront's stores of the phase have reached the L2
     c.epoch += 1;
     if (threadIdx.x == 0) {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");   // write the phase's data back past this XCD's L2
-        __hip_atomic_fetch_add(c.bar, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (c.epoch == 1) {   // nobody knows the XCD's members yet: everyone writes back and reports for itself
+            __hip_atomic_fetch_add(c.bar + FU_MEMBERS + FU_XLINE * c.xcd, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+            __hip_atomic_fetch_add(c.bar, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        } else {
+            const unsigned old = __hip_atomic_fetch_add(c.bar + FU_ARRIVED + FU_XLINE * c.xcd, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (old + 1 == c.members * (c.epoch - 1)) {
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");   // write the XCD's data back past its L2
+                __hip_atomic_fetch_add(c.bar, c.members, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
         const unsigned target = c.epoch * c.G;
         // Every workgroup reaches every barrier, so the wait ends as soon as the slowest one arrives.  The spin is
         // bounded all the same (about a second): should a workgroup ever fail to arrive, the others leave with wrong
@@ -69,6 +88,7 @@ __device__ __forceinline__ void grid_barrier(FuCtx& c)
             }
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        if (c.epoch == 1) c.members = __hip_atomic_load(c.bar + FU_MEMBERS + FU_XLINE * c.xcd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (c.stamps && blockIdx.x == 0) c.stamps[c.epoch] = wall_clock64();
     }
     __syncthreads();
@@ -399,6 +419,8 @@ __global__ __launch_bounds__(FU_THREADS) void k_fused_dense_step(FusedArgs a)
     c.stamps = a.stamps;
     c.epoch = 0;
     c.G = gridDim.x;
+    c.xcd = __builtin_amdgcn_s_getreg(20 | (3 << 11)) & (FU_XCDS - 1);   // HW_REG_XCC_ID, bits 0 .. 3
+    c.members = 1;
     c.gtid = (int)blockIdx.x * FU_THREADS + (int)threadIdx.x;
     c.gsz = (int)gridDim.x * FU_THREADS;
     const int k = a.k, B = a.B;
@@ -831,6 +853,10 @@ __global__ __launch_bounds__(FU_THREADS) void k_fused_dense_step(FusedArgs a)
         if (old == c.G - 1) {
             __hip_atomic_store(c.bar + 0, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __hip_atomic_store(c.bar + 2, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            for (int x = 0; x < FU_XCDS; ++x) {
+                __hip_atomic_store(c.bar + FU_MEMBERS + FU_XLINE * x, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(c.bar + FU_ARRIVED + FU_XLINE * x, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
         }
     }
 }
