@@ -143,21 +143,21 @@ static bool wgrad_from_patches(const Dims& d)
 }
 // Columns of the weight-gradient contraction: operands read reduction-major are worked on in whole 16-byte chunks
 // (GemmArgs::conv == 2).
-static int64_t wgrad_cols(const Dims& d, bool have_aqt)
+static int64_t wgrad_cols(const Dims& d)
 {
-    if (d.kind != FF_CONV2D || (have_aqt && d.pointwise)) return d.K;
+    if (d.kind != FF_CONV2D) return d.K;
     if (wgrad_from_patches(d)) return (d.K + 15) & ~int64_t(15);
     return (int64_t)d.g.ks * d.g.ks * ((d.g.Cin + 15) & ~15);
 }
 // Sample chunks of equal size go into one launch as further problems of the batch.
 static bool chunks_together(const Dims& d) { return d.n_chunks > 1 && d.B == d.n_chunks * d.chunk_b; }
 // Scratch for the partial results of a split weight gradient: [launch][pass][chunk of the launch][split][N, pitch32(K)].
-static size_t wgrad_part_bytes(const Dims& d, int nb, bool have_aqt)
+static size_t wgrad_part_bytes(const Dims& d, int nb)
 {
     if (d.kind == FF_DWCONV2D) return 0;
-    const int extra = d.kind == FF_DENSE || (have_aqt && d.pointwise) ? 0 : GEMM_TABLE_BYTES;
+    const int extra = d.kind == FF_DENSE ? 0 : GEMM_TABLE_BYTES;
     const int problems = nb * (chunks_together(d) ? d.n_chunks : 1);
-    const GemmPlan p = gemm_plan(d.N, wgrad_cols(d, have_aqt), min(d.M, d.chunk_b * d.rps), problems, true, extra);
+    const GemmPlan p = gemm_plan(d.N, wgrad_cols(d), min(d.M, d.chunk_b * d.rps), problems, true, extra);
     if (p.splits <= 1) return 0;
     return align_up((size_t)(nb * d.n_chunks) * (size_t)p.splits * (size_t)(d.N * pitch32(d.K)) * sizeof(int32_t), 256);
 }
@@ -190,7 +190,7 @@ struct WsLayout {
     size_t off_part, part_bytes;     // int32 scratch: partial sums of split weight gradients (see wgrad_part_bytes)
     size_t off_xmax;                 // uint32 [2][ABSMAX_MAX_BLOCKS]: per-workgroup absmax of the net input
     size_t off_aq[MAX_LAYERS], st_aq[MAX_LAYERS];    // quantised layer input [2][st]: dense layers share one scratch
-    size_t off_aqt[MAX_LAYERS], st_aqt[MAX_LAYERS];  // dense and 1x1 stride-1 conv: transposed quantised input [2][st], retained
+    size_t off_aqt[MAX_LAYERS], st_aqt[MAX_LAYERS];  // dense: transposed quantised input [2][st], retained
     size_t off_acc[MAX_LAYERS], st_acc[MAX_LAYERS];  // int32 accumulators [2][st] (bytes), retained
     size_t off_y[MAX_LAYERS], st_y[MAX_LAYERS];      // residual layers: fp32 block output [2][st] (bytes), retained
     // exact-derivative look-ahead only (all sizes 0 otherwise)
@@ -296,7 +296,7 @@ static ff_status make_layout(const ff_net_desc* net, WsLayout* w)
         if (d.kind == FF_DENSE) aq_dense = max(aq_dense, (size_t)(d.in_rows * pitch8(d.in_cols)));
         gy = max(gy, d.kind == FF_DWCONV2D ? (size_t)(d.M * pitch8(d.N)) : (size_t)(d.N * pitch8(d.M)));
         dw = max(dw, (size_t)(d.N * pitch32(d.K)) * sizeof(int32_t));
-        part = max(part, wgrad_part_bytes(d, 2, true));
+        part = max(part, wgrad_part_bytes(d, 2));
     }
     aq_dense = align_up(aq_dense, A);
     const size_t off_aq_dense = off;
@@ -373,9 +373,7 @@ static ff_status make_layout(const ff_net_desc* net, WsLayout* w)
             w->st_aq[i] = align_up((size_t)(d.in_rows * pitch8(d.in_cols)), A);
             w->off_aq[i] = off;
             off += 2 * w->st_aq[i];
-            w->st_aqt[i] = d.pointwise ? align_up((size_t)(d.K * pitch8(d.M)), A) : 0;
-            w->off_aqt[i] = d.pointwise ? off : 0;
-            off += 2 * w->st_aqt[i];
+            w->st_aqt[i] = w->off_aqt[i] = 0;
         }
         w->st_col[i] = explicit_patches(d) ? align_up((size_t)(d.M * pitch8(d.K)), A) : 0;
         w->off_col[i] = off;
@@ -575,14 +573,13 @@ struct WgradTerms {
 };
 
 // Weight gradient: dw[z][c] = gy_q_t[z][:, chunk c] x (patches of chunk c)^T for every chunk c.
-// `aqt` is the transposed quantised input (dense; also a 1x1 stride-1 convolution when aqt_transposed is set) or the
-// NHWC quantised input (conv), which the contraction reads reduction-major as it is -- or the row-major patch matrix
+// `aqt` is the transposed quantised input (dense) or the NHWC quantised input (conv), which the contraction reads reduction-major as it is -- or the row-major patch matrix
 // [M, pitch(K)] (wgrad_from_patches).  dw accumulators of one pass are dw_elems apart.  `part`: part_elems elements for the
 // partial results of a split reduction.  terms == null: split results are added up into dw; otherwise they are left as
 // they are for the update, and *terms says where everything is.
 static ff_status run_wgrad(const Dims& d, const int8_t* gy_t, int64_t st_gy, const int8_t* aqt, int64_t st_aqt,
                            int32_t* part, int64_t part_elems, int32_t* dw, int64_t st_dw, int64_t dw_elems, int nb,
-                           hipStream_t s, bool aqt_transposed, WgradTerms* terms)
+                           hipStream_t s, WgradTerms* terms)
 {
     const int64_t elems = d.N * pitch32(d.K);
     if (terms) {
@@ -642,7 +639,7 @@ static ff_status run_wgrad(const Dims& d, const int8_t* gy_t, int64_t st_gy, con
         g.rows_per_sample = 1;
         g.nb = nb * together;
         g.nc = together;
-        if (d.kind == FF_DENSE || aqt_transposed) {   // a 1x1 stride-1 convolution is a dense layer over its pixels
+        if (d.kind == FF_DENSE) {
             g.Q = aqt + m0;
             g.st_q = st_aqt;
             g.st_q2 = mc;
@@ -664,7 +661,7 @@ static ff_status run_wgrad(const Dims& d, const int8_t* gy_t, int64_t st_gy, con
             g.st_q2 = d.chunk_b * q.H * q.W * q.cpitch;
             g.ldq = 16;   // unused by this loader
             g.conv = 2;
-            g.J = (int32_t)wgrad_cols(d, false);
+            g.J = (int32_t)wgrad_cols(d);
             g.H = q.H; g.W = q.W; g.Cin = (q.Cin + 15) & ~15; g.cin_out = q.Cin; g.cpitch = q.cpitch; g.ks = q.ks;
             g.stride = q.stride; g.pad = q.pad; g.Ho = q.Ho; g.Wo = q.Wo;
             g.p_bytes = (b1 - b0) * q.H * q.W * q.cpitch;
@@ -968,7 +965,7 @@ ff_status ff_layer_backward_local(const ff_layer_desc* layer, const int32_t* acc
         room -= layer_col_bytes(d);
     }
     return run_wgrad(d, gy_q_t, 0, operand, 0, (int32_t*)scratch, (int64_t)(room / sizeof(int32_t)), dw_acc, 0, dw_elems, 1, s,
-                     false, nullptr);
+                     nullptr);
 }
 
 // ---- the entry point that allocates nothing: its scratch is a fixed array in the library's own device image ----
@@ -1367,7 +1364,7 @@ static ff_status train_step_impl(const ff_net_desc* net, const ff_net_state* sta
         a.q = (int8_t*)(base + w.off_aq[i]);
         a.st_q = (int64_t)w.st_aq[i];
         a.ldq = pitch8(d.in_cols);
-        if (dense || d.pointwise) {
+        if (dense) {
             a.q_t = (int8_t*)(base + w.off_aqt[i]);
             a.st_qt = (int64_t)w.st_aqt[i];
             a.ldqt = pitch8(d.M);
@@ -1578,7 +1575,7 @@ static ff_status train_step_impl(const ff_net_desc* net, const ff_net_state* sta
         hipStream_t s = lane_stream[lane];                        // (shadows the caller's stream inside the chain)
         char* base = (char*)ws + (size_t)lane * w.lane_stride;   // lane-scoped scratch: gy, dw, part, wbmax
         char* const base0 = (char*)ws;                            // what lives outside the lanes
-        const bool dense = d.kind == FF_DENSE || d.pointwise;   // layers that keep a transposed copy of their input
+        const bool dense = d.kind == FF_DENSE;   // layers that keep a transposed copy of their input
         const int64_t dw_elems = (int64_t)(w.dw_bytes / sizeof(int32_t));
         const bool patches = wgrad_from_patches(d);
         const size_t off_q = dense ? w.off_aqt[t] : (patches ? w.off_col[t] : w.off_aq[t]);
@@ -1587,7 +1584,7 @@ static ff_status train_step_impl(const ff_net_desc* net, const ff_net_state* sta
         const ff_status ws_ = run_wgrad(d, (const int8_t*)(base + w.off_gy), (int64_t)w.st_gy,
                                         (const int8_t*)(base0 + off_q), (int64_t)st_q, (int32_t*)(base + w.off_part),
                                         (int64_t)(w.part_bytes / sizeof(int32_t)), (int32_t*)(base + w.off_dw),
-                                        (int64_t)(w.st_dw / sizeof(int32_t)), dw_elems, 2, s, d.pointwise, &terms);
+                                        (int64_t)(w.st_dw / sizeof(int32_t)), dw_elems, 2, s, &terms);
         if (ws_ != FF_OK) return ws_;
 
         UpdateArgs u;

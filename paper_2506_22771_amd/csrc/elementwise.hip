@@ -409,6 +409,44 @@ __global__ __launch_bounds__(QT_THREADS) void k_quantize(QuantArgs a)
     else quantize_tile<SRC, STOCH, FORM, CB, U, false>(a, tileT);
 }
 
+// fp32 tensors of at most four columns, row-major codes only (the pixels of a first layer: one or three channels, 16 bytes
+// of codes per pixel): a thread takes a row.  In the tiles above fifteen of sixteen lanes would have nothing to do
+// (3 channels, 32x32 maps, 512 images: 25 us there, 7 us here).
+template <bool STOCH>
+__global__ __launch_bounds__(QT_THREADS) void k_quantize_pixels(QuantArgs a)
+{
+    const int z = blockIdx.y;
+    uint32_t amax_word = a.amax_bits[z * a.st_amax];
+    if (a.amax_n > 1) {   // (uniform) the producer left one candidate per workgroup
+        __shared__ uint32_t amx[QT_THREADS / 64];
+        uint32_t mm = 0;
+        for (int i = threadIdx.x; i < a.amax_n; i += QT_THREADS) mm = max(mm, a.amax_bits[z * a.st_amax + i]);
+        mm = wave_max_u32(mm);
+        if ((threadIdx.x & 63) == 0) amx[threadIdx.x >> 6] = mm;
+        __syncthreads();
+        amax_word = max(max(amx[0], amx[1]), max(amx[2], amx[3]));
+    }
+    const float amax = __uint_as_float(amax_word);
+    const bool live = amax >= 0x1p-100f;
+    const float inv = live ? 127.0f / amax : 0.0f;
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.scale[z * a.st_scale] = live ? amax / 127.0f : 1.0f;
+    SrKey key = z ? a.key2 : a.key;
+    if (a.step_dev) key = make_sr_key(a.seed, stream_tag_of(a.step_dev[0], a.tag_layer, (uint32_t)z, a.tag_kind));
+    const int cols = (int)a.cols;
+    for (int64_t row = (int64_t)blockIdx.x * QT_THREADS + threadIdx.x; row < a.rows; row += (int64_t)gridDim.x * QT_THREADS) {
+        const float* px = a.x + z * a.st_x + row * cols;
+        const uint32_t idx = (uint32_t)row * (uint32_t)cols;
+        float v[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) v[c] = c < cols ? px[c] : 0.0f;
+        uint32_t pack = 0;
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            if (c < cols) pack |= ((uint32_t)quant_code<STOCH>(v[c], inv, (idx + (uint32_t)c) ^ key.k0) & 0xFFu) << (8 * c);
+        *(u32x4*)(a.q + z * a.st_q + row * a.ldq) = (u32x4){pack, 0u, 0u, 0u};   // (the row pitch of up to four columns is 16)
+    }
+}
+
 template <int SRC, bool STOCH, int FORM, int CB, int U>
 static void launch_quantize_tiles(const QuantArgs& a, int64_t span, hipStream_t s)
 {
@@ -424,6 +462,11 @@ static void launch_quantize_t(const QuantArgs& a, hipStream_t s)
 {
     constexpr bool F32SRC = SRC == QSRC_F32 || SRC == QSRC_F32_GRAD;
     constexpr int GENERAL = F32SRC ? 0 : 1;
+    if (SRC == QSRC_F32 && a.cols <= 4 && a.q && !a.q_t) {
+        const int64_t blocks = min((a.rows + QT_THREADS - 1) / QT_THREADS, (int64_t)8 * num_cus());
+        hipLaunchKernelGGL((k_quantize_pixels<STOCH>), dim3((unsigned)blocks, (unsigned)a.nb), dim3(QT_THREADS), 0, s, a);
+        return;
+    }
     const bool cols4 = (a.cols & 3) == 0;
     const bool vec = !F32SRC || (cols4 && (((uintptr_t)a.x) & 15) == 0 && ((a.st_x & 3) == 0 || a.nb == 1));
     const bool narrow = a.cols <= QTile<8, 2>::COLS && vec;

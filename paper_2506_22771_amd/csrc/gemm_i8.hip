@@ -695,6 +695,10 @@ GemmPlan gemm_plan(int64_t I, int64_t J, int64_t R, int nb, bool allow_split, in
         // splitting the reduction: about two workgroups per compute unit, never more (a third partial round
         // would idle most of the chip), at least 16 reduction steps per split.
         p.bm = edge(I);
+        // Reduction-major operands, 128-row tiles: twice the columns even where the last tile is half empty -- a wavefront's
+        // 64 x 128 share reads a third less LDS per multiply than 64 x 64 (128 x 576 outputs: 64 -> 128 channels at 32x32,
+        // backward 178 -> 170 us).
+        if (lds_extra > 0 && p.bm == 128 && p.bn == 128 && J > 256) p.bn = 256;
         // (a tile whose stages take more than half of the LDS has one workgroup per compute unit: one round of 256
         // workgroups, each with twice the reduction steps, writes and re-reads half the partial sums of two rounds of 512)
         int64_t sp = (2 * (p.bm + p.bn) * BK + lds_extra > 80 * 1024 ? FF_SPLIT_TARGET_BIG : 512) / tiles(p.bm, p.bn);

@@ -153,3 +153,17 @@ def test_step_goodness_after_the_forward_pass_or_per_layer(ff, B, l2, depth):
     than a workgroup of the single launch takes at a time."""
     wl = Workload("g", mlp([20] + [24, 17] * (depth // 2) + [16] * (depth % 2), l2), B, "normal", lam=0.3)
     _run_steps(ff, wl, 2, theta_layer=_matched_thetas(wl), launch_mode="kernels")
+
+
+@pytest.mark.parametrize("rows", [1, 255, 257, 1000003])
+@pytest.mark.parametrize("cols", [1, 2, 3, 4])
+@pytest.mark.parametrize("mode", [0, 1])
+def test_quantize_few_columns_row_major_only(ff, rows, cols, mode):
+    rng = np.random.default_rng(rows + cols)
+    x = rng.standard_normal((rows, cols), dtype=np.float32)
+    q_ref, s_ref = O.quantize(x, mode, 5, 77)
+    q, s = empty8(rows, cols), scalar()
+    ff.ff_quantize(dev(x), rows, cols, mode, 5, 77, q, None, s, workspace())
+    torch.cuda.synchronize()
+    assert s.item() == s_ref
+    check_q(q, q_ref, "q")
