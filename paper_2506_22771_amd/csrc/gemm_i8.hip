@@ -51,12 +51,6 @@ constexpr int BK = 128;  // reduction bytes per LDS stage
 #ifndef FF_SPLIT_ISSUE
 #define FF_SPLIT_ISSUE 1
 #endif
-#ifndef FF_DEEP
-// 1: tiles smaller than 256 x 256 use three or four LDS stages (two or three copies in flight).  Measured: the contraction
-// launches get 4-5 % shorter on their own, but the steps of the small and convolution configurations get 2-3 % longer
-// (a workgroup that holds most of the LDS keeps the next kernel's workgroups off the compute unit while the launch drains).
-#define FF_DEEP 0
-#endif
 #ifndef FF_SPLIT_TARGET_BIG
 #define FF_SPLIT_TARGET_BIG 256
 #endif
@@ -96,7 +90,10 @@ __device__ __forceinline__ v2i tr_read8(const int8_t* p)
     typedef __attribute__((address_space(3))) v2i* lds_ptr;
     return __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_ptr)p);
 }
-__device__ __forceinline__ int swz(int row, int kc) { return row * BK + ((kc ^ ((row >> 1) & 7)) << 4); }
+// 16-byte chunks are XOR-swizzled inside a row so that 16 consecutive rows put one chunk into 16 different bank groups
+// (two 128-byte rows, or four 64-byte rows, span the 64 banks)
+template <int BKT> __device__ __forceinline__ int swz_of(int row) { return BKT == 128 ? (row >> 1) & 7 : (row >> 2) & 3; }
+template <int BKT> __device__ __forceinline__ int swz(int row, int kc) { return row * BKT + ((kc ^ swz_of<BKT>(row)) << 4); }
 
 // MODE 0: store C; 1: store C and accumulate the per-sample goodness sums / maxima; 2: split reduction, this
 // workgroup stores the partial sums of its share of the reduction steps at C + blockIdx.y * st_split.
@@ -113,28 +110,28 @@ __device__ __forceinline__ int swz(int row, int kc) { return row * BK + ((kc ^ (
 // Measured against the transposed patch matrices / column-shifted planes this replaces (which had to be written first):
 // 64 -> 128 channels at 32x32, 256 images, both sets: contraction 115 -> 104 us and 46 us of plane writing gone; maps whose
 // size is no multiple of 16 (byte gathers before) several times faster: 120 -> 160 at 21x21, 27 images, 196 -> 106 us in all.
-template <int BM, int BN, int WM, int WN, int MODE, int CONV>
-__global__ __launch_bounds__(WM* WN * 64) void k_gemm_nt_i8(GemmArgs a)
+template <int BM, int BN, int WM, int WN, int MODE, int CONV, int BKT = 128, int NS = 2>
+__global__ __launch_bounds__(WM* WN * 64) __attribute__((amdgpu_waves_per_eu(BKT == 64 ? 2 : 1))) void k_gemm_nt_i8(GemmArgs a)
 {
+    constexpr int BK = BKT;             // reduction bytes per LDS stage
+    constexpr int CPB = BK / 16;        // 16-byte chunks per staged row
+    constexpr int SUB = BK / 32;        // MFMA sub-steps per stage
     constexpr bool EPI = MODE == 1;
     constexpr int T = WM * WN * 64;
     constexpr int WTM = BM / WM, WTN = BN / WN;
     constexpr int TI = WTM / 32, TJ = WTN / 32;
-    constexpr int CH_P = BM * 8 / T, CH_Q = BN * 8 / T;
+    constexpr int CH_P = BM * CPB / T, CH_Q = BN * CPB / T;
     constexpr int STAGE_BYTES = (BM + BN) * BK;
-    static_assert(BM * 8 % T == 0 && BN * 8 % T == 0, "tile/threads mismatch");
+    static_assert(BM * CPB % T == 0 && BN * CPB % T == 0 && (T / CPB) % 16 == 0, "tile/threads mismatch");
     // epilogue staging: one slice of EROWS rows of a wave's tile, rows padded by 16 bytes to spread the banks.  The
     // 256-row tiles stage in the SECOND operand stage (and a little beyond it; 16 rows at a time for the 256 x 256 tile,
     // so that it fits), which leaves the first stage free for the first copies of the workgroup's next tile (persistent
     // launches); the others 32 rows from 0.
-    constexpr bool PREFETCH = FF_NEXT_TILE_PREFETCH && BM == 256 && CONV < 2 && MODE != 2;
-    constexpr int EROWS = PREFETCH && BN == 256 ? 16 : 32;
+    constexpr bool PREFETCH = FF_NEXT_TILE_PREFETCH && (BM == 256 || BK == 64) && CONV < 2 && MODE != 2;
+    constexpr int EROWS = PREFETCH && (BN == 256 || BK == 64) ? 16 : 32;
     constexpr int EROW = WTN * 4 + 16;
     constexpr int ESLICE = EROWS * EROW;
     constexpr int EOFF = PREFETCH ? STAGE_BYTES : 0;
-    // LDS stages: two for the big tile (128 KB); the smaller tiles, whose launches are short chains of reduction steps
-    // that each wait for a round trip to memory, keep up to three copies in flight
-    constexpr int NS = (FF_DEEP && !(BM == 256 && BN == 256)) ? (4 * STAGE_BYTES <= 160 * 1024 ? 4 : 3) : 2;
     constexpr int CH = CH_P + CH_Q;   // copy instructions of one thread per reduction step
     static_assert((NS - 1) * CH < 64, "vmcnt range");
     constexpr int LDS_BYTES = NS * STAGE_BYTES > EOFF + WM * WN * ESLICE ? NS * STAGE_BYTES : EOFF + WM * WN * ESLICE;
@@ -145,7 +142,7 @@ __global__ __launch_bounds__(WM* WN * 64) void k_gemm_nt_i8(GemmArgs a)
     constexpr int CPR = BN / 16;                 // CONV 2: chunks per pixel row of the staged Q tile
     constexpr int RSQ = T / CPR;                 // pixel rows one copy instruction of the workgroup covers
     constexpr int GSH = CPR == 16 ? 0 : (CPR == 8 ? 1 : 2), GMASK = CPR / 2 - 1;   // g(r) = (r >> GSH) & GMASK
-    static_assert(CONV != 2 || (NS == 2 && RSQ % 8 == 0 && (CPR == 16 || CPR == 8 || CPR == 4)), "pixel-row tiling");
+    static_assert(CONV != 2 || (NS == 2 && BK == 128 && RSQ % 8 == 0 && (CPR == 16 || CPR == 8 || CPR == 4)), "pixel-row tiling");
 
     // clock probe: the counters are wavefront-uniform (scalar registers); only the final atomics are per thread
     unsigned long long clk0 = 0, rt0 = 0;
@@ -186,9 +183,9 @@ __global__ __launch_bounds__(WM* WN * 64) void k_gemm_nt_i8(GemmArgs a)
                                           : __builtin_amdgcn_make_buffer_rsrc((void*)(P + (int64_t)i0 * a.ldp), 0, (int)(rows_p * a.ldp), 0x00020000);
     __amdgpu_buffer_rsrc_t rq = CONV >= 2 ? __builtin_amdgcn_make_buffer_rsrc((void*)Q, 0, (int)a.p_bytes, 0x00020000)
                                           : __builtin_amdgcn_make_buffer_rsrc((void*)(Q + (int64_t)j0 * a.ldq), 0, (int)(rows_q * a.ldq), 0x00020000);
-    // Every chunk of one thread has the same k column: chunk index c = s*T + tid, T a multiple of 8,
-    // LDS slot (row = c >> 3, c & 7) holds reduction chunk (c & 7) ^ ((row >> 1) & 7) of that row.
-    const int kcol = (((tid & 7) ^ ((tid >> 4) & 7))) * 16;
+    // Every chunk of one thread has the same k column: chunk index c = s*T + tid, T / CPB a multiple of 16,
+    // LDS slot (row = c / CPB, c % CPB) holds the reduction chunk of that row that swz puts there.
+    const int kcol = ((tid % CPB) ^ swz_of<BK>(tid / CPB)) * 16;
     int offP[CH_P], offQ[CH_Q];
     int hi0[CONV == 1 ? CH_P : 1], wi0[CONV == 1 ? CH_P : 1];   // conv: input pixel of tap (0,0) for the chunk's output pixel
     int tap_off = 0, tap_bit = 31;                              // CONV 2: this thread's (tap, channels) chunk, the same in every copy
@@ -231,7 +228,7 @@ __global__ __launch_bounds__(WM* WN * 64) void k_gemm_nt_i8(GemmArgs a)
     };
 #pragma unroll
     for (int s = 0; s < CH_P; ++s) {
-        const int row = (s * T + tid) >> 3;
+        const int row = (s * T + tid) / CPB;
         if (CONV == 1) {
             const int m = i0 + row;
             const int b = m / (a.Ho * a.Wo), rem = m - b * (a.Ho * a.Wo);
@@ -245,7 +242,7 @@ __global__ __launch_bounds__(WM* WN * 64) void k_gemm_nt_i8(GemmArgs a)
     }
 #pragma unroll
     for (int s = 0; s < CH_Q; ++s) {
-        const int row = (s * T + tid) >> 3;
+        const int row = (s * T + tid) / CPB;
         if (CONV != 2) {
             offQ[s] = row * (int)a.ldq + kcol;
         }
@@ -312,14 +309,14 @@ __global__ __launch_bounds__(WM* WN * 64) void k_gemm_nt_i8(GemmArgs a)
     }
     auto ldfrag = [&](int set, const int8_t* sb, int ks) {
 #pragma unroll
-        for (int ti = 0; ti < TI; ++ti) fp[set][ti] = *(const v4i*)(sb + swz(wm * WTM + ti * 32 + lr, ks * 2 + lh));
+        for (int ti = 0; ti < TI; ++ti) fp[set][ti] = *(const v4i*)(sb + swz<BK>(wm * WTM + ti * 32 + lr, ks * 2 + lh));
 #pragma unroll
         for (int tj = 0; tj < TJ; ++tj) {
             if (CONV == 2) {   // pixels 16 lh .. + 15 of the sub-step, in the order the P fragment holds them
                 const v2i lo = tr_read8(sb + qa[tj] + ks * 32 * BN), hi = tr_read8(sb + qa[tj] + ks * 32 * BN + 8 * BN);
                 fq[set][tj] = (v4i){lo.x, lo.y, hi.x, hi.y};
             } else {
-                fq[set][tj] = *(const v4i*)(sb + BM * BK + swz(wn * WTN + tj * 32 + lr, ks * 2 + lh));
+                fq[set][tj] = *(const v4i*)(sb + BM * BK + swz<BK>(wn * WTN + tj * 32 + lr, ks * 2 + lh));
             }
         }
     };
@@ -340,7 +337,9 @@ __global__ __launch_bounds__(WM* WN * 64) void k_gemm_nt_i8(GemmArgs a)
         // Step 0 is in LDS already: every wavefront waited for its own copies of it before the stores of the previous
         // epilogue, and the barrier at the end of that tile made them visible to all.  Only step 1 goes out now; the
         // main loop waits for it (and, copies and stores completing in issue order, for the previous tile's stores).
-        if (kt0 + 1 < nk) issue(kt0 + 1, 1);
+#pragma unroll
+        for (int i = 1; i < NS; ++i)
+            if (kt0 + i < nk) issue(kt0 + i, i);
         ldfrag(0, lds, 0);
     } else {
     // all stages are free at the start of a tile: the copies of the first NS steps go out together, so that only
@@ -373,13 +372,12 @@ __global__ __launch_bounds__(WM* WN * 64) void k_gemm_nt_i8(GemmArgs a)
         const int nxt = cur + 1 == NS ? 0 : cur + 1;
         const int8_t* sb = lds + cur * STAGE_BYTES;
         const int8_t* sn = lds + nxt * STAGE_BYTES;
-        ldfrag(1, sb, 1);
-        mma(0);
-        ldfrag(0, sb, 2);
-        mma(1);
-        ldfrag(1, sb, 3);
-        if (CONV == 2) decode(cur);   // step kt + 2; this table's readers have passed the barrier of step kt - 1
-        mma(0);
+#pragma unroll
+        for (int u = 0; u < SUB - 1; ++u) {
+            ldfrag((u + 1) & 1, sb, u + 1);
+            if (CONV == 2 && u == SUB - 2) decode(cur);   // step kt + 2; this table's readers have passed the barrier of step kt - 1
+            mma(u & 1);
+        }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         // the copies of step kt + 1 must have landed; those of the NS - 2 steps after it may stay in flight (near the
         // end of the reduction fewer are outstanding: wait for all)
@@ -426,7 +424,7 @@ __global__ __launch_bounds__(WM* WN * 64) void k_gemm_nt_i8(GemmArgs a)
             rp = __builtin_amdgcn_make_buffer_rsrc((void*)(a.P + znp * a.st_p), 0, (int)a.p_bytes, 0x00020000);
 #pragma unroll
             for (int s = 0; s < CH_P; ++s) {
-                const int m = i0n + ((s * T + tid) >> 3);
+                const int m = i0n + (s * T + tid) / CPB;
                 const int b = m / (a.Ho * a.Wo), rem = m - b * (a.Ho * a.Wo);
                 const int ho = rem / a.Wo, wo = rem - ho * a.Wo;
                 hi0[s] = m < a.I ? ho * a.stride - a.pad : -(1 << 20);
@@ -631,6 +629,24 @@ int num_cus()
 }
 
 template <int BM, int BN, int WM, int WN>
+static hipError_t launch_paired(const GemmArgs& a, hipStream_t s)
+{
+    constexpr int BKT = 64, NS = 3;   // 73 728 bytes of LDS per workgroup
+    const int64_t ntiles = (int64_t)((a.I + BM - 1) / BM) * ((a.J + BN - 1) / BN) * a.nb;
+    if (ntiles > 0x7FFFFFFF || a.splits > 1 || a.conv == 2) return hipErrorInvalidValue;
+    const int64_t resident = (int64_t)2 * num_cus();
+    const dim3 grid((unsigned)min(ntiles, resident)), block(WM * WN * 64);
+    if (a.conv == 1) {
+        if (a.gsum) hipLaunchKernelGGL((k_gemm_nt_i8<BM, BN, WM, WN, 1, 1, BKT, NS>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((k_gemm_nt_i8<BM, BN, WM, WN, 0, 1, BKT, NS>), grid, block, 0, s, a);
+    } else {
+        if (a.gsum) hipLaunchKernelGGL((k_gemm_nt_i8<BM, BN, WM, WN, 1, 0, BKT, NS>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((k_gemm_nt_i8<BM, BN, WM, WN, 0, 0, BKT, NS>), grid, block, 0, s, a);
+    }
+    return hipGetLastError();
+}
+
+template <int BM, int BN, int WM, int WN>
 static hipError_t launch_cfg(const GemmArgs& a, hipStream_t s)
 {
     const int tiles_i = (a.I + BM - 1) / BM, tiles_j = (a.J + BN - 1) / BN;
@@ -674,10 +690,12 @@ GemmPlan gemm_plan(int64_t I, int64_t J, int64_t R, int nb, bool allow_split, in
     GemmPlan p;
     p.splits = 1;
     // edge of the tile along one dimension: weigh the padding it leaves against the lower efficiency of narrow
-    // tiles (relative MFMA rates measured on this kernel: 256 -> 1, 128 -> 0.85, 64 -> 0.65)
-    auto edge = [](int64_t n) {
+    // tiles (relative MFMA rates measured on this kernel: 256 -> 1, 128 -> 0.85, 64 -> 0.65; with a reduction of one or two
+    // steps the stores count, hardly the multiplies: 24 -> 144 channels, three 64-column tiles instead of one of 256,
+    // 107 -> 97 us for 512 images of 32x32)
+    auto edge = [R](int64_t n) {
         const int e[3] = {256, 128, 64};
-        const double eff[3] = {1.0, 0.85, 0.65};
+        const double eff[3] = {1.0, R <= 256 ? 0.95 : 0.85, R <= 256 ? 0.9 : 0.65};
         int best = 64;
         double score = -1.0;
         for (int i = 0; i < 3; ++i) {
@@ -823,6 +841,15 @@ hipError_t launch_gemm_nt_i8(const GemmArgs& a_in, hipStream_t s)
     a.cin_shift = a.conv == 1 ? shift_of(a.Cin) : -1;
     const GemmPlan p = gemm_plan(a.I, a.J, a.R, a.nb, a.splits > 1, a.conv == 2 ? GEMM_TABLE_BYTES : 0);
     const int bm = p.bm, bn = p.bn;
+    if (a.splits == 1 && a.conv < 2) {
+        // Mid-sized tiles without a split (forward launches of convolutions above all): two workgroups of four wavefronts per
+        // compute unit, with stages of 64 bytes, so that one's stores run under the other's multiplies; a single 256 x 128
+        // workgroup per unit stores for as long as it multiplies when the reduction is short.  64 -> 128 channels at
+        // 32x32, 512 images: 118 -> 93 us, 128 -> 256 at 16x16: 45 -> 39 us.  Not for 256 x 256: half the tile moves half
+        // as much again per multiply (128 -> 256 at 32x32 262 -> 283 us, 16384 x 4096 x 4096 252 -> 321 us).
+        if (bm == 256 && bn == 128) return launch_paired<256, 128, 4, 1>(a, s);
+        if (bm == 128 && bn == 256) return launch_paired<128, 256, 2, 2>(a, s);
+    }
     if (bn == 256) {
         if (bm == 256) return launch_cfg<256, 256, 4, 2>(a, s);
         if (bm == 128) return launch_cfg<128, 256, 2, 2>(a, s);

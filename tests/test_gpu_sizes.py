@@ -167,3 +167,26 @@ def test_quantize_few_columns_row_major_only(ff, rows, cols, mode):
     torch.cuda.synchronize()
     assert s.item() == s_ref
     check_q(q, q_ref, "q")
+
+
+@pytest.mark.parametrize("B,K,N,relu", [
+    (140000, 20, 100, 1), (135000, 150, 101, 0), (131100, 260, 128, 1),   # 256 x 128 tiles: one, three and five short steps
+    (70000, 300, 250, 1), (66000, 70, 256, 0), (33000, 64, 500, 1),       # 128 x 256 tiles
+    (9000, 48, 144, 1), (9000, 48, 96, 1), (5000, 200, 320, 0)])          # short reductions, narrow last tiles
+def test_forward_tiles_two_workgroups_per_compute_unit(ff, B, K, N, relu):
+    """Several tiles per workgroup, a count that does not divide evenly, ragged rows and columns in the last ones."""
+    rng = np.random.default_rng(B + K)
+    layer = Layer("dense", in_features=K, out_features=N, relu=relu)
+    desc = ff.layer_desc(layer, B)
+    a_q = rng.integers(-127, 128, (B, K)).astype(np.int8)
+    w_q = rng.integers(-127, 128, (N, K)).astype(np.int8)
+    acc_ref = (a_q.astype(np.float32) @ w_q.astype(np.float32).T).astype(np.int32)   # exact: |sum| < 2^24
+    g_ref = O.goodness(acc_ref, relu, O.goodness_shift(K, N), np.float32(0.01), np.float32(0.02))
+    acc = empty32(B, N)
+    gsum = torch.full((B,), 7, dtype=torch.int64, device="cuda")
+    vmax = torch.full((B,), 9, dtype=torch.int32, device="cuda")
+    ff.ff_layer_forward(desc, dev(pad8(a_q)), dev(pad8(w_q)), acc, gsum, vmax, workspace())
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(acc.cpu().numpy()[:, :N], acc_ref)
+    np.testing.assert_array_equal(gsum.cpu().numpy().view(np.uint64), g_ref["g_int"])
+    np.testing.assert_array_equal(vmax.cpu().numpy(), g_ref["vmax"])
