@@ -154,7 +154,9 @@ static bool chunks_together(const Dims& d) { return d.n_chunks > 1 && d.B == d.n
 // Scratch for the partial results of a split weight gradient: [launch][pass][chunk of the launch][split][N, pitch32(K)].
 static size_t wgrad_part_bytes(const Dims& d, int nb)
 {
-    if (d.kind == FF_DWCONV2D) return 0;
+    if (d.kind == FF_DWCONV2D)
+        return align_up((size_t)(nb * d.n_chunks) * (size_t)dwconv_wgrad_splits(d.g, d.chunk_b, nb * d.n_chunks) *
+                            (size_t)(d.N * pitch32(d.K)) * sizeof(int32_t), 256);
     const int extra = d.kind == FF_DENSE ? 0 : GEMM_TABLE_BYTES;
     const int problems = nb * (chunks_together(d) ? d.n_chunks : 1);
     const GemmPlan p = gemm_plan(d.N, wgrad_cols(d), min(d.M, d.chunk_b * d.rps), problems, true, extra);
@@ -590,31 +592,38 @@ static ff_status run_wgrad(const Dims& d, const int8_t* gy_t, int64_t st_gy, con
         }
     }
     if (d.kind == FF_DWCONV2D) {
-        // depthwise accumulators are added to with atomics and must start at zero: one fill over all passes and chunks
-        // when that span is small (it usually is: C x 12 words per accumulator), else one per accumulator
-        const int64_t dw_span = (int64_t)(nb - 1) * st_dw + (int64_t)(d.n_chunks - 1) * dw_elems + elems;
-        const bool dw_one_fill = dw_span <= (int64_t(1) << 20);
-        if (dw_one_fill) HIPCHK_T(FF_K_SMALL, launch_fill_u32((uint32_t*)dw, dw_span, 0u, s));
-        for (int c = 0; c < d.n_chunks; ++c) {
-            // gy_t holds the ROW-MAJOR int8 gradient [M, pitch(C)] for this layer kind
-            for (int z = 0; z < nb && !dw_one_fill; ++z)
-                HIPCHK_T(FF_K_SMALL, launch_fill_u32((uint32_t*)(dw + z * st_dw + c * dw_elems), elems, 0u, s));
-            DwArgs p;
-            memset(&p, 0, sizeof(p));
-            p.a = aqt;
-            p.st_a = st_aqt;
-            p.g = d.g;
-            p.B = (int32_t)d.B;
-            p.gy = gy_t;
-            p.ldg = pitch8(d.N);
-            p.st_gy = st_gy;
-            p.dw = dw + c * dw_elems;
+        // gy_t holds the ROW-MAJOR int8 gradient [M, pitch(C)] for this layer kind
+        DwArgs p;
+        memset(&p, 0, sizeof(p));
+        p.a = aqt;
+        p.st_a = st_aqt;
+        p.g = d.g;
+        p.B = (int32_t)d.B;
+        p.gy = gy_t;
+        p.ldg = pitch8(d.N);
+        p.st_gy = st_gy;
+        p.nb = nb;
+        p.nc = d.n_chunks;
+        p.chunk_b = (int32_t)d.chunk_b;
+        p.splits = dwconv_wgrad_splits(d.g, d.chunk_b, nb * d.n_chunks);
+        if (terms && part_elems >= nb * d.n_chunks * p.splits * elems) {
+            p.dw = part;
+            p.st_split = elems;
+            p.st_dw2 = p.splits * elems;
+            p.st_dw = d.n_chunks * p.st_dw2;
+            for (int c = 0; c < d.n_chunks; ++c) {
+                terms->splits[c] = p.splits;
+                for (int z = 0; z < nb; ++z) terms->term[z][c] = part + z * p.st_dw + c * p.st_dw2;
+            }
+        } else {   // accumulators that are added to with atomics start at zero
+            p.dw = dw;
             p.st_dw = st_dw;
-            p.b0 = (int32_t)(c * d.chunk_b);
-            p.b1 = (int32_t)min(d.B, (c + 1) * d.chunk_b);
-            p.nb = nb;
-            HIPCHK_T(FF_K_DWCONV, launch_dwconv_wgrad(p, s));
+            p.st_dw2 = dw_elems;
+            for (int z = 0; z < nb; ++z)
+                for (int c = 0; c < d.n_chunks; ++c)
+                    HIPCHK_T(FF_K_SMALL, launch_fill_u32((uint32_t*)(dw + z * st_dw + c * dw_elems), elems, 0u, s));
         }
+        HIPCHK_T(FF_K_DWCONV, launch_dwconv_wgrad(p, s));
         return FF_OK;
     }
     // one launch for all chunks, or one per chunk (chunks of different sizes)
@@ -680,14 +689,17 @@ static ff_status run_wgrad(const Dims& d, const int8_t* gy_t, int64_t st_gy, con
             g.st_c2 = g.splits * elems;
             g.st_c = together * g.st_c2;
             HIPCHK_T(FF_K_GEMM_DW, launch_gemm_nt_i8(g, s));
-            for (int c = 0; c < together; ++c) {
-                if (terms) {
+            if (terms) {
+                for (int c = 0; c < together; ++c) {
                     terms->splits[l + c] = g.splits;
                     for (int z = 0; z < nb; ++z) terms->term[z][l + c] = mine + z * g.st_c + c * g.st_c2;
-                } else {
-                    HIPCHK_T(FF_K_GEMM_DW, launch_reduce_splits(mine + c * g.st_c2, g.splits, elems, g.st_c,
-                                                                out + c * dw_elems, st_dw, elems, nb, s));
                 }
+            } else {
+                // (one launch over the passes of a chunk, or over the chunks of a pass)
+                const int inner = nb == 1 ? together : nb, outer = nb == 1 ? 1 : together;
+                for (int c = 0; c < outer; ++c)
+                    HIPCHK_T(FF_K_GEMM_DW, launch_reduce_splits(mine + c * g.st_c2, g.splits, elems, nb == 1 ? g.st_c2 : g.st_c,
+                                                                out + c * dw_elems, nb == 1 ? dw_elems : st_dw, elems, inner, s));
             }
         } else {
             HIPCHK_T(FF_K_GEMM_DW, launch_gemm_nt_i8(g, s));
@@ -1580,41 +1592,74 @@ static ff_status train_step_impl(const ff_net_desc* net, const ff_net_state* sta
         const bool patches = wgrad_from_patches(d);
         const size_t off_q = dense ? w.off_aqt[t] : (patches ? w.off_col[t] : w.off_aq[t]);
         const size_t st_q = dense ? w.st_aqt[t] : (patches ? w.st_col[t] : w.st_aq[t]);
-        WgradTerms terms;
-        const ff_status ws_ = run_wgrad(d, (const int8_t*)(base + w.off_gy), (int64_t)w.st_gy,
-                                        (const int8_t*)(base0 + off_q), (int64_t)st_q, (int32_t*)(base + w.off_part),
-                                        (int64_t)(w.part_bytes / sizeof(int32_t)), (int32_t*)(base + w.off_dw),
-                                        (int64_t)(w.st_dw / sizeof(int32_t)), dw_elems, 2, s, &terms);
-        if (ws_ != FF_OK) return ws_;
-
-        UpdateArgs u;
-        memset(&u, 0, sizeof(u));
-        u.w = state->w_master[t];
-        u.N = d.N;
-        u.K = d.K;
-        u.lddw = pitch32(d.K);
-        u.n_terms = 2 * d.n_chunks;
-        u.st_split = terms.st_split;
-        for (int p = 0; p < 2; ++p)
-            for (int cc = 0; cc < d.n_chunks; ++cc) {
-                const int tt = p * d.n_chunks + cc;
-                u.dw[tt] = terms.term[p][cc];
-                u.splits[tt] = terms.splits[cc];
-                u.s_g[tt] = s_g + 2 * gl + p;
-                u.s_a[tt] = s_a + 2 * t + p;
-            }
-        u.lr = lr;
-        u.total_samples = (int32_t)(2 * B);
         uint32_t* wbmax = (uint32_t*)(base + w.off_wbmax);
-        u.block_max = wbmax;
-        u.max_blocks = UPDATE_MAX_BLOCKS;
-        HIPCHK_T(FF_K_UPDATE, launch_update(u, s));
+        int candidates = 0;   // absmax candidates the update leaves at wbmax
+        // Both passes in one workgroup halve the launch's workgroups: alone on the chip it has to have two per compute unit all
+        // the same (1500 x 1500 at 1500 samples, 288 tiles: the chain's step 259 -> 269 us); beside other lanes it need not.
+        const int fused = d.kind == FF_DENSE && d.n_chunks == 1 && aligned16(state->w_master[t]) ? gemm_update_blocks(d.N, d.K, d.M) : 0;
+        if (fused && (n_lanes > 1 || fused >= 2 * num_cus())) {
+            GemmArgs g;
+            memset(&g, 0, sizeof(g));
+            g.P = (const int8_t*)(base + w.off_gy);
+            g.st_p = (int64_t)w.st_gy;
+            g.ldp = pitch8(d.M);
+            g.Q = (const int8_t*)(base0 + off_q);
+            g.st_q = (int64_t)st_q;
+            g.ldq = pitch8(d.M);
+            g.I = (int32_t)d.N;
+            g.J = (int32_t)d.K;
+            g.R = (int32_t)d.M;
+            g.rows_per_sample = 1;
+            g.nb = 2;
+            g.splits = 1;
+            g.upd_w = state->w_master[t];
+            for (int p = 0; p < 2; ++p) {
+                g.upd_s_g[p] = s_g + 2 * gl + p;
+                g.upd_s_a[p] = s_a + 2 * t + p;
+            }
+            g.upd_lr = lr;
+            g.upd_samples = (int32_t)(2 * B);
+            g.upd_max = wbmax;
+            g.clk = g_clock_probe;
+            HIPCHK_T(FF_K_GEMM_DW, launch_gemm_nt_i8(g, s));
+            candidates = fused;
+        } else {
+            WgradTerms terms;
+            const ff_status ws_ = run_wgrad(d, (const int8_t*)(base + w.off_gy), (int64_t)w.st_gy,
+                                            (const int8_t*)(base0 + off_q), (int64_t)st_q, (int32_t*)(base + w.off_part),
+                                            (int64_t)(w.part_bytes / sizeof(int32_t)), (int32_t*)(base + w.off_dw),
+                                            (int64_t)(w.st_dw / sizeof(int32_t)), dw_elems, 2, s, &terms);
+            if (ws_ != FF_OK) return ws_;
+
+            UpdateArgs u;
+            memset(&u, 0, sizeof(u));
+            u.w = state->w_master[t];
+            u.N = d.N;
+            u.K = d.K;
+            u.lddw = pitch32(d.K);
+            u.n_terms = 2 * d.n_chunks;
+            u.st_split = terms.st_split;
+            for (int p = 0; p < 2; ++p)
+                for (int cc = 0; cc < d.n_chunks; ++cc) {
+                    const int tt = p * d.n_chunks + cc;
+                    u.dw[tt] = terms.term[p][cc];
+                    u.splits[tt] = terms.splits[cc];
+                    u.s_g[tt] = s_g + 2 * gl + p;
+                    u.s_a[tt] = s_a + 2 * t + p;
+                }
+            u.lr = lr;
+            u.total_samples = (int32_t)(2 * B);
+            u.block_max = wbmax;
+            u.max_blocks = UPDATE_MAX_BLOCKS;
+            HIPCHK_T(FF_K_UPDATE, launch_update(u, s));
+            candidates = update_blocks(u);
+        }
 
         QuantArgs qa;
         memset(&qa, 0, sizeof(qa));
         qa.x = state->w_master[t];
         qa.amax_bits = wbmax;
-        qa.amax_n = update_blocks(u);
+        qa.amax_n = candidates;
         qa.round_mode = FF_ROUND_NEAREST_EVEN;
         qa.rows = d.N;
         qa.cols = d.K;

@@ -319,12 +319,23 @@ struct GemmArgs {
     // log2 of C_in (conv == 1) when that is a power of two, else -1: the loader then indexes with shifts instead of
     // integer divisions.  Filled in by launch_gemm_nt_i8.
     int32_t cin_shift;
+    // weight gradient and update in one launch (upd_w non-null; nb == 2 passes, no split, no fused reductions): C is not
+    // written; the weights [I, J] (contiguous, 16-byte aligned, J % 4 == 0) are updated from the accumulators of both passes and
+    // workgroup b leaves the largest magnitude of its new weights at upd_max[b]
+    float* upd_w;
+    const float* upd_s_g[2];
+    const float* upd_s_a[2];
+    float upd_lr;
+    int32_t upd_samples;
+    uint32_t* upd_max;
     // instrumentation (null normally): every workgroup adds the shader-clock cycles and the 100 MHz constant-clock
     // ticks it was alive to clk[0] and clk[1] (their ratio is the mean shader clock during the launch) and the
     // shader clocks of each tile by phase to clk[2..6] / clk[8..12]
     unsigned long long* clk;   // 16 counters, see ff_timing_clock_probe
 };
 hipError_t launch_gemm_nt_i8(const GemmArgs& a, hipStream_t s);
+// workgroups of the launch with the fused update, or 0 where that is not the better way (see gemm_update_blocks)
+int gemm_update_blocks(int64_t I, int64_t J, int64_t R);
 int num_cus();   // compute units of the current device (256 when the query fails)
 // register-resident MFMA loop (see ff_probe_mfma_ceiling): one workgroup of 512 threads per compute unit
 hipError_t launch_mfma_ceiling(int32_t* sink, int iters, int kind, unsigned long long* clk, int* workgroups, hipStream_t s);
@@ -406,14 +417,15 @@ struct DwArgs {
     int32_t* vmax;
     int64_t st_g;
     int32_t relu, rshift;
-    // weight gradient over the samples [b0, b1)
+    // weight gradient over nc chunks of chunk_b samples each (the last may be shorter)
     const int8_t* gy;   // row-major int8 local gradient [B*Ho*Wo, ldg]
     int64_t ldg, st_gy;
-    int32_t* dw;        // [C, 12] int32, zeroed
-    int64_t st_dw;
-    int32_t b0, b1;
+    int32_t* dw;        // [C, 12] int32 per pass and chunk (st_dw, st_dw2 apart): splits partial results st_split apart, or
+    int64_t st_dw, st_dw2, st_split;   // (st_split == 0) one zeroed accumulator
+    int32_t nc, chunk_b, splits;
     int32_t nb;
 };
+int dwconv_wgrad_splits(const ConvGeom& g, int64_t chunk_b, int problems);
 hipError_t launch_dwconv_forward(const DwArgs& p, hipStream_t s);
 hipError_t launch_dwconv_wgrad(const DwArgs& p, hipStream_t s);
 

@@ -8,7 +8,7 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 from oracle import ff_oracle as O  # noqa: E402
-from workloads import Layer, Workload, conv_stack, mlp  # noqa: E402
+from workloads import Layer, Workload, bottleneck_stack, conv_stack, mlp  # noqa: E402
 
 
 @pytest.fixture(scope="module")
@@ -190,3 +190,23 @@ def test_forward_tiles_two_workgroups_per_compute_unit(ff, B, K, N, relu):
     np.testing.assert_array_equal(acc.cpu().numpy()[:, :N], acc_ref)
     np.testing.assert_array_equal(gsum.cpu().numpy().view(np.uint64), g_ref["g_int"])
     np.testing.assert_array_equal(vmax.cpu().numpy(), g_ref["vmax"])
+
+
+@pytest.mark.parametrize("blocks,H,W,B", [
+    ([(2, 16, 1), (3, 24, 2)], 10, 12, 20),     # strips that end inside a map, then a stride of two
+    ([(5, 8, 1)], 9, 8, 33), ([(9, 16, 1)], 7, 7, 40),   # two channel groups; a width that is no multiple of four
+    ([(1, 8, 1)], 32, 32, 140)])                # two sample chunks of different sizes
+def test_depthwise_step_partial_results(ff, blocks, H, W, B):
+    wl = Workload("dw", bottleneck_stack(16, blocks, H, W), B, "normal", lam=0.05)
+    _run_steps(ff, wl, 1, theta_layer=_matched_thetas(wl), live=True)
+
+
+@pytest.mark.parametrize("widths,B", [([132, 260, 64], 70), ([1000, 333, 96], 200), ([64, 1001, 500, 40], 33), ([516, 130], 130)])
+@pytest.mark.parametrize("mode", ["kernels", "lanes"])
+def test_dense_step_with_the_update_in_the_weight_gradient(ff, widths, B, mode):
+    """Reduction lengths of one, two and three steps, ragged output tiles; a layer of 333 or 1001 inputs keeps the update as
+    a launch of its own."""
+    if mode == "lanes" and len(widths) < 3:
+        pytest.skip("one layer: no lanes")
+    wl = Workload("upd", mlp(widths, False), B, "normal", lam=0.3)
+    _run_steps(ff, wl, 2, theta_layer=_matched_thetas(wl), launch_mode=mode)
