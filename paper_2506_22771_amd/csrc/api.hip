@@ -1278,14 +1278,14 @@ static ff_status train_step_impl(const ff_net_desc* net, const ff_net_state* sta
     }
     uint32_t* const xmax = (uint32_t*)(base + w.off_xmax);
     HIPCHK_T(FF_K_ABSMAX, launch_absmax(x_pos, st_x, 2, n_in, xmax, s, (uint32_t*)base, (int64_t)(w.zero_bytes / 4)));
-    // Small batches: one kernel forms every layer's goodness, loss and coefficients after the forward pass, and the hand-off
-    // quantisers take their range from the per-sample maxima.  Each of their workgroups reads all samples of the pass
-    // (256 threads: a few loads each; with normalisation also a square root and a division per sample), which for larger
-    // batches costs more than the launch per layer it saves.
-    bool normalised = false;
-    for (int i = 0; i < k; ++i) normalised = normalised || net->layers[i].l2norm_out;
-    const bool goodness_last = B <= (normalised ? 1024 : 4096);
-
+    // One kernel forms every layer's goodness, loss and coefficients after the forward pass; the hand-off needs only the range
+    // of a layer's output.  Small batches: each of the quantiser's workgroups takes it from the per-sample maxima (256
+    // threads: a few loads each; with normalisation also a square root and a division per sample).  Larger ones: a small
+    // launch of its own.  Beyond 16384 samples the reported loss of a layer wants more than one workgroup: the kernels per layer.
+    // With normalisation, step by the kernels per layer against this: 784-1000-1000-1000 with 4000 samples 261 -> 252 us,
+    // 500-600-700-300 with 2000 161 -> 148; without, 784-1000-1000-1000 with 6000 316 -> 304, 4096^3 with 8192 1370 -> 1369.
+    const bool goodness_last = B <= 16384;
+    auto range_launch = [&](const ff_layer_desc& L) { return B > (L.l2norm_out ? 1024 : 4096); };
     // ---- streams: the caller's, plus the library's own where the step runs independent work side by side
     hipStream_t lane_stream[MAX_LANES];
     for (int l = 0; l < MAX_LANES; ++l) lane_stream[l] = s;
@@ -1354,7 +1354,7 @@ static ff_status train_step_impl(const ff_net_desc* net, const ff_net_state* sta
             a.relu = Lp.relu ? 1 : 0;
             a.l2norm = Lp.l2norm_out ? 1 : 0;
             if (goodness_last) {
-                a.vmax = vmax + (int64_t)j * 2 * B;
+                if (!range_launch(Lp)) a.vmax = vmax + (int64_t)j * 2 * B;
                 a.gsum = gsum + (int64_t)j * 2 * B;
                 a.B = (int32_t)B;
                 a.rshift = goodness_shift(dp.K, dp.rps * dp.N);
@@ -1461,7 +1461,22 @@ static ff_status train_step_impl(const ff_net_desc* net, const ff_net_state* sta
             HIPCHK_T(FF_K_RESIDUAL, launch_goodness_fx(fa, s));
         }
 
-        if (goodness_last) continue;
+        if (goodness_last) {
+            if (plain && i + 1 < k && range_launch(L)) {
+                RangeArgs r;
+                memset(&r, 0, sizeof(r));
+                r.vmax = vmax + (int64_t)i * 2 * B;
+                r.gsum = gsum + (int64_t)i * 2 * B;
+                r.s_a = s_a + 2 * i;
+                r.s_w = state->s_w[i];
+                r.rshift = goodness_shift(d.K, d.rps * d.N);
+                r.l2norm = L.l2norm_out ? 1 : 0;
+                r.B = B;
+                r.out = out_amax + 2 * (i + 1);
+                HIPCHK_T(FF_K_SMALL, launch_handoff_range(r, s));
+            }
+            continue;
+        }
         GoodnessArgs ga;
         memset(&ga, 0, sizeof(ga));
         ga.gsum = gsum + (int64_t)i * 2 * B;

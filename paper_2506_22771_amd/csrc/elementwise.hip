@@ -293,7 +293,7 @@ __device__ __forceinline__ void quantize_tile(const QuantArgs& a, uint32_t* tile
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 if (!row_in(QT_RH * u + j)) rowf[u][j] = 0.0f;
-                else if (norm && a.vmax) rowf[u][j] = goodness_value(a.gsum[z * a.st_b + smp], pow2r, s_yd);
+                else if (norm && a.gsum) rowf[u][j] = goodness_value(a.gsum[z * a.st_b + smp], pow2r, s_yd);
                 else rowf[u][j] = per_sample[smp];
                 if (++rem >= rps) { rem = 0; ++smp; }
             }
@@ -815,6 +815,32 @@ hipError_t launch_grad_amax(const float* ct, const int32_t* vmax, const float* s
 // is worked out side by side, the coefficients meet in LDS and every thread forms its own suffix sum.  The workgroups
 // after them: the loss of one layer each, in a fixed order.
 // ------------------------------------------------------------------------------------------------
+// The range of one layer's output for the hand-off of a larger batch: one workgroup per pass.  Bound by its latency (two
+// dependent loads, a square root, a reduction): a batch of 16384 is 16 samples per thread, too few to split further.
+__global__ __launch_bounds__(1024) void k_handoff_range(RangeArgs a)
+{
+    const int z = blockIdx.x;
+    const float s_y = a.s_a[z] * a.s_w[0];
+    const double s_yd = (double)s_y, pow2r = (double)(1ull << a.rshift);
+    uint32_t m = 0;
+    for (int64_t b = threadIdx.x; b < a.B; b += 1024) {
+        float y = (float)a.vmax[z * a.B + b] * s_y;
+        if (a.l2norm) {
+            const float nrm = sqrtf(goodness_value(a.gsum[z * a.B + b], pow2r, s_yd));
+            y = nrm > 0.0f ? y / nrm : 0.0f;
+        }
+        m = max(m, __float_as_uint(y));
+    }
+    block_store_max_bits<1024>(m, a.out + z);
+}
+
+hipError_t launch_handoff_range(const RangeArgs& a, hipStream_t s)
+{
+    if (a.B <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_handoff_range, dim3(2), dim3(1024), 0, s, a);
+    return hipGetLastError();
+}
+
 constexpr int GA_WAVES = 16, GA_THREADS = 64 * GA_WAVES;
 
 __device__ __forceinline__ float goodness_of(const GoodnessAllArgs& a, const GoodnessLayer& L, int i, int p, int64_t b, float& s_y)

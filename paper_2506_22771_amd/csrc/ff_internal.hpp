@@ -63,9 +63,9 @@ struct QuantArgs {
     const float* per_sample; // HANDOFF with l2norm: goodness[B]; GRAD, F32_GRAD: coeff_total[B]
     int32_t rows_per_sample;
     int32_t relu, l2norm;
-    // HANDOFF, optional: the range (and with l2norm the goodness of a row's sample) straight from the contraction's
-    // per-sample maxima and sums of B samples per pass (st_b apart); amax_bits and per_sample are then unused.  Every
-    // workgroup reads all B of them: for batches small beside the tensor.
+    // HANDOFF, optional: gsum: with l2norm the goodness of a row's sample straight from the contraction's sums (st_b apart
+    // per pass) instead of per_sample.  vmax: the range straight from its per-sample maxima (and sums) instead of
+    // amax_bits; every workgroup reads all B of them, for batches small beside the tensor.
     const int32_t* vmax;
     const unsigned long long* gsum;
     int32_t B, rshift;
@@ -136,6 +136,18 @@ struct GoodnessArgs {
 };
 constexpr int GL_MAX_WG = 32;
 hipError_t launch_goodness_loss(const GoodnessArgs& a, hipStream_t s);
+
+// max over the samples of the handed-on activity (act(s_y acc), or that divided by sqrt(goodness)), both passes -> out[0], out[1]
+struct RangeArgs {
+    const int32_t* vmax;              // [2][B]
+    const unsigned long long* gsum;   // [2][B]
+    const float* s_a;                 // [2]
+    const float* s_w;
+    int32_t rshift, l2norm;
+    int64_t B;
+    uint32_t* out;
+};
+hipError_t launch_handoff_range(const RangeArgs& a, hipStream_t s);
 
 // Goodness, loss, dL/dG and look-ahead of all layers of a step in one launch (two passes, [k][2][B] arrays).
 struct GoodnessLayer {

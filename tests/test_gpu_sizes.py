@@ -147,7 +147,7 @@ def test_quantize_tile_sizes(ff, rows, cols, mode):
 
 
 @pytest.mark.parametrize("B,l2,depth", [(1, True, 2), (63, True, 3), (65, False, 3), (1024, True, 3), (1025, True, 2), (4096, False, 2),
-                                        (4097, False, 2), (130, False, 19)])
+                                        (4097, False, 2), (16384, True, 2), (16385, True, 2), (130, False, 19)])
 def test_step_goodness_after_the_forward_pass_or_per_layer(ff, B, l2, depth):
     """Batches on both sides of the line between one goodness / look-ahead launch and one launch per layer; more layers
     than a workgroup of the single launch takes at a time."""
