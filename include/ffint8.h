@@ -136,7 +136,7 @@ typedef struct {
 /* How ff_train_step issues its work.
  * FF_LAUNCH_KERNELS: one kernel per operation (quantise, contraction, goodness/loss, ...), about nine launches per
  *   layer.
- * FF_LAUNCH_FUSED: the whole step as ONE persistent kernel (after the fill that clears the workspace head) whose
+ * FF_LAUNCH_FUSED: the whole step as ONE persistent kernel whose
  *   workgroups meet at device-wide barriers where the method has device-wide dependencies (a per-tensor absmax, a
  *   per-sample goodness).  For the launch-bound regime of small networks and batches, the one nearest the paper's
  *   own batch of 32 (Section V-A).  Plain dense stacks (no convolutions, residual wiring or FF_LOOKAHEAD_CHAIN) of at
