@@ -42,24 +42,8 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 
 constexpr int BK = 128;  // reduction bytes per LDS stage
 
-#ifndef FF_PRO2
-#define FF_PRO2 1
-#endif
-#ifndef FF_PERSIST
-#define FF_PERSIST 1
-#endif
-#ifndef FF_NEXT_TILE_PREFETCH
-#define FF_NEXT_TILE_PREFETCH 1
-#endif
-#ifndef FF_SPLIT_ISSUE
-#define FF_SPLIT_ISSUE 1
-#endif
-#ifndef FF_SPLIT_TARGET_BIG
-#define FF_SPLIT_TARGET_BIG 256
-#endif
-#ifndef FF_STAGED_EPI
-#define FF_STAGED_EPI 1   // 1: interior tiles leave through LDS as whole rows (see the epilogue)
-#endif
+// workgroups a split reduction of one-per-compute-unit tiles is cut into (see gemm_plan)
+constexpr int64_t SPLIT_TARGET_BIG = 256;
 
 template <int N> __device__ __forceinline__ void wait_vmcnt() {
     static_assert(N >= 0 && N < 64, "vmcnt range");
@@ -132,7 +116,7 @@ __global__ __launch_bounds__(WM* WN * 64) __attribute__((amdgpu_waves_per_eu(BKT
     // 256-row tiles stage in the SECOND operand stage (and a little beyond it; 16 rows at a time for the 256 x 256 tile,
     // so that it fits), which leaves the first stage free for the first copies of the workgroup's next tile (persistent
     // launches); the others 32 rows from 0.
-    constexpr bool PREFETCH = FF_NEXT_TILE_PREFETCH && (BM == 256 || BK == 64) && CONV < 2 && MODE < 2;
+    constexpr bool PREFETCH = (BM == 256 || BK == 64) && CONV < 2 && MODE < 2;
     constexpr int EROWS = PREFETCH && (BN == 256 || BK == 64) ? 16 : 32;
     constexpr int EROW = WTN * 4 + 16;
     constexpr int ESLICE = EROWS * EROW;
@@ -339,7 +323,6 @@ __global__ __launch_bounds__(WM* WN * 64) __attribute__((amdgpu_waves_per_eu(BKT
     // stage kt are issued before the barrier of step kt, so its buffer is free right after that barrier and
     // the copy of stage kt+2 is issued there: one copy is in flight at every moment, each with a whole step
     // of time to land.
-#if FF_PRO2
     if (PREFETCH && prefetched) {
         // Step 0 is in LDS already: every wavefront waited for its own copies of it before the stores of the previous
         // epilogue, and the barrier at the end of that tile made them visible to all.  Only step 1 goes out now; the
@@ -366,13 +349,6 @@ __global__ __launch_bounds__(WM* WN * 64) __attribute__((amdgpu_waves_per_eu(BKT
     __builtin_amdgcn_s_barrier();
     ldfrag(0, lds, 0);
     }
-#else
-    issue(kt0, 0);
-    wait_vmcnt<0>();
-    __builtin_amdgcn_s_barrier();
-    ldfrag(0, lds, 0);
-    if (kt0 + 1 < nk) issue(kt0 + 1, 1);
-#endif
     if (a.clk) ph1 = clock64();
     int cur = 0;   // stage of step kt: (kt - kt0) % NS
     for (int kt = kt0; kt < nk; ++kt) {
@@ -391,7 +367,6 @@ __global__ __launch_bounds__(WM* WN * 64) __attribute__((amdgpu_waves_per_eu(BKT
         if (NS > 2 && kt + NS - 1 < nk) wait_vmcnt<(NS - 2) * CH>();
         else wait_vmcnt<0>();
         __builtin_amdgcn_s_barrier();
-#if FF_SPLIT_ISSUE
         // The copy instructions of a step keep the address unit busy for about a thousand clocks (64 KB at 64 bytes
         // per clock).  Half of the wavefronts -- one of the two on every SIMD -- issue theirs before the last
         // multiplies of the step, the other half after them, so that every SIMD has multiplies to run while the
@@ -401,11 +376,6 @@ __global__ __launch_bounds__(WM* WN * 64) __attribute__((amdgpu_waves_per_eu(BKT
         if (kt + 1 < nk) ldfrag(0, sn, 0);
         mma(1);
         if (!early && kt + NS < nk) issue(kt + NS, cur);
-#else
-        if (kt + NS < nk) issue(kt + NS, cur);
-        if (kt + 1 < nk) ldfrag(0, sn, 0);
-        mma(1);
-#endif
         cur = nxt;
     }
 
@@ -473,7 +443,7 @@ __global__ __launch_bounds__(WM* WN * 64) __attribute__((amdgpu_waves_per_eu(BKT
     // CONV 2 with channel counts that are no multiple of 16: the columns run over whole 16-channel chunks and the store
     // leaves the channels beyond C_in out
     const bool compact = CONV == 2 && a.cin_out != a.Cin;
-    const bool staged = FF_STAGED_EPI && (interior || (a.J & 3) == 0) && !compact;
+    const bool staged = (interior || (a.J & 3) == 0) && !compact;
     const bool fast_sq = a.relu && a.rshift == 0;
     int8_t* const ebase = lds + EOFF + wave * ESLICE;
     if (wait_copies && !staged) {   // (copies and stores complete in issue order: wait before the first store)
@@ -711,7 +681,7 @@ static hipError_t launch_cfg(const GemmArgs& a, hipStream_t s)
     // once -- one per compute unit, two where a workgroup takes at most half of the LDS -- when each has at least two
     // whole tiles
     int64_t gx = ntiles;
-    if (FF_PERSIST && FF_NEXT_TILE_PREFETCH && BM == 256 && a.conv < 2 && mode != 2) {
+    if (BM == 256 && a.conv < 2 && mode != 2) {
         const int stage = (BM + BN) * BK, eslice = (BN == 256 ? 16 : 32) * (BN / WN * 4 + 16);
         const int lds = 2 * stage > stage + WM * WN * eslice ? 2 * stage : stage + WM * WN * eslice;   // as in the kernel
         const int64_t resident = (int64_t)num_cus() * (lds <= 80 * 1024 ? 2 : 1);
@@ -773,7 +743,7 @@ GemmPlan gemm_plan(int64_t I, int64_t J, int64_t R, int nb, bool allow_split, in
         if (lds_extra > 0 && p.bm == 128 && p.bn == 128 && J > 256) p.bn = 256;
         // (a tile whose stages take more than half of the LDS has one workgroup per compute unit: one round of 256
         // workgroups, each with twice the reduction steps, writes and re-reads half the partial sums of two rounds of 512)
-        int64_t sp = (2 * (p.bm + p.bn) * BK + lds_extra > 80 * 1024 ? FF_SPLIT_TARGET_BIG : 512) / tiles(p.bm, p.bn);
+        int64_t sp = (2 * (p.bm + p.bn) * BK + lds_extra > 80 * 1024 ? SPLIT_TARGET_BIG : 512) / tiles(p.bm, p.bn);
         // ... (8 where one partial result is small, at most 256 KB: writing and adding up the partials then costs little)
         const int64_t min_steps = I * J * 4 <= (256 << 10) ? 8 : 16;
         if (sp > nk / min_steps) sp = nk / min_steps;
