@@ -135,12 +135,8 @@ static size_t layer_part_bytes(const Dims& d, int nb)
 // Convolutions whose forward pass materialises the row-major patch matrix (1x1 stride-1 ones never do).
 static bool explicit_patches(const Dims& d) { return d.kind == FF_CONV2D && !d.implicit && !d.pointwise; }
 // ... and whose weight gradient reads it again, reduction-major: up to four channels, where the NHWC input is mostly pad
-// channels (9 * 16 columns for 27).  Other layers' weight gradients read the NHWC input itself.  (The contraction
-// addresses the operand of one weight-gradient chunk with 32-bit offsets; layer_dims keeps the NHWC input below 2^31 bytes.)
-static bool wgrad_from_patches(const Dims& d)
-{
-    return explicit_patches(d) && d.g.Cin <= 4 && min(d.M, d.chunk_b * d.rps) * pitch8(d.K) < (int64_t(1) << 31);
-}
+// channels (9 * 16 columns for 27).  Other layers' weight gradients read the NHWC input itself.
+static bool wgrad_from_patches(const Dims& d) { return explicit_patches(d) && d.g.Cin <= 4; }
 // Columns of the weight-gradient contraction: operands read reduction-major are worked on in whole 16-byte chunks
 // (GemmArgs::conv == 2).
 static int64_t wgrad_cols(const Dims& d)
@@ -188,7 +184,9 @@ struct WsLayout {
     size_t off_c, off_ct;  // fp32 [k][2][B]
     size_t off_gy, st_gy;  // int8 scratch [2][st_gy]: transposed quantised local gradient
     size_t off_dw, st_dw, dw_bytes;  // int32 scratch [2][MAX_CHUNKS][dw_bytes]; st_dw = pass stride (bytes)
-    size_t off_col[MAX_LAYERS], st_col[MAX_LAYERS];   // explicit patch matrices [2][st] (see explicit_patches), retained
+    // explicit patch matrices [2][st]: retained where the weight gradient reads them again (wgrad_from_patches); all other
+    // layers that have one share a scratch, which only their forward contraction on the caller's stream reads
+    size_t off_col[MAX_LAYERS], st_col[MAX_LAYERS];
     size_t off_part, part_bytes;     // int32 scratch: partial sums of split weight gradients (see wgrad_part_bytes)
     size_t off_xmax;                 // uint32 [2][ABSMAX_MAX_BLOCKS]: per-workgroup absmax of the net input
     size_t off_aq[MAX_LAYERS], st_aq[MAX_LAYERS];    // quantised layer input [2][st]: dense layers share one scratch
@@ -292,17 +290,21 @@ static ff_status make_layout(const ff_net_desc* net, WsLayout* w)
     off = align_up(off + sizeof(float) * k * 2 * B, A);
     w->off_ct = off;
     off = align_up(off + sizeof(float) * k * 2 * B, A);
-    size_t aq_dense = 0, gy = 0, dw = 0, part = 0;
+    size_t aq_dense = 0, gy = 0, dw = 0, part = 0, col = 0;
     for (int i = 0; i < w->k; ++i) {
         const Dims& d = w->d[i];
         if (d.kind == FF_DENSE) aq_dense = max(aq_dense, (size_t)(d.in_rows * pitch8(d.in_cols)));
         gy = max(gy, d.kind == FF_DWCONV2D ? (size_t)(d.M * pitch8(d.N)) : (size_t)(d.N * pitch8(d.M)));
         dw = max(dw, (size_t)(d.N * pitch32(d.K)) * sizeof(int32_t));
         part = max(part, wgrad_part_bytes(d, 2));
+        if (explicit_patches(d) && !wgrad_from_patches(d)) col = max(col, (size_t)(d.M * pitch8(d.K)));
     }
     aq_dense = align_up(aq_dense, A);
     const size_t off_aq_dense = off;
     off += 2 * aq_dense;
+    col = align_up(col, A);
+    const size_t off_col_shared = off;
+    off += 2 * col;
     if (net->launch_mode != FF_LAUNCH_AUTO && net->launch_mode != FF_LAUNCH_KERNELS && net->launch_mode != FF_LAUNCH_FUSED &&
         net->launch_mode != FF_LAUNCH_LANES)
         return FF_ERR_INVALID_ARG;
@@ -377,9 +379,10 @@ static ff_status make_layout(const ff_net_desc* net, WsLayout* w)
             off += 2 * w->st_aq[i];
             w->st_aqt[i] = w->off_aqt[i] = 0;
         }
-        w->st_col[i] = explicit_patches(d) ? align_up((size_t)(d.M * pitch8(d.K)), A) : 0;
-        w->off_col[i] = off;
-        off += 2 * w->st_col[i];
+        const bool keep = wgrad_from_patches(d);
+        w->st_col[i] = keep ? align_up((size_t)(d.M * pitch8(d.K)), A) : (explicit_patches(d) ? col : 0);
+        w->off_col[i] = keep ? off : off_col_shared;
+        if (keep) off += 2 * w->st_col[i];
         w->st_acc[i] = align_up((size_t)(d.M * pitch32(d.N)) * sizeof(int32_t), A);
         w->off_acc[i] = off;
         off += 2 * w->st_acc[i];

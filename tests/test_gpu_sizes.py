@@ -210,3 +210,10 @@ def test_dense_step_with_the_update_in_the_weight_gradient(ff, widths, B, mode):
         pytest.skip("one layer: no lanes")
     wl = Workload("upd", mlp(widths, False), B, "normal", lam=0.3)
     _run_steps(ff, wl, 2, theta_layer=_matched_thetas(wl), launch_mode=mode)
+
+
+@pytest.mark.parametrize("channels,side,B", [([3, 18, 30, 22], 9, 20), ([2, 6, 6, 9], 14, 33), ([5, 7], 11, 12)])
+def test_step_with_patch_matrices_in_one_scratch(ff, channels, side, B):
+    """Several layers whose forward pass goes through a patch matrix: those of more than four channels share the scratch."""
+    wl = Workload("patches", conv_stack(channels, side, side), B, "normal", lam=0.05)
+    _run_steps(ff, wl, 1, theta_layer=_matched_thetas(wl), live=True)
