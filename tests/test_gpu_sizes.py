@@ -217,3 +217,20 @@ def test_step_with_patch_matrices_in_one_scratch(ff, channels, side, B):
     """Several layers whose forward pass goes through a patch matrix: those of more than four channels share the scratch."""
     wl = Workload("patches", conv_stack(channels, side, side), B, "normal", lam=0.05)
     _run_steps(ff, wl, 1, theta_layer=_matched_thetas(wl), live=True)
+
+
+@pytest.mark.parametrize("n", [1, 7, 8191, 8193, 2048 * 1024 + 5, 256 * 8192, 2 * 256 * 8192 - 3, 2 * 256 * 8192 + 8193, 12_000_001])
+@pytest.mark.parametrize("skew", [0, 1, 3])
+def test_absmax_finds_the_largest_element_wherever_it_is(ff, n, skew):
+    """The range of a tensor of one and several trips per workgroup, from any 4-byte aligned address: the largest magnitude at
+    the ends, on the borders of the spans and in the unaligned head and tail."""
+    buf = torch.full((n + skew,), 0.25, dtype=torch.float32, device="cuda")
+    x = buf[skew:]
+    q, s, ws = empty8(1, n), scalar(), workspace()
+    for at in sorted({0, 1, 2, 3, n // 2, 8191, 8192, 256 * 8192 - 1, 256 * 8192, 256 * 8192 + 1, n - 5, n - 2, n - 1}):
+        if not 0 <= at < n:
+            continue
+        x[at] = -508.0
+        ff.ff_quantize(x, 1, n, 0, 0, 0, q, None, s, ws)
+        assert s.item() == 4.0, at
+        x[at] = 0.25
