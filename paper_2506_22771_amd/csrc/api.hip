@@ -127,10 +127,9 @@ static size_t layer_col_bytes(const Dims& d)
 static size_t layer_part_bytes(const Dims& d, int nb)
 {
     if (d.kind == FF_DWCONV2D) return 0;
-    // (up to 512 splits of every tile but the largest, more than the contraction uses today: the published size stays)
-    const GemmPlan p = gemm_plan(d.N, d.K, min(d.M, d.chunk_b * d.rps), nb, true, -20000);
-    if (p.splits <= 1) return 0;
-    return align_up((size_t)p.splits * (size_t)(d.N * pitch32(d.K)) * sizeof(int32_t), 256);
+    const int splits = gemm_plan(d.N, d.K, min(d.M, d.chunk_b * d.rps), nb, true, false).most_splits;
+    if (splits <= 1) return 0;
+    return align_up((size_t)splits * (size_t)(d.N * pitch32(d.K)) * sizeof(int32_t), 256);
 }
 // Convolutions whose forward pass materialises the row-major patch matrix (1x1 stride-1 ones never do).
 static bool explicit_patches(const Dims& d) { return d.kind == FF_CONV2D && !d.implicit && !d.pointwise; }
@@ -153,11 +152,13 @@ static size_t wgrad_part_bytes(const Dims& d, int nb)
     if (d.kind == FF_DWCONV2D)
         return align_up((size_t)(nb * d.n_chunks) * (size_t)dwconv_wgrad_splits(d.g, d.chunk_b, nb * d.n_chunks) *
                             (size_t)(d.N * pitch32(d.K)) * sizeof(int32_t), 256);
-    const int extra = d.kind == FF_DENSE ? 0 : GEMM_TABLE_BYTES;
     const int problems = nb * (chunks_together(d) ? d.n_chunks : 1);
-    const GemmPlan p = gemm_plan(d.N, wgrad_cols(d), min(d.M, d.chunk_b * d.rps), problems, true, extra);
-    if (p.splits <= 1) return 0;
-    return align_up((size_t)(nb * d.n_chunks) * (size_t)p.splits * (size_t)(d.N * pitch32(d.K)) * sizeof(int32_t), 256);
+    const int64_t chunk_rows = min(d.M, d.chunk_b * d.rps), last_rows = d.M - (d.n_chunks - 1) * chunk_rows;
+    int splits = 1;   // (the last chunk of a pass may be shorter and cut into other tiles)
+    for (const int64_t rows : {chunk_rows, last_rows})
+        splits = max(splits, gemm_plan(d.N, wgrad_cols(d), rows, problems, true, d.kind != FF_DENSE).splits);
+    if (splits <= 1) return 0;
+    return align_up((size_t)(nb * d.n_chunks) * (size_t)splits * (size_t)(d.N * pitch32(d.K)) * sizeof(int32_t), 256);
 }
 static size_t layer_scratch_bytes(const Dims& d) { return layer_col_bytes(d) + layer_part_bytes(d, 1); }
 
@@ -678,7 +679,7 @@ static ff_status run_wgrad(const Dims& d, const int8_t* gy_t, int64_t st_gy, con
             g.stride = q.stride; g.pad = q.pad; g.Ho = q.Ho; g.Wo = q.Wo;
             g.p_bytes = (b1 - b0) * q.H * q.W * q.cpitch;
         }
-        g.splits = gemm_plan(g.I, g.J, g.R, g.nb, true, g.conv == 2 ? GEMM_TABLE_BYTES : 0).splits;
+        g.splits = gemm_plan(g.I, g.J, g.R, g.nb, true, g.conv == 2).splits;
         const int64_t room = part_elems / launches;            // this launch's share of the scratch
         const int64_t fit = room / (elems * g.nb);             // partial results per accumulator it holds
         if (g.splits > fit) g.splits = split_evenly(g.R, fit < 1 ? 1 : fit);

@@ -353,8 +353,10 @@ int num_cus();   // compute units of the current device (256 when the query fail
 hipError_t launch_mfma_ceiling(int32_t* sink, int iters, int kind, unsigned long long* clk, int* workgroups, hipStream_t s);
 struct GemmPlan {
     int bm, bn, splits;
+    int most_splits;   // splits at two workgroups per compute unit for every tile but 256 x 256: what scratch is sized for
 };
-GemmPlan gemm_plan(int64_t I, int64_t J, int64_t R, int nb, bool allow_split, int lds_extra = 0);
+// reduction_major: the launch is a GemmArgs::conv == 2 one
+GemmPlan gemm_plan(int64_t I, int64_t J, int64_t R, int nb, bool allow_split, bool reduction_major);
 constexpr int GEMM_TABLE_BYTES = 2048;   // LDS the reduction-major loader (conv == 2) takes beside the operand stages
 int split_evenly(int64_t R, int64_t splits);   // at most `splits` shares of a reduction of R, none of them empty
 // out[z][e] = sum over s < splits of part[z][s][e], e < n (n a multiple of 4); strides in elements

@@ -709,10 +709,10 @@ static hipError_t launch_cfg(const GemmArgs& a, hipStream_t s)
 //    quarters of the MFMA work) and tall only if that still leaves about two workgroups per compute unit.
 //  * allow_split (weight gradients): when the output alone has too few tiles -- a convolution's weight
 //    gradient has few output elements and a very long reduction -- a split reduction fills the chip.
-GemmPlan gemm_plan(int64_t I, int64_t J, int64_t R, int nb, bool allow_split, int lds_extra)
+GemmPlan gemm_plan(int64_t I, int64_t J, int64_t R, int nb, bool allow_split, bool reduction_major)
 {
     GemmPlan p;
-    p.splits = 1;
+    p.splits = p.most_splits = 1;
     // edge of the tile along one dimension: weigh the padding it leaves against the lower efficiency of narrow
     // tiles (relative MFMA rates measured on this kernel: 256 -> 1, 128 -> 0.85, 64 -> 0.65; with a reduction of one or two
     // steps the stores count, hardly the multiplies: 24 -> 144 channels, three 64-column tiles instead of one of 256,
@@ -737,19 +737,36 @@ GemmPlan gemm_plan(int64_t I, int64_t J, int64_t R, int nb, bool allow_split, in
         // splitting the reduction: about two workgroups per compute unit, never more (a third partial round
         // would idle most of the chip), at least 16 reduction steps per split.
         p.bm = edge(I);
-        // Reduction-major operands, 128-row tiles: twice the columns even where the last tile is half empty -- a wavefront's
-        // 64 x 128 share reads a third less LDS per multiply than 64 x 64 (128 x 576 outputs: 64 -> 128 channels at 32x32,
-        // backward 178 -> 170 us).
-        if (lds_extra > 0 && p.bm == 128 && p.bn == 128 && J > 256) p.bn = 256;
-        // (a tile whose stages take more than half of the LDS has one workgroup per compute unit: one round of 256
-        // workgroups, each with twice the reduction steps, writes and re-reads half the partial sums of two rounds of 512)
-        int64_t sp = (2 * (p.bm + p.bn) * BK + lds_extra > 80 * 1024 ? SPLIT_TARGET_BIG : 512) / tiles(p.bm, p.bn);
         // ... (8 where one partial result is small, at most 256 KB: writing and adding up the partials then costs little)
         const int64_t min_steps = I * J * 4 <= (256 << 10) ? 8 : 16;
-        if (sp > nk / min_steps) sp = nk / min_steps;
-        if (sp < 1) sp = 1;
-        const int64_t per = (nk + sp - 1) / sp;
-        p.splits = (int)((nk + per - 1) / per);   // no split without reduction steps
+        if (reduction_major) {
+            // 128-row tiles: twice the columns even where the last tile is half empty -- a wavefront's 64 x 128 share reads a
+            // third less LDS per multiply than 64 x 64 --, if the last block of rows is nearly full and there is work
+            // for at least twelve steps in every compute unit.  One pass's weight gradient with 128 columns against 256: 128 x 576
+            // outputs, 256 images of 32x32 85 -> 76 us, 128 images 50.7 -> 50.3, but 64 images 34 -> 41 and 200 of
+            // 28x28 (two launches) 74 -> 85; 384 x 576 197 -> 182 and 72 x 576 75.7 -> 77.0 for 256 images of 32x32.
+            if (p.bm == 128 && p.bn == 128 && J > 256 && (I - 1) % 128 >= 95 && tiles(128, 256) * nk >= 12 * 256) p.bn = 256;
+            // A reduction too short to give half of the compute units a workgroup with tiles this large: smaller ones.
+            // Backward, large tiles against this: 128 -> 256 channels, 64 images of 16x16, 50 -> 32 us, of 8x8 41 -> 22; 96 -> 128,
+            // 128 images of 16x16, 40 -> 30; 13 -> 256, 64 images of 8x8, 37 -> 21.  A line at all compute units instead of
+            // half makes 104 -> 256 on 100 images of 28x28 67 -> 77 us.
+            while (tiles(p.bm, p.bn) * (nk / min_steps) < 128 && (p.bm > 64 || p.bn > 64)) {
+                if (p.bn >= p.bm) p.bn /= 2;
+                else p.bm /= 2;
+            }
+        }
+        auto split = [&](int64_t workgroups) {
+            int64_t sp = workgroups / tiles(p.bm, p.bn);
+            if (sp > nk / min_steps) sp = nk / min_steps;
+            if (sp < 1) sp = 1;
+            const int64_t per = (nk + sp - 1) / sp;
+            return (int)((nk + per - 1) / per);   // no split without reduction steps
+        };
+        // (a tile whose stages take more than half of the LDS has one workgroup per compute unit: one round of 256
+        // workgroups, each with twice the reduction steps, writes and re-reads half the partial sums of two rounds of 512)
+        const int lds = 2 * (p.bm + p.bn) * BK + (reduction_major ? GEMM_TABLE_BYTES : 0);
+        p.splits = split(lds > 80 * 1024 ? SPLIT_TARGET_BIG : 512);
+        p.most_splits = split(p.bm == 256 && p.bn == 256 ? SPLIT_TARGET_BIG : 512);
         return p;
     }
     // tall tiles only if that still leaves about two workgroups per compute unit
@@ -793,7 +810,7 @@ __global__ __launch_bounds__(256) void k_reduce_splits(const int32_t* __restrict
 int gemm_update_blocks(int64_t I, int64_t J, int64_t R)
 {
     if ((J & 3) != 0) return 0;
-    const GemmPlan p = gemm_plan(I, J, R, 2, true);
+    const GemmPlan p = gemm_plan(I, J, R, 2, true, false);
     if (p.splits > 1 || p.bm != 64) return 0;
     const int64_t tiles = ((I + 63) / 64) * ((J + 127) / 128);
     return tiles <= UPDATE_MAX_BLOCKS ? (int)tiles : 0;
@@ -883,7 +900,7 @@ hipError_t launch_gemm_nt_i8(const GemmArgs& a_in, hipStream_t s)
         return sh;
     };
     a.cin_shift = a.conv == 1 ? shift_of(a.Cin) : -1;
-    const GemmPlan p = gemm_plan(a.I, a.J, a.R, a.nb, a.splits > 1, a.conv == 2 ? GEMM_TABLE_BYTES : 0);
+    const GemmPlan p = gemm_plan(a.I, a.J, a.R, a.nb, a.splits > 1, a.conv == 2);
     const int bm = p.bm, bn = p.bn;
     if (a.splits == 1 && a.conv < 2) {
         // Mid-sized tiles without a split (forward launches of convolutions above all): two workgroups of four wavefronts per

@@ -234,3 +234,35 @@ def test_absmax_finds_the_largest_element_wherever_it_is(ff, n, skew):
         ff.ff_quantize(x, 1, n, 0, 0, 0, q, None, s, ws)
         assert s.item() == 4.0, at
         x[at] = 0.25
+
+
+@pytest.mark.parametrize("B,H,W,Cin,Cout", [
+    (128, 32, 32, 576, 128), (64, 32, 32, 320, 352),   # 128 x 256 tiles, the last columns half empty, rows nearly full
+    (64, 32, 32, 320, 351), (200, 28, 28, 288, 128),   # one row less; two launches, the second too short for wide tiles
+    (16, 16, 16, 256, 256), (64, 16, 16, 250, 256), (60, 17, 15, 256, 255), (64, 16, 16, 520, 130),   # short reductions:
+    (16, 18, 15, 64, 300), (33, 13, 11, 29, 100)])                                                    # smaller tiles
+def test_weight_gradient_tiles_of_long_and_short_reductions(ff, B, H, W, Cin, Cout):
+    """A 1x1 convolution's weight gradient is a plain product, formed here in float64 (exact: sums below 2^31)."""
+    rng = np.random.default_rng(B + Cin)
+    layer = Layer("conv", H=H, W=W, C_in=Cin, C_out=Cout, ksize=1, stride=1, pad=0)
+    desc = ff.layer_desc(layer, B)
+    M, n_chunks = B * H * W, ff.ff_layer_dw_chunks(desc)
+    a_q = rng.integers(-127, 128, (M, Cin)).astype(np.int8)
+    acc = rng.integers(-200000, 200000, (M, Cout)).astype(np.int32)
+    vmax = np.maximum(acc, 0).reshape(B, -1).max(axis=1).astype(np.int32)
+    s_a, s_w = np.float32(0.0041), np.float32(0.0007)
+    ct = (rng.standard_normal(B) * 0.3).astype(np.float32)
+    gq_ref, sg_ref = O.quantize(O.local_grad(acc.reshape(B, H, W, Cout), 1, s_a, s_w, ct), 1, 4, 55)
+    gq_ref = gq_ref.reshape(M, Cout)
+    gy_t, s_g = empty8(Cout, M), scalar()
+    dw = torch.full((n_chunks, Cout, ff.ff_pitch32(Cin)), 0x5A5A5A5A, dtype=torch.int32, device="cuda")
+    ws = workspace(ff.ff_layer_workspace_bytes(desc))
+    ws.fill_(0x5A)
+    ff.ff_layer_backward_local(desc, dev(pad32(acc)), dev(vmax), dev(np.array([s_a])), dev(np.array([s_w])), dev(ct), 1, 4, 55,
+                               dev(pad8(a_q)), gy_t, s_g, dw, ws)
+    torch.cuda.synchronize()
+    assert s_g.item() == sg_ref
+    check_q(gy_t, gq_ref.T, "gy_q_t")
+    got = dw.cpu().numpy()[:, :, :Cin].astype(np.int64).sum(axis=0)
+    ref = dev(gq_ref).double().t().contiguous() @ dev(a_q).double()
+    np.testing.assert_array_equal(got, ref.cpu().numpy().astype(np.int64))
