@@ -82,6 +82,7 @@ struct QuantArgs {
     int8_t* q_t;  // [cols, ldqt] or null
     int64_t ldqt;
     int32_t qt_streaming;  // q_t is not read again soon: store it with a streaming hint
+    int32_t row_per_xcd;   // filled in by the launch: a row of tiles is worked on by one XCD
     float* scale;  // device scalar out
     // batching (second problem = first + strides, in elements of the respective type)
     int32_t nb;
