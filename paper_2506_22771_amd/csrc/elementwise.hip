@@ -1080,8 +1080,8 @@ hipError_t launch_transpose_i8(const int8_t* q, int8_t* q_t, int64_t N, int64_t 
 // weight update (HBM-bound: 4 B x (1 + n_terms x splits) read + 4 B written per weight) with fused absmax.  The matrix is
 // walked as a flat sequence of four-column groups.  A split weight gradient is summed here, while its partial results are
 // still in the caches, instead of by a kernel of its own that writes the sum for this one to read.
-// LPG (lanes per group) 1: a thread owns groups; four of them, 256 apart, per trip, all loads before the arithmetic.
-// LPG 16: many splits of a small output (a thread that walked them alone would issue one load after the other): sixteen
+// k_update: a thread owns groups; G of them, 256 apart, per trip, all loads before the arithmetic.
+// k_update_wide: many splits of a small output (a thread that walked them alone would issue one load after the other): sixteen
 // lanes share the splits of a group and meet in LDS.
 // ------------------------------------------------------------------------------------------------
 struct UpdateScale {
@@ -1119,19 +1119,20 @@ __device__ __forceinline__ int update_group(const UpdateArgs& a, int64_t e, int6
     return (int)min((int64_t)4, a.K - k);
 }
 
-template <bool VEC>
+template <bool VEC, int G>
 __global__ __launch_bounds__(256) void k_update(UpdateArgs a)
 {
+    constexpr int UNROLL = 4 / G;   // four loads in flight either way
     const UpdateScale us = update_scale(a);
     const int64_t total = a.N * ((a.K + 3) >> 2);
     uint32_t m = 0;
-    for (int64_t e0 = (int64_t)blockIdx.x * 1024; e0 < total; e0 += (int64_t)gridDim.x * 1024) {
-        float w[4][4];
-        int4 d[4][4];
-        int64_t at_w[4], at_d[4];
-        int cnt[4];
+    for (int64_t e0 = (int64_t)blockIdx.x * 256 * G; e0 < total; e0 += (int64_t)gridDim.x * 256 * G) {
+        float w[G][4];
+        int4 d[G][4];
+        int64_t at_w[G], at_d[G];
+        int cnt[G];
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
+        for (int g = 0; g < G; ++g) {
             const int64_t e = e0 + g * 256 + threadIdx.x;
             cnt[g] = 0;
             at_w[g] = at_d[g] = 0;
@@ -1156,10 +1157,11 @@ __global__ __launch_bounds__(256) void k_update(UpdateArgs a)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             if (j >= a.n_terms) break;
+#pragma unroll UNROLL
             for (int sp = 1; sp < a.splits[j]; ++sp) {
                 const int32_t* __restrict__ part = a.dw[j] + sp * a.st_split;
 #pragma unroll
-                for (int g = 0; g < 4; ++g)
+                for (int g = 0; g < G; ++g)
                     if (cnt[g]) {
                         const int4 v = *(const int4*)(part + at_d[g]);
                         d[g][j].x += v.x; d[g][j].y += v.y; d[g][j].z += v.z; d[g][j].w += v.w;
@@ -1167,7 +1169,7 @@ __global__ __launch_bounds__(256) void k_update(UpdateArgs a)
             }
         }
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
+        for (int g = 0; g < G; ++g) {
             w[g][0] = update_weight(a, us, w[g][0], d[g][0].x, d[g][1].x, d[g][2].x, d[g][3].x);
             w[g][1] = update_weight(a, us, w[g][1], d[g][0].y, d[g][1].y, d[g][2].y, d[g][3].y);
             w[g][2] = update_weight(a, us, w[g][2], d[g][0].z, d[g][1].z, d[g][2].z, d[g][3].z);
@@ -1234,17 +1236,27 @@ __global__ __launch_bounds__(256) void k_update_wide(UpdateArgs a)
     block_store_max_bits<256>(m, a.block_max + blockIdx.x);
 }
 
-// sixteen lanes per group where a thread would have many splits to walk and there are too few groups to hide that
-static bool update_wide(const UpdateArgs& a)
+static int most_splits(const UpdateArgs& a)
 {
     int most = 1;
     for (int j = 0; j < a.n_terms; ++j) most = max(most, a.splits[j]);
-    return most >= 8 && a.N * ((a.K + 3) >> 2) <= (int64_t(1) << 17);
+    return most;
 }
+// Sixteen lanes per group where a thread would have many splits to walk and there are too few groups to hide that.  A thread
+// alone against sixteen lanes: 64 -> 64 channels (9 thousand groups, 64 splits) 32 -> 8 us, 256 x 256 (16 thousand, 16 to 32)
+// 16 -> 7; past the line 700 x 700 (122 thousand, 16) 12.1 and 18.4, 500 x 500 (62 thousand, 8) 10.7 and 12.0.
+static bool update_wide(const UpdateArgs& a)
+{
+    const int most = most_splits(a);
+    return most >= 4 && a.N * ((a.K + 3) >> 2) <= (int64_t)most << 12;
+}
+// Groups of a thread per trip: four, or one where partial results are summed and four would leave the update with fewer than
+// two workgroups per compute unit (590 thousand weights, 14 splits: 38 -> 16 us; 1000 x 1000, 8 splits: 28 -> 16).
+static int update_groups(const UpdateArgs& a) { return most_splits(a) > 1 && a.N * ((a.K + 3) >> 2) <= (int64_t(1) << 19) ? 1 : 4; }
 
 int update_blocks(const UpdateArgs& a)
 {
-    const int64_t total = a.N * ((a.K + 3) >> 2), per = update_wide(a) ? 16 : 1024;
+    const int64_t total = a.N * ((a.K + 3) >> 2), per = update_wide(a) ? 16 : 256 * update_groups(a);
     return (int)max((int64_t)1, min((int64_t)a.max_blocks, (total + per - 1) / per));
 }
 
@@ -1257,8 +1269,11 @@ hipError_t launch_update(const UpdateArgs& a, hipStream_t s)
         if (vec) hipLaunchKernelGGL(k_update_wide<true>, grid, dim3(256), 0, s, a);
         else hipLaunchKernelGGL(k_update_wide<false>, grid, dim3(256), 0, s, a);
     } else {
-        if (vec) hipLaunchKernelGGL(k_update<true>, grid, dim3(256), 0, s, a);
-        else hipLaunchKernelGGL(k_update<false>, grid, dim3(256), 0, s, a);
+        const bool one = update_groups(a) == 1;
+        if (vec && one) hipLaunchKernelGGL((k_update<true, 1>), grid, dim3(256), 0, s, a);
+        else if (vec) hipLaunchKernelGGL((k_update<true, 4>), grid, dim3(256), 0, s, a);
+        else if (one) hipLaunchKernelGGL((k_update<false, 1>), grid, dim3(256), 0, s, a);
+        else hipLaunchKernelGGL((k_update<false, 4>), grid, dim3(256), 0, s, a);
     }
     return hipGetLastError();
 }

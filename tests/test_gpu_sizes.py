@@ -266,3 +266,12 @@ def test_weight_gradient_tiles_of_long_and_short_reductions(ff, B, H, W, Cin, Co
     got = dw.cpu().numpy()[:, :, :Cin].astype(np.int64).sum(axis=0)
     ref = dev(gq_ref).double().t().contiguous() @ dev(a_q).double()
     np.testing.assert_array_equal(got, ref.cpu().numpy().astype(np.int64))
+
+
+@pytest.mark.parametrize("widths,B", [
+    ([300, 301, 260], 4200),          # two partial results, one group of four columns per thread; a row that ends inside a group
+    ([130, 127, 64], 9000),           # eight, sixteen lanes per group
+    ([520, 516], 8200)])              # four, on the other side of the line between the two
+def test_dense_update_sums_the_partial_results(ff, widths, B):
+    wl = Workload("parts", mlp(widths, False), B, "normal", lam=0.05)
+    _run_steps(ff, wl, 1, theta_layer=_matched_thetas(wl), launch_mode="kernels")
