@@ -255,30 +255,31 @@ __device__ __forceinline__ void quantize_tile(const QuantArgs& a, uint32_t* tile
         (F32SRC ? (const uint32_t*)(a.x + z * a.st_x) : (const uint32_t*)(a.acc + z * a.st_acc)) + rowb * ld + col;
     uint32_t raw[U][4][4];
     const bool ragged = FORM == 1 && (a.cols & 3) != 0;   // the int32 sources' pad columns hold junk: mask them at load
+    // A tile that reaches beyond the matrix loads from its last row and first columns instead and drops what it got: with a
+    // branch around every load each would wait for the one before (hand-off of 35322 x 224, every fourth tile of a row half
+    // outside: 18.0 us with branches, 14.0 this way).
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         const uint32_t* __restrict__ ps = src + (u ? (int64_t)QT_RH * ld : 0);
+        if (FORM != 0 && !WHOLE) ps -= (col_in ? 0 : col) + max((int64_t)0, rowb + QT_RH * u - (a.rows - 1)) * ld;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             uint32_t w0 = 0, w1 = 0, w2 = 0, w3 = 0;
-            if (row_in(QT_RH * u + j) && col_in) {
-                if (FORM != 0) {
-                    const uint4 f = ld_stream16(ps);
-                    w0 = f.x; w1 = f.y; w2 = f.z; w3 = f.w;
-                    if (ragged) {
-                        if (col + 1 >= a.cols) w1 = 0;
-                        if (col + 2 >= a.cols) w2 = 0;
-                        if (col + 3 >= a.cols) w3 = 0;
-                    }
-                } else {
-                    w0 = ps[0];
-                    if (col + 1 < a.cols) w1 = ps[1];
-                    if (col + 2 < a.cols) w2 = ps[2];
-                    if (col + 3 < a.cols) w3 = ps[3];
-                }
+            const bool in = row_in(QT_RH * u + j) && col_in;
+            if (FORM != 0) {
+                const uint4 f = ld_stream16(ps);
+                w0 = in ? f.x : 0u;
+                w1 = in && !(ragged && col + 1 >= a.cols) ? f.y : 0u;
+                w2 = in && !(ragged && col + 2 >= a.cols) ? f.z : 0u;
+                w3 = in && !(ragged && col + 3 >= a.cols) ? f.w : 0u;
+            } else if (in) {
+                w0 = ps[0];
+                if (col + 1 < a.cols) w1 = ps[1];
+                if (col + 2 < a.cols) w2 = ps[2];
+                if (col + 3 < a.cols) w3 = ps[3];
             }
             raw[u][j][0] = w0; raw[u][j][1] = w1; raw[u][j][2] = w2; raw[u][j][3] = w3;
-            ps += ld;
+            ps += FORM == 0 || row_in(QT_RH * u + j + 1) ? ld : 0;
         }
     }
     // ---- per-row factor (local gradients: 2*coeff; normalised hand-off: sqrt(goodness) and its reciprocal)
@@ -462,12 +463,13 @@ __global__ __launch_bounds__(QT_THREADS) void k_quantize_pixels(QuantArgs a)
 template <int SRC, bool STOCH, int FORM, int CB, int U>
 static void launch_quantize_tiles(QuantArgs a, int64_t span, hipStream_t s)
 {
-    // Rows of the source that do not start on 128-byte lines: two neighbouring tiles of a row of tiles share a line of every
-    // source row.  Workgroups go to the eight XCDs in turn, so the line would be fetched into two L2s; with a row of tiles
-    // on one XCD it is fetched once.  Local gradient of 65536 x 1000: backward 132 -> 114 us, x 500: 88 -> 79, 40000 x 2000:
-    // 142 -> 122.  Rows that start on lines keep the plain order (a normalised hand-off of 8192 x 4096: 36 us, 40 this way).
+    // Rows of the source, or of the codes, that do not start on 128-byte lines: two neighbouring tiles of a row of tiles share
+    // a line of every row.  Workgroups go to the eight XCDs in turn, so the line would be fetched into, or written back from,
+    // two L2s; with a row of tiles on one XCD it is one.  Local gradient of 65536 x 1000: backward 132 -> 114 us, x 500:
+    // 88 -> 79, 40000 x 2000: 142 -> 122; hand-off of 35322 x 224 with its transposed copy 14.0 -> 11.5, of 16384 x 1000
+    // 25.5 -> 20.5.  Rows that start on lines keep the plain order (a normalised hand-off of 8192 x 4096: 36 us, 40 this way).
     constexpr bool F32SRC = SRC == QSRC_F32 || SRC == QSRC_F32_GRAD;
-    a.row_per_xcd = ((F32SRC ? a.cols : a.ldacc) & 31) != 0 && span > QTile<CB, U>::COLS;
+    a.row_per_xcd = (((F32SRC ? a.cols : a.ldacc) & 31) != 0 || (a.q && (a.ldq & 127) != 0)) && span > QTile<CB, U>::COLS;
     // (row tiles up to the row pitch of q_t, for the same reason)
     const int64_t rspan = a.q_t && a.ldqt > a.rows ? a.ldqt : a.rows;
     const dim3 grid((unsigned)((span + QTile<CB, U>::COLS - 1) / QTile<CB, U>::COLS),
@@ -490,10 +492,13 @@ static void launch_quantize_t(const QuantArgs& a, hipStream_t s)
     const bool narrow = a.cols <= QTile<8, 2>::COLS && vec;
     // (column tiles up to the row pitch of q, so that its pad bytes are written too: zeros)
     const int64_t span = a.q && a.ldq > a.cols ? a.ldq : a.cols;
-    // Tensors that would give a compute unit fewer than eight tiles of two blocks per thread are bound by the latency of one
-    // wavefront's chain (loads, hash, stores), not by HBM: half the tile, twice the wavefronts.  (Steps of 784-2000^4 at
-    // 1024 samples 302 -> 290 us, 1000-1500^2-1001 with the chain 284 -> 267 us; lines at 4 and 16 measure the same.)
-    constexpr int64_t Q_FEW = 8;
+    // Tensors that would give a compute unit fewer than four tiles of two blocks per thread are bound by the latency of one
+    // wavefront's chain (loads, hash, stores), not by HBM: half the tile, twice the wavefronts (steps of 784-2000^4 at
+    // 1024 samples 302 -> 290 us, 1000-1500^2-1001 with the chain 284 -> 267 us).  At five and more the whole tile is better, whose
+    // transposed stores are whole lines: hand-off with the transposed copy, halves against whole tiles, 65536 x 128
+    // 13.0 -> 11.0 us, 16384 x 500 13.5 -> 11.0, 8000 x 1500 19.3 -> 15.6; at 860 tiles (5493 x 1232) 11.7 and 10.7 with, 8.9
+    // and 9.1 without the copy.
+    constexpr int64_t Q_FEW = 4;
     const int64_t tiles = narrow ? (a.rows + QTile<8, 2>::ROWS - 1) / QTile<8, 2>::ROWS
                                  : ((span + QTile<16, 2>::COLS - 1) / QTile<16, 2>::COLS) * ((a.rows + QTile<16, 2>::ROWS - 1) / QTile<16, 2>::ROWS);
     const bool few = tiles * a.nb < Q_FEW * num_cus() && (a.rows + 127) / QTile<16, 1>::ROWS < 65535;   // (grid.y)

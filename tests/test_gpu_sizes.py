@@ -275,3 +275,32 @@ def test_weight_gradient_tiles_of_long_and_short_reductions(ff, B, H, W, Cin, Co
 def test_dense_update_sums_the_partial_results(ff, widths, B):
     wl = Workload("parts", mlp(widths, False), B, "normal", lam=0.05)
     _run_steps(ff, wl, 1, theta_layer=_matched_thetas(wl), launch_mode="kernels")
+
+
+@pytest.mark.parametrize("rows,N", [(33111, 224), (17001, 500), (16500, 510), (70003, 72), (130001, 66)])
+def test_codes_of_large_matrices_with_partial_tiles(ff, rows, N):
+    """Whole-size quantiser tiles over int32 sources: partial tiles at both edges, rows of the source and of the codes that do
+    not start on cache lines, a number of tile rows that is no multiple of eight."""
+    rng = np.random.default_rng(rows + N)
+    desc = ff.layer_desc(Layer("dense", in_features=24, out_features=N), rows)
+    acc = rng.integers(-200000, 200000, (rows, N)).astype(np.int32)
+    s_a, s_w = np.float32(0.0041), np.float32(0.0007)
+    g = O.goodness(acc, 1, O.goodness_shift(24, N), s_a, s_w)
+    a = O.handoff(acc, 1, 0, s_a, s_w, g["G"])
+    q_ref, s_ref = O.quantize(a, 1, 3, 21)
+    q, q_t, s = empty8(rows, N), empty8(N, rows), scalar()
+    d_acc, d_sa, d_sw = dev(pad32(acc)), dev(np.array([s_a])), dev(np.array([s_w]))
+    ff.ff_layer_handoff(desc, d_acc, d_sa, d_sw, dev(g["G"]), dev(np.array([np.abs(a).max()], np.float32)), 1, 3, 21, q, q_t, s)
+    torch.cuda.synchronize()
+    assert s.item() == s_ref
+    check_q(q, q_ref, "hand-off codes")
+    check_q(q_t, q_ref.T, "transposed hand-off codes")
+    ct = (rng.standard_normal(rows) * 0.3).astype(np.float32)
+    gq_ref, sg_ref = O.quantize(O.local_grad(acc, 1, s_a, s_w, ct), 1, 4, 55)
+    gy_t, s_g, dw = empty8(N, rows), scalar(), empty32(N, 24)
+    a_q = rng.integers(-127, 128, (rows, 24)).astype(np.int8)
+    ff.ff_layer_backward_local(desc, d_acc, dev(g["vmax"]), d_sa, d_sw, dev(ct), 1, 4, 55, dev(pad8(np.ascontiguousarray(a_q.T))), gy_t, s_g,
+                               dw, workspace(ff.ff_layer_workspace_bytes(desc)))
+    torch.cuda.synchronize()
+    assert s_g.item() == sg_ref
+    check_q(gy_t, gq_ref.T, "gy_q_t")
