@@ -341,7 +341,8 @@ def other_config(ff, torch, name, steps=10, warmup=3):
             "whole_step_int8_TOPs": round(ops / (ms * 1e-3) / 1e12, 1),
             "whole_step_frac_of_int8_peak": round(ops / (ms * 1e-3) / 1e12 / INT8_MFMA_PEAK_TOPS, 4),
             "contraction_launches_frac_of_int8_peak": round(g["achieved"] / INT8_MFMA_PEAK_TOPS, 4),
-            "contraction_note": "from the one-stream per-operation pass (launch durations are only meaningful unoverlapped)"}
+            "contraction_note": "from the one-stream per-operation pass (launch durations are only meaningful unoverlapped); "
+                                "a weight-gradient launch that applies the update as well counts whole"}
 
 
 def main() -> int:

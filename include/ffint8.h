@@ -134,11 +134,11 @@ typedef struct {
 } ff_net_desc;
 
 /* How ff_train_step issues its work.
- * FF_LAUNCH_KERNELS: one kernel per operation (quantise, contraction, goodness/loss, ...), about nine launches per
- *   layer.
+ * FF_LAUNCH_KERNELS: one kernel per operation (quantise, contraction, update, ...), about six launches per layer and two
+ *   for all of them (range of the input; goodness, loss and look-ahead).
  * FF_LAUNCH_FUSED: the whole step as ONE persistent kernel whose
- *   workgroups meet at device-wide barriers where the method has device-wide dependencies (a per-tensor absmax, a
- *   per-sample goodness).  For the launch-bound regime of small networks and batches, the one nearest the paper's
+ *   workgroups meet at device-wide barriers between its phases (a per-tensor absmax or a per-sample goodness is complete
+ *   there, or a tensor of codes).  For the launch-bound regime of small networks and batches, the one nearest the paper's
  *   own batch of 32 (Section V-A).  Plain dense stacks (no convolutions, residual wiring or FF_LOOKAHEAD_CHAIN) of at
  *   most 8 layers and 1024 samples per pass; FF_ERR_UNSUPPORTED otherwise.  Same results, bit for bit.
  * FF_LAUNCH_LANES: one kernel per operation, but the update chains of different layers (local gradient -> weight
@@ -231,8 +231,8 @@ ff_status ff_layer_forward(const ff_layer_desc* layer, const int8_t* a_q, const 
  *   - ff_layer_forward runs an implicit GEMM when C_in % 4 == 0 and C_in > 4 (a 1x1 stride-1 convolution reads a_q as the
  *     dense operand it is, for any C_in); otherwise it first writes the patch matrix into ws.  ff_layer_backward_local
  *     takes the SAME NHWC a_q in its a_q_t argument and reads it as it is (up to four channels: through the patch
- *     matrix, in ws).  Both need
- *     ws_bytes >= ff_layer_workspace_bytes(layer).
+ *     matrix, in ws).  ff_layer_backward_local needs ws_bytes >= ff_layer_workspace_bytes(layer), ff_layer_forward
+ *     likewise when C_in % 16 != 0; the size is an upper bound, larger than what the present routes use.
  *   - A weight-gradient reduction over more than 133144 rows (M * 127^2 would not fit int32) is split into
  *     ff_layer_dw_chunks(layer) equal blocks of samples, block size = the largest power of two whose rows still
  *     fit; dw_acc then holds that many [N, ff_pitch32(K)] accumulators back to back, and ff_layer_update
@@ -405,11 +405,11 @@ size_t ff_workspace_bytes(const ff_net_desc* net);
  * ------------------------------------------------------------------------------------------- */
 enum {
     FF_K_GEMM_FWD = 0,   /* forward contraction (+ fused goodness reductions) */
-    FF_K_GEMM_DW = 1,    /* weight-gradient contraction                       */
+    FF_K_GEMM_DW = 1,    /* weight-gradient contraction (with the weight update where a dense layer's runs in its epilogue) */
     FF_K_QUANT_ACT = 2,  /* activation quantise (fp32 input or hand-off)      */
     FF_K_QUANT_GRAD = 3, /* local-gradient quantise                           */
     FF_K_QUANT_W = 4,    /* weight requantise                                 */
-    FF_K_UPDATE = 5,     /* weight update                                     */
+    FF_K_UPDATE = 5,     /* weight update as a launch of its own              */
     FF_K_ABSMAX = 6,     /* absmax of the fp32 input                          */
     FF_K_SMALL = 7,      /* fills, goodness/loss, look-ahead                  */
     FF_K_IM2COL = 8,     /* patch matrices of convolution layers              */

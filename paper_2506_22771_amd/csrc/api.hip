@@ -19,7 +19,7 @@ struct Dims {
     int64_t B, M, K, N, rps;   // M rows per pass (dense: B; conv: B*Ho*Wo), rps rows per sample
     int64_t in_rows, in_cols;  // 2-D view of the layer input: dense [B, K]; conv [B*H*W, C_in]
     bool implicit;             // conv whose forward runs as an implicit GEMM (C_in % 4 == 0, more than a handful of channels)
-    bool pointwise;            // 1x1 stride-1 convolution: its transposed patch matrix is the transposed input itself
+    bool pointwise;            // 1x1 stride-1 convolution: its patch matrix is the NHWC input itself
     ConvGeom g;                // conv only
     int n_chunks;              // weight-gradient accumulators per pass
     int64_t chunk_b;           // samples per accumulator
@@ -78,7 +78,8 @@ static ff_status layer_dims(const ff_layer_desc* L, Dims* d)
     }
     // Launch limits of the kernels behind this layer, checked here so that an unsupported size is reported before
     // anything has been enqueued: the quantisers index elements with 32 bits and put 128 rows per workgroup on
-    // grid.y; the update puts one weight row (or four) on grid.y; the depthwise kernels one sample.
+    // grid.y; the depthwise forward kernel one sample.  (65535 output features is a limit of the interface; the update, which
+    // once put a weight row on grid.y, walks the matrix flat and no longer needs it.)
     if (!quant_shape_ok(d->in_rows, d->in_cols) || !quant_shape_ok(d->M, d->N) || !quant_shape_ok(d->N, d->K) ||
         d->N > 65535 || (L->kind == FF_DWCONV2D && d->B > 65535))
         return FF_ERR_UNSUPPORTED;
@@ -113,10 +114,10 @@ static int32_t goodness_shift(int64_t K, int64_t terms)
     return r;
 }
 
-// Scratch one layer needs per pass beyond FF_WS_MIN_BYTES.
-// `col`: the row-major patch matrix of an explicit-im2col forward or the transposed patch matrix of one
-// weight-gradient chunk (conv only).  `part`: partial accumulators of a split weight-gradient reduction.
-// These sizes are what the entry points ask their callers for (ff_layer_workspace_bytes); they cover every route below.
+// Scratch the single-operation entry points ask their callers for per pass beyond FF_WS_MIN_BYTES
+// (ff_layer_workspace_bytes): a size of the interface, at least what the routes below use and for convolutions a good deal
+// more.  `col`: room for a row-major patch matrix [M, pitch(K)], and for a transposed one of a weight-gradient chunk, which no
+// route writes any more.  `part`: partial accumulators of a split weight-gradient reduction.
 static size_t layer_col_bytes(const Dims& d)
 {
     if (d.kind != FF_CONV2D) return 0;   // dense and depthwise layers need no patch matrix
@@ -169,7 +170,7 @@ struct WsLayout {
     Dims d[MAX_LAYERS];
     // byte offsets
     size_t off_slots;      // uint32: out_amax[k+1][2] (slot 0: the net input, slot j+1: output of layer j),
-                           // g_amax[k][2], w_amax[k]
+                           // g_amax[k][2], w_amax[k] (single-launch step)
     size_t off_gsum;       // uint64 [k][2][B]
     size_t off_vmax;       // int32  [k][2][B]
     size_t off_gl;         // scratch of the goodness / loss kernel (see GoodnessArgs::loss_part)
@@ -276,8 +277,7 @@ static ff_status make_layout(const ff_net_desc* net, WsLayout* w)
     size_t off = 0;
     const size_t k = (size_t)w->k, B = (size_t)w->B;
     w->off_slots = off;
-    // + h_amax[k][2], wt_amax[k] (exact-derivative look-ahead)
-    off = align_up(off + sizeof(uint32_t) * (k * 8 + 2), A);
+    off = align_up(off + sizeof(uint32_t) * (k * 5 + 2), A);
     w->off_gsum = off;
     off = align_up(off + sizeof(uint64_t) * k * 2 * B, A);
     w->off_vmax = off;
@@ -501,7 +501,7 @@ static Im2colArgs im2col_args(const Dims& d, const int8_t* aq, int64_t st_aq, in
 
 // ---- the two contractions of a layer, for nb passes at once ------------------------------------------
 // Forward: acc[z] = A_q[z] x W_q^T (+ per-sample sums).  `aq` is the quantised layer input (dense: [M, pitch(K)];
-// conv: NHWC), `col` scratch for an explicit patch matrix (3x3 or strided conv with C_in % 16 != 0).
+// conv: NHWC), `col` scratch for an explicit patch matrix (see explicit_patches).
 static ff_status run_forward(const Dims& d, int relu, const int8_t* aq, int64_t st_aq, const int8_t* w_q, int32_t* acc,
                              int64_t st_acc, unsigned long long* gsum, int32_t* vmax, int64_t st_g, int8_t* col,
                              int64_t st_col, int nb, hipStream_t s)
@@ -579,15 +579,17 @@ struct WgradTerms {
 };
 
 // Weight gradient: dw[z][c] = gy_q_t[z][:, chunk c] x (patches of chunk c)^T for every chunk c.
-// `aqt` is the transposed quantised input (dense) or the NHWC quantised input (conv), which the contraction reads reduction-major as it is -- or the row-major patch matrix
-// [M, pitch(K)] (wgrad_from_patches).  dw accumulators of one pass are dw_elems apart.  `part`: part_elems elements for the
-// partial results of a split reduction.  terms == null: split results are added up into dw; otherwise they are left as
-// they are for the update, and *terms says where everything is.
+// `aqt` is the transposed quantised input (dense) or the NHWC quantised input (conv), which the contraction reads
+// reduction-major as it is -- or the row-major patch matrix [M, pitch(K)] (wgrad_from_patches).  dw accumulators of one pass
+// are dw_elems apart.  `part`: part_elems elements for the partial results of a split reduction.  terms == null (one pass
+// only): split results are added up into dw; otherwise they are left as they are for the update, and *terms says where
+// everything is.
 static ff_status run_wgrad(const Dims& d, const int8_t* gy_t, int64_t st_gy, const int8_t* aqt, int64_t st_aqt,
                            int32_t* part, int64_t part_elems, int32_t* dw, int64_t st_dw, int64_t dw_elems, int nb,
                            hipStream_t s, WgradTerms* terms)
 {
     const int64_t elems = d.N * pitch32(d.K);
+    if (!terms && nb != 1) return FF_ERR_INVALID_ARG;
     if (terms) {
         terms->st_split = elems;
         for (int c = 0; c < d.n_chunks; ++c) {
@@ -699,11 +701,7 @@ static ff_status run_wgrad(const Dims& d, const int8_t* gy_t, int64_t st_gy, con
                     for (int z = 0; z < nb; ++z) terms->term[z][l + c] = mine + z * g.st_c + c * g.st_c2;
                 }
             } else {
-                // (one launch over the passes of a chunk, or over the chunks of a pass)
-                const int inner = nb == 1 ? together : nb, outer = nb == 1 ? 1 : together;
-                for (int c = 0; c < outer; ++c)
-                    HIPCHK_T(FF_K_GEMM_DW, launch_reduce_splits(mine + c * g.st_c2, g.splits, elems, nb == 1 ? g.st_c2 : g.st_c,
-                                                                out + c * dw_elems, nb == 1 ? dw_elems : st_dw, elems, inner, s));
+                HIPCHK_T(FF_K_GEMM_DW, launch_reduce_splits(mine, g.splits, elems, g.st_c2, out, dw_elems, elems, together, s));
             }
         } else {
             HIPCHK_T(FF_K_GEMM_DW, launch_gemm_nt_i8(g, s));
@@ -816,7 +814,7 @@ ff_status ff_layer_forward(const ff_layer_desc* layer, const int8_t* a_q, const 
     if (!aligned16(a_q) || !aligned16(w_q) || !aligned16(acc) || (((uintptr_t)gsum_int) & 7) || !aligned4(vmax))
         return FF_ERR_ALIGN;
     if (d.K > INT32_SAFE_LEN) return FF_ERR_OVERFLOW_BOUND;
-    const bool need_col = d.kind == FF_CONV2D && (d.g.Cin & 15) != 0;   // the layers that are asked for scratch
+    const bool need_col = d.kind == FF_CONV2D && (d.g.Cin & 15) != 0;   // the layers that are asked for scratch (explicit_patches(d) use it)
     if (need_col) {
         if (!ws) return FF_ERR_INVALID_ARG;
         if (!aligned16(ws)) return FF_ERR_ALIGN;

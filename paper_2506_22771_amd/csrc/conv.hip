@@ -1,10 +1,10 @@
 // Patch matrices and depthwise convolutions of the FF-INT8 step (gfx950).
 //
-// A convolution's forward pass runs as an implicit GEMM inside k_gemm_nt_i8 whenever C_in is a multiple of 16, and its
-// weight gradient (Section IV-B: only g^W is formed) reads the NHWC input reduction-major there.  A layer with another
-// channel count -- above all a first layer with one or three channels, whose reduction rows of 9 or 27 bytes no
-// 16-byte copy can address -- has its patches written row-major, col[m][(kh,kw,ci)], and both contractions read those.
-// Pure data movement; taps outside the image give 0.
+// A convolution's forward pass runs as an implicit GEMM inside k_gemm_nt_i8 whenever C_in is a multiple of 4 greater than
+// 4, and its weight gradient (Section IV-B: only g^W is formed) reads the NHWC input reduction-major there.  Another channel
+// count -- above all that of a first layer with one or three channels, whose reduction rows of 9 or 27 bytes no 16-byte
+// copy can address -- has its patches written row-major, col[m][(kh,kw,ci)], for the forward contraction; up to four channels
+// the weight gradient reads them as well.  Pure data movement; taps outside the image give 0.
 #include "ff_internal.hpp"
 
 namespace ffi {

@@ -72,7 +72,7 @@ __device__ __forceinline__ void sr_mix4(uint32_t v, uint32_t h[4])
 }
 
 // STOCH: floor + Bernoulli(frac) from the counter-based word; else round-to-nearest-even.
-// `word_in` is (low 32 bits of the element index) ^ key, already adjusted for the high index half.
+// (quant_code: `word_in` is the element index ^ key; tensors have fewer than 2^32 elements.)
 template <bool STOCH>
 __device__ __forceinline__ int quant_code_of_word(float v, float inv, uint32_t random_word)
 {

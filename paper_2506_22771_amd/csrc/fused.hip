@@ -4,9 +4,11 @@
 // a step of 784 -> 500 -> 500 at 64 + 64 samples is 18 dependent kernels of 2-10 us each.  Here the whole step --
 // quantise (Section IV-B), int8 forward contraction with the goodness sums (Algorithm 1), losses and their
 // derivatives (Eq. (1), Eq. (2)), look-ahead (Eq. (3), Eq. (4)), int8 local gradient, int8 weight gradient, update and
-// requantisation -- runs in ONE launch of a few dozen workgroups that meet at a device-wide barrier wherever the
-// method has a true device-wide dependency (a per-tensor absmax, a per-sample goodness).  The arithmetic is the one
-// the per-operation kernels use (device_math.hpp; same operation order), so both paths give the same bits.
+// requantisation -- runs in ONE launch of a few dozen workgroups that meet at a device-wide barrier between phases.  k + 2
+// of the 2k + 3 barriers wait for a device-wide dependency of the method (a per-tensor absmax, a per-sample goodness); the
+// others, after the quantisation of each layer's input and of the gradients, are there because the codes are made once for
+// all tiles that read them.  The arithmetic is the one the per-operation kernels use (device_math.hpp; same operation
+// order), so both paths give the same bits.
 //
 // Work inside a phase is spread by grid-stride loops over all threads of the launch; contractions give every
 // wavefront 32 x 32 output tiles (v_mfma_i32_32x32x32_i8, fragments straight from global memory: the operands of such

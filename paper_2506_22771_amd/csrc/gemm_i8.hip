@@ -10,10 +10,11 @@
 //
 // Structure (measured choices, see the design notes):
 //  * A workgroup of WM x WN wavefronts computes a BM x BN tile in steps of BK = 128 reduction bytes,
-//    i.e. whole 128-byte lines of both operands per row (half lines halve the useful L2 bandwidth).
+//    i.e. whole 128-byte lines of both operands per row (half lines halve the useful L2 bandwidth); unsplit
+//    256 x 128 and 128 x 256 tiles in steps of 64, three of them staged, so that two workgroups share a compute unit.
 //  * Operand tiles go from global memory straight into LDS with buffer_load_dwordx4 ... lds (no VGPR
 //    staging; rows and reduction tails beyond the matrix read as zero through the buffer's range
-//    check).  Two LDS stages; the copy of step k+1 is in flight while step k is multiplied.  The copies
+//    check).  Two LDS stages (or three); the copy of step k+1 is in flight while step k is multiplied.  The copies
 //    are issued from inline assembly and tracked by hand with vmcnt: through the compiler's builtin
 //    every LDS read would wait for all outstanding copies, and __syncthreads() would drain them too.
 //  * 16-byte chunks are XOR-swizzled inside each 128-byte row so that the MFMA fragment reads
@@ -670,7 +671,8 @@ static hipError_t launch_paired(const GemmArgs& a, hipStream_t s)
     return hipGetLastError();
 }
 
-template <int BM, int BN, int WM, int WN>
+// WHOLE: false for the tiles whose unsplit launches go to launch_paired; only the split and the reduction-major forms exist
+template <int BM, int BN, int WM, int WN, bool WHOLE = true>
 static hipError_t launch_cfg(const GemmArgs& a, hipStream_t s)
 {
     const int tiles_i = (a.I + BM - 1) / BM, tiles_j = (a.J + BN - 1) / BN;
@@ -681,25 +683,27 @@ static hipError_t launch_cfg(const GemmArgs& a, hipStream_t s)
     // once -- one per compute unit, two where a workgroup takes at most half of the LDS -- when each has at least two
     // whole tiles
     int64_t gx = ntiles;
-    if (BM == 256 && a.conv < 2 && mode != 2) {
+    if (WHOLE && BM == 256 && a.conv < 2 && mode != 2) {
         const int stage = (BM + BN) * BK, eslice = (BN == 256 ? 16 : 32) * (BN / WN * 4 + 16);
         const int lds = 2 * stage > stage + WM * WN * eslice ? 2 * stage : stage + WM * WN * eslice;   // as in the kernel
         const int64_t resident = (int64_t)num_cus() * (lds <= 80 * 1024 ? 2 : 1);
         if (ntiles >= 2 * resident && ntiles % resident == 0) gx = resident;
     }
     const dim3 grid((unsigned)gx, (unsigned)a.splits, 1), block(WM * WN * 64);
-    if (a.conv == 1) {
-        if (mode == 1) hipLaunchKernelGGL((k_gemm_nt_i8<BM, BN, WM, WN, 1, 1>), grid, block, 0, s, a);
-        else if (mode == 0) hipLaunchKernelGGL((k_gemm_nt_i8<BM, BN, WM, WN, 0, 1>), grid, block, 0, s, a);
-        else return hipErrorInvalidValue;
-    } else if (a.conv == 2) {
+    if (a.conv == 2) {
+        if (mode == 1) return hipErrorInvalidValue;
         if (mode == 2) hipLaunchKernelGGL((k_gemm_nt_i8<BM, BN, WM, WN, 2, 2>), grid, block, 0, s, a);
-        else if (mode == 0) hipLaunchKernelGGL((k_gemm_nt_i8<BM, BN, WM, WN, 0, 2>), grid, block, 0, s, a);
-        else return hipErrorInvalidValue;
+        else hipLaunchKernelGGL((k_gemm_nt_i8<BM, BN, WM, WN, 0, 2>), grid, block, 0, s, a);
+    } else if (mode == 2) {
+        if (a.conv == 1) return hipErrorInvalidValue;
+        hipLaunchKernelGGL((k_gemm_nt_i8<BM, BN, WM, WN, 2, 0>), grid, block, 0, s, a);
+    } else if constexpr (WHOLE) {
+        if (a.conv == 1 && mode == 1) hipLaunchKernelGGL((k_gemm_nt_i8<BM, BN, WM, WN, 1, 1>), grid, block, 0, s, a);
+        else if (a.conv == 1) hipLaunchKernelGGL((k_gemm_nt_i8<BM, BN, WM, WN, 0, 1>), grid, block, 0, s, a);
+        else if (mode == 1) hipLaunchKernelGGL((k_gemm_nt_i8<BM, BN, WM, WN, 1, 0>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((k_gemm_nt_i8<BM, BN, WM, WN, 0, 0>), grid, block, 0, s, a);
     } else {
-        if (mode == 1) hipLaunchKernelGGL((k_gemm_nt_i8<BM, BN, WM, WN, 1, 0>), grid, block, 0, s, a);
-        else if (mode == 0) hipLaunchKernelGGL((k_gemm_nt_i8<BM, BN, WM, WN, 0, 0>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((k_gemm_nt_i8<BM, BN, WM, WN, 2, 0>), grid, block, 0, s, a);
+        return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
@@ -913,11 +917,11 @@ hipError_t launch_gemm_nt_i8(const GemmArgs& a_in, hipStream_t s)
     }
     if (bn == 256) {
         if (bm == 256) return launch_cfg<256, 256, 4, 2>(a, s);
-        if (bm == 128) return launch_cfg<128, 256, 2, 2>(a, s);
+        if (bm == 128) return launch_cfg<128, 256, 2, 2, false>(a, s);
         return launch_cfg<64, 256, 1, 4>(a, s);
     }
     if (bn == 128) {
-        if (bm == 256) return launch_cfg<256, 128, 4, 2>(a, s);
+        if (bm == 256) return launch_cfg<256, 128, 4, 2, false>(a, s);
         if (bm == 128) return launch_cfg<128, 128, 2, 2>(a, s);
         return launch_cfg<64, 128, 2, 2>(a, s);
     }
