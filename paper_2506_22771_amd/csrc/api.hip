@@ -428,7 +428,7 @@ static ff_status make_layout(const ff_net_desc* net, WsLayout* w)
     }
     for (int i = 0; i < w->k; ++i) w->off_fgy[i] = w->st_fgy[i] = 0;
     if (net->launch_mode == FF_LAUNCH_FUSED && !w->fused_ok) return FF_ERR_UNSUPPORTED;
-    if (w->fused_ok && net->launch_mode != FF_LAUNCH_KERNELS && (w->fused_auto || net->launch_mode == FF_LAUNCH_FUSED)) {
+    if (w->fused_ok && (net->launch_mode == FF_LAUNCH_FUSED || (net->launch_mode == FF_LAUNCH_AUTO && w->fused_auto))) {
         for (int i = 0; i < w->k; ++i) {
             const Dims& d = w->d[i];
             w->st_fgy[i] = align_up((size_t)(d.N * pitch8(d.M)), A);

@@ -304,3 +304,19 @@ def test_codes_of_large_matrices_with_partial_tiles(ff, rows, N):
     torch.cuda.synchronize()
     assert s_g.item() == sg_ref
     check_q(gy_t, gq_ref.T, "gy_q_t")
+
+
+@pytest.mark.parametrize("mode,fused", [("auto", 1), ("fused", 1), ("kernels", 0), ("lanes", 0)])
+def test_launch_mode_of_a_small_stack_is_the_one_asked_for(ff, mode, fused):
+    """A stack that FF_LAUNCH_AUTO would run as one launch: the other modes issue their own kernels."""
+    wl = Workload("mode", mlp([40, 36, 20], False), 30, "normal", lam=0.3)
+    thetas = _matched_thetas(wl)
+    ff.ff_timing_reset()
+    ff.ff_timing_enable(True, ["fused"])
+    try:
+        _run_steps(ff, wl, 2, theta_layer=thetas, launch_mode=mode)
+        launches = ff.ff_timing_read(ff.KERNEL_CLASSES.index("fused"))[1]
+    finally:
+        ff.ff_timing_enable(False)
+        ff.ff_timing_reset()
+    assert launches == 2 * fused
