@@ -201,15 +201,24 @@ def test_depthwise_step_partial_results(ff, blocks, H, W, B):
     _run_steps(ff, wl, 1, theta_layer=_matched_thetas(wl), live=True)
 
 
-@pytest.mark.parametrize("widths,B", [([132, 260, 64], 70), ([1000, 333, 96], 200), ([64, 1001, 500, 40], 33), ([516, 130], 130)])
-@pytest.mark.parametrize("mode", ["kernels", "lanes"])
-def test_dense_step_with_the_update_in_the_weight_gradient(ff, widths, B, mode):
-    """Reduction lengths of one, two and three steps, ragged output tiles; a layer of 333 or 1001 inputs keeps the update as
-    a launch of its own."""
-    if mode == "lanes" and len(widths) < 3:
-        pytest.skip("one layer: no lanes")
+@pytest.mark.parametrize("mode,widths,B,updates", [
+    ("lanes", [132, 260, 64], 70, 0), ("lanes", [1000, 333, 96], 200, 1), ("lanes", [64, 1001, 500, 40], 33, 1), ("lanes", [516, 132, 68], 130, 0),
+    ("kernels", [2004, 2101, 40], 40, 1), ("kernels", [2000, 2048, 2001], 140, 0)])
+def test_dense_step_with_the_update_in_the_weight_gradient(ff, mode, widths, B, updates):
+    """Reduction lengths of one, two and three steps, ragged output tiles; a layer of 333, 1001 or 2101 inputs keeps the update
+    as a launch of its own.  Beside other chains any small layer takes this route, alone on the chip one of at least two
+    tiles per compute unit: the update launches of a step are counted."""
     wl = Workload("upd", mlp(widths, False), B, "normal", lam=0.3)
-    _run_steps(ff, wl, 2, theta_layer=_matched_thetas(wl), launch_mode=mode)
+    thetas = _matched_thetas(wl)
+    ff.ff_timing_reset()
+    ff.ff_timing_enable(True, ["update"])
+    try:
+        _run_steps(ff, wl, 2, theta_layer=thetas, launch_mode=mode)
+        launches = ff.ff_timing_read(ff.KERNEL_CLASSES.index("update"))[1]
+    finally:
+        ff.ff_timing_enable(False)
+        ff.ff_timing_reset()
+    assert launches == 2 * updates
 
 
 @pytest.mark.parametrize("channels,side,B", [([3, 18, 30, 22], 9, 20), ([2, 6, 6, 9], 14, 33), ([5, 7], 11, 12)])
