@@ -1283,11 +1283,18 @@ static ff_status train_step_impl(const ff_net_desc* net, const ff_net_state* sta
     // One kernel forms every layer's goodness, loss and coefficients after the forward pass; the hand-off needs only the range
     // of a layer's output.  Small batches: each of the quantiser's workgroups takes it from the per-sample maxima (256
     // threads: a few loads each; with normalisation also a square root and a division per sample).  Larger ones: a small
-    // launch of its own.  Beyond 16384 samples the reported loss of a layer wants more than one workgroup: the kernels per layer.
-    // With normalisation, step by the kernels per layer against this: 784-1000-1000-1000 with 4000 samples 261 -> 252 us,
-    // 500-600-700-300 with 2000 161 -> 148; without, 784-1000-1000-1000 with 6000 316 -> 304, 4096^3 with 8192 1370 -> 1369.
-    const bool goodness_last = B <= 16384;
-    auto range_launch = [&](const ff_layer_desc& L) { return B > (L.l2norm_out ? 1024 : 4096); };
+    // launch of its own, one workgroup per pass, and beyond that the kernels per layer, which spread a layer's samples over
+    // several workgroups.
+    // The small launch against taking the range in the quantiser: 784-1000-1000-1000 with 512 samples 120 -> 118 us, 2000
+    // 164 -> 163, 3000 213 -> 215, 8000 396 -> 416; with normalisation 512 116 -> 114, 1500 153 -> 153, 2000 171 -> 174, 4000
+    // 298 -> 307; 16-64-128 channels on 4x4 maps cross at the same batches.
+    // The kernels per layer against this, with normalisation: 784-1000-1000-1000 with 5000 samples 356 -> 354 us, 8192 402 ->
+    // 408, 16384 645 -> 677, 300-64-64-64 with 5000 122 -> 117, 12000 146 -> 151; without: 5000 345 -> 337 and 114 -> 105,
+    // 12000 505 -> 503 and 142 -> 138, 16384 634 -> 638 and 153 -> 159.
+    bool normalised = false;   // a hand-off range of square roots and divisions
+    for (int i = 0; i + 1 < k; ++i) normalised = normalised || net->layers[i].l2norm_out;
+    const bool goodness_last = B <= (normalised ? 6144 : 12288);
+    auto range_launch = [&](const ff_layer_desc& L) { return B > (L.l2norm_out ? 1024 : 2048); };
     // ---- streams: the caller's, plus the library's own where the step runs independent work side by side
     hipStream_t lane_stream[MAX_LANES];
     for (int l = 0; l < MAX_LANES; ++l) lane_stream[l] = s;

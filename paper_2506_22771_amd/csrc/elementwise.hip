@@ -839,7 +839,7 @@ hipError_t launch_grad_amax(const float* ct, const int32_t* vmax, const float* s
 // after them: the loss of one layer each, in a fixed order.
 // ------------------------------------------------------------------------------------------------
 // The range of one layer's output for the hand-off of a larger batch: one workgroup per pass.  Bound by its latency (two
-// dependent loads, a square root, a reduction): a batch of 16384 is 16 samples per thread, too few to split further.
+// dependent loads, a square root, a reduction): a batch of 12288 is 12 samples per thread, too few to split further.
 __global__ __launch_bounds__(1024) void k_handoff_range(RangeArgs a)
 {
     const int z = blockIdx.x;

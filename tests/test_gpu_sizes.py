@@ -146,8 +146,9 @@ def test_quantize_tile_sizes(ff, rows, cols, mode):
     check_q(q_t, q_ref.T, "q_t")
 
 
-@pytest.mark.parametrize("B,l2,depth", [(1, True, 2), (63, True, 3), (65, False, 3), (1024, True, 3), (1025, True, 2), (4096, False, 2),
-                                        (4097, False, 2), (16384, True, 2), (16385, True, 2), (130, False, 19)])
+@pytest.mark.parametrize("B,l2,depth", [(1, True, 2), (63, True, 3), (65, False, 3), (1024, True, 3), (1025, True, 2), (2048, False, 3), (2049, False, 3), (4096, False, 2),
+                                        (4097, False, 2), (6144, True, 2), (6145, True, 2), (12288, False, 2), (12289, False, 2),
+                                        (16384, True, 2), (16385, True, 2), (130, False, 19)])
 def test_step_goodness_after_the_forward_pass_or_per_layer(ff, B, l2, depth):
     """Batches on both sides of the line between one goodness / look-ahead launch and one launch per layer; more layers
     than a workgroup of the single launch takes at a time."""
