@@ -810,7 +810,7 @@ __global__ __launch_bounds__(256) void k_reduce_splits(const int32_t* __restrict
 // The fused weight gradient + update: dense weight gradients whose output is cut into the smallest tiles anyway (a few
 // hundred of them, a reduction of a few steps), where writing both passes' accumulators, reading them back and one more
 // launch weigh as much as the contraction.  2000 x 2000 at 1024 samples a pass: 19 + 12 us as two launches, 23.5 as one; the
-// step of 784-2000^4 270 -> 252 us.
+// step of 784-2000^4 276 -> 254 us.
 int gemm_update_blocks(int64_t I, int64_t J, int64_t R)
 {
     if ((J & 3) != 0) return 0;
