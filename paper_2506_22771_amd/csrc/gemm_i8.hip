@@ -718,12 +718,18 @@ GemmPlan gemm_plan(int64_t I, int64_t J, int64_t R, int nb, bool allow_split, bo
     GemmPlan p;
     p.splits = p.most_splits = 1;
     // edge of the tile along one dimension: weigh the padding it leaves against the lower efficiency of narrow
-    // tiles (relative MFMA rates measured on this kernel: 256 -> 1, 128 -> 0.85, 64 -> 0.65; with a reduction of one or two
+    // tiles (relative MFMA rates measured on this kernel: 256 -> 1, 128 -> 0.85, 64 -> 0.65).  With a reduction of one or two
     // steps the stores count, hardly the multiplies: 24 -> 144 channels, three 64-column tiles instead of one of 256,
-    // 107 -> 97 us for 512 images of 32x32)
-    auto edge = [R](int64_t n) {
+    // 107 -> 97 us for 512 images of 32x32; 64 -> 576 with 200000 rows 109 -> 96, but 200 -> 576 131 -> 143 (128 columns there).
+    // Only where rows of the output start on 64-byte boundaries, or the output stays in the caches (up to 40 MB): else narrow
+    // tiles split more of its lines (64 -> 300 with 200000 rows 111 us with the wide tiles, 127 with the narrow ones, 64 -> 1810
+    // with 24000 rows 63 and 73, 27 -> 1400 with 9000 rows, 50 MB, 19.9 and 21.7; but 64 -> 300 with 24000 rows, 29 MB, 18.1 and
+    // 17.4).
+    const bool even = (J & 15) == 0 || I * J * nb <= (int64_t(10) << 20);
+    const double eff128 = !even || R > 256 ? 0.85 : (R > 128 ? 0.91 : 0.95), eff64 = !even || R > 256 ? 0.65 : (R > 128 ? 0.8 : 0.9);
+    auto edge = [=](int64_t n) {
         const int e[3] = {256, 128, 64};
-        const double eff[3] = {1.0, R <= 256 ? 0.95 : 0.85, R <= 256 ? 0.9 : 0.65};
+        const double eff[3] = {1.0, eff128, eff64};
         int best = 64;
         double score = -1.0;
         for (int i = 0; i < 3; ++i) {
