@@ -37,38 +37,72 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v)
     return max(max(a, b), max(c, d));
 }
 
-// one random word per element: two multiply / xor-shift stages over (low index word ^ key)
-__device__ __forceinline__ uint32_t sr_mix(uint32_t v)
+// one random word per element: two multiply / xor-shift stages over (low index word ^ key).  sr_head leaves out the last
+// xor-shift; the 24 bits that decide a code are then sr_bits24 of what it returns.
+__device__ __forceinline__ uint32_t sr_head(uint32_t v)
 {
     v ^= v >> 16;
     v *= 0x7FEB352Du;
     v ^= v >> 15;
     v *= 0x846CA68Bu;
-    v ^= v >> 16;
     return v;
+}
+__device__ __forceinline__ uint32_t sr_bits24(uint32_t head) { return (head >> 8) ^ (head >> 24); }   // (head ^ head >> 16) >> 8
+__device__ __forceinline__ uint32_t sr_mix(uint32_t v)
+{
+    v = sr_head(v);
+    return v ^ (v >> 16);
 }
 
 // The same for four elements whose indices are base, base + 1, base + 2, base + 3 with base a multiple of four (v = base ^
-// key, h[c] = sr_mix(v ^ c)).  The four inputs differ in their two lowest bits only, so the first xor-shift is shared
-// and the first of the two quarter-rate multiplies becomes one multiply plus additions:
+// key, w[c] = sr_head(v ^ c)).  The four inputs differ in their two lowest bits only, so the first xor-shift is shared
+// and the first of the two multiplies becomes one multiply plus additions:
 // (x ^ 1) * m = x * m + (x & 1 ? -m : m), (x ^ 2) * m = x * m + (x & 2 ? -2m : 2m).
-__device__ __forceinline__ void sr_mix4(uint32_t v, uint32_t h[4])
+__device__ __forceinline__ void sr_head4(uint32_t v, uint32_t w[4])
 {
     constexpr uint32_t M = 0x7FEB352Du;
     const uint32_t x = v ^ (v >> 16);
     const uint32_t s1 = (uint32_t)((int32_t)(x << 31) >> 31), s2 = (uint32_t)((int32_t)(x << 30) >> 31);   // all ones or zero
     const uint32_t d1 = (M ^ s1) - s1, d2 = ((2u * M) ^ s2) - s2;
-    h[0] = x * M;
-    h[1] = h[0] + d1;
-    h[2] = h[0] + d2;
-    h[3] = h[1] + d2;
+    w[0] = x * M;
+    w[1] = w[0] + d1;
+    w[2] = w[0] + d2;
+    w[3] = w[1] + d2;
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-        uint32_t w = h[c];
-        w ^= w >> 15;
-        w *= 0x846CA68Bu;
-        h[c] = w ^ (w >> 16);
+        w[c] ^= w[c] >> 15;
+        w[c] *= 0x846CA68Bu;
     }
+}
+
+// ------------------------------------------------------------------------------------------------
+// Stochastic rounding in fixed point.  The code of t = v * inv is floor(t) + [k * 2^-24 < frac(t)], k the element's 24 random
+// bits (quant_code below says it in floating point).  With X = ceil(t * 2^24) that is floor((X + 2^24 - 1 - k) / 2^24): the top
+// byte of ~(k - 2^24 - X), |X| <= 127 * 2^24 once t is clamped.  t >= 1/2 is a multiple of 2^-24 already; for t < 0
+// the floating-point form rounds frac(t) = t + 1 to fp32, which (t + 1) - 1 does here.  One clamp, one conversion and one
+// addition instead of floor, two conversions, a compare, a carry and a clamp; the gfx950 VALU issues additions, multiplications and
+// shifts at twice the rate of those.  Quantisers of tensors that fit the caches are bound by that issue.
+// `sr_top` holds -X - 2^24 + k; four of them make a word of codes.  Only for finite t.
+// ------------------------------------------------------------------------------------------------
+constexpr float SR_MOST = 127.0f * 0x1p24f;
+__device__ __forceinline__ int floor_to_int(float x)   // |x| < 2^31
+{
+    int r;
+    asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(r) : "v"(x));
+    return r;
+}
+// scaled: -t * 2^24, rounded as above where t < 0; lo, hi: bounds of it (-SR_MOST, SR_MOST, or 0 where one sign is rectified away)
+__device__ __forceinline__ uint32_t sr_top(float scaled, float lo, float hi, uint32_t head)
+{
+    const float c = __builtin_amdgcn_fmed3f(scaled, lo, hi);
+    return __builtin_amdgcn_bitop3_b32(head >> 8, head >> 24, 0xFF000000u, 0x96) + (uint32_t)floor_to_int(c);   // (0x96: three-way xor)
+}
+// -t * 2^24 for t of either sign; one = 1 where t < 0, else 0
+__device__ __forceinline__ float sr_scale(float t, float one) { return __builtin_fmaf(t + one, -0x1p24f, one * 0x1p24f); }
+__device__ __forceinline__ float sr_one_if_negative(float t) { return __uint_as_float((uint32_t)(__float_as_int(t) >> 31) & 0x3F800000u); }
+__device__ __forceinline__ uint32_t sr_pack(uint32_t a, uint32_t b, uint32_t c, uint32_t d)
+{
+    return ~(__builtin_amdgcn_perm(b, a, 0x0C0C0703u) | __builtin_amdgcn_perm(d, c, 0x07030C0Cu));
 }
 
 // STOCH: floor + Bernoulli(frac) from the counter-based word; else round-to-nearest-even.

@@ -6,6 +6,8 @@
 // rounding of the layer input, int8 local gradient), Eq. (1)/(2) (losses) and Eq. (3)/(4)
 // (look-ahead).  Every fp32 operation that decides an int8 code is a single correctly rounded IEEE
 // operation in a fixed order; this file must be compiled with -ffp-contract=off.
+#include <type_traits>
+
 #include "ff_internal.hpp"
 #include "device_math.hpp"
 
@@ -186,59 +188,55 @@ template <int CB, int U> struct QTile {
     static constexpr int CHUNKS = ROWS / 16;           // 16-byte pieces of one transposed column
 };
 
+// Maximum over the workgroup, in every thread.  The barrier is a bare one behind the LDS write: __syncthreads() would wait for
+// the loads of the source tensor, which are in flight across it.
+__device__ __forceinline__ uint32_t workgroup_max(uint32_t v)
+{
+    __shared__ uint32_t red[QT_THREADS / 64];
+    v = wave_max_u32(v);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    return max(max(red[0], red[1]), max(red[2], red[3]));
+}
+// ... of the n candidates a producer left, one per workgroup; four loads per thread in flight
+__device__ __forceinline__ uint32_t max_of_candidates(const uint32_t* __restrict__ c, int n)
+{
+    uint32_t m = 0;
+    for (int i0 = threadIdx.x; i0 < n; i0 += 4 * QT_THREADS) {
+        uint32_t v[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = c[i0 + e * QT_THREADS < n ? i0 + e * QT_THREADS : i0];
+        m = max(m, max(max(v[0], v[1]), max(v[2], v[3])));
+    }
+    return workgroup_max(m);
+}
+
 // Each thread owns U 4x4 element blocks (rows 4*rb+j, cols 4*cb+c).  Codes are packed four columns
 // to a word for q, byte-transposed in registers for q_t and regrouped through LDS so that q_t is
 // written in 16-byte pieces.  All 4 U 16-byte loads of a thread are issued before any arithmetic.
 // FORM 0: element loads (an fp32 source whose columns or base are not 16-byte friendly).  1: 16-byte loads (always legal
-// for the int32 sources).  2: 16-byte loads and cols % 4 == 0, so that four neighbours share a hash head (sr_mix4).
+// for the int32 sources).  2: 16-byte loads and cols % 4 == 0, so that four neighbours share a hash head (sr_head4).
 // Tensors have fewer than 2^32 elements (checked by the entry points), so the low word of the element index is the
 // whole index.
-// What bounds it: for tensors of tens of megabytes HBM, below that the vector ALUs (26 issue slots an element for a local
-// gradient, of which the hash takes 14).  Hence: whole tiles take a body without bounds checks, row pointers advance by
+// What bounds it: for tensors of tens of megabytes HBM, below that the vector ALUs and, for a few tiles per compute unit, the
+// chain of a wavefront.  Hence: whole tiles take a body without bounds checks, row pointers advance by
 // additions, and the sample of a row comes from one 32-bit division per four rows (local gradient of 2 x 8192 x 4096:
-// 71 -> 64 us, 5.2 TB/s; 144 channels at 32x32, 512 images: 84 -> 72 us; 2 x 1024 x 2000: 16 -> 12 us).
+// 71 -> 64 us, 5.2 TB/s).  The loads of the tile go out first, those of the rows' factors and of the range behind them, so
+// that they are all in flight together; the rounding is done in fixed point where that is exact (device_math.hpp).  Local gradient of
+// 2 x 1024 x 2000 10.6 -> 8.5 us, normalised hand-off 14.5 -> 12.4, requantised weights 7.1 -> 6.3; gradients of a
+// MobileNet-shaped step 90 -> 76 us on average.
 template <int SRC, bool STOCH, int FORM, int CB, int U, bool WHOLE>
 __device__ __forceinline__ void quantize_tile(const QuantArgs& a, uint32_t* tileT, int bx, int by)
 {
     constexpr int QT_ROWS = QTile<CB, U>::ROWS, QT_COLS = QTile<CB, U>::COLS, QT_LDW = QTile<CB, U>::LDW, QT_RH = QTile<CB, U>::RH;
     constexpr bool F32SRC = SRC == QSRC_F32 || SRC == QSRC_F32_GRAD;   // the source is an fp32 tensor
+    constexpr bool GRAD = SRC == QSRC_GRAD || SRC == QSRC_F32_GRAD, norm = SRC == QSRC_HANDOFF_NORM;
     const int z = blockIdx.z;
     const float* __restrict__ per_sample = a.per_sample ? a.per_sample + z * a.st_per_sample : nullptr;
     int8_t* __restrict__ q = a.q ? a.q + z * a.st_q : nullptr;
     int8_t* __restrict__ q_t = a.q_t ? a.q_t + z * a.st_qt : nullptr;
-
-    // a vanishing range (absmax < 2^-100, all-zero tensor included) quantises to zero codes with scale 1
-    uint32_t amax_word = a.amax_bits ? a.amax_bits[z * a.st_amax] : 0u;
-    if (a.amax_n > 1) {   // (uniform) the producer left one candidate per workgroup
-        __shared__ uint32_t amx[QT_THREADS / 64];
-        uint32_t mm = 0;
-        for (int i = threadIdx.x; i < a.amax_n; i += QT_THREADS) mm = max(mm, a.amax_bits[z * a.st_amax + i]);
-        mm = wave_max_u32(mm);
-        if ((threadIdx.x & 63) == 0) amx[threadIdx.x >> 6] = mm;
-        __syncthreads();
-        amax_word = max(max(amx[0], amx[1]), max(amx[2], amx[3]));
-    }
-    float s_y = 1.0f;
-    if (!F32SRC) s_y = a.s_a[z * a.st_s_a] * a.s_w[z * a.st_s_w];
-    const double s_yd = (double)s_y, pow2r = (double)(1ull << a.rshift);
-    if (SRC == QSRC_HANDOFF && a.vmax) {   // (uniform) straight from the contraction's per-sample maxima (and sums)
-        __shared__ uint32_t smx[QT_THREADS / 64];
-        const int32_t* vm = a.vmax + z * a.st_b;
-        uint32_t mm = 0;
-        for (int i = threadIdx.x; i < a.B; i += QT_THREADS) {
-            if (!a.l2norm) {
-                mm = max(mm, (uint32_t)vm[i]);
-            } else {
-                const float nrm = sqrtf(goodness_value(a.gsum[z * a.st_b + i], pow2r, s_yd));
-                mm = max(mm, __float_as_uint(nrm > 0.0f ? ((float)vm[i] * s_y) / nrm : 0.0f));
-            }
-        }
-        mm = wave_max_u32(mm);
-        if ((threadIdx.x & 63) == 0) smx[threadIdx.x >> 6] = mm;
-        __syncthreads();
-        mm = max(max(smx[0], smx[1]), max(smx[2], smx[3]));
-        amax_word = a.l2norm ? mm : __float_as_uint((float)(int)mm * s_y);
-    }
 
     const int64_t r0 = (int64_t)by * QT_ROWS;
     const int64_t c0 = (int64_t)bx * QT_COLS;
@@ -282,32 +280,85 @@ __device__ __forceinline__ void quantize_tile(const QuantArgs& a, uint32_t* tile
             ps += FORM == 0 || row_in(QT_RH * u + j + 1) ? ld : 0;
         }
     }
-    // ---- per-row factor (local gradients: 2*coeff; normalised hand-off: sqrt(goodness) and its reciprocal)
-    constexpr bool GRAD = SRC == QSRC_GRAD || SRC == QSRC_F32_GRAD;
-    const bool norm = SRC == QSRC_HANDOFF && a.l2norm;
+    // ---- what the rows' factors are made of: one load per row, all of them in flight
     float rowf[U][4];
+    unsigned long long rows[U][4];
     if (GRAD || norm) {
-        const uint32_t rps = (uint32_t)a.rows_per_sample;
+        const uint32_t rps = (uint32_t)a.rows_per_sample, last = (uint32_t)a.rows - 1u;
+        uint32_t smp[U][4];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const uint32_t rfirst = (uint32_t)rowb + QT_RH * u;
-            uint32_t smp = rfirst, rem = 0;
+            const uint32_t rfirst = WHOLE ? (uint32_t)rowb + QT_RH * u : min((uint32_t)rowb + QT_RH * u, last);
+            smp[u][0] = rfirst;
+            uint32_t rem = 0;
             if (rps != 1) {
-                smp = rfirst / rps;
-                rem = rfirst - smp * rps;
+                smp[u][0] = rfirst / rps;
+                rem = rfirst - smp[u][0] * rps;
             }
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                if (!row_in(QT_RH * u + j)) rowf[u][j] = 0.0f;
-                else if (norm && a.gsum) rowf[u][j] = goodness_value(a.gsum[z * a.st_b + smp], pow2r, s_yd);
-                else rowf[u][j] = per_sample[smp];
-                if (++rem >= rps) { rem = 0; ++smp; }
+            for (int j = 1; j < 4; ++j) {
+                smp[u][j] = smp[u][j - 1];
+                if (row_in(QT_RH * u + j) && ++rem >= rps) { rem = 0; ++smp[u][j]; }
             }
         }
+        if (norm && a.gsum) {
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) rows[u][j] = a.gsum[z * a.st_b + smp[u][j]];
+        } else {
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) rowf[u][j] = per_sample[smp[u][j]];
+        }
+    }
+
+    // ---- range.  A vanishing one (absmax < 2^-100, all-zero tensor included) quantises to zero codes with scale 1
+    uint32_t amax_word = a.amax_bits ? a.amax_bits[z * a.st_amax] : 0u;
+    if (a.amax_n > 1) amax_word = max_of_candidates(a.amax_bits + z * a.st_amax, a.amax_n);   // (uniform) one per workgroup of the producer
+    float s_y = 1.0f;
+    if (!F32SRC) s_y = a.s_a[z * a.st_s_a] * a.s_w[z * a.st_s_w];
+    const double s_yd = (double)s_y, pow2r = (double)(1ull << a.rshift);
+    if ((SRC == QSRC_HANDOFF || norm) && a.vmax) {   // (uniform) straight from the contraction's per-sample maxima (and sums)
+        const int32_t* vm = a.vmax + z * a.st_b;
+        const unsigned long long* gs = a.gsum + z * a.st_b;
+        // (four samples at a time, all loads before the arithmetic; beyond the batch: a sample of this thread's once more)
+        uint32_t mm = 0;
+        for (int i0 = threadIdx.x; i0 < a.B; i0 += 4 * QT_THREADS) {
+            int i[4];
+            int32_t v[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                i[e] = i0 + e * QT_THREADS < a.B ? i0 + e * QT_THREADS : i0;
+                v[e] = vm[i[e]];
+            }
+            if (norm) {
+                unsigned long long g[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) g[e] = gs[i[e]];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float nrm = sqrtf(goodness_value(g[e], pow2r, s_yd));
+                    mm = max(mm, __float_as_uint(nrm > 0.0f ? ((float)v[e] * s_y) / nrm : 0.0f));
+                }
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) mm = max(mm, (uint32_t)v[e]);
+            }
+        }
+        mm = workgroup_max(mm);
+        amax_word = norm ? mm : __float_as_uint((float)(int)mm * s_y);
+    }
+    // ---- per-row factor (local gradients: 2*coeff; normalised hand-off: sqrt(goodness) and its reciprocal)
+    if (GRAD || norm) {
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) rowf[u][j] = GRAD ? 2.0f * rowf[u][j] : sqrtf(rowf[u][j]);
+            for (int j = 0; j < 4; ++j) {
+                if (norm && a.gsum) rowf[u][j] = goodness_value(rows[u][j], pow2r, s_yd);
+                rowf[u][j] = !row_in(QT_RH * u + j) ? 0.0f : (GRAD ? 2.0f * rowf[u][j] : sqrtf(rowf[u][j]));
+            }
     }
 
     const float amax = __uint_as_float(amax_word);
@@ -320,9 +371,15 @@ __device__ __forceinline__ void quantize_tile(const QuantArgs& a, uint32_t* tile
     // (the smallest nonzero activity is s_y, the largest 2^31 s_y: with these bounds every quotient and remainder is normal)
     const bool plain_range = s_y > 0x1p-40f && s_y < 0x1p40f;
 
+    // fixed-point rounding where every t is finite: a finite range, of activities that cannot have overflowed, and a sign that is known
+    // per row (or taken from t)
+    const bool fixed = STOCH && live && amax < __builtin_inff() && (SRC == QSRC_F32 || a.relu) && (F32SRC || s_y < 0x1p80f);
+
     // ---- quantise
     const uint32_t idx0 = (uint32_t)rowb * (uint32_t)a.cols + (uint32_t)col;   // element index of (row rowb, col)
     int8_t* __restrict__ pq0 = q ? q + rowb * a.ldq + col : nullptr;
+    auto codes = [&](auto form) {
+    constexpr bool FIXED = decltype(form)::value;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         uint32_t rowpack[4];
@@ -330,23 +387,24 @@ __device__ __forceinline__ void quantize_tile(const QuantArgs& a, uint32_t* tile
         int8_t* __restrict__ pq = pq0 + (u ? (int64_t)QT_RH * a.ldq : 0);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            uint32_t h[4];
+            uint32_t w[4];
             if (STOCH) {
                 if (FORM == 2) {
-                    sr_mix4(idx ^ key.k0, h);
+                    sr_head4(idx ^ key.k0, w);
                 } else {
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) h[c] = sr_mix((idx + (uint32_t)c) ^ key.k0);
+                    for (int c = 0; c < 4; ++c) w[c] = sr_head((idx + (uint32_t)c) ^ key.k0);
                 }
             }
             float v[4];
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
                 v[c] = F32SRC ? __uint_as_float(raw[u][j][c]) : (float)(int)raw[u][j][c];
-                if (!F32SRC) v[c] = fmaxf(v[c] * s_y, floor_y);
+                if (!F32SRC) v[c] = v[c] * s_y;
+                if (!F32SRC && !FIXED) v[c] = fmaxf(v[c], floor_y);   // (the fixed-point rounding rectifies with its bounds)
                 if (GRAD) v[c] = rowf[u][j] * v[c];
             }
-            if (norm) {   // (uniform)
+            if (norm) {
                 const float d = rowf[u][j];
                 if (plain_range && d > 0x1p-40f && d < 0x1p40f && a.relu) {
                     const float y = 1.0f / d;
@@ -359,12 +417,27 @@ __device__ __forceinline__ void quantize_tile(const QuantArgs& a, uint32_t* tile
             }
             // elements outside the tensor were loaded as zero and a dead range has inv == 0: in both
             // cases t == 0, so the code is 0 in either rounding mode without any masking
-            int code[4];
+            if constexpr (FIXED) {
+                uint32_t top[4];
+                // a rectified source: t has the sign of the row's factor, or of nothing at all
+                const bool down = GRAD && rowf[u][j] < 0.0f;
+                const float one = down ? 1.0f : 0.0f;
+                const float lo = SRC == QSRC_F32 || !down ? -SR_MOST : 0.0f, hi = SRC == QSRC_F32 || down ? SR_MOST : 0.0f;
 #pragma unroll
-            for (int c = 0; c < 4; ++c) code[c] = quant_code_of_word<STOCH>(v[c], inv, STOCH ? h[c] : 0u);
-            const uint32_t lo = __builtin_amdgcn_perm((uint32_t)code[1], (uint32_t)code[0], 0x0C0C0400u);
-            const uint32_t hi = __builtin_amdgcn_perm((uint32_t)code[3], (uint32_t)code[2], 0x04000C0Cu);
-            rowpack[j] = lo | hi;
+                for (int c = 0; c < 4; ++c) {
+                    const float t = v[c] * inv;
+                    const float scaled = SRC == QSRC_F32 ? sr_scale(t, sr_one_if_negative(t)) : (GRAD ? sr_scale(t, one) : t * -0x1p24f);
+                    top[c] = sr_top(scaled, lo, hi, w[c]);
+                }
+                rowpack[j] = sr_pack(top[0], top[1], top[2], top[3]);
+            } else {
+                int code[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) code[c] = quant_code_of_word<STOCH>(v[c], inv, STOCH ? w[c] ^ (w[c] >> 16) : 0u);
+                const uint32_t lo = __builtin_amdgcn_perm((uint32_t)code[1], (uint32_t)code[0], 0x0C0C0400u);
+                const uint32_t hi = __builtin_amdgcn_perm((uint32_t)code[3], (uint32_t)code[2], 0x04000C0Cu);
+                rowpack[j] = lo | hi;
+            }
             if (q && row_in(QT_RH * u + j) && (WHOLE || col < a.ldq)) *(uint32_t*)pq = rowpack[j];
             idx += (uint32_t)a.cols;
             pq += a.ldq;
@@ -381,6 +454,13 @@ __device__ __forceinline__ void quantize_tile(const QuantArgs& a, uint32_t* tile
             tileT[(4 * cb + 2) * QT_LDW + rb] = __builtin_amdgcn_perm(t3, t1, 0x05040100u);
             tileT[(4 * cb + 3) * QT_LDW + rb] = __builtin_amdgcn_perm(t3, t1, 0x07060302u);
         }
+    }
+    };
+    if constexpr (STOCH) {
+        if (fixed) codes(std::true_type{});   // (uniform)
+        else codes(std::false_type{});
+    } else {
+        codes(std::false_type{});
     }
     if (q_t) {
         __syncthreads();
@@ -430,15 +510,7 @@ __global__ __launch_bounds__(QT_THREADS) void k_quantize_pixels(QuantArgs a)
 {
     const int z = blockIdx.y;
     uint32_t amax_word = a.amax_bits[z * a.st_amax];
-    if (a.amax_n > 1) {   // (uniform) the producer left one candidate per workgroup
-        __shared__ uint32_t amx[QT_THREADS / 64];
-        uint32_t mm = 0;
-        for (int i = threadIdx.x; i < a.amax_n; i += QT_THREADS) mm = max(mm, a.amax_bits[z * a.st_amax + i]);
-        mm = wave_max_u32(mm);
-        if ((threadIdx.x & 63) == 0) amx[threadIdx.x >> 6] = mm;
-        __syncthreads();
-        amax_word = max(max(amx[0], amx[1]), max(amx[2], amx[3]));
-    }
+    if (a.amax_n > 1) amax_word = max_of_candidates(a.amax_bits + z * a.st_amax, a.amax_n);   // (uniform) one per workgroup of the producer
     const float amax = __uint_as_float(amax_word);
     const bool live = amax >= 0x1p-100f;
     const float inv = live ? 127.0f / amax : 0.0f;
@@ -525,7 +597,9 @@ hipError_t launch_quantize(int src, const QuantArgs& a, hipStream_t s)
             else launch_quantize_t<QSRC_F32, false>(a, s);
             break;
         case QSRC_HANDOFF:
-            if (st) launch_quantize_t<QSRC_HANDOFF, true>(a, s);
+            if (a.l2norm && st) launch_quantize_t<QSRC_HANDOFF_NORM, true>(a, s);
+            else if (a.l2norm) launch_quantize_t<QSRC_HANDOFF_NORM, false>(a, s);
+            else if (st) launch_quantize_t<QSRC_HANDOFF, true>(a, s);
             else launch_quantize_t<QSRC_HANDOFF, false>(a, s);
             break;
         case QSRC_F32_GRAD:

@@ -50,7 +50,8 @@ __host__ __device__ inline uint64_t stream_tag_of(uint64_t step, uint32_t layer,
 
 // ---- quantise kernels (elementwise.hip) -----------------------------------------------------
 // QSRC_F32_GRAD: fp32 activities times the per-sample factor 2*coeff_total (local gradient of a residual layer)
-enum QSource { QSRC_F32 = 0, QSRC_HANDOFF = 1, QSRC_GRAD = 2, QSRC_F32_GRAD = 3 };
+// QSRC_HANDOFF_NORM: a hand-off with QuantArgs::l2norm; launch_quantize picks it
+enum QSource { QSRC_F32 = 0, QSRC_HANDOFF = 1, QSRC_GRAD = 2, QSRC_F32_GRAD = 3, QSRC_HANDOFF_NORM = 4 };
 
 // One quantisation problem; `nb` problems (1 or 2) are launched together with the strides below.
 struct QuantArgs {
