@@ -206,9 +206,27 @@ struct WsLayout {
     int fused_ok;                  // the stack qualifies for the single-launch kernel
     int fused_auto;                // ... and is small enough that FF_LAUNCH_AUTO picks it
     int fused_wgs;                 // workgroups of that launch
+    bool rework[MAX_LAYERS];       // the layer's accumulators are not kept: every pass that needs them contracts again (rows.hip)
     size_t off_fgy[MAX_LAYERS], st_fgy[MAX_LAYERS];   // per layer: transposed int8 local gradient [2][st]
     size_t total;
 };
+
+// Layers whose accumulators are worked out again by each pass that needs them instead of being stored: convolutions whose
+// patch matrix exists as rows of up to ROWS_MAX_R bytes (1x1 stride-1 ones over their input, first layers over their patches), short
+// beside the outputs that one row gives.  Per output the stored form moves 12 bytes (written, read by the hand-off and by the
+// local gradient), this one the row twice more: up to four bytes of row per output that is a third less and worth it (a
+// MobileNet-shaped step, whose 96 -> 24 layer lies on that line, 1681 -> 1635 us against a line at two bytes).
+static bool rework_accumulators(const ff_net_desc* net, const WsLayout& w, int i)
+{
+    const Dims& d = w.d[i];
+    const ff_layer_desc& L = net->layers[i];
+    if (net->launch_mode == FF_LAUNCH_KERNELS) return false;   // one kernel per operation, every tensor in memory
+    if (!(d.pointwise || wgrad_from_patches(d)) || d.role != FF_ROLE_LAYER || d.skip != FF_SKIP_NONE || L.l2norm_out) return false;
+    if (d.K > ROWS_MAX_R || (d.N & 3) != 0 || d.N > 512 || pitch8(d.K) > 4 * d.N) return false;
+    for (int j = i + 1; j < w.k; ++j)   // (a dense layer also takes its input transposed)
+        if (w.d[j].src == i && w.d[j].kind == FF_DENSE) return false;
+    return true;
+}
 
 static ff_status make_layout(const ff_net_desc* net, WsLayout* w)
 {
@@ -440,6 +458,7 @@ static ff_status make_layout(const ff_net_desc* net, WsLayout* w)
         if (net->launch_mode != FF_LAUNCH_FUSED) w->fused_ok = 0;
     }
     w->total = off;
+    for (int i = 0; i < w->k; ++i) w->rework[i] = rework_accumulators(net, *w, i);
     return FF_OK;
 }
 
@@ -497,6 +516,28 @@ static Im2colArgs im2col_args(const Dims& d, const int8_t* aq, int64_t st_aq, in
     ic.ld_out = pitch8(d.K);
     ic.nb = nb;
     return ic;
+}
+
+static RowsArgs rows_of(const GemmArgs& g)
+{
+    RowsArgs r;
+    memset(&r, 0, sizeof(r));
+    r.P = g.P;
+    r.Q = g.Q;
+    r.ldp = g.ldp;
+    r.ldq = g.ldq;
+    r.st_p = g.st_p;
+    r.I = g.I;
+    r.J = g.J;
+    r.R = g.R;
+    r.nb = g.nb;
+    r.rows_per_sample = g.rows_per_sample;
+    r.relu = g.relu;
+    r.rshift = g.rshift;
+    r.gsum = g.gsum;
+    r.vmax = g.vmax;
+    r.st_g = g.st_g;
+    return r;
 }
 
 // ---- the two contractions of a layer, for nb passes at once ------------------------------------------
@@ -564,6 +605,10 @@ static ff_status run_forward(const Dims& d, int relu, const int8_t* aq, int64_t 
         g.P = col;
         g.st_p = st_col;
         g.ldp = pitch8(d.K);
+    }
+    if (!acc) {
+        HIPCHK_T(FF_K_GEMM_FWD, launch_rows(ROWS_GOODNESS, rows_of(g), QuantArgs{}, s));
+        return FF_OK;
     }
     g.clk = g_clock_probe;
     HIPCHK_T(FF_K_GEMM_FWD, launch_gemm_nt_i8(g, s));
@@ -1311,6 +1356,22 @@ static ff_status train_step_impl(const ff_net_desc* net, const ff_net_state* sta
     }
     const hipStream_t s_main = s;
 
+    auto rows_of_layer = [&](int t) {   // operands of a layer whose accumulators are not kept (pre-step weights, both passes)
+        const Dims& d = w.d[t];
+        RowsArgs r;
+        memset(&r, 0, sizeof(r));
+        r.P = (const int8_t*)(base + (d.pointwise ? w.off_aq[t] : w.off_col[t]));
+        r.st_p = (int64_t)(d.pointwise ? w.st_aq[t] : w.st_col[t]);
+        r.Q = state->w_q[t];
+        r.ldp = r.ldq = pitch8(d.K);
+        r.I = (int32_t)d.M;
+        r.J = (int32_t)d.N;
+        r.R = (int32_t)d.K;
+        r.nb = 2;
+        r.rows_per_sample = (int32_t)d.rps;
+        return r;
+    };
+
     // ---- forward pass through all layers, both data sets together (Algorithm 1) -----------------
     bool proj_pending = false;   // a projection's forward pass is running on the second stream
     for (int i = 0; i < k; ++i) {
@@ -1403,9 +1464,10 @@ static ff_status train_step_impl(const ff_net_desc* net, const ff_net_state* sta
                 HIPCHK_T(FF_K_SMALL, launch_fill_u32((uint32_t*)(goodness + (int64_t)i * 2 * B), 2 * B, 0u, s));
                 HIPCHK_T(FF_K_SMALL, launch_fill_u32((uint32_t*)(loss + 2 * i), 2, 0u, s));
             }
-            HIPCHK_T(FF_K_QUANT_ACT, launch_quantize(src, a, s));
+            if (src == QSRC_HANDOFF && w.rework[d.src]) HIPCHK_T(FF_K_QUANT_ACT, launch_rows(ROWS_HANDOFF, rows_of_layer(d.src), a, s));
+            else HIPCHK_T(FF_K_QUANT_ACT, launch_quantize(src, a, s));
             return run_forward(d, L.relu ? 1 : 0, (const int8_t*)(base + w.off_aq[i]), (int64_t)w.st_aq[i], state->w_q[i],
-                               (int32_t*)(base + w.off_acc[i]), (int64_t)(w.st_acc[i] / sizeof(int32_t)),
+                               w.rework[i] ? nullptr : (int32_t*)(base + w.off_acc[i]), (int64_t)(w.st_acc[i] / sizeof(int32_t)),
                                plain ? gsum + (int64_t)i * 2 * B : nullptr, vmax + (int64_t)i * 2 * B, B,
                                (int8_t*)(base + w.off_col[i]), (int64_t)w.st_col[i], 2, s);
         }();
@@ -1892,7 +1954,11 @@ static ff_status train_step_impl(const ff_net_desc* net, const ff_net_state* sta
         a.scale = s_g + 2 * i;
         a.st_scale = 1;
         a.nb = 2;
-        HIPCHK_T(FF_K_QUANT_GRAD, launch_quantize(src, a, ls));
+        {
+            hipStream_t s = ls;   // (the launch's stream, for its timing events)
+            if (w.rework[i]) HIPCHK_T(FF_K_QUANT_GRAD, launch_rows(ROWS_GRAD, rows_of_layer(i), a, s));
+            else HIPCHK_T(FF_K_QUANT_GRAD, launch_quantize(src, a, s));
+        }
 
         if (trained(i)) {
             const ff_status us = wgrad_update(i, i);

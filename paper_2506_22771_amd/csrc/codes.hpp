@@ -1,0 +1,115 @@
+// Device code that turns a 32x32 block of int32 accumulators, as v_mfma_i32_32x32x32_i8 leaves it, into int8 codes: the
+// arithmetic of the quantiser (elementwise.hip, sources QSRC_HANDOFF and QSRC_GRAD, stochastic rounding) on values that never
+// leave the registers.  Include it only in files compiled with -ffp-contract=off.
+#pragma once
+
+#include <type_traits>
+
+#include "ff_internal.hpp"
+#include "device_math.hpp"
+
+namespace ffi {
+
+// What every element of a pass shares.
+struct CodeScale {
+    float s_y, inv, floor_y;
+    uint32_t key;
+    bool fixed, live;   // fixed-point rounding applies (see quantize_tile); the range does not vanish
+    float amax;
+};
+
+// Maximum over a workgroup of `THREADS` threads, in every thread.
+template <int THREADS>
+__device__ __forceinline__ uint32_t block_max_u32(uint32_t v)
+{
+    __shared__ uint32_t red[THREADS / 64];
+    v = wave_max_u32(v);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < THREADS / 64; ++i) v = max(v, red[i]);
+    return v;
+}
+
+// Range, factors and random key of pass z.  Every thread of the workgroup calls it.
+template <int THREADS>
+__device__ __forceinline__ CodeScale code_scale(const QuantArgs& a, int z)
+{
+    CodeScale c;
+    c.s_y = a.s_a[z * a.st_s_a] * a.s_w[z * a.st_s_w];
+    uint32_t word;
+    if (a.vmax) {   // (uniform) a hand-off that takes its range from the contraction's per-sample maxima
+        const int32_t* vm = a.vmax + z * a.st_b;
+        uint32_t mm = 0;
+        for (int i = threadIdx.x; i < a.B; i += THREADS) mm = max(mm, (uint32_t)vm[i]);
+        word = __float_as_uint((float)(int)block_max_u32<THREADS>(mm) * c.s_y);
+    } else {
+        word = a.amax_bits[z * a.st_amax];
+    }
+    c.amax = __uint_as_float(word);
+    c.live = c.amax >= 0x1p-100f;
+    c.inv = c.live ? 127.0f / c.amax : 0.0f;
+    c.floor_y = a.relu ? 0.0f : -__builtin_inff();
+    c.key = (z ? a.key2 : a.key).k0;
+    if (a.step_dev) c.key = make_sr_key(a.seed, stream_tag_of(a.step_dev[0], a.tag_layer, (uint32_t)z, a.tag_kind)).k0;
+    c.fixed = c.live && c.amax < __builtin_inff() && a.relu && c.s_y < 0x1p80f;
+    return c;
+}
+
+// How a block is rounded: in floating point, or in fixed point with the sign of the row's factor (GRAD) known for the whole
+// wavefront -- codes up from zero, or down -- or per lane.
+enum CodeForm { CODE_FLOAT, CODE_UP, CODE_DOWN, CODE_LANE };
+
+// Codes of four neighbouring columns of one row, packed; idx: element index of the first, a multiple of four.  rowf: the
+// row's factor (GRAD).
+template <bool GRAD, int FORM>
+__device__ __forceinline__ uint32_t quad_codes(const CodeScale& s, int c0, int c1, int c2, int c3, uint32_t idx, float rowf)
+{
+    uint32_t w[4];
+    sr_head4(idx ^ s.key, w);
+    const int cc[4] = {c0, c1, c2, c3};
+    if constexpr (FORM != CODE_FLOAT) {
+        uint32_t top[4];
+        const bool down = FORM == CODE_DOWN || (FORM == CODE_LANE && rowf < 0.0f);
+        const float one = down ? 1.0f : 0.0f;
+        const float lo = down ? 0.0f : -SR_MOST, hi = down ? SR_MOST : 0.0f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            float v = (float)cc[e] * s.s_y;
+            if (GRAD) v = rowf * v;
+            const float t = v * s.inv;
+            top[e] = sr_top(FORM != CODE_UP ? sr_scale(t, one) : t * -0x1p24f, lo, hi, w[e]);
+        }
+        return sr_pack(top[0], top[1], top[2], top[3]);
+    } else {
+        uint32_t word = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            float v = fmaxf((float)cc[e] * s.s_y, s.floor_y);
+            if (GRAD) v = rowf * v;
+            word |= ((uint32_t)quant_code_of_word<true>(v, s.inv, w[e] ^ (w[e] >> 16)) & 0xFFu) << (8 * e);
+        }
+        return word;
+    }
+}
+
+// A block's words: lane (lr = lane & 31, lh = lane >> 5) holds for its row the words g = 0 .. 3 of columns 8 g + 4 lh .. + 3.
+// Row-major: afterwards lane lh holds columns 16 lh .. + 15 of its row, 16 bytes in order.
+__device__ __forceinline__ uint4 words_row_major(const uint32_t w[4])
+{
+    const auto p = __builtin_amdgcn_permlane32_swap(w[0], w[2], false, false);
+    const auto q = __builtin_amdgcn_permlane32_swap(w[1], w[3], false, false);
+    return make_uint4(p[0], p[1], q[0], q[1]);
+}
+// Transposed: four neighbouring lanes 4 a + e exchange bytes; afterwards lane e holds, for column 8 g + 4 lh + e, the codes
+// of the four rows of lanes 4 a .. 4 a + 3.
+__device__ __forceinline__ uint32_t word_transposed(uint32_t w)
+{
+    const uint32_t lane = threadIdx.x;
+    const uint32_t y = dpp_u32<0xB1>(w);   // quad_perm [1,0,3,2]
+    const uint32_t r = __builtin_amdgcn_perm(y, w, lane & 1 ? 0x03070105u : 0x06020400u);
+    const uint32_t x = dpp_u32<0x4E>(r);   // quad_perm [2,3,0,1]
+    return __builtin_amdgcn_perm(x, r, lane & 2 ? 0x03020706u : 0x05040100u);
+}
+
+}  // namespace ffi

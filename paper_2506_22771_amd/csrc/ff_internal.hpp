@@ -365,6 +365,26 @@ int split_evenly(int64_t R, int64_t splits);   // at most `splits` shares of a r
 hipError_t launch_reduce_splits(const int32_t* part, int splits, int64_t st_split, int64_t st_part_z, int32_t* out,
                                 int64_t st_out_z, int64_t n, int nb, hipStream_t s);
 
+// ---- contraction of short rows without stored accumulators (rows.hip) ------------------------------------------------
+// Rows P [I, ldp] x Q [J, ldq]^T over R <= ROWS_MAX_R bytes, nb passes (st_p, st_g apart), J a multiple of four.
+constexpr int ROWS_MAX_R = 128;
+enum RowsResult {
+    ROWS_GOODNESS = 0,   // per-sample goodness sums and maxima into gsum, vmax (added to what is there)
+    ROWS_HANDOFF = 1,    // codes of the activities, row-major: what launch_quantize(QSRC_HANDOFF) makes of the accumulators
+    ROWS_GRAD = 2        // codes of the local gradient, transposed: what launch_quantize(QSRC_GRAD) makes of them
+};
+struct RowsArgs {
+    const int8_t* P;
+    const int8_t* Q;
+    int64_t ldp, ldq, st_p;
+    int32_t I, J, R, nb;
+    int32_t rows_per_sample, relu, rshift;
+    unsigned long long* gsum;
+    int32_t* vmax;
+    int64_t st_g;
+};
+hipError_t launch_rows(int what, const RowsArgs& r, const QuantArgs& a, hipStream_t s);
+
 // ---- single-launch step of a small dense stack (fused.hip) ---------------------------------------------------------
 constexpr int FU_MAX_LAYERS = 8;
 constexpr int FU_THREADS = 512;

@@ -1,0 +1,72 @@
+"""Steps whose layers work their accumulators out again instead of storing them, against the CPU oracle: remainders of the row
+and column blocks, every reduction length class, maps of any size, frozen layers, rectified and plain activations."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+from workloads import Layer, Workload  # noqa: E402
+
+
+@pytest.fixture(scope="module")
+def ff():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2506_22771_amd as m
+    m.lib()
+    return m
+
+
+from test_gpu_parity import _matched_thetas, _run_steps  # noqa: E402
+
+
+def _stack(H, W, C, ks, relu=1):
+    """Convolutions of stride 1, ks[i] wide, over C[0] -> C[1] -> ... channels; ks 0: depthwise."""
+    return tuple(Layer("conv" if k else "dwconv", H=H, W=W, C_in=a, C_out=b, ksize=k or 3, stride=1, pad=(k or 3) // 2, relu=relu)
+                 for a, b, k in zip(C, C[1:], ks))
+
+
+@pytest.mark.parametrize("H,W,B,C,ks", [
+    (16, 16, 5, [3, 32, 64, 68], [3, 1, 1]),      # two rows of 128 per sample; two chunks of the reduction; a third column block
+    (7, 7, 11, [1, 20, 36, 20], [3, 1, 1]),       # samples of 49 rows; columns that end inside a block
+    (28, 28, 2, [1, 32, 24, 132], [3, 1, 1]),     # samples of 784 rows, five column blocks
+    (1, 1, 130, [16, 24, 12], [1, 1]),            # a row per sample, two rows beyond a block
+    (4, 8, 9, [4, 128, 72, 64], [3, 1, 1]),       # samples of 32 rows; the longest reduction
+    (8, 16, 3, [12, 100, 100, 56], [1, 0, 1]),    # into and out of a depthwise layer; a sample per block
+    (9, 5, 6, [2, 96, 512], [3, 1])])             # the widest row of codes
+def test_step_without_stored_accumulators(ff, H, W, B, C, ks):
+    wl = Workload("rework", _stack(H, W, C, ks), B, "normal", lam=0.05)
+    _run_steps(ff, wl, 1, theta_layer=_matched_thetas(wl), live=True, launch_mode="lanes")
+
+
+def test_step_without_stored_accumulators_forms(ff):
+    """Plain activations (floating-point rounding), both signs of the row's factor inside a block, and an all-zero input."""
+    wl = Workload("rework", _stack(6, 7, [3, 24, 40], [3, 1], relu=0), 9, "normal", lam=0.05)
+    _run_steps(ff, wl, 1, theta_layer=_matched_thetas(wl))
+    wl = Workload("rework", _stack(6, 7, [3, 24, 40], [3, 1]), 9, "normal", lam=-3.0)
+    _run_steps(ff, wl, 1, theta_layer=_matched_thetas(wl))
+    zero = np.zeros((9, 6, 7, 3), np.float32)
+    _run_steps(ff, wl, 1, inputs=(zero, zero))
+
+
+@pytest.mark.parametrize("train", [[0, 1, 1], [1, 0, 1], [1, 1, 0]])
+def test_step_without_stored_accumulators_frozen(ff, train):
+    """The same layers stored (one kernel per operation) and worked out again, with frozen ones among them."""
+    from paper_2506_22771_amd import schedule
+    layers, B = _stack(8, 8, [3, 32, 48, 40], [3, 1, 1]), 10
+    out = []
+    for mode in ("kernels", "lanes"):
+        g = torch.Generator(device="cuda").manual_seed(3)
+        w = [torch.rand((l.N, l.K), generator=g, device="cuda") * 0.4 - 0.2 for l in layers]
+        x = [torch.randn((B, layers[0].in_elems_per_sample), generator=g, device="cuda") for _ in range(2)]
+        st = schedule.TrainState.from_weights(layers, B, w)
+        net = ff.Net(layers, B, st.w_master, st.w_q, st.s_w, launch_mode=mode, theta_layer=[40.0] * 3, train_layer=train)
+        loss, good = torch.empty((3, 2), device="cuda"), torch.empty((3, 2, B), device="cuda")
+        ws = torch.empty(net.workspace_bytes(), dtype=torch.uint8, device="cuda")
+        for step in range(3):
+            ff.ff_train_step(net, x[0], x[1], 2.0, 0.05, 1e-4, 5, step, loss, good, ws)
+        torch.cuda.synchronize()
+        out.append([t.cpu() for t in (loss, good, *st.w_master, *st.w_q, *st.s_w)])
+    assert all(torch.equal(a, b) for a, b in zip(*out))
