@@ -211,6 +211,45 @@ struct WsLayout {
     size_t total;
 };
 
+// Operands of a layer's forward contraction (not a depthwise one): P, Q and the shape.
+static GemmArgs forward_args(const Dims& d, int relu, const int8_t* aq, int64_t st_aq, const int8_t* w_q, const int8_t* col,
+                             int64_t st_col, int nb)
+{
+    GemmArgs g;
+    memset(&g, 0, sizeof(g));
+    g.Q = w_q;
+    g.I = (int32_t)d.M;
+    g.J = (int32_t)d.N;
+    g.R = (int32_t)d.K;
+    g.ldq = pitch8(d.K);
+    g.ldc = pitch32(d.N);
+    g.rows_per_sample = (int32_t)d.rps;
+    g.relu = relu;
+    g.rshift = goodness_shift(d.K, d.rps * d.N);
+    g.nb = nb;
+    g.splits = 1;
+    if (d.kind == FF_DENSE || d.pointwise) {
+        // (a 1x1 stride-1 convolution: the NHWC input [B*H*W, pitch(C_in)] is its own patch matrix)
+        g.P = aq;
+        g.st_p = st_aq;
+        g.ldp = pitch8(d.K);
+    } else if (d.implicit) {
+        g.P = aq;
+        g.st_p = st_aq;
+        g.ldp = 16;  // unused by the implicit loader
+        g.conv = 1;
+        g.R = d.g.ks * d.g.ks * ((d.g.Cin + 15) & ~15);
+        g.H = d.g.H; g.W = d.g.W; g.Cin = (d.g.Cin + 15) & ~15; g.cin_out = d.g.Cin; g.cpitch = d.g.cpitch; g.ks = d.g.ks;
+        g.stride = d.g.stride; g.pad = d.g.pad; g.Ho = d.g.Ho; g.Wo = d.g.Wo;
+        g.p_bytes = d.in_rows * d.g.cpitch;
+    } else {
+        g.P = col;
+        g.st_p = st_col;
+        g.ldp = pitch8(d.K);
+    }
+    return g;
+}
+
 // Layers whose accumulators are worked out again by each pass that needs them instead of being stored: convolutions whose
 // patch matrix exists as rows of up to ROWS_MAX_R bytes (1x1 stride-1 ones over their input, first layers over their patches), short
 // beside the outputs that one row gives.  Per output the stored form moves 12 bytes (written, read by the hand-off and by the
@@ -221,8 +260,8 @@ static bool rework_accumulators(const ff_net_desc* net, const WsLayout& w, int i
     const Dims& d = w.d[i];
     const ff_layer_desc& L = net->layers[i];
     if (net->launch_mode == FF_LAUNCH_KERNELS) return false;   // one kernel per operation, every tensor in memory
-    if (!(d.pointwise || wgrad_from_patches(d)) || d.role != FF_ROLE_LAYER || d.skip != FF_SKIP_NONE || L.l2norm_out) return false;
-    if (d.K > ROWS_MAX_R || (d.N & 3) != 0 || d.N > 512 || pitch8(d.K) > 4 * d.N) return false;
+    if (d.kind != FF_CONV2D || d.role != FF_ROLE_LAYER || d.skip != FF_SKIP_NONE || L.l2norm_out || (d.N & 3) != 0 || d.N > 512) return false;
+    if (!(d.pointwise || wgrad_from_patches(d)) || d.K > ROWS_MAX_R || pitch8(d.K) > 4 * d.N) return false;
     for (int j = i + 1; j < w.k; ++j)   // (a dense layer also takes its input transposed)
         if (w.d[j].src == i && w.d[j].kind == FF_DENSE) return false;
     return true;
@@ -518,7 +557,8 @@ static Im2colArgs im2col_args(const Dims& d, const int8_t* aq, int64_t st_aq, in
     return ic;
 }
 
-static RowsArgs rows_of(const GemmArgs& g)
+// One of the passes over a layer whose accumulators are not kept (RowsResult); q: what the codes are made of.
+static hipError_t launch_rework(int what, const GemmArgs& g, const QuantArgs& q, hipStream_t s)
 {
     RowsArgs r;
     memset(&r, 0, sizeof(r));
@@ -537,7 +577,7 @@ static RowsArgs rows_of(const GemmArgs& g)
     r.gsum = g.gsum;
     r.vmax = g.vmax;
     r.st_g = g.st_g;
-    return r;
+    return launch_rows(what, r, q, s);
 }
 
 // ---- the two contractions of a layer, for nb passes at once ------------------------------------------
@@ -567,47 +607,19 @@ static ff_status run_forward(const Dims& d, int relu, const int8_t* aq, int64_t 
         HIPCHK_T(FF_K_DWCONV, launch_dwconv_forward(p, s));
         return FF_OK;
     }
-    GemmArgs g;
-    memset(&g, 0, sizeof(g));
-    g.Q = w_q;
-    g.st_q = 0;
+    GemmArgs g = forward_args(d, relu, aq, st_aq, w_q, col, st_col, nb);
     g.C = acc;
     g.st_c = st_acc;
-    g.I = (int32_t)d.M;
-    g.J = (int32_t)d.N;
-    g.R = (int32_t)d.K;
-    g.ldq = pitch8(d.K);
-    g.ldc = pitch32(d.N);
     g.gsum = gsum;
     g.vmax = vmax;
     g.st_g = st_g;
-    g.rows_per_sample = (int32_t)d.rps;
-    g.relu = relu;
-    g.rshift = goodness_shift(d.K, d.rps * d.N);
-    g.nb = nb;
-    g.splits = 1;
-    if (d.kind == FF_DENSE || d.pointwise) {
-        // (a 1x1 stride-1 convolution: the NHWC input [B*H*W, pitch(C_in)] is its own patch matrix)
-        g.P = aq;
-        g.st_p = st_aq;
-        g.ldp = pitch8(d.K);
-    } else if (d.implicit) {
-        g.P = aq;
-        g.st_p = st_aq;
-        g.ldp = 16;  // unused by the implicit loader
-        g.conv = 1;
-        g.R = d.g.ks * d.g.ks * ((d.g.Cin + 15) & ~15);
-        g.H = d.g.H; g.W = d.g.W; g.Cin = (d.g.Cin + 15) & ~15; g.cin_out = d.g.Cin; g.cpitch = d.g.cpitch; g.ks = d.g.ks;
-        g.stride = d.g.stride; g.pad = d.g.pad; g.Ho = d.g.Ho; g.Wo = d.g.Wo;
-        g.p_bytes = d.in_rows * d.g.cpitch;
-    } else {
-        HIPCHK_T(FF_K_IM2COL, launch_im2col(im2col_args(d, aq, st_aq, col, st_col, nb), s));
-        g.P = col;
-        g.st_p = st_col;
-        g.ldp = pitch8(d.K);
-    }
+    if (explicit_patches(d)) HIPCHK_T(FF_K_IM2COL, launch_im2col(im2col_args(d, aq, st_aq, col, st_col, nb), s));
     if (!acc) {
-        HIPCHK_T(FF_K_GEMM_FWD, launch_rows(ROWS_GOODNESS, rows_of(g), QuantArgs{}, s));
+        HIPCHK_T(FF_K_GEMM_FWD, launch_rework(ROWS_GOODNESS, g, QuantArgs{}, s));
+        return FF_OK;
+    }
+    if (conv3_ok(g)) {
+        HIPCHK_T(FF_K_GEMM_FWD, launch_conv3(g, s));
         return FF_OK;
     }
     g.clk = g_clock_probe;
@@ -1356,20 +1368,11 @@ static ff_status train_step_impl(const ff_net_desc* net, const ff_net_state* sta
     }
     const hipStream_t s_main = s;
 
-    auto rows_of_layer = [&](int t) {   // operands of a layer whose accumulators are not kept (pre-step weights, both passes)
-        const Dims& d = w.d[t];
-        RowsArgs r;
-        memset(&r, 0, sizeof(r));
-        r.P = (const int8_t*)(base + (d.pointwise ? w.off_aq[t] : w.off_col[t]));
-        r.st_p = (int64_t)(d.pointwise ? w.st_aq[t] : w.st_col[t]);
-        r.Q = state->w_q[t];
-        r.ldp = r.ldq = pitch8(d.K);
-        r.I = (int32_t)d.M;
-        r.J = (int32_t)d.N;
-        r.R = (int32_t)d.K;
-        r.nb = 2;
-        r.rows_per_sample = (int32_t)d.rps;
-        return r;
+    // a pass over layer t, whose accumulators are not kept (both passes; the weights are those before the layer's update)
+    auto rework = [&](int what, int t, const QuantArgs& qa, hipStream_t s) {
+        const GemmArgs g = forward_args(w.d[t], qa.relu, (const int8_t*)(base + w.off_aq[t]), (int64_t)w.st_aq[t], state->w_q[t],
+                                  (const int8_t*)(base + w.off_col[t]), (int64_t)w.st_col[t], 2);
+        return launch_rework(what, g, qa, s);
     };
 
     // ---- forward pass through all layers, both data sets together (Algorithm 1) -----------------
@@ -1464,7 +1467,7 @@ static ff_status train_step_impl(const ff_net_desc* net, const ff_net_state* sta
                 HIPCHK_T(FF_K_SMALL, launch_fill_u32((uint32_t*)(goodness + (int64_t)i * 2 * B), 2 * B, 0u, s));
                 HIPCHK_T(FF_K_SMALL, launch_fill_u32((uint32_t*)(loss + 2 * i), 2, 0u, s));
             }
-            if (src == QSRC_HANDOFF && w.rework[d.src]) HIPCHK_T(FF_K_QUANT_ACT, launch_rows(ROWS_HANDOFF, rows_of_layer(d.src), a, s));
+            if (src == QSRC_HANDOFF && w.rework[d.src]) HIPCHK_T(FF_K_QUANT_ACT, rework(ROWS_HANDOFF, d.src, a, s));
             else HIPCHK_T(FF_K_QUANT_ACT, launch_quantize(src, a, s));
             return run_forward(d, L.relu ? 1 : 0, (const int8_t*)(base + w.off_aq[i]), (int64_t)w.st_aq[i], state->w_q[i],
                                w.rework[i] ? nullptr : (int32_t*)(base + w.off_acc[i]), (int64_t)(w.st_acc[i] / sizeof(int32_t)),
@@ -1956,7 +1959,7 @@ static ff_status train_step_impl(const ff_net_desc* net, const ff_net_state* sta
         a.nb = 2;
         {
             hipStream_t s = ls;   // (the launch's stream, for its timing events)
-            if (w.rework[i]) HIPCHK_T(FF_K_QUANT_GRAD, launch_rows(ROWS_GRAD, rows_of_layer(i), a, s));
+            if (w.rework[i]) HIPCHK_T(FF_K_QUANT_GRAD, rework(ROWS_GRAD, i, a, s));
             else HIPCHK_T(FF_K_QUANT_GRAD, launch_quantize(src, a, s));
         }
 

@@ -93,6 +93,77 @@ __device__ __forceinline__ uint32_t quad_codes(const CodeScale& s, int c0, int c
     }
 }
 
+__device__ __forceinline__ unsigned long long xor_lane_u64(unsigned long long v, int d)
+{
+    const unsigned lo = (unsigned)__shfl_xor((int)(unsigned)v, d), hi = (unsigned)__shfl_xor((int)(unsigned)(v >> 32), d);
+    return ((unsigned long long)hi << 32) | lo;
+}
+
+// Sum of squares and maximum of one block's activities, added to a lane's own.
+__device__ __forceinline__ void goodness_terms(int relu, int rshift, const int* v, int n, unsigned long long& sq, int& vm)
+{
+    if (relu && rshift == 0) {
+#pragma unroll
+        for (int e = 0; e < n; ++e) {
+            const unsigned y = (unsigned)max(v[e], 0);
+            sq += (unsigned long long)y * y;
+            vm = max(vm, (int)y);
+        }
+    } else {
+#pragma unroll
+        for (int e = 0; e < n; ++e) {
+            const int y = relu ? max(v[e], 0) : v[e];
+            const long long yl = (long long)y;
+            sq += ((unsigned long long)(yl * yl)) >> rshift;
+            vm = max(vm, y < 0 ? -y : y);
+        }
+    }
+}
+// A wavefront's sums into the words of one sample.
+__device__ __forceinline__ void goodness_one(unsigned long long sq, int vm, unsigned long long* gsum, int32_t* vmax)
+{
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        sq += xor_lane_u64(sq, d);
+        vm = max(vm, __shfl_xor(vm, d));
+    }
+    if ((threadIdx.x & 63) == 0) {
+        atomicAdd(gsum, sq);
+        atomicMax(vmax, vm);
+    }
+}
+// ... of rows i0 + (lane & 31) that belong to several samples: the rows of a sample are a run of lanes, one atomic per run.
+// The two half-waves hold the two halves of a row's columns.
+__device__ __forceinline__ void goodness_runs(unsigned long long sq, int vm, int i0, int I, uint32_t rps,
+                                              unsigned long long* gsum, int32_t* vmax)
+{
+    const int lane = threadIdx.x & 63, lr = lane & 31;
+    sq += xor_lane_u64(sq, 32);
+    vm = max(vm, __shfl_xor(vm, 32));
+    const int i = i0 + lr, smp = (int)((uint32_t)i / rps);
+#pragma unroll
+    for (int d = 1; d < 32; d <<= 1) {
+        const unsigned lo = (unsigned)__shfl_down((int)(unsigned)sq, d, 32);
+        const unsigned hi = (unsigned)__shfl_down((int)(unsigned)(sq >> 32), d, 32);
+        const int ov = __shfl_down(vm, d, 32), os = __shfl_down(smp, d, 32);
+        if (lr + d < 32 && os == smp) {
+            sq += ((unsigned long long)hi << 32) | lo;
+            vm = max(vm, ov);
+        }
+    }
+    const int before = __shfl_up(smp, 1, 32);
+    if (lane < 32 && i < I && (lr == 0 || before != smp)) {
+        atomicAdd(gsum + smp, sq);
+        atomicMax(vmax + smp, vm);
+    }
+}
+// Sample of the rows r0 .. r0 + n - 1 (r0 < I; those beyond I do not count), or -1 if they belong to several.
+__device__ __forceinline__ int one_sample_of(int r0, int n, int I, uint32_t rps)
+{
+    const uint32_t a = (uint32_t)r0 / rps, b = (uint32_t)min(r0 + n - 1, I - 1) / rps;
+    return a == b ? (int)a : -1;
+}
+
 // A block's words: lane (lr = lane & 31, lh = lane >> 5) holds for its row the words g = 0 .. 3 of columns 8 g + 4 lh .. + 3.
 // Row-major: afterwards lane lh holds columns 16 lh .. + 15 of its row, 16 bytes in order.
 __device__ __forceinline__ uint4 words_row_major(const uint32_t w[4])

@@ -365,6 +365,13 @@ int split_evenly(int64_t R, int64_t splits);   // at most `splits` shares of a r
 hipError_t launch_reduce_splits(const int32_t* part, int splits, int64_t st_split, int64_t st_part_z, int32_t* out,
                                 int64_t st_out_z, int64_t n, int nb, hipStream_t s);
 
+// ---- 3x3 stride-1 convolutions with resident weights (conv3.hip) --------------------------------------------------------
+struct Conv3Geom {   // filled in by the launch: 16-byte chunks of a pixel, of a pixel in LDS, pixels and chunks of a window, ...
+    int32_t cpp, pc, swz_mask, window, chunks, ncb, per;
+};
+bool conv3_ok(const GemmArgs& a);   // covers this implicit convolution, and there are enough tiles
+hipError_t launch_conv3(const GemmArgs& a, hipStream_t s);
+
 // ---- contraction of short rows without stored accumulators (rows.hip) ------------------------------------------------
 // Rows P [I, ldp] x Q [J, ldq]^T over R <= ROWS_MAX_R bytes, nb passes (st_p, st_g apart), J a multiple of four.
 constexpr int ROWS_MAX_R = 128;

@@ -25,12 +25,6 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 constexpr int ROWS_THREADS = 256, ROWS_WAVES = ROWS_THREADS / 64;
 constexpr int UNIT = 128;   // rows of one item
 
-__device__ __forceinline__ unsigned long long xor_lane_u64(unsigned long long v, int d)
-{
-    const unsigned lo = (unsigned)__shfl_xor((int)(unsigned)v, d), hi = (unsigned)__shfl_xor((int)(unsigned)(v >> 32), d);
-    return ((unsigned long long)hi << 32) | lo;
-}
-
 template <int WHAT, int KS>
 __global__ __launch_bounds__(ROWS_THREADS) __attribute__((amdgpu_waves_per_eu(KS == 1 ? 4 : KS == 2 ? 3 : 2))) void k_rows_i8(RowsArgs r, QuantArgs a, int per)
 {
@@ -46,7 +40,6 @@ __global__ __launch_bounds__(ROWS_THREADS) __attribute__((amdgpu_waves_per_eu(KS
     const uint32_t tj = (uint32_t)(r.J + 31) >> 5, units = (uint32_t)(r.I + UNIT - 1) / UNIT, items = units * tj;
     const int rpad = (r.R + 15) & ~15;
     const uint32_t rps = (uint32_t)r.rows_per_sample;
-    const bool one_sample = rps % UNIT == 0;   // ... per item
     // (consecutive items: the columns of one group of rows after the other)
     const uint32_t item0 = (blockIdx.x * ROWS_WAVES + wave) * (uint32_t)per, item1 = min(items, item0 + (uint32_t)per);
     unsigned long long sq = 0;   // goodness sum and maximum of the sample (or of the block) at hand
@@ -54,6 +47,7 @@ __global__ __launch_bounds__(ROWS_THREADS) __attribute__((amdgpu_waves_per_eu(KS
     for (uint32_t item = item0; item < item1; ++item) {
         const uint32_t unit = item / tj;
         const int i0 = (int)(unit * UNIT), j0 = (int)(item - unit * tj) << 5;
+        const int smp = one_sample_of(i0, UNIT, r.I, rps);   // (-1: several)
         // rows and columns beyond the matrices read as zero (range check); so do chunks beyond the reduction, in Q
         const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc((void*)(r.P + z * r.st_p + (int64_t)i0 * r.ldp), 0, (int)(min(UNIT, r.I - i0) * r.ldp), 0x00020000);
         const __amdgpu_buffer_rsrc_t rq = __builtin_amdgcn_make_buffer_rsrc((void*)(r.Q + (int64_t)j0 * r.ldq), 0, (int)(min(32, r.J - j0) * r.ldq), 0x00020000);
@@ -74,8 +68,8 @@ __global__ __launch_bounds__(ROWS_THREADS) __attribute__((amdgpu_waves_per_eu(KS
         float rowf[4] = {0.0f, 0.0f, 0.0f, 0.0f};
         if (GRAD) {
             const float* per_sample = a.per_sample + z * a.st_per_sample;
-            if (one_sample) {
-                const float f = 2.0f * per_sample[(uint32_t)i0 / rps];
+            if (smp >= 0) {
+                const float f = 2.0f * per_sample[smp];
 #pragma unroll
                 for (int ti = 0; ti < 4; ++ti) rowf[ti] = f;
             } else {
@@ -95,55 +89,17 @@ __global__ __launch_bounds__(ROWS_THREADS) __attribute__((amdgpu_waves_per_eu(KS
 #pragma unroll
             for (int ti = 0; ti < 4; ++ti) {
                 const v16i acc = contract(ti);
-                if (r.relu && r.rshift == 0) {
+                int v[16];
 #pragma unroll
-                    for (int v = 0; v < 16; ++v) {
-                        const unsigned y = (unsigned)max(acc[v], 0);
-                        sq += (unsigned long long)y * y;
-                        vm = max(vm, (int)y);
-                    }
+                for (int e = 0; e < 16; ++e) v[e] = acc[e];
+                goodness_terms(r.relu, r.rshift, v, 16, sq, vm);
+                if (smp >= 0) {   // one reduction and two atomics for all consecutive items of a sample
+                    if (ti < 3) continue;
+                    const int next = (int)((item + 1) / tj * UNIT);
+                    if (item + 1 < item1 && (next == i0 || one_sample_of(next, UNIT, r.I, rps) == smp)) continue;
+                    goodness_one(sq, vm, r.gsum + z * r.st_g + smp, r.vmax + z * r.st_g + smp);
                 } else {
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) {
-                        const int y = r.relu ? max(acc[v], 0) : acc[v];
-                        const long long yl = (long long)y;
-                        sq += ((unsigned long long)(yl * yl)) >> r.rshift;
-                        vm = max(vm, y < 0 ? -y : y);
-                    }
-                }
-                // one reduction for all consecutive items of a sample
-                if (one_sample && (ti < 3 || (item + 1 < item1 && (item + 1) / tj * UNIT / rps == (uint32_t)i0 / rps))) continue;
-                sq += xor_lane_u64(sq, 32);   // the two half-waves hold the two halves of a row's columns
-                vm = max(vm, __shfl_xor(vm, 32));
-                if (rps % 32 == 0) {
-#pragma unroll
-                    for (int d = 1; d < 32; d <<= 1) {
-                        sq += xor_lane_u64(sq, d);
-                        vm = max(vm, __shfl_xor(vm, d));
-                    }
-                    const int first = one_sample ? i0 : i0 + 32 * ti;
-                    if (lane == 0 && first < r.I) {
-                        const uint32_t smp = (uint32_t)first / rps;
-                        atomicAdd(r.gsum + z * r.st_g + smp, sq);
-                        atomicMax(r.vmax + z * r.st_g + smp, vm);
-                    }
-                } else {   // runs of rows of one sample (as in the contraction kernel)
-                    const int i = i0 + 32 * ti + lr, smp = (int)((uint32_t)i / rps);
-#pragma unroll
-                    for (int d = 1; d < 32; d <<= 1) {
-                        const unsigned lo = (unsigned)__shfl_down((int)(unsigned)sq, d, 32);
-                        const unsigned hi = (unsigned)__shfl_down((int)(unsigned)(sq >> 32), d, 32);
-                        const int ov = __shfl_down(vm, d, 32), os = __shfl_down(smp, d, 32);
-                        if (lr + d < 32 && os == smp) {
-                            sq += ((unsigned long long)hi << 32) | lo;
-                            vm = max(vm, ov);
-                        }
-                    }
-                    const int before = __shfl_up(smp, 1, 32);
-                    if (lh == 0 && i < r.I && (lr == 0 || before != smp)) {
-                        atomicAdd(r.gsum + z * r.st_g + smp, sq);
-                        atomicMax(r.vmax + z * r.st_g + smp, vm);
-                    }
+                    goodness_runs(sq, vm, i0 + 32 * ti, r.I, rps, r.gsum + z * r.st_g, r.vmax + z * r.st_g);
                 }
                 sq = 0;
                 vm = 0;
@@ -182,7 +138,7 @@ __global__ __launch_bounds__(ROWS_THREADS) __attribute__((amdgpu_waves_per_eu(KS
             // (all uniform)
             if (!cs.fixed) codes(std::integral_constant<int, CODE_FLOAT>{});
             else if (!GRAD) codes(std::integral_constant<int, CODE_UP>{});
-            else if (!one_sample) codes(std::integral_constant<int, CODE_LANE>{});
+            else if (smp < 0) codes(std::integral_constant<int, CODE_LANE>{});
             else if (rowf[0] < 0.0f) codes(std::integral_constant<int, CODE_DOWN>{});
             else codes(std::integral_constant<int, CODE_UP>{});
         }

@@ -1,0 +1,52 @@
+"""Forward contraction of 3x3 stride-1 convolutions with resident weights, against the CPU oracle: windows that cross images and
+the ends of the tensor, odd widths, channel counts with half-empty pieces, ragged column blocks, tiles that end inside a pass."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+from oracle import ff_oracle as O  # noqa: E402
+from workloads import Layer  # noqa: E402
+
+
+@pytest.fixture(scope="module")
+def ff():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2506_22771_amd as m
+    m.lib()
+    return m
+
+
+from gpu_util import dev, empty32, pad8, pad_nhwc, workspace  # noqa: E402
+
+
+@pytest.mark.parametrize("B,H,W,Cin,Cout,relu", [
+    (16, 32, 32, 64, 64, 1),      # whole tiles of whole samples
+    (3, 41, 29, 16, 260, 1),      # one piece a pixel, half of it empty; nine narrow column blocks, the last nearly empty
+    (2, 30, 75, 32, 256, 0),      # a wide map: the widest windows; plain activations
+    (5, 33, 31, 40, 228, 1),      # three chunks a pixel of which the last is half pad channels
+    (9, 16, 16, 20, 512, 1),      # two chunks, the last a quarter full; eight column blocks
+    (16, 12, 11, 64, 512, 1),     # samples of 132 rows
+    (33, 16, 8, 8, 100, 1),       # 128 rows: two samples per tile; eight channels
+    (70, 16, 16, 60, 36, 0)])     # one column block that is half empty
+def test_conv_forward_with_resident_weights(ff, B, H, W, Cin, Cout, relu):
+    rng = np.random.default_rng(B * W + Cin)
+    layer = Layer("conv", H=H, W=W, C_in=Cin, C_out=Cout, ksize=3, stride=1, pad=1, relu=relu)
+    desc = ff.layer_desc(layer, B)
+    M, K = B * H * W, 9 * Cin
+    a_q = rng.integers(-127, 128, (B, H, W, Cin)).astype(np.int8)
+    w_q = rng.integers(-127, 128, (Cout, 3, 3, Cin)).astype(np.int8)
+    acc = O.conv_forward(a_q, w_q, 1, 1).reshape(M, Cout)
+    gd = O.goodness(acc.reshape(B, H * W * Cout), relu, O.goodness_shift(K, layer.terms_per_sample), np.float32(1), np.float32(1))
+    d_acc = empty32(M, Cout)
+    gsum = torch.full((B,), 7, dtype=torch.int64, device="cuda")
+    vmax = torch.full((B,), 7, dtype=torch.int32, device="cuda")
+    ws = workspace(ff.ff_layer_workspace_bytes(desc))
+    ff.ff_layer_forward(desc, dev(pad_nhwc(a_q)), dev(pad8(w_q.reshape(Cout, K))), d_acc, gsum, vmax, ws)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(d_acc.cpu().numpy()[:, :Cout], acc)
+    np.testing.assert_array_equal(gsum.cpu().numpy().view(np.uint64), gd["g_int"])
+    np.testing.assert_array_equal(vmax.cpu().numpy(), gd["vmax"])
