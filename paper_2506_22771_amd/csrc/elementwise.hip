@@ -350,6 +350,23 @@ __device__ __forceinline__ void quantize_tile(const QuantArgs& a, uint32_t* tile
         mm = workgroup_max(mm);
         amax_word = norm ? mm : __float_as_uint((float)(int)mm * s_y);
     }
+    if (SRC == QSRC_GRAD && a.vmax) {   // (uniform) the absmax of the gradient, from the per-sample factors and maxima
+        const int32_t* vm = a.vmax + z * a.st_b;
+        uint32_t mm = 0;
+        for (int i0 = threadIdx.x; i0 < a.B; i0 += 4 * QT_THREADS) {
+            int32_t v[4];
+            float ct[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int i = i0 + e * QT_THREADS < a.B ? i0 + e * QT_THREADS : i0;
+                v[e] = vm[i];
+                ct[e] = per_sample[i];
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) mm = max(mm, __float_as_uint(fabsf(2.0f * ct[e]) * ((float)v[e] * s_y)));
+        }
+        amax_word = workgroup_max(mm);
+    }
     // ---- per-row factor (local gradients: 2*coeff; normalised hand-off: sqrt(goodness) and its reciprocal)
     if (GRAD || norm) {
 #pragma unroll

@@ -66,7 +66,8 @@ struct QuantArgs {
     int32_t relu, l2norm;
     // HANDOFF, optional: gsum: with l2norm the goodness of a row's sample straight from the contraction's sums (st_b apart
     // per pass) instead of per_sample.  vmax: the range straight from its per-sample maxima (and sums) instead of
-    // amax_bits; every workgroup reads all B of them, for batches small beside the tensor.
+    // amax_bits; every workgroup reads all B of them, for batches small beside the tensor.  GRAD, optional: vmax, likewise (with
+    // the per-sample factors).
     const int32_t* vmax;
     const unsigned long long* gsum;
     int32_t B, rshift;
