@@ -250,18 +250,35 @@ static GemmArgs forward_args(const Dims& d, int relu, const int8_t* aq, int64_t 
     return g;
 }
 
-// Layers whose accumulators are worked out again by each pass that needs them instead of being stored: convolutions whose
+static DwArgs dw_forward_args(const Dims& d, int relu, const int8_t* aq, int64_t st_aq, const int8_t* w_q, int nb)
+{
+    DwArgs p;
+    memset(&p, 0, sizeof(p));
+    p.a = aq;
+    p.st_a = st_aq;
+    p.w_q = w_q;
+    p.g = d.g;
+    p.B = (int32_t)d.B;
+    p.ldacc = pitch32(d.N);
+    p.relu = relu;
+    p.rshift = goodness_shift(d.K, d.rps * d.N);
+    p.nb = nb;
+    return p;
+}
+
+// Layers whose accumulators are worked out again by each pass that needs them instead of being stored: depthwise ones, and convolutions whose
 // patch matrix exists as rows of up to ROWS_MAX_R bytes (1x1 stride-1 ones over their input, first layers over their patches), short
 // beside the outputs that one row gives.  Per output the stored form moves 12 bytes (written, read by the hand-off and by the
 // local gradient), this one the row twice more: up to four bytes of row per output that is a third less and worth it (a
-// MobileNet-shaped step, whose 96 -> 24 layer lies on that line, 1681 -> 1635 us against a line at two bytes).
+// MobileNet-shaped step, whose 96 -> 24 layer lies on that line, 1681 -> 1635 us against a line at two bytes).  Depthwise layers read a
+// byte per output and pass: the same step 1635 -> 1450.
 static bool rework_accumulators(const ff_net_desc* net, const WsLayout& w, int i)
 {
     const Dims& d = w.d[i];
     const ff_layer_desc& L = net->layers[i];
     if (net->launch_mode == FF_LAUNCH_KERNELS) return false;   // one kernel per operation, every tensor in memory
-    if (d.kind != FF_CONV2D || d.role != FF_ROLE_LAYER || d.skip != FF_SKIP_NONE || L.l2norm_out || (d.N & 3) != 0 || d.N > 512) return false;
-    if (!(d.pointwise || wgrad_from_patches(d)) || d.K > ROWS_MAX_R || pitch8(d.K) > 4 * d.N) return false;
+    if (d.kind == FF_DENSE || d.role != FF_ROLE_LAYER || d.skip != FF_SKIP_NONE || L.l2norm_out || (d.N & 3) != 0 || d.N > 512) return false;
+    if (d.kind == FF_CONV2D && (!(d.pointwise || wgrad_from_patches(d)) || d.K > ROWS_MAX_R || pitch8(d.K) > 4 * d.N)) return false;
     for (int j = i + 1; j < w.k; ++j)   // (a dense layer also takes its input transposed)
         if (w.d[j].src == i && w.d[j].kind == FF_DENSE) return false;
     return true;
@@ -588,23 +605,14 @@ static ff_status run_forward(const Dims& d, int relu, const int8_t* aq, int64_t 
                              int64_t st_col, int nb, hipStream_t s)
 {
     if (d.kind == FF_DWCONV2D) {
-        DwArgs p;
-        memset(&p, 0, sizeof(p));
-        p.a = aq;
-        p.st_a = st_aq;
-        p.w_q = w_q;
-        p.g = d.g;
-        p.B = (int32_t)d.B;
+        DwArgs p = dw_forward_args(d, relu, aq, st_aq, w_q, nb);
         p.acc = acc;
-        p.ldacc = pitch32(d.N);
         p.st_acc = st_acc;
         p.gsum = gsum;
         p.vmax = vmax;
         p.st_g = st_g;
-        p.relu = relu;
-        p.rshift = goodness_shift(d.K, d.rps * d.N);
-        p.nb = nb;
-        HIPCHK_T(FF_K_DWCONV, launch_dwconv_forward(p, s));
+        if (acc) HIPCHK_T(FF_K_DWCONV, launch_dwconv_forward(p, s));
+        else HIPCHK_T(FF_K_DWCONV, launch_dwconv_rework(ROWS_GOODNESS, p, QuantArgs{}, s));
         return FF_OK;
     }
     GemmArgs g = forward_args(d, relu, aq, st_aq, w_q, col, st_col, nb);
@@ -1378,6 +1386,8 @@ static ff_status train_step_impl(const ff_net_desc* net, const ff_net_state* sta
 
     // a pass over layer t, whose accumulators are not kept (both passes; the weights are those before the layer's update)
     auto rework = [&](int what, int t, const QuantArgs& qa, hipStream_t s) {
+        if (w.d[t].kind == FF_DWCONV2D)
+            return launch_dwconv_rework(what, dw_forward_args(w.d[t], qa.relu, (const int8_t*)(base + w.off_aq[t]), (int64_t)w.st_aq[t], state->w_q[t], 2), qa, s);
         const GemmArgs g = forward_args(w.d[t], qa.relu, (const int8_t*)(base + w.off_aq[t]), (int64_t)w.st_aq[t], state->w_q[t],
                                   (const int8_t*)(base + w.off_col[t]), (int64_t)w.st_col[t], 2);
         return launch_rework(what, g, qa, s);

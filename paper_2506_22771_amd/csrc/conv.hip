@@ -5,7 +5,7 @@
 // count -- above all that of a first layer with one or three channels, whose reduction rows of 9 or 27 bytes no 16-byte
 // copy can address -- has its patches written row-major, col[m][(kh,kw,ci)], for the forward contraction; up to four channels
 // the weight gradient reads them as well.  Pure data movement; taps outside the image give 0.
-#include "ff_internal.hpp"
+#include "codes.hpp"
 
 namespace ffi {
 
@@ -334,6 +334,186 @@ hipError_t launch_dwconv_forward(const DwArgs& p, hipStream_t s)
     return hipGetLastError();
 }
 
+// Depthwise layers whose accumulators are not stored: nine taps are worked out again by each pass that needs them (goodness sums,
+// codes handed on, codes of the local gradient, all row-major), where the stored form writes four bytes per output and reads them
+// twice.  Threads are numbered through (piece, channel quad), so that every lane has channels whatever their number; blockIdx.y =
+// sample, blockIdx.z = pass.  A piece is a strip of four columns x DW_STRIP rows (stride 1, rows of whole 4-pixel groups: the
+// input rows slide through a window of three, each loaded and transposed once), or DW_PIX pixels in a row.  Bound by integer and
+// quantiser arithmetic.  144 channels, two passes of 256 images of 32x32: forward with stores, hand-off and local gradient 122 + 81 +
+// 103 us, goodness, hand-off and local gradient here 32 + 64 + 70 (beside other chains up to 119); with a stride of two 46 + 25 + 31
+// and 28 + 34 + 40.
+constexpr int DW_STRIP = 8;
+
+// input row hi of columns wi0 .. wi0 + 5, four channels: word [e][j] = bytes of channel e from column j on
+__device__ __forceinline__ void dw_row_words(const ConvGeom& g, const int8_t* __restrict__ ab, int hi, int wi0, int c0, uint32_t row[4][4])
+{
+    uint32_t X[8];
+    const bool in = (unsigned)hi < (unsigned)g.H;
+    const int8_t* arow = ab + (int64_t)hi * g.W * g.cpitch + c0;
+#pragma unroll
+    for (int j = 0; j < 6; ++j) {
+        const int wi = wi0 + j;
+        X[j] = in && (unsigned)wi < (unsigned)g.W ? *(const uint32_t*)(arow + wi * g.cpitch) : 0u;
+    }
+    X[6] = 0u;
+    X[7] = 0u;
+    uint32_t TA[4], TB[4];
+    dw_transpose4x4(X, TA);
+    dw_transpose4x4(X + 4, TB);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        row[e][0] = TA[e];
+        row[e][1] = __builtin_amdgcn_alignbyte(TB[e], TA[e], 1u);
+        row[e][2] = __builtin_amdgcn_alignbyte(TB[e], TA[e], 2u);
+        row[e][3] = __builtin_amdgcn_alignbyte(TB[e], TA[e], 3u);
+    }
+}
+
+template <int WHAT, bool STRIPS>
+__global__ __launch_bounds__(256) void k_dwconv_rework(DwArgs p, QuantArgs qa, int nq)
+{
+    constexpr bool GRAD = WHAT == ROWS_GRAD;
+    const ConvGeom& g = p.g;
+    const int z = blockIdx.z, b = blockIdx.y;
+    CodeScale cs = {};
+    float rowf = 0.0f;
+    if (WHAT != ROWS_GOODNESS) {
+        cs = code_scale<256>(qa, z);
+        if (blockIdx.x == 0 && b == 0 && threadIdx.x == 0) qa.scale[z * qa.st_scale] = cs.live ? cs.amax / 127.0f : 1.0f;
+        if (GRAD) rowf = 2.0f * qa.per_sample[z * qa.st_per_sample + b];
+    }
+    const int hw = g.Ho * g.Wo, wgroups = g.Wo >> 2;
+    const int pieces = STRIPS ? wgroups * ((g.Ho + DW_STRIP - 1) / DW_STRIP) : (hw + DW_PIX - 1) / DW_PIX;
+    const int at = (int)blockIdx.x * 256 + (int)threadIdx.x, piece = at / nq, c0 = 4 * (at - piece * nq);
+    const int8_t* __restrict__ ab = p.a + z * p.st_a + (int64_t)b * g.H * g.W * g.cpitch;
+    unsigned long long sq = 0;
+    int vm = 0;
+    auto run = [&](auto form) {
+        constexpr int FORM = decltype(form)::value;
+        // four channels of output pixel `pix`
+        auto result = [&](int pix, const int acc[4]) {
+            if constexpr (WHAT == ROWS_GOODNESS) {
+                goodness_terms(p.relu, p.rshift, acc, 4, sq, vm);
+            } else {
+                const uint32_t m = (uint32_t)(b * hw + pix);
+                *(uint32_t*)(qa.q + z * qa.st_q + (int64_t)m * qa.ldq + c0) =
+                    quad_codes<GRAD, FORM>(cs, acc[0], acc[1], acc[2], acc[3], m * (uint32_t)g.Cin + (uint32_t)c0, rowf);
+            }
+        };
+        // the nine taps of a channel are nine consecutive bytes of its weight row
+        uint32_t w[4][3];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            uint4 wr = make_uint4(0u, 0u, 0u, 0u);
+            if (c0 + e < g.Cin) wr = *(const uint4*)(p.w_q + (int64_t)(c0 + e) * 16);
+            w[e][0] = wr.x; w[e][1] = wr.y; w[e][2] = wr.z;
+        }
+        if constexpr (STRIPS) {
+            uint32_t wk[4][3];   // three taps of a kernel row, fourth byte zero
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                wk[e][0] = w[e][0] & 0x00FFFFFFu;
+                wk[e][1] = __builtin_amdgcn_alignbyte(w[e][1], w[e][0], 3u) & 0x00FFFFFFu;
+                wk[e][2] = __builtin_amdgcn_alignbyte(w[e][2], w[e][1], 2u) & 0x00FFFFFFu;
+            }
+            const int hb = piece / wgroups, wo = 4 * (piece - hb * wgroups), h0 = hb * DW_STRIP;
+            uint32_t win[3][4][4];
+            dw_row_words(g, ab, h0 - 1, wo - 1, c0, win[0]);
+            dw_row_words(g, ab, h0, wo - 1, c0, win[1]);
+#pragma unroll
+            for (int r = 0; r < DW_STRIP; ++r) {
+                if (h0 + r >= g.Ho) break;
+                dw_row_words(g, ab, h0 + r + 1, wo - 1, c0, win[(r + 2) % 3]);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    int acc[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        acc[e] = 0;
+#pragma unroll
+                        for (int kh = 0; kh < 3; ++kh) acc[e] = __builtin_amdgcn_sdot4((int)win[(r + kh) % 3][e][j], (int)wk[e][kh], acc[e], false);
+                    }
+                    result((h0 + r) * g.Wo + wo + j, acc);
+                }
+            }
+        } else {
+#pragma unroll 2
+            for (int i = 0; i < DW_PIX; ++i) {
+                const int pix = piece * DW_PIX + i;
+                if (pix >= hw) break;
+                const int ho = pix / g.Wo, wo = pix - ho * g.Wo;
+                uint32_t x[9];   // tap words: byte e = channel c0 + e
+#pragma unroll
+                for (int t = 0; t < 9; ++t) {
+                    const int hi = ho * g.stride + t / 3 - g.pad, wi = wo * g.stride + t % 3 - g.pad;
+                    x[t] = (unsigned)hi < (unsigned)g.H && (unsigned)wi < (unsigned)g.W
+                               ? *(const uint32_t*)(ab + ((int64_t)hi * g.W + wi) * g.cpitch + c0) : 0u;
+                }
+                uint32_t lo[4], hi4[4];
+                dw_transpose4x4(x, lo);
+                dw_transpose4x4(x + 4, hi4);
+                int acc[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    acc[e] = (int)(int8_t)(x[8] >> (8 * e)) * (int)(int8_t)(w[e][2] & 0xFFu);
+                    acc[e] = __builtin_amdgcn_sdot4((int)lo[e], (int)w[e][0], acc[e], false);
+                    acc[e] = __builtin_amdgcn_sdot4((int)hi4[e], (int)w[e][1], acc[e], false);
+                }
+                result(pix, acc);
+            }
+        }
+    };
+    if (piece < pieces) {   // (the forms are uniform)
+        if (WHAT == ROWS_GOODNESS) run(std::integral_constant<int, CODE_FLOAT>{});
+        else if (!cs.fixed) run(std::integral_constant<int, CODE_FLOAT>{});
+        else if (GRAD && rowf < 0.0f) run(std::integral_constant<int, GRAD ? CODE_DOWN : CODE_UP>{});
+        else run(std::integral_constant<int, CODE_UP>{});
+    }
+    if constexpr (WHAT == ROWS_GOODNESS) {
+        __shared__ unsigned long long rs[4];
+        __shared__ int rm[4];
+        sq = dw_wave_sum_u64(sq);
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) vm = max(vm, __shfl_xor(vm, d));
+        if ((threadIdx.x & 63) == 0) { rs[threadIdx.x >> 6] = sq; rm[threadIdx.x >> 6] = vm; }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            const unsigned long long t = rs[0] + rs[1] + rs[2] + rs[3];
+            const int m = max(max(rm[0], rm[1]), max(rm[2], rm[3]));
+            if (t) atomicAdd(p.gsum + z * p.st_g + b, t);
+            if (m) atomicMax(p.vmax + z * p.st_g + b, m);
+        }
+    }
+}
+
+template <int WHAT>
+static hipError_t launch_dwconv_rework_t(const DwArgs& p, const QuantArgs& q, hipStream_t s)
+{
+    const ConvGeom& g = p.g;
+    const bool strips = g.stride == 1 && (g.Wo & 3) == 0;
+    // (codes: quads up to the row pitch, whose pad bytes become zeros)
+    const int nq = (int)((WHAT == ROWS_GOODNESS ? g.Cin : q.ldq) + 3) >> 2;
+    const int64_t pieces = strips ? (int64_t)(g.Wo >> 2) * ((g.Ho + DW_STRIP - 1) / DW_STRIP) : ((int64_t)g.Ho * g.Wo + DW_PIX - 1) / DW_PIX;
+    const int64_t blocks = (pieces * nq + 255) / 256;
+    if (blocks > (int64_t(1) << 22)) return hipErrorInvalidValue;   // (thread numbers in 32 bits)
+    const dim3 grid((unsigned)blocks, (unsigned)p.B, (unsigned)p.nb);
+    if (strips) hipLaunchKernelGGL((k_dwconv_rework<WHAT, true>), grid, dim3(256), 0, s, p, q, nq);
+    else hipLaunchKernelGGL((k_dwconv_rework<WHAT, false>), grid, dim3(256), 0, s, p, q, nq);
+    return hipGetLastError();
+}
+
+hipError_t launch_dwconv_rework(int what, const DwArgs& p, const QuantArgs& q, hipStream_t s)
+{
+    const ConvGeom& g = p.g;
+    if (p.B <= 0) return hipSuccess;
+    if (g.ks != 3 || p.B > 65535 || (g.Cin & 3) != 0 || p.nb < 1 || p.nb > 2) return hipErrorInvalidValue;
+    if (what == ROWS_GOODNESS) return p.gsum && p.vmax ? launch_dwconv_rework_t<ROWS_GOODNESS>(p, q, s) : hipErrorInvalidValue;
+    if (q.round_mode != FF_ROUND_STOCHASTIC || q.l2norm || !q.q || q.q_t || q.ldq != g.cpitch || q.cols != g.Cin || q.rows != (int64_t)p.B * g.Ho * g.Wo)
+        return hipErrorInvalidValue;
+    if (what == ROWS_HANDOFF) return launch_dwconv_rework_t<ROWS_HANDOFF>(p, q, s);
+    return what == ROWS_GRAD && q.per_sample ? launch_dwconv_rework_t<ROWS_GRAD>(p, q, s) : hipErrorInvalidValue;
+}
+
 // Weight gradient of a depthwise convolution: dw[c][tap] = sum over output pixels of gy[m][c] * a[pixel(m) + tap][c].
 // A workgroup owns a share of the output pixels of one sample chunk and a group of up to 64 channels; a thread owns four
 // channels and every (256 / quads)-th piece of the share, keeps 36 int32 partial sums and adds them to LDS accumulators with
@@ -344,8 +524,6 @@ hipError_t launch_dwconv_forward(const DwArgs& p, hipStream_t s)
 // output rows, a (channel, tap) of a group is one packed dot product over its four pixels.  Integer issue and 4-byte loads
 // bound it (10 loads and 68 operations a group, 22 and 116 when every group fetched its three rows).  Together with the
 // partial results in place of 900 thousand atomics: step of the MobileNet-shaped stack 2489 -> 2474 us.
-constexpr int DW_STRIP = 8;
-
 __device__ __forceinline__ void dw_load_row(const DwArgs& p, const int8_t* __restrict__ ab, int hi, int wi0, int c0, uint32_t row[4][3])
 {
     const ConvGeom& g = p.g;

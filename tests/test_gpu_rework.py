@@ -35,7 +35,10 @@ def _stack(H, W, C, ks, relu=1):
     (1, 1, 130, [16, 24, 12], [1, 1]),            # a row per sample, two rows beyond a block
     (4, 8, 9, [4, 128, 72, 64], [3, 1, 1]),       # samples of 32 rows; the longest reduction
     (8, 16, 3, [12, 100, 100, 56], [1, 0, 1]),    # into and out of a depthwise layer; a sample per block
-    (9, 5, 6, [2, 96, 512], [3, 1])])             # the widest row of codes
+    (9, 5, 6, [2, 96, 512], [3, 1]),              # the widest row of codes
+    (10, 12, 6, [8, 144, 144, 24], [1, 0, 1]),    # depthwise strips that end inside a map; several channels beyond a wavefront's
+    (9, 7, 5, [16, 40, 40, 20], [1, 0, 1]),       # depthwise pixels one by one (an odd width), quads of pad channels
+    (1, 4, 40, [24, 24, 12], [0, 1])])      # a depthwise first layer, one row of pixels
 def test_step_without_stored_accumulators(ff, H, W, B, C, ks):
     wl = Workload("rework", _stack(H, W, C, ks), B, "normal", lam=0.05)
     _run_steps(ff, wl, 1, theta_layer=_matched_thetas(wl), live=True, launch_mode="lanes")
@@ -43,9 +46,9 @@ def test_step_without_stored_accumulators(ff, H, W, B, C, ks):
 
 def test_step_without_stored_accumulators_forms(ff):
     """Plain activations (floating-point rounding), both signs of the row's factor inside a block, and an all-zero input."""
-    wl = Workload("rework", _stack(6, 7, [3, 24, 40], [3, 1], relu=0), 9, "normal", lam=0.05)
+    wl = Workload("rework", _stack(6, 8, [3, 24, 40, 40], [3, 1, 0], relu=0), 9, "normal", lam=0.05)
     _run_steps(ff, wl, 1, theta_layer=_matched_thetas(wl))
-    wl = Workload("rework", _stack(6, 7, [3, 24, 40], [3, 1]), 9, "normal", lam=-3.0)
+    wl = Workload("rework", _stack(6, 7, [3, 24, 40, 40], [3, 1, 0]), 9, "normal", lam=-3.0)
     _run_steps(ff, wl, 1, theta_layer=_matched_thetas(wl))
     zero = np.zeros((9, 6, 7, 3), np.float32)
     _run_steps(ff, wl, 1, inputs=(zero, zero))
