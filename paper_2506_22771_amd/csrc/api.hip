@@ -602,7 +602,7 @@ static hipError_t launch_rework(int what, const GemmArgs& g, const QuantArgs& q,
 // conv: NHWC), `col` scratch for an explicit patch matrix (see explicit_patches).
 static ff_status run_forward(const Dims& d, int relu, const int8_t* aq, int64_t st_aq, const int8_t* w_q, int32_t* acc,
                              int64_t st_acc, unsigned long long* gsum, int32_t* vmax, int64_t st_g, int8_t* col,
-                             int64_t st_col, int nb, hipStream_t s)
+                             int64_t st_col, int nb, hipStream_t s, const ResidualArgs* res = nullptr)
 {
     if (d.kind == FF_DWCONV2D) {
         DwArgs p = dw_forward_args(d, relu, aq, st_aq, w_q, nb);
@@ -621,6 +621,7 @@ static ff_status run_forward(const Dims& d, int relu, const int8_t* aq, int64_t 
     g.gsum = gsum;
     g.vmax = vmax;
     g.st_g = st_g;
+    if (res) g.res = *res;
     if (explicit_patches(d)) HIPCHK_T(FF_K_IM2COL, launch_im2col(im2col_args(d, aq, st_aq, col, st_col, nb), s));
     if (!acc) {
         HIPCHK_T(FF_K_GEMM_FWD, launch_rework(ROWS_GOODNESS, g, QuantArgs{}, s));
@@ -1393,6 +1394,18 @@ static ff_status train_step_impl(const ff_net_desc* net, const ff_net_state* sta
         return launch_rework(what, g, qa, s);
     };
 
+    // The goodness sums of a residual block's output need its range over the pass first, and so does the quantiser of the next
+    // layer: where nothing asks for them before the end of the pass, the quantiser forms them as it reads the tensor (its workgroups
+    // read the B maxima each, hence the bound).  fx_reader[i]: that layer, or -1: a launch of its own (the last block).
+    // 64 channels, two passes of 256 images of 32x32: 26 + 29 us as two launches.
+    int fx_reader[MAX_LAYERS];
+    for (int i = 0; i < k; ++i) {
+        fx_reader[i] = -1;
+        if (w.d[i].skip == FF_SKIP_NONE || !goodness_last || B > 2048) continue;
+        for (int j = k - 1; j > i; --j)
+            if (w.d[j].src == i && w.d[j].role == FF_ROLE_LAYER) fx_reader[i] = j;
+    }
+
     // ---- forward pass through all layers, both data sets together (Algorithm 1) -----------------
     bool proj_pending = false;   // a projection's forward pass is running on the second stream
     for (int i = 0; i < k; ++i) {
@@ -1422,7 +1435,13 @@ static ff_status train_step_impl(const ff_net_desc* net, const ff_net_state* sta
             src = QSRC_F32;
             a.x = (const float*)(base + w.off_y[d.src]);
             a.st_x = (int64_t)(w.st_y[d.src] / sizeof(float));
-            a.rows_per_sample = 1;
+            a.rows_per_sample = dense ? 1 : (int32_t)w.d[d.src].rps;
+            if (fx_reader[d.src] == i) {
+                src = QSRC_F32_FX;
+                a.fx_gsum = gsum + (int64_t)d.src * 2 * B;
+                a.st_b = B;
+                a.fx_amax = out_amax + 2 * (d.src + 1);
+            }
         } else {
             const int j = d.src;
             const Dims& dp = w.d[j];
@@ -1455,6 +1474,11 @@ static ff_status train_step_impl(const ff_net_desc* net, const ff_net_state* sta
         a.amax_bits = d.src < 0 ? xmax : out_amax + 2 * (d.src + 1);
         a.st_amax = d.src < 0 ? ABSMAX_MAX_BLOCKS : 1;
         a.amax_n = d.src < 0 ? absmax_blocks(n_in) : 0;
+        if (d.src >= 0 && fx_reader[d.src] >= 0) {   // the range straight from the block's per-sample maxima
+            a.amax_bits = (const uint32_t*)(vmax + (int64_t)d.src * 2 * B);
+            a.st_amax = (int32_t)B;
+            a.amax_n = (int32_t)B;
+        }
         a.round_mode = FF_ROUND_STOCHASTIC;
         a.key = make_sr_key(seed, ff_stream_tag(step, (uint32_t)i, 0, FF_KIND_ACT));
         a.key2 = make_sr_key(seed, ff_stream_tag(step, (uint32_t)i, 1, FF_KIND_ACT));
@@ -1477,31 +1501,9 @@ static ff_status train_step_impl(const ff_net_desc* net, const ff_net_state* sta
         a.st_scale = 1;
         a.nb = 2;
         const bool plain = d.role == FF_ROLE_LAYER && d.skip == FF_SKIP_NONE;   // goodness straight from the accumulators
-        ff_status fs = [&]() -> ff_status {
-            if (d.role == FF_ROLE_PROJECTION && !goodness_last) {
-                // no activity of its own: zero coefficients (nothing enters the look-ahead sums), zero loss / goodness rows
-                // (on the projection's own stream: nothing reads them before the look-ahead kernel)
-                HIPCHK_T(FF_K_SMALL, launch_fill_u32((uint32_t*)(c + (int64_t)i * 2 * B), 2 * B, 0u, s));
-                HIPCHK_T(FF_K_SMALL, launch_fill_u32((uint32_t*)(goodness + (int64_t)i * 2 * B), 2 * B, 0u, s));
-                HIPCHK_T(FF_K_SMALL, launch_fill_u32((uint32_t*)(loss + 2 * i), 2, 0u, s));
-            }
-            if (src == QSRC_HANDOFF && w.rework[d.src]) HIPCHK_T(FF_K_QUANT_ACT, rework(ROWS_HANDOFF, d.src, a, s));
-            else HIPCHK_T(FF_K_QUANT_ACT, launch_quantize(src, a, s));
-            return run_forward(d, L.relu ? 1 : 0, (const int8_t*)(base + w.off_aq[i]), (int64_t)w.st_aq[i], state->w_q[i],
-                               w.rework[i] ? nullptr : (int32_t*)(base + w.off_acc[i]), (int64_t)(w.st_acc[i] / sizeof(int32_t)),
-                               plain ? gsum + (int64_t)i * 2 * B : nullptr, vmax + (int64_t)i * 2 * B, B,
-                               (int8_t*)(base + w.off_col[i]), (int64_t)w.st_col[i], 2, s);
-        }();
-        if (side) {   // (whatever happened on the second stream, it is joined back)
-            if (hipEventRecord(pool->join[0], s) != hipSuccess) fs = fs != FF_OK ? fs : FF_ERR_HIP;
-            proj_pending = true;
-            if (fs != FF_OK) (void)hipStreamWaitEvent(s_main, pool->join[0], 0);
-        }
-        if (fs != FF_OK) return fs;
-        if (d.role == FF_ROLE_PROJECTION) continue;
-        if (!plain) {
-            ResidualArgs ra;
-            memset(&ra, 0, sizeof(ra));
+        ResidualArgs ra;
+        memset(&ra, 0, sizeof(ra));
+        if (!plain && d.role != FF_ROLE_PROJECTION) {
             ra.acc = (const int32_t*)(base + w.off_acc[i]);
             ra.ldacc = pitch32(d.N);
             ra.st_acc = (int64_t)(w.st_acc[i] / sizeof(int32_t));
@@ -1532,11 +1534,40 @@ static ff_status train_step_impl(const ff_net_desc* net, const ff_net_state* sta
             ra.ymax_bits = (uint32_t*)(vmax + (int64_t)i * 2 * B);
             ra.st_b = B;
             ra.nb = 2;
+        }
+        // Implicit contractions form the block output from the accumulators; behind others a launch of its own does, and where samples
+        // have so few rows that most of a wavefront's slices hold several (one atomic per row then: 512 channels on 4x4 maps 87 us
+        // against 39 + 10).
+        const bool in_contraction = ra.y && d.implicit && !d.pointwise && d.rps >= 64;
+        ff_status fs = [&]() -> ff_status {
+            if (d.role == FF_ROLE_PROJECTION && !goodness_last) {
+                // no activity of its own: zero coefficients (nothing enters the look-ahead sums), zero loss / goodness rows
+                // (on the projection's own stream: nothing reads them before the look-ahead kernel)
+                HIPCHK_T(FF_K_SMALL, launch_fill_u32((uint32_t*)(c + (int64_t)i * 2 * B), 2 * B, 0u, s));
+                HIPCHK_T(FF_K_SMALL, launch_fill_u32((uint32_t*)(goodness + (int64_t)i * 2 * B), 2 * B, 0u, s));
+                HIPCHK_T(FF_K_SMALL, launch_fill_u32((uint32_t*)(loss + 2 * i), 2, 0u, s));
+            }
+            if (src == QSRC_HANDOFF && w.rework[d.src]) HIPCHK_T(FF_K_QUANT_ACT, rework(ROWS_HANDOFF, d.src, a, s));
+            else HIPCHK_T(FF_K_QUANT_ACT, launch_quantize(src, a, s));
             if (d.skip == FF_SKIP_PROJECTION && proj_pending) {   // the projection's accumulators are read from here on
                 if (hipStreamWaitEvent(s_main, pool->join[0], 0) != hipSuccess) return FF_ERR_HIP;
                 proj_pending = false;
             }
-            HIPCHK_T(FF_K_RESIDUAL, launch_residual_act(ra, s));
+            return run_forward(d, L.relu ? 1 : 0, (const int8_t*)(base + w.off_aq[i]), (int64_t)w.st_aq[i], state->w_q[i],
+                               w.rework[i] ? nullptr : (int32_t*)(base + w.off_acc[i]), (int64_t)(w.st_acc[i] / sizeof(int32_t)),
+                               plain ? gsum + (int64_t)i * 2 * B : nullptr, vmax + (int64_t)i * 2 * B, B,
+                               (int8_t*)(base + w.off_col[i]), (int64_t)w.st_col[i], 2, s, in_contraction ? &ra : nullptr);
+        }();
+        if (side) {   // (whatever happened on the second stream, it is joined back)
+            if (hipEventRecord(pool->join[0], s) != hipSuccess) fs = fs != FF_OK ? fs : FF_ERR_HIP;
+            proj_pending = true;
+            if (fs != FF_OK) (void)hipStreamWaitEvent(s_main, pool->join[0], 0);
+        }
+        if (fs != FF_OK) return fs;
+        if (d.role == FF_ROLE_PROJECTION) continue;
+        if (!plain) {
+            if (!in_contraction) HIPCHK_T(FF_K_RESIDUAL, launch_residual_act(ra, s));
+            if (fx_reader[i] >= 0) continue;
             GoodnessFxArgs fa;
             memset(&fa, 0, sizeof(fa));
             fa.y = ra.y;

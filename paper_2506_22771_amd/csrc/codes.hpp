@@ -164,6 +164,78 @@ __device__ __forceinline__ int one_sample_of(int r0, int n, int I, uint32_t rps)
     return a == b ? (int)a : -1;
 }
 
+// Block output of a residual layer from four accumulators of a row: y = act(fp32(acc) * s_y + u), one rounding per operation,
+// u the block input's codes or the projection's accumulators at the same place.
+struct ResidualScale {
+    float s_y, s_u;
+};
+__device__ __forceinline__ ResidualScale residual_scale(const ResidualArgs& a, int z)
+{
+    return {a.s_a[z * a.st_s_a] * a.s_w[0],
+            a.skip == FF_SKIP_IDENTITY ? a.s_x[z * a.st_s_x] : a.s_ap[z * a.st_s_ap] * a.s_wp[0]};
+}
+__device__ __forceinline__ int4 residual_skip(const ResidualArgs& a, int z, int64_t row, int col)   // (raw: codes or accumulators)
+{
+    if (a.skip != FF_SKIP_IDENTITY) return *(const int4*)(a.accp + z * a.st_accp + row * a.ldaccp + col);
+    const uint32_t x = *(const uint32_t*)(a.xq + z * a.st_xq + row * a.ldx + col);
+    return make_int4((int8_t)x, (int8_t)(x >> 8), (int8_t)(x >> 16), (int8_t)(x >> 24));
+}
+__device__ __forceinline__ float4 residual_value(const ResidualScale& s, int relu, const int c[4], const int4 skip, uint32_t& m)
+{
+    const int u[4] = {skip.x, skip.y, skip.z, skip.w};
+    float y[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const float t = (float)c[q] * s.s_y;
+        float w = t + (float)u[q] * s.s_u;
+        if (relu) w = fmaxf(w, 0.0f);
+        y[q] = w;
+        m = max(m, __float_as_uint(fabsf(w)));
+    }
+    return make_float4(y[0], y[1], y[2], y[3]);
+}
+// Rows row0 + rl + r RPI, r < NR, of a wavefront's output, LPR lanes of four columns to a row: value(r) gives the accumulators,
+// `in` says whether the lane has columns at all.  Stores y and each sample's largest magnitude.
+template <int LPR, int NR, typename F>
+__device__ __forceinline__ void residual_rows(const ResidualArgs& a, const ResidualScale& s, int z, int row0, int col, bool in, F value)
+{
+    constexpr int RPI = 64 / LPR;
+    const int lane = threadIdx.x & 63, rl = lane / LPR;
+    const int M = (int)a.M;
+    if (row0 >= M) return;   // (uniform)
+    int4 u[NR];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+        const int row = row0 + r * RPI + rl;
+        u[r] = make_int4(0, 0, 0, 0);
+        if (in && row < M) u[r] = residual_skip(a, z, row, col);
+    }
+    const int smp = one_sample_of(row0, NR * RPI, M, (uint32_t)a.rows_per_sample);
+    uint32_t* const ymax = a.ymax_bits + z * a.st_b;
+    uint32_t m = 0;
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+        const int row = row0 + r * RPI + rl;
+        int c[4];
+        value(r, c);
+        uint32_t mr = 0;
+        const float4 y = residual_value(s, a.relu, c, u[r], mr);
+        if (in && row < M) *(float4*)(a.y + z * a.st_y + (int64_t)row * a.N + col) = y;
+        else mr = 0;
+        if (smp >= 0) {   // (uniform)
+            m = max(m, mr);
+        } else {
+#pragma unroll
+            for (int d = 1; d < LPR; d <<= 1) mr = max(mr, (uint32_t)__shfl_xor((int)mr, d));
+            if (lane % LPR == 0 && row < M && mr) atomicMax(ymax + (uint32_t)row / (uint32_t)a.rows_per_sample, mr);
+        }
+    }
+    if (smp >= 0) {
+        m = wave_max_u32(m);
+        if (lane == 0 && m) atomicMax(ymax + smp, m);
+    }
+}
+
 // A block's words: lane (lr = lane & 31, lh = lane >> 5) holds for its row the words g = 0 .. 3 of columns 8 g + 4 lh .. + 3.
 // Row-major: afterwards lane lh holds columns 16 lh .. + 15 of its row, 16 bytes in order.
 __device__ __forceinline__ uint4 words_row_major(const uint32_t w[4])

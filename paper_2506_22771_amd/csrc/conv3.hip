@@ -44,10 +44,14 @@ template <int KT, int TJ> struct C3Shape {
     static_assert(BUF >= 4 * ESLICE, "staging");
 };
 
-template <bool GOODNESS, int KT, int TJ>
+// what becomes of the accumulators: stored, stored with the goodness sums, or the output of a residual block
+enum { C3_STORE, C3_STORE_GOODNESS, C3_RESIDUAL };
+
+template <int WHAT, int KT, int TJ>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_conv3_i8(GemmArgs a, Conv3Geom c)
 {
     using S = C3Shape<KT, TJ>;
+    constexpr bool GOODNESS = WHAT == C3_STORE_GOODNESS, RESIDUAL = WHAT == C3_RESIDUAL;
     constexpr int T = S::T, BN = S::BN, KW = S::KW;
     __shared__ __attribute__((aligned(16))) int8_t lds[S::LDS];
     const int tid = threadIdx.x, lane = tid & 63, lr = lane & 31, lh = lane >> 5;
@@ -155,6 +159,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
         // sixteen rows at a time through the window that was just read, then whole row segments
         int8_t* const slice = win + wave * S::ESLICE;
         int32_t* const C = a.C + z * a.st_c;
+        ResidualScale rs = {};
+        if (RESIDUAL) rs = residual_scale(a.res, z);
 #pragma unroll
         for (int ti = 0; ti < 2; ++ti)
 #pragma unroll
@@ -170,6 +176,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
                 wave_fence();
                 constexpr int LPR = 8 * TJ, RPI = 64 / LPR;   // lanes per row, rows per store instruction
                 const int rl = lane / LPR, cc = 4 * (lane % LPR);
+                if constexpr (RESIDUAL) {
+                    residual_rows<LPR, 16 / RPI>(a.res, rs, z, i0 + 64 * wave + 32 * ti + 16 * h, j0 + cc, j0 + cc < a.J, [&](int r, int c[4]) {
+                        const v4i v = *(const v4i*)(slice + (r * RPI + rl) * S::EROW + cc * 4);
+                        c[0] = v[0]; c[1] = v[1]; c[2] = v[2]; c[3] = v[3];
+                    });
+                    wave_fence();
+                    continue;
+                }
 #pragma unroll
                 for (int r = 0; r < 16 / RPI; ++r) {
                     const int m = i0 + 64 * wave + 32 * ti + 16 * h + r * RPI + rl;
@@ -222,8 +236,9 @@ static hipError_t launch_conv3_cfg(const GemmArgs& a, Conv3Geom c, hipStream_t s
     const int64_t slots = ((tiles + rounds - 1) / rounds + 7) / 8 * 8;
     c.per = (int)rounds;
     const dim3 grid((unsigned)(slots * c.ncb));
-    if (a.gsum) hipLaunchKernelGGL((k_conv3_i8<true, KT, TJ>), grid, dim3(S::T), 0, s, a, c);
-    else hipLaunchKernelGGL((k_conv3_i8<false, KT, TJ>), grid, dim3(S::T), 0, s, a, c);
+    if (a.res.y) hipLaunchKernelGGL((k_conv3_i8<C3_RESIDUAL, KT, TJ>), grid, dim3(S::T), 0, s, a, c);
+    else if (a.gsum) hipLaunchKernelGGL((k_conv3_i8<C3_STORE_GOODNESS, KT, TJ>), grid, dim3(S::T), 0, s, a, c);
+    else hipLaunchKernelGGL((k_conv3_i8<C3_STORE, KT, TJ>), grid, dim3(S::T), 0, s, a, c);
     return hipGetLastError();
 }
 
@@ -268,7 +283,8 @@ hipError_t launch_conv3(const GemmArgs& a, hipStream_t s)
 {
     Conv3Plan p;
     if (a.I <= 0 || a.J <= 0) return hipSuccess;
-    if (!conv3_plan(a, &p) || !a.C || (a.gsum && !a.vmax)) return hipErrorInvalidValue;
+    if (!conv3_plan(a, &p) || (!a.C && !a.res.y) || (a.gsum && (a.res.y || !a.vmax))) return hipErrorInvalidValue;
+    if (a.res.y && (a.res.M != a.I || a.res.N != a.J)) return hipErrorInvalidValue;
     if (p.kt == 1) return p.tj == 2 ? launch_conv3_cfg<1, 2>(a, p.c, s) : launch_conv3_cfg<1, 1>(a, p.c, s);
     return p.tj == 2 ? launch_conv3_cfg<2, 2>(a, p.c, s) : launch_conv3_cfg<2, 1>(a, p.c, s);
 }

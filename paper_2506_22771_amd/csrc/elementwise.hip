@@ -176,6 +176,16 @@ __device__ __forceinline__ uint4 ld_stream16(const void* p)
     return make_uint4(v.x, v.y, v.z, v.w);
 }
 
+__device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v)
+{
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const unsigned lo = (unsigned)__shfl_xor((int)(unsigned)v, d), hi = (unsigned)__shfl_xor((int)(unsigned)(v >> 32), d);
+        v += ((unsigned long long)hi << 32) | lo;
+    }
+    return v;
+}
+
 constexpr int QT_THREADS = 256;
 // Tile of one workgroup: CB column blocks of four columns, U x (256 / CB) row blocks of four rows: 128 x 64 elements
 // for CB = 16, 256 x 32 for CB = 8 (matrices of at most 32 columns: no idle column lanes, and with a row pitch of
@@ -231,7 +241,8 @@ template <int SRC, bool STOCH, int FORM, int CB, int U, bool WHOLE>
 __device__ __forceinline__ void quantize_tile(const QuantArgs& a, uint32_t* tileT, int bx, int by)
 {
     constexpr int QT_ROWS = QTile<CB, U>::ROWS, QT_COLS = QTile<CB, U>::COLS, QT_LDW = QTile<CB, U>::LDW, QT_RH = QTile<CB, U>::RH;
-    constexpr bool F32SRC = SRC == QSRC_F32 || SRC == QSRC_F32_GRAD;   // the source is an fp32 tensor
+    constexpr bool FX = SRC == QSRC_F32_FX, PLAIN = SRC == QSRC_F32 || FX;
+    constexpr bool F32SRC = PLAIN || SRC == QSRC_F32_GRAD;   // the source is an fp32 tensor
     constexpr bool GRAD = SRC == QSRC_GRAD || SRC == QSRC_F32_GRAD, norm = SRC == QSRC_HANDOFF_NORM;
     const int z = blockIdx.z;
     const float* __restrict__ per_sample = a.per_sample ? a.per_sample + z * a.st_per_sample : nullptr;
@@ -390,7 +401,7 @@ __device__ __forceinline__ void quantize_tile(const QuantArgs& a, uint32_t* tile
 
     // fixed-point rounding where every t is finite: a finite range, of activities that cannot have overflowed, and a sign that is known
     // per row (or taken from t)
-    const bool fixed = STOCH && live && amax < __builtin_inff() && (SRC == QSRC_F32 || a.relu) && (F32SRC || s_y < 0x1p80f);
+    const bool fixed = STOCH && live && amax < __builtin_inff() && (PLAIN || a.relu) && (F32SRC || s_y < 0x1p80f);
 
     // ---- quantise
     const uint32_t idx0 = (uint32_t)rowb * (uint32_t)a.cols + (uint32_t)col;   // element index of (row rowb, col)
@@ -439,11 +450,11 @@ __device__ __forceinline__ void quantize_tile(const QuantArgs& a, uint32_t* tile
                 // a rectified source: t has the sign of the row's factor, or of nothing at all
                 const bool down = GRAD && rowf[u][j] < 0.0f;
                 const float one = down ? 1.0f : 0.0f;
-                const float lo = SRC == QSRC_F32 || !down ? -SR_MOST : 0.0f, hi = SRC == QSRC_F32 || down ? SR_MOST : 0.0f;
+                const float lo = PLAIN || !down ? -SR_MOST : 0.0f, hi = PLAIN || down ? SR_MOST : 0.0f;
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
                     const float t = v[c] * inv;
-                    const float scaled = SRC == QSRC_F32 ? sr_scale(t, sr_one_if_negative(t)) : (GRAD ? sr_scale(t, one) : t * -0x1p24f);
+                    const float scaled = PLAIN ? sr_scale(t, sr_one_if_negative(t)) : (GRAD ? sr_scale(t, one) : t * -0x1p24f);
                     top[c] = sr_top(scaled, lo, hi, w[c]);
                 }
                 rowpack[j] = sr_pack(top[0], top[1], top[2], top[3]);
@@ -478,6 +489,52 @@ __device__ __forceinline__ void quantize_tile(const QuantArgs& a, uint32_t* tile
         else codes(std::false_type{});
     } else {
         codes(std::false_type{});
+    }
+    if constexpr (FX) {
+        // The goodness sums of the tensor at hand (the output of a residual block), in the fixed point of k_goodness_fx: per element
+        // floor(r r 2^40), r = y / amax.  Products and sums of a thread are exact in fp64 (24-bit factors, at most 32 terms).
+        const float fx_inv = live ? 1.0f / amax : 0.0f;
+        const uint32_t rps = (uint32_t)a.rows_per_sample, last = (uint32_t)a.rows - 1u;
+        unsigned long long* const gs = a.fx_gsum + z * a.st_b;
+        if (blockIdx.x == 0 && blockIdx.y == 0 && t == 0) a.fx_amax[z] = amax_word;
+        double sum[U][4];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                sum[u][j] = 0.0;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const double r = (double)(__uint_as_float(raw[u][j][c]) * fx_inv);
+                    sum[u][j] += __builtin_trunc(r * r * 0x1p40);
+                }
+            }
+        const uint32_t s0 = (uint32_t)r0 / rps, s1 = min((uint32_t)r0 + QT_ROWS - 1u, last) / rps;
+        if (s0 == s1) {   // (uniform) one atomic per tile
+            double w = 0.0;
+#pragma unroll
+            for (int u = 0; u < U; ++u) w += (sum[u][0] + sum[u][1]) + (sum[u][2] + sum[u][3]);
+            const unsigned long long part = wave_sum_u64((unsigned long long)w);
+            __shared__ unsigned long long reds[QT_THREADS / 64];
+            if ((t & 63) == 0) reds[t >> 6] = part;
+            __syncthreads();
+            if (t == 0) atomicAdd(gs + s0, (reds[0] + reds[1]) + (reds[2] + reds[3]));
+        } else {   // the CB lanes of a row, or of four rows of one sample, meet; one atomic for each
+            const bool fours = (rps & 3u) == 0;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (fours) sum[u][0] = (sum[u][0] + sum[u][1]) + (sum[u][2] + sum[u][3]);
+                for (int j = 0; j < (fours ? 1 : 4); ++j) {
+                    unsigned long long v = (unsigned long long)(j == 0 ? sum[u][0] : j == 1 ? sum[u][1] : j == 2 ? sum[u][2] : sum[u][3]);
+#pragma unroll
+                    for (int d = 1; d < CB; d <<= 1) {
+                        const unsigned lo = (unsigned)__shfl_xor((int)(unsigned)v, d), hi = (unsigned)__shfl_xor((int)(unsigned)(v >> 32), d);
+                        v += ((unsigned long long)hi << 32) | lo;
+                    }
+                    if (cb == 0 && v) atomicAdd(gs + min((uint32_t)rowb + QT_RH * u + j, last) / rps, v);
+                }
+            }
+        }
     }
     if (q_t) {
         __syncthreads();
@@ -557,7 +614,7 @@ static void launch_quantize_tiles(QuantArgs a, int64_t span, hipStream_t s)
     // two L2s; with a row of tiles on one XCD it is one.  Local gradient of 65536 x 1000: backward 132 -> 114 us, x 500:
     // 88 -> 79, 40000 x 2000: 142 -> 122; hand-off of 35322 x 224 with its transposed copy 14.0 -> 11.5, of 16384 x 1000
     // 25.5 -> 20.5.  Rows that start on lines keep the plain order (a normalised hand-off of 8192 x 4096: 36 us, 40 this way).
-    constexpr bool F32SRC = SRC == QSRC_F32 || SRC == QSRC_F32_GRAD;
+    constexpr bool F32SRC = SRC == QSRC_F32 || SRC == QSRC_F32_GRAD || SRC == QSRC_F32_FX;
     a.row_per_xcd = (((F32SRC ? a.cols : a.ldacc) & 31) != 0 || (a.q && (a.ldq & 127) != 0)) && span > QTile<CB, U>::COLS;
     // (row tiles up to the row pitch of q_t, for the same reason)
     const int64_t rspan = a.q_t && a.ldqt > a.rows ? a.ldqt : a.rows;
@@ -569,7 +626,7 @@ static void launch_quantize_tiles(QuantArgs a, int64_t span, hipStream_t s)
 template <int SRC, bool STOCH>
 static void launch_quantize_t(const QuantArgs& a, hipStream_t s)
 {
-    constexpr bool F32SRC = SRC == QSRC_F32 || SRC == QSRC_F32_GRAD;
+    constexpr bool F32SRC = SRC == QSRC_F32 || SRC == QSRC_F32_GRAD || SRC == QSRC_F32_FX;
     constexpr int GENERAL = F32SRC ? 0 : 1;
     if (SRC == QSRC_F32 && a.cols <= 4 && a.q && !a.q_t) {
         const int64_t blocks = min((a.rows + QT_THREADS - 1) / QT_THREADS, (int64_t)8 * num_cus());
@@ -594,11 +651,11 @@ static void launch_quantize_t(const QuantArgs& a, hipStream_t s)
     if (narrow) {
         if (cols4 && few) launch_quantize_tiles<SRC, STOCH, 2, 8, 1>(a, QTile<8, 1>::COLS, s);
         else if (cols4) launch_quantize_tiles<SRC, STOCH, 2, 8, 2>(a, QTile<8, 2>::COLS, s);
-        else launch_quantize_tiles<SRC, STOCH, 1, 8, 2>(a, QTile<8, 2>::COLS, s);
+        else if constexpr (!F32SRC) launch_quantize_tiles<SRC, STOCH, 1, 8, 2>(a, QTile<8, 2>::COLS, s);
     } else if (vec && cols4) {
         if (few) launch_quantize_tiles<SRC, STOCH, 2, 16, 1>(a, span, s);
         else launch_quantize_tiles<SRC, STOCH, 2, 16, 2>(a, span, s);
-    } else {
+    } else if constexpr (SRC != QSRC_F32_FX) {
         if (few) launch_quantize_tiles<SRC, STOCH, GENERAL, 16, 1>(a, span, s);
         else launch_quantize_tiles<SRC, STOCH, GENERAL, 16, 2>(a, span, s);
     }
@@ -609,6 +666,11 @@ hipError_t launch_quantize(int src, const QuantArgs& a, hipStream_t s)
     if (a.rows <= 0 || a.cols <= 0) return hipSuccess;
     const bool st = a.round_mode == FF_ROUND_STOCHASTIC;
     switch (src) {
+        case QSRC_F32_FX:   // (block outputs are 16-byte aligned rows of a multiple of four columns)
+            if ((a.cols & 3) != 0 || (((uintptr_t)a.x) & 15) != 0 || (a.st_x & 3) != 0 || !st || !a.fx_gsum || !a.fx_amax || a.rows_per_sample < 1)
+                return hipErrorInvalidValue;
+            launch_quantize_t<QSRC_F32_FX, true>(a, s);
+            break;
         case QSRC_F32:
             if (st) launch_quantize_t<QSRC_F32, true>(a, s);
             else launch_quantize_t<QSRC_F32, false>(a, s);
@@ -716,16 +778,6 @@ hipError_t launch_goodness_loss(const GoodnessArgs& a, hipStream_t s)
 // residual layers: block output y = act(fp32(acc) * s_y + skip), one rounding per operation, stored as
 // fp32; max|y| per sample and over the pass (bit patterns, atomic max).  A thread owns four columns.
 // ------------------------------------------------------------------------------------------------
-__device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v)
-{
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const unsigned lo = (unsigned)__shfl_xor((int)(unsigned)v, d), hi = (unsigned)__shfl_xor((int)(unsigned)(v >> 32), d);
-        v += ((unsigned long long)hi << 32) | lo;
-    }
-    return v;
-}
-
 // Work split of the two residual kernels: blockIdx.y = sample, blockIdx.x = a contiguous share of the sample's
 // terms (RES_VPT four-element vectors per thread), blockIdx.z = pass.  A workgroup therefore reduces for ONE
 // sample and issues one atomic.

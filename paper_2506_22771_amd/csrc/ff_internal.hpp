@@ -51,7 +51,8 @@ __host__ __device__ inline uint64_t stream_tag_of(uint64_t step, uint32_t layer,
 // ---- quantise kernels (elementwise.hip) -----------------------------------------------------
 // QSRC_F32_GRAD: fp32 activities times the per-sample factor 2*coeff_total (local gradient of a residual layer)
 // QSRC_HANDOFF_NORM: a hand-off with QuantArgs::l2norm; launch_quantize picks it
-enum QSource { QSRC_F32 = 0, QSRC_HANDOFF = 1, QSRC_GRAD = 2, QSRC_F32_GRAD = 3, QSRC_HANDOFF_NORM = 4 };
+// QSRC_F32_FX: the fp32 output of a residual block; the launch also forms its goodness sums (fx_gsum)
+enum QSource { QSRC_F32 = 0, QSRC_HANDOFF = 1, QSRC_GRAD = 2, QSRC_F32_GRAD = 3, QSRC_HANDOFF_NORM = 4, QSRC_F32_FX = 5 };
 
 // One quantisation problem; `nb` problems (1 or 2) are launched together with the strides below.
 struct QuantArgs {
@@ -72,6 +73,9 @@ struct QuantArgs {
     const unsigned long long* gsum;
     int32_t B, rshift;
     int64_t st_b;
+    // F32_FX: per-sample fixed-point goodness sums (as launch_goodness_fx; added to, st_b apart) and a word per pass for the absmax
+    unsigned long long* fx_gsum;
+    uint32_t* fx_amax;
     // quantiser
     const uint32_t* amax_bits;  // device: bit pattern of the non-negative fp32 absmax
     int32_t amax_n;             // > 1: amax_bits is an array of that many candidates, the absmax is their maximum
@@ -347,6 +351,9 @@ struct GemmArgs {
     // ticks it was alive to clk[0] and clk[1] (their ratio is the mean shader clock during the launch) and the
     // shader clocks of each tile by phase to clk[2..6] / clk[8..12]
     unsigned long long* clk;   // 16 counters, see ff_timing_clock_probe
+    // residual layer (res.y non-null; implicit convolutions, no split, no fused reductions): C is not written, the block output is
+    // formed from the accumulators
+    ResidualArgs res;
 };
 hipError_t launch_gemm_nt_i8(const GemmArgs& a, hipStream_t s);
 // workgroups of the launch with the fused update, or 0 where that is not the better way (see gemm_update_blocks)

@@ -32,6 +32,7 @@
 //    multiplies and half after them: every SIMD keeps multiplying while the copy instructions queue up.
 #include "ff_internal.hpp"
 #include "device_math.hpp"
+#include "codes.hpp"
 
 namespace ffi {
 
@@ -87,6 +88,7 @@ template <int BKT> __device__ __forceinline__ int swz(int row, int kc) { return 
 // workgroup stores the partial sums of its share of the reduction steps at C + blockIdx.y * st_split; 3: weight gradient
 // and update -- a workgroup contracts its tile for the positive pass, keeps fp32(acc) * scale in registers, contracts the same
 // tile for the negative pass and applies both to its tile of the weights (the update's own sequence of roundings).
+// MODE 4: the output of a residual block (GemmArgs::res) instead of the accumulators.
 // CONV 0: both operands are matrices.  1: P is an NHWC tensor, row i of the contraction is an output pixel and
 // the reduction runs over (tap, channel) (forward pass of a convolution as an implicit GEMM).
 // CONV 2: Q is the NHWC tensor itself, column j of the contraction's output is (tap, channel) and the reduction runs over
@@ -106,7 +108,7 @@ __global__ __launch_bounds__(WM* WN * 64) __attribute__((amdgpu_waves_per_eu(BKT
     constexpr int BK = BKT;             // reduction bytes per LDS stage
     constexpr int CPB = BK / 16;        // 16-byte chunks per staged row
     constexpr int SUB = BK / 32;        // MFMA sub-steps per stage
-    constexpr bool EPI = MODE == 1, UPD = MODE == 3;
+    constexpr bool EPI = MODE == 1, UPD = MODE == 3, RES = MODE == 4;
     constexpr int T = WM * WN * 64;
     constexpr int WTM = BM / WM, WTN = BN / WN;
     constexpr int TI = WTM / 32, TJ = WTN / 32;
@@ -117,7 +119,7 @@ __global__ __launch_bounds__(WM* WN * 64) __attribute__((amdgpu_waves_per_eu(BKT
     // 256-row tiles stage in the SECOND operand stage (and a little beyond it; 16 rows at a time for the 256 x 256 tile,
     // so that it fits), which leaves the first stage free for the first copies of the workgroup's next tile (persistent
     // launches); the others 32 rows from 0.
-    constexpr bool PREFETCH = (BM == 256 || BK == 64) && CONV < 2 && MODE < 2;
+    constexpr bool PREFETCH = (BM == 256 || BK == 64) && CONV < 2 && (MODE < 2 || RES);
     constexpr int EROWS = PREFETCH && (BN == 256 || BK == 64) ? 16 : 32;
     constexpr int EROW = WTN * 4 + 16;
     constexpr int ESLICE = EROWS * EROW;
@@ -444,8 +446,10 @@ __global__ __launch_bounds__(WM* WN * 64) __attribute__((amdgpu_waves_per_eu(BKT
     // CONV 2 with channel counts that are no multiple of 16: the columns run over whole 16-channel chunks and the store
     // leaves the channels beyond C_in out
     const bool compact = CONV == 2 && a.cin_out != a.Cin;
-    const bool staged = (interior || (a.J & 3) == 0) && !compact;
+    const bool staged = RES || ((interior || (a.J & 3) == 0) && !compact);
     const bool fast_sq = a.relu && a.rshift == 0;
+    ResidualScale res_scale = {};
+    if (RES) res_scale = residual_scale(a.res, z);
     int8_t* const ebase = lds + EOFF + wave * ESLICE;
     if (wait_copies && !staged) {   // (copies and stores complete in issue order: wait before the first store)
         wait_vmcnt<0>();
@@ -531,6 +535,15 @@ __global__ __launch_bounds__(WM* WN * 64) __attribute__((amdgpu_waves_per_eu(BKT
                 constexpr int RPI = 64 / LPR;         // rows per store instruction
                 const int rl = lane / LPR, cc = lane - rl * LPR;
                 const int row0 = i0 + wm * WTM + ti * 32 + h * EROWS;
+                if constexpr (RES) {
+                    const int col = j0 + wn * WTN + cc * 4;
+                    residual_rows<LPR, EROWS / RPI>(a.res, res_scale, z, row0, col, col < a.J, [&](int r, int c[4]) {
+                        const v4i v = *(const v4i*)(ebase + (r * RPI + rl) * EROW + cc * 16);
+                        c[0] = v[0]; c[1] = v[1]; c[2] = v[2]; c[3] = v[3];
+                    });
+                    wave_lds_fence();
+                    continue;
+                }
                 int32_t* const ctile = C + (int64_t)row0 * a.ldc + j0 + wn * WTN + cc * 4;
 #pragma unroll
                 for (int r = 0; r < EROWS / RPI; ++r) {
@@ -662,7 +675,8 @@ static hipError_t launch_paired(const GemmArgs& a, hipStream_t s)
     const int64_t resident = (int64_t)2 * num_cus();
     const dim3 grid((unsigned)min(ntiles, resident)), block(WM * WN * 64);
     if (a.conv == 1) {
-        if (a.gsum) hipLaunchKernelGGL((k_gemm_nt_i8<BM, BN, WM, WN, 1, 1, BKT, NS>), grid, block, 0, s, a);
+        if (a.res.y) hipLaunchKernelGGL((k_gemm_nt_i8<BM, BN, WM, WN, 4, 1, BKT, NS>), grid, block, 0, s, a);
+        else if (a.gsum) hipLaunchKernelGGL((k_gemm_nt_i8<BM, BN, WM, WN, 1, 1, BKT, NS>), grid, block, 0, s, a);
         else hipLaunchKernelGGL((k_gemm_nt_i8<BM, BN, WM, WN, 0, 1, BKT, NS>), grid, block, 0, s, a);
     } else {
         if (a.gsum) hipLaunchKernelGGL((k_gemm_nt_i8<BM, BN, WM, WN, 1, 0, BKT, NS>), grid, block, 0, s, a);
@@ -698,7 +712,8 @@ static hipError_t launch_cfg(const GemmArgs& a, hipStream_t s)
         if (a.conv == 1) return hipErrorInvalidValue;
         hipLaunchKernelGGL((k_gemm_nt_i8<BM, BN, WM, WN, 2, 0>), grid, block, 0, s, a);
     } else if constexpr (WHOLE) {
-        if (a.conv == 1 && mode == 1) hipLaunchKernelGGL((k_gemm_nt_i8<BM, BN, WM, WN, 1, 1>), grid, block, 0, s, a);
+        if (a.res.y) hipLaunchKernelGGL((k_gemm_nt_i8<BM, BN, WM, WN, 4, 1>), grid, block, 0, s, a);
+        else if (a.conv == 1 && mode == 1) hipLaunchKernelGGL((k_gemm_nt_i8<BM, BN, WM, WN, 1, 1>), grid, block, 0, s, a);
         else if (a.conv == 1) hipLaunchKernelGGL((k_gemm_nt_i8<BM, BN, WM, WN, 0, 1>), grid, block, 0, s, a);
         else if (mode == 1) hipLaunchKernelGGL((k_gemm_nt_i8<BM, BN, WM, WN, 1, 0>), grid, block, 0, s, a);
         else hipLaunchKernelGGL((k_gemm_nt_i8<BM, BN, WM, WN, 0, 0>), grid, block, 0, s, a);
@@ -896,6 +911,7 @@ hipError_t launch_gemm_nt_i8(const GemmArgs& a_in, hipStream_t s)
         a.adv_w = BK - a.adv_b * hw - a.adv_h * a.Wo;
     }
     if (a.splits < 1 || (a.splits > 1 && (a.gsum || a.conv == 1))) return hipErrorInvalidValue;
+    if (a.res.y && (a.conv != 1 || a.gsum || a.nc != 1 || a.upd_w || (a.J & 3) != 0 || a.res.M != a.I || a.res.N != a.J)) return hipErrorInvalidValue;
     if (a.upd_w) {
         const int tiles = gemm_update_blocks(a.I, a.J, a.R);
         if (tiles == 0 || a.nb != 2 || a.nc != 1 || a.conv || a.gsum || a.splits != 1 || (((uintptr_t)a.upd_w) & 15) != 0)
