@@ -95,7 +95,8 @@ __device__ __forceinline__ int floor_to_int(float x)   // |x| < 2^31
 __device__ __forceinline__ uint32_t sr_top(float scaled, float lo, float hi, uint32_t head)
 {
     const float c = __builtin_amdgcn_fmed3f(scaled, lo, hi);
-    return __builtin_amdgcn_bitop3_b32(head >> 8, head >> 24, 0xFF000000u, 0x96) + (uint32_t)floor_to_int(c);   // (0x96: three-way xor)
+    // (ones shifted in from above: one operation for the shift and the 0xFF000000; the other shift is an operand's byte select)
+    return (__builtin_amdgcn_alignbit(0xFFFFFFFFu, head, 8) ^ (head >> 24)) + (uint32_t)floor_to_int(c);
 }
 // -t * 2^24 for t of either sign; one = 1 where t < 0, else 0
 __device__ __forceinline__ float sr_scale(float t, float one) { return __builtin_fmaf(t + one, -0x1p24f, one * 0x1p24f); }
