@@ -1539,6 +1539,14 @@ static ff_status train_step_impl(const ff_net_desc* net, const ff_net_state* sta
         // have so few rows that most of a wavefront's slices hold several (one atomic per row then: 512 channels on 4x4 maps 87 us
         // against 39 + 10).
         const bool in_contraction = ra.y && d.implicit && !d.pointwise && d.rps >= 64;
+        // The projection's accumulators are read by whichever launch forms the block output: until then its stream runs beside this one.
+        // (At 38 and 237 images with maps of 49 and 16 pixels last, a step takes as long with the wait ahead of every second
+        // convolution: 820 and 1780 us.)
+        auto join_projection = [&] {
+            if (d.skip != FF_SKIP_PROJECTION || !proj_pending) return true;
+            proj_pending = false;
+            return hipStreamWaitEvent(s_main, pool->join[0], 0) == hipSuccess;
+        };
         ff_status fs = [&]() -> ff_status {
             if (d.role == FF_ROLE_PROJECTION && !goodness_last) {
                 // no activity of its own: zero coefficients (nothing enters the look-ahead sums), zero loss / goodness rows
@@ -1549,10 +1557,7 @@ static ff_status train_step_impl(const ff_net_desc* net, const ff_net_state* sta
             }
             if (src == QSRC_HANDOFF && w.rework[d.src]) HIPCHK_T(FF_K_QUANT_ACT, rework(ROWS_HANDOFF, d.src, a, s));
             else HIPCHK_T(FF_K_QUANT_ACT, launch_quantize(src, a, s));
-            if (d.skip == FF_SKIP_PROJECTION && proj_pending) {   // the projection's accumulators are read from here on
-                if (hipStreamWaitEvent(s_main, pool->join[0], 0) != hipSuccess) return FF_ERR_HIP;
-                proj_pending = false;
-            }
+            if (in_contraction && !join_projection()) return FF_ERR_HIP;
             return run_forward(d, L.relu ? 1 : 0, (const int8_t*)(base + w.off_aq[i]), (int64_t)w.st_aq[i], state->w_q[i],
                                w.rework[i] ? nullptr : (int32_t*)(base + w.off_acc[i]), (int64_t)(w.st_acc[i] / sizeof(int32_t)),
                                plain ? gsum + (int64_t)i * 2 * B : nullptr, vmax + (int64_t)i * 2 * B, B,
@@ -1566,7 +1571,10 @@ static ff_status train_step_impl(const ff_net_desc* net, const ff_net_state* sta
         if (fs != FF_OK) return fs;
         if (d.role == FF_ROLE_PROJECTION) continue;
         if (!plain) {
-            if (!in_contraction) HIPCHK_T(FF_K_RESIDUAL, launch_residual_act(ra, s));
+            if (!in_contraction) {
+                if (!join_projection()) return FF_ERR_HIP;
+                HIPCHK_T(FF_K_RESIDUAL, launch_residual_act(ra, s));
+            }
             if (fx_reader[i] >= 0) continue;
             GoodnessFxArgs fa;
             memset(&fa, 0, sizeof(fa));
