@@ -509,7 +509,8 @@ __device__ __forceinline__ void quantize_tile(const QuantArgs& a, uint32_t* tile
                     sum[u][j] += __builtin_trunc(r * r * 0x1p40);
                 }
             }
-        const uint32_t s0 = (uint32_t)r0 / rps, s1 = min((uint32_t)r0 + QT_ROWS - 1u, last) / rps;
+        // (a tile may begin beyond the tensor, where the pitch of q_t does: nothing but zeros)
+        const uint32_t s0 = min((uint32_t)r0, last) / rps, s1 = min((uint32_t)r0 + QT_ROWS - 1u, last) / rps;
         if (s0 == s1) {   // (uniform) one atomic per tile
             double w = 0.0;
 #pragma unroll
@@ -519,7 +520,13 @@ __device__ __forceinline__ void quantize_tile(const QuantArgs& a, uint32_t* tile
             if ((t & 63) == 0) reds[t >> 6] = part;
             __syncthreads();
             if (t == 0) atomicAdd(gs + s0, (reds[0] + reds[1]) + (reds[2] + reds[3]));
-        } else {   // the CB lanes of a row, or of four rows of one sample, meet; one atomic for each
+        } else {
+            // The CB lanes of a row, or of four rows of one sample, meet and add to their sample's word in LDS; one global atomic per
+            // sample of the tile.  Per row they meet in a few cache lines at 2 to 4 ns each: 256 channels on 7x7 maps of 38 images
+            // (two passes) 35.8 us, 5.6 this way.
+            __shared__ unsigned long long part[QT_ROWS];
+            for (int i = t; i < QT_ROWS; i += QT_THREADS) part[i] = 0;
+            __syncthreads();
             const bool fours = (rps & 3u) == 0;
 #pragma unroll
             for (int u = 0; u < U; ++u) {
@@ -531,9 +538,12 @@ __device__ __forceinline__ void quantize_tile(const QuantArgs& a, uint32_t* tile
                         const unsigned lo = (unsigned)__shfl_xor((int)(unsigned)v, d), hi = (unsigned)__shfl_xor((int)(unsigned)(v >> 32), d);
                         v += ((unsigned long long)hi << 32) | lo;
                     }
-                    if (cb == 0 && v) atomicAdd(gs + min((uint32_t)rowb + QT_RH * u + j, last) / rps, v);
+                    if (cb == 0 && v) atomicAdd(part + (min((uint32_t)rowb + QT_RH * u + j, last) / rps - s0), v);
                 }
             }
+            __syncthreads();
+            for (uint32_t i = t; i <= s1 - s0; i += QT_THREADS)
+                if (part[i]) atomicAdd(gs + s0 + i, part[i]);
         }
     }
     if (q_t) {
