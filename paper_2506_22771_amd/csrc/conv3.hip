@@ -284,7 +284,7 @@ hipError_t launch_conv3(const GemmArgs& a, hipStream_t s)
     Conv3Plan p;
     if (a.I <= 0 || a.J <= 0) return hipSuccess;
     if (!conv3_plan(a, &p) || (!a.C && !a.res.y) || (a.gsum && (a.res.y || !a.vmax))) return hipErrorInvalidValue;
-    if (a.res.y && (a.res.M != a.I || a.res.N != a.J)) return hipErrorInvalidValue;
+    if (a.res.y && (a.res.M != a.I || a.res.N != a.J || a.res.rows_per_sample < RESIDUAL_MIN_ROWS)) return hipErrorInvalidValue;
     if (p.kt == 1) return p.tj == 2 ? launch_conv3_cfg<1, 2>(a, p.c, s) : launch_conv3_cfg<1, 1>(a, p.c, s);
     return p.tj == 2 ? launch_conv3_cfg<2, 2>(a, p.c, s) : launch_conv3_cfg<2, 1>(a, p.c, s);
 }

@@ -911,7 +911,9 @@ hipError_t launch_gemm_nt_i8(const GemmArgs& a_in, hipStream_t s)
         a.adv_w = BK - a.adv_b * hw - a.adv_h * a.Wo;
     }
     if (a.splits < 1 || (a.splits > 1 && (a.gsum || a.conv == 1))) return hipErrorInvalidValue;
-    if (a.res.y && (a.conv != 1 || a.gsum || a.nc != 1 || a.upd_w || (a.J & 3) != 0 || a.res.M != a.I || a.res.N != a.J)) return hipErrorInvalidValue;
+    if (a.res.y && (a.conv != 1 || a.gsum || a.nc != 1 || a.upd_w || (a.J & 3) != 0 || a.res.M != a.I || a.res.N != a.J ||
+                    a.res.rows_per_sample < RESIDUAL_MIN_ROWS))
+        return hipErrorInvalidValue;
     if (a.upd_w) {
         const int tiles = gemm_update_blocks(a.I, a.J, a.R);
         if (tiles == 0 || a.nb != 2 || a.nc != 1 || a.conv || a.gsum || a.splits != 1 || (((uintptr_t)a.upd_w) & 15) != 0)
