@@ -621,7 +621,7 @@ static ff_status run_forward(const Dims& d, int relu, const int8_t* aq, int64_t 
     g.gsum = gsum;
     g.vmax = vmax;
     g.st_g = st_g;
-    if (res) g.res = *res;
+    g.residual = res;
     if (explicit_patches(d)) HIPCHK_T(FF_K_IM2COL, launch_im2col(im2col_args(d, aq, st_aq, col, st_col, nb), s));
     if (!acc) {
         HIPCHK_T(FF_K_GEMM_FWD, launch_rework(ROWS_GOODNESS, g, QuantArgs{}, s));

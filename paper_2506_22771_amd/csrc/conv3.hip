@@ -45,10 +45,10 @@ template <int KT, int TJ> struct C3Shape {
 };
 
 // what becomes of the accumulators: stored, stored with the goodness sums, or the output of a residual block
-enum { C3_STORE, C3_STORE_GOODNESS, C3_RESIDUAL };
+enum Conv3Result { C3_STORE, C3_STORE_GOODNESS, C3_RESIDUAL };
 
 template <int WHAT, int KT, int TJ>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_conv3_i8(GemmArgs a, Conv3Geom c)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_conv3_i8(std::conditional_t<WHAT == C3_RESIDUAL, GemmResidualArgs, GemmArgs> a, Conv3Geom c)
 {
     using S = C3Shape<KT, TJ>;
     constexpr bool GOODNESS = WHAT == C3_STORE_GOODNESS, RESIDUAL = WHAT == C3_RESIDUAL;
@@ -160,7 +160,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
         int8_t* const slice = win + wave * S::ESLICE;
         int32_t* const C = a.C + z * a.st_c;
         ResidualScale rs = {};
-        if (RESIDUAL) rs = residual_scale(a.res, z);
+        if constexpr (RESIDUAL) rs = residual_scale(a.res, z);
 #pragma unroll
         for (int ti = 0; ti < 2; ++ti)
 #pragma unroll
@@ -236,7 +236,7 @@ static hipError_t launch_conv3_cfg(const GemmArgs& a, Conv3Geom c, hipStream_t s
     const int64_t slots = ((tiles + rounds - 1) / rounds + 7) / 8 * 8;
     c.per = (int)rounds;
     const dim3 grid((unsigned)(slots * c.ncb));
-    if (a.res.y) hipLaunchKernelGGL((k_conv3_i8<C3_RESIDUAL, KT, TJ>), grid, dim3(S::T), 0, s, a, c);
+    if (a.residual) hipLaunchKernelGGL((k_conv3_i8<C3_RESIDUAL, KT, TJ>), grid, dim3(S::T), 0, s, GemmResidualArgs{a, *a.residual}, c);
     else if (a.gsum) hipLaunchKernelGGL((k_conv3_i8<C3_STORE_GOODNESS, KT, TJ>), grid, dim3(S::T), 0, s, a, c);
     else hipLaunchKernelGGL((k_conv3_i8<C3_STORE, KT, TJ>), grid, dim3(S::T), 0, s, a, c);
     return hipGetLastError();
@@ -283,8 +283,8 @@ hipError_t launch_conv3(const GemmArgs& a, hipStream_t s)
 {
     Conv3Plan p;
     if (a.I <= 0 || a.J <= 0) return hipSuccess;
-    if (!conv3_plan(a, &p) || (!a.C && !a.res.y) || (a.gsum && (a.res.y || !a.vmax))) return hipErrorInvalidValue;
-    if (a.res.y && (a.res.M != a.I || a.res.N != a.J || a.res.rows_per_sample < RESIDUAL_MIN_ROWS)) return hipErrorInvalidValue;
+    if (!conv3_plan(a, &p) || (!a.C && !a.residual) || (a.gsum && (a.residual || !a.vmax))) return hipErrorInvalidValue;
+    if (a.residual && (a.residual->M != a.I || a.residual->N != a.J || a.residual->rows_per_sample < RESIDUAL_MIN_ROWS)) return hipErrorInvalidValue;
     if (p.kt == 1) return p.tj == 2 ? launch_conv3_cfg<1, 2>(a, p.c, s) : launch_conv3_cfg<1, 1>(a, p.c, s);
     return p.tj == 2 ? launch_conv3_cfg<2, 2>(a, p.c, s) : launch_conv3_cfg<2, 1>(a, p.c, s);
 }

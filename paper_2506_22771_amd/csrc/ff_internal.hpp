@@ -352,8 +352,12 @@ struct GemmArgs {
     // ticks it was alive to clk[0] and clk[1] (their ratio is the mean shader clock during the launch) and the
     // shader clocks of each tile by phase to clk[2..6] / clk[8..12]
     unsigned long long* clk;   // 16 counters, see ff_timing_clock_probe
-    // residual layer (res.y non-null; implicit convolutions, no split, no fused reductions): C is not written, the block output is
-    // formed from the accumulators
+    // residual layer, or null (implicit convolutions, no split, no fused reductions): C is not written, the block output is formed
+    // from the accumulators.  [host] The kernels that form one take a copy behind these arguments (GemmResidualArgs); with it in every
+    // launch's arguments the single operations of a forward pass, 128 -> 256 channels on 256 images of 16x16, took 74.5 us, 73.7 without
+    const ResidualArgs* residual;
+};
+struct GemmResidualArgs : GemmArgs {
     ResidualArgs res;
 };
 hipError_t launch_gemm_nt_i8(const GemmArgs& a, hipStream_t s);

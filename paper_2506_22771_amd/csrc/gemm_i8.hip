@@ -88,7 +88,7 @@ template <int BKT> __device__ __forceinline__ int swz(int row, int kc) { return 
 // workgroup stores the partial sums of its share of the reduction steps at C + blockIdx.y * st_split; 3: weight gradient
 // and update -- a workgroup contracts its tile for the positive pass, keeps fp32(acc) * scale in registers, contracts the same
 // tile for the negative pass and applies both to its tile of the weights (the update's own sequence of roundings).
-// MODE 4: the output of a residual block (GemmArgs::res) instead of the accumulators.
+// MODE 4: the output of a residual block (GemmArgs::residual) instead of the accumulators.
 // CONV 0: both operands are matrices.  1: P is an NHWC tensor, row i of the contraction is an output pixel and
 // the reduction runs over (tap, channel) (forward pass of a convolution as an implicit GEMM).
 // CONV 2: Q is the NHWC tensor itself, column j of the contraction's output is (tap, channel) and the reduction runs over
@@ -103,7 +103,7 @@ template <int BKT> __device__ __forceinline__ int swz(int row, int kc) { return 
 // 64 -> 128 channels at 32x32, 256 images, both sets: contraction 115 -> 104 us and 46 us of plane writing gone; maps whose
 // size is no multiple of 16 (byte gathers before) several times faster: 120 -> 160 at 21x21, 27 images, 196 -> 106 us in all.
 template <int BM, int BN, int WM, int WN, int MODE, int CONV, int BKT = 128, int NS = 2>
-__global__ __launch_bounds__(WM* WN * 64) __attribute__((amdgpu_waves_per_eu(BKT == 64 ? 2 : 1))) void k_gemm_nt_i8(GemmArgs a)
+__global__ __launch_bounds__(WM* WN * 64) __attribute__((amdgpu_waves_per_eu(BKT == 64 ? 2 : 1))) void k_gemm_nt_i8(std::conditional_t<MODE == 4, GemmResidualArgs, GemmArgs> a)
 {
     constexpr int BK = BKT;             // reduction bytes per LDS stage
     constexpr int CPB = BK / 16;        // 16-byte chunks per staged row
@@ -449,7 +449,7 @@ __global__ __launch_bounds__(WM* WN * 64) __attribute__((amdgpu_waves_per_eu(BKT
     const bool staged = RES || ((interior || (a.J & 3) == 0) && !compact);
     const bool fast_sq = a.relu && a.rshift == 0;
     ResidualScale res_scale = {};
-    if (RES) res_scale = residual_scale(a.res, z);
+    if constexpr (RES) res_scale = residual_scale(a.res, z);
     int8_t* const ebase = lds + EOFF + wave * ESLICE;
     if (wait_copies && !staged) {   // (copies and stores complete in issue order: wait before the first store)
         wait_vmcnt<0>();
@@ -675,7 +675,7 @@ static hipError_t launch_paired(const GemmArgs& a, hipStream_t s)
     const int64_t resident = (int64_t)2 * num_cus();
     const dim3 grid((unsigned)min(ntiles, resident)), block(WM * WN * 64);
     if (a.conv == 1) {
-        if (a.res.y) hipLaunchKernelGGL((k_gemm_nt_i8<BM, BN, WM, WN, 4, 1, BKT, NS>), grid, block, 0, s, a);
+        if (a.residual) hipLaunchKernelGGL((k_gemm_nt_i8<BM, BN, WM, WN, 4, 1, BKT, NS>), grid, block, 0, s, GemmResidualArgs{a, *a.residual});
         else if (a.gsum) hipLaunchKernelGGL((k_gemm_nt_i8<BM, BN, WM, WN, 1, 1, BKT, NS>), grid, block, 0, s, a);
         else hipLaunchKernelGGL((k_gemm_nt_i8<BM, BN, WM, WN, 0, 1, BKT, NS>), grid, block, 0, s, a);
     } else {
@@ -712,7 +712,7 @@ static hipError_t launch_cfg(const GemmArgs& a, hipStream_t s)
         if (a.conv == 1) return hipErrorInvalidValue;
         hipLaunchKernelGGL((k_gemm_nt_i8<BM, BN, WM, WN, 2, 0>), grid, block, 0, s, a);
     } else if constexpr (WHOLE) {
-        if (a.res.y) hipLaunchKernelGGL((k_gemm_nt_i8<BM, BN, WM, WN, 4, 1>), grid, block, 0, s, a);
+        if (a.residual) hipLaunchKernelGGL((k_gemm_nt_i8<BM, BN, WM, WN, 4, 1>), grid, block, 0, s, GemmResidualArgs{a, *a.residual});
         else if (a.conv == 1 && mode == 1) hipLaunchKernelGGL((k_gemm_nt_i8<BM, BN, WM, WN, 1, 1>), grid, block, 0, s, a);
         else if (a.conv == 1) hipLaunchKernelGGL((k_gemm_nt_i8<BM, BN, WM, WN, 0, 1>), grid, block, 0, s, a);
         else if (mode == 1) hipLaunchKernelGGL((k_gemm_nt_i8<BM, BN, WM, WN, 1, 0>), grid, block, 0, s, a);
@@ -911,8 +911,8 @@ hipError_t launch_gemm_nt_i8(const GemmArgs& a_in, hipStream_t s)
         a.adv_w = BK - a.adv_b * hw - a.adv_h * a.Wo;
     }
     if (a.splits < 1 || (a.splits > 1 && (a.gsum || a.conv == 1))) return hipErrorInvalidValue;
-    if (a.res.y && (a.conv != 1 || a.gsum || a.nc != 1 || a.upd_w || (a.J & 3) != 0 || a.res.M != a.I || a.res.N != a.J ||
-                    a.res.rows_per_sample < RESIDUAL_MIN_ROWS))
+    if (a.residual && (a.conv != 1 || a.gsum || a.nc != 1 || a.upd_w || (a.J & 3) != 0 || a.residual->M != a.I || a.residual->N != a.J ||
+                       a.residual->rows_per_sample < RESIDUAL_MIN_ROWS))
         return hipErrorInvalidValue;
     if (a.upd_w) {
         const int tiles = gemm_update_blocks(a.I, a.J, a.R);
