@@ -233,8 +233,8 @@ __device__ __forceinline__ uint32_t max_of_candidates(const uint32_t* __restrict
 // What bounds it: for tensors of tens of megabytes HBM, below that the vector ALUs and, for a few tiles per compute unit, the
 // chain of a wavefront.  Hence: whole tiles take a body without bounds checks, row pointers advance by
 // additions, and the sample of a row comes from one 32-bit division per four rows (local gradient of 2 x 8192 x 4096:
-// 71 -> 64 us, 5.2 TB/s).  The loads of the tile go out first, those of the rows' factors and of the range behind them, so
-// that they are all in flight together; the rounding is done in fixed point where that is exact (device_math.hpp).  Local gradient of
+// 71 -> 64 us, 5.2 TB/s).  The loads of the tile go out first, those of the rows' factors and (RANGE_FIRST apart) of the range behind
+// them, so that they are all in flight together; the rounding is done in fixed point where that is exact (device_math.hpp).  Local gradient of
 // 2 x 1024 x 2000 10.6 -> 8.5 us, normalised hand-off 14.5 -> 12.4, requantised weights 7.1 -> 6.3; gradients of a
 // MobileNet-shaped step 90 -> 76 us on average.
 template <int SRC, bool STOCH, int FORM, int CB, int U, bool WHOLE>
@@ -248,6 +248,17 @@ __device__ __forceinline__ void quantize_tile(const QuantArgs& a, uint32_t* tile
     const float* __restrict__ per_sample = a.per_sample ? a.per_sample + z * a.st_per_sample : nullptr;
     int8_t* __restrict__ q = a.q ? a.q + z * a.st_q : nullptr;
     int8_t* __restrict__ q_t = a.q_t ? a.q_t + z * a.st_qt : nullptr;
+
+    // ---- range.  A vanishing one (absmax < 2^-100, all-zero tensor included) quantises to zero codes with scale 1
+    uint32_t amax_word;
+    auto range = [&] {
+        amax_word = a.amax_bits ? a.amax_bits[z * a.st_amax] : 0u;
+        if (a.amax_n > 1) amax_word = max_of_candidates(a.amax_bits + z * a.st_amax, a.amax_n);   // (uniform) one per workgroup of the producer
+    };
+    // Stochastic rounding of an fp32 tensor forms it before the tile's loads go out, every other form behind them: layer inputs
+    // of 256 x 16 x 16 x 128 10.0 us behind and 9.4 first, of 154 x 28 x 28 x 120 21.3 and 19.6.
+    constexpr bool RANGE_FIRST = SRC == QSRC_F32 && STOCH;
+    if constexpr (RANGE_FIRST) range();
 
     const int64_t r0 = (int64_t)by * QT_ROWS;
     const int64_t c0 = (int64_t)bx * QT_COLS;
@@ -325,9 +336,7 @@ __device__ __forceinline__ void quantize_tile(const QuantArgs& a, uint32_t* tile
         }
     }
 
-    // ---- range.  A vanishing one (absmax < 2^-100, all-zero tensor included) quantises to zero codes with scale 1
-    uint32_t amax_word = a.amax_bits ? a.amax_bits[z * a.st_amax] : 0u;
-    if (a.amax_n > 1) amax_word = max_of_candidates(a.amax_bits + z * a.st_amax, a.amax_n);   // (uniform) one per workgroup of the producer
+    if constexpr (!RANGE_FIRST) range();
     float s_y = 1.0f;
     if (!F32SRC) s_y = a.s_a[z * a.st_s_a] * a.s_w[z * a.st_s_w];
     const double s_yd = (double)s_y, pow2r = (double)(1ull << a.rshift);
@@ -401,7 +410,9 @@ __device__ __forceinline__ void quantize_tile(const QuantArgs& a, uint32_t* tile
 
     // fixed-point rounding where every t is finite: a finite range, of activities that cannot have overflowed, and a sign that is known
     // per row (or taken from t)
-    const bool fixed = STOCH && live && amax < __builtin_inff() && (PLAIN || a.relu) && (F32SRC || s_y < 0x1p80f);
+    // (half-size tiles of an fp32 tensor, which has no sign known beforehand, in floating point: 1000 x 784 4.4 us, 4.7 with the fixed form)
+    constexpr bool MAY_FIX = STOCH && !(SRC == QSRC_F32 && U == 1);
+    const bool fixed = MAY_FIX && live && amax < __builtin_inff() && (PLAIN || a.relu) && (F32SRC || s_y < 0x1p80f);
 
     // ---- quantise
     const uint32_t idx0 = (uint32_t)rowb * (uint32_t)a.cols + (uint32_t)col;   // element index of (row rowb, col)
@@ -484,7 +495,7 @@ __device__ __forceinline__ void quantize_tile(const QuantArgs& a, uint32_t* tile
         }
     }
     };
-    if constexpr (STOCH) {
+    if constexpr (MAY_FIX) {
         if (fixed) codes(std::true_type{});   // (uniform)
         else codes(std::false_type{});
     } else {
