@@ -134,14 +134,14 @@ typedef struct {
 } ff_net_desc;
 
 /* How ff_train_step issues its work.
- * FF_LAUNCH_KERNELS: one kernel per operation (quantise, contraction, update, ...), about six launches per layer and two
- *   for all of them (range of the input; goodness, loss and look-ahead).
+ * FF_LAUNCH_KERNELS: one kernel per operation (quantise, contraction, block output, update, ...) with every tensor between
+ *   them in memory, about six launches per layer and two for all of them (range of the input; goodness, loss and look-ahead).
  * FF_LAUNCH_FUSED: the whole step as ONE persistent kernel whose
  *   workgroups meet at device-wide barriers between its phases (a per-tensor absmax or a per-sample goodness is complete
  *   there, or a tensor of codes).  For the launch-bound regime of small networks and batches, the one nearest the paper's
  *   own batch of 32 (Section V-A).  Plain dense stacks (no convolutions, residual wiring or FF_LOOKAHEAD_CHAIN) of at
  *   most 8 layers and 1024 samples per pass; FF_ERR_UNSUPPORTED otherwise.  Same results, bit for bit.
- * FF_LAUNCH_LANES: one kernel per operation, but the update chains of different layers (local gradient -> weight
+ * FF_LAUNCH_LANES: kernels per operation, some of them several in one (as FF_LAUNCH_AUTO), and the update chains of different layers (local gradient -> weight
  *   gradient -> update -> requantise; independent of each other, the learning being layer-local) go to up to three
  *   streams at once: the caller's and two that the library creates once per device (default priority) and keeps.  The
  *   chains are forked off the caller's stream after the look-ahead kernel and joined back before the call returns, so
@@ -153,7 +153,9 @@ typedef struct {
  *   the same time (steps issued one after the other, on any streams, are fine).
  * FF_LAUNCH_AUTO: FF_LAUNCH_FUSED when the stack qualifies and one pass through it is at most 2^27 multiply-adds
  *   (784 -> 500 -> 500 at 64 samples is 41 M); else lanes when the layers are small -- three below 2^33 multiply-adds
- *   per layer and pass on average, two below 2^36 -- else FF_LAUNCH_KERNELS.
+ *   per layer and pass on average, two below 2^36 -- else the caller's stream alone.  Beside lanes, here too operations of
+ *   convolution stacks share a kernel where that is faster: accumulators worked out again instead of stored, the output of a
+ *   residual block formed in its contraction and its goodness sums in the next layer's quantiser.  Same results, bit for bit.
  * ff_workspace_bytes depends on the mode (the fused step keeps every layer's int8 local gradient; lanes multiply the
  * chain scratch). */
 enum { FF_LAUNCH_AUTO = 0, FF_LAUNCH_KERNELS = 1, FF_LAUNCH_FUSED = 2, FF_LAUNCH_LANES = 3 };

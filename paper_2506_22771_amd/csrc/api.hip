@@ -1401,7 +1401,7 @@ static ff_status train_step_impl(const ff_net_desc* net, const ff_net_state* sta
     int fx_reader[MAX_LAYERS];
     for (int i = 0; i < k; ++i) {
         fx_reader[i] = -1;
-        if (w.d[i].skip == FF_SKIP_NONE || !goodness_last || B > 2048) continue;
+        if (w.d[i].skip == FF_SKIP_NONE || !goodness_last || B > 2048 || net->launch_mode == FF_LAUNCH_KERNELS) continue;
         for (int j = k - 1; j > i; --j)
             if (w.d[j].src == i && w.d[j].role == FF_ROLE_LAYER) fx_reader[i] = j;
     }
@@ -1538,7 +1538,7 @@ static ff_status train_step_impl(const ff_net_desc* net, const ff_net_state* sta
         // Implicit contractions form the block output from the accumulators; behind others a launch of its own does, and where samples
         // have so few rows that most of a wavefront's slices hold several (one atomic per row then: 512 channels on 4x4 maps 87 us
         // against 39 + 10).
-        const bool in_contraction = ra.y && d.implicit && !d.pointwise && d.rps >= 64;
+        const bool in_contraction = ra.y && d.implicit && !d.pointwise && d.rps >= 64 && net->launch_mode != FF_LAUNCH_KERNELS;
         // The projection's accumulators are read by whichever launch forms the block output: until then its stream runs beside this one.
         // (At 38 and 237 images with maps of 49 and 16 pixels last, a step takes as long with the wait ahead of every second
         // convolution: 820 and 1780 us.)
