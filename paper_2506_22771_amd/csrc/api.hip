@@ -266,12 +266,19 @@ static DwArgs dw_forward_args(const Dims& d, int relu, const int8_t* aq, int64_t
     return p;
 }
 
-// Layers whose accumulators are worked out again by each pass that needs them instead of being stored: depthwise ones, and convolutions whose
-// patch matrix exists as rows of up to ROWS_MAX_R bytes (1x1 stride-1 ones over their input, first layers over their patches), short
-// beside the outputs that one row gives.  Per output the stored form moves 12 bytes (written, read by the hand-off and by the
-// local gradient), this one the row twice more: up to four bytes of row per output that is a third less and worth it (a
-// MobileNet-shaped step, whose 96 -> 24 layer lies on that line, 1681 -> 1635 us against a line at two bytes).  Depthwise layers read a
-// byte per output and pass: the same step 1635 -> 1450.
+// Layers whose accumulators are worked out again by each pass that needs them instead of being stored: large depthwise ones
+// (dwconv_rework_pays), and convolutions whose patch matrix exists as rows of up to ROWS_MAX_R bytes (1x1 stride-1 ones over their input,
+// first layers over their patches).  Per output the stored form moves 12 bytes (written, read by the hand-off and by the
+// local gradient), this one the row twice more, whose bytes are shared by the outputs it gives.  Up to four bytes of row per output
+// are taken (a MobileNet-shaped step, whose 96 -> 24 layer lies on that line, 1681 -> 1635 us against a line at two).  Steps of three 1x1
+// layers, the one in the middle stored and reworked, 256 images of 32x32: 32 -> 32 channels 193 and 153 us, 64 -> 16 213 and 180, 96 -> 24 236 and
+// 216, 128 -> 32 260 and 246 (beyond the line: 96 -> 12 238 and 210, 128 -> 16 258 and 238).
+// Rows of more than 96 bytes go through 32 KB of operands per 32 columns in every pass: into more than 64 columns they pay only once
+// the stored accumulators leave the caches, at 3 x 2^23 outputs a pass: 128 -> 256 channels, 256 images of 32x32 (67 M) 676 and 598, 128 -> 512, 256 of
+// 16x16 (34 M) 311 and 293, 128 -> 384 (25 M) 263 and 250; below, 128 -> 384, 256 of 14x14 (19 M) 228 and 238, 128 -> 256, 64 of 28x28 (13 M) 208
+// and 226, 128 -> 512, 128 of 14x14 (13 M) 179 and 204, 128 -> 128, 256 of 14x14 (6.4 M) 153 and 161.  96 -> 384, 256 of 14x14 (19 M) 221 and 205.
+// (512 columns: rows.hip stores a row of codes in whole items of 32 columns, and longer rows have a wider pitch; depthwise layers beyond were
+// not measured.)
 static bool rework_accumulators(const ff_net_desc* net, const WsLayout& w, int i)
 {
     const Dims& d = w.d[i];
@@ -279,6 +286,8 @@ static bool rework_accumulators(const ff_net_desc* net, const WsLayout& w, int i
     if (net->launch_mode == FF_LAUNCH_KERNELS) return false;   // one kernel per operation, every tensor in memory
     if (d.kind == FF_DENSE || d.role != FF_ROLE_LAYER || d.skip != FF_SKIP_NONE || L.l2norm_out || (d.N & 3) != 0 || d.N > 512) return false;
     if (d.kind == FF_CONV2D && (!(d.pointwise || wgrad_from_patches(d)) || d.K > ROWS_MAX_R || pitch8(d.K) > 4 * d.N)) return false;
+    if (d.kind == FF_CONV2D && d.K > 96 && d.N > 64 && d.M * d.N < (int64_t(3) << 23)) return false;
+    if (d.kind == FF_DWCONV2D && !dwconv_rework_pays(d.g, d.B)) return false;
     for (int j = i + 1; j < w.k; ++j)   // (a dense layer also takes its input transposed)
         if (w.d[j].src == i && w.d[j].kind == FF_DENSE) return false;
     return true;
@@ -1010,8 +1019,9 @@ ff_status ff_layer_backward_local(const ff_layer_desc* layer, const int32_t* acc
     QuantArgs a;
     memset(&a, 0, sizeof(a));
     // Range of the gradient: by the quantiser's workgroups themselves, or by a launch before it for batches of which each would read a
-    // good part again (as for the hand-off).  Backward of 2048 x 2000 x 2000 70.1 -> 68.4 us, of 64 -> 128 channels on 256 images of
-    // 32x32 167 -> 160.
+    // good part again (as for the hand-off).  Backward with the launch and without: 2000 -> 2000 features, 2048 samples 70.0 and 68.2
+    // us, 3072 82.7 and 83.3, 8192 163 and 171; 64 -> 128 channels on 256 images of 32x32 167 and 160.  (Narrow layers gain beyond the line
+    // too: 500 -> 500, 4096 samples 79.6 and 77.2.)
     if (d.B <= 2048) {
         a.vmax = vmax;
         a.B = (int32_t)d.B;

@@ -337,11 +337,10 @@ hipError_t launch_dwconv_forward(const DwArgs& p, hipStream_t s)
 // Depthwise layers whose accumulators are not stored: nine taps are worked out again by each pass that needs them (goodness sums,
 // codes handed on, codes of the local gradient, all row-major), where the stored form writes four bytes per output and reads them
 // twice.  Threads are numbered through (piece, channel quad), so that every lane has channels whatever their number; blockIdx.y =
-// sample, blockIdx.z = pass.  A piece is a strip of four columns x DW_STRIP rows (stride 1, rows of whole 4-pixel groups: the
-// input rows slide through a window of three, each loaded and transposed once), or DW_PIX pixels in a row.  Bound by integer and
-// quantiser arithmetic.  144 channels, two passes of 256 images of 32x32: forward with stores, hand-off and local gradient 122 + 81 +
-// 103 us, goodness, hand-off and local gradient here 32 + 64 + 70 (beside other chains up to 119); with a stride of two 46 + 25 + 31
-// and 28 + 34 + 40.
+// sample, blockIdx.z = pass.  A piece is a strip of four columns x DW_STRIP rows: the input rows slide through a window of three,
+// each loaded and transposed once.  Bound by integer and quantiser arithmetic.  144 channels, two passes of 256 images of 32x32:
+// forward with stores, hand-off and local gradient 122 + 81 + 103 us, goodness, hand-off and local gradient here 32 + 64 + 70 (beside
+// other chains up to 119).
 constexpr int DW_STRIP = 8;
 
 // input row hi of columns wi0 .. wi0 + 5, four channels: word [e][j] = bytes of channel e from column j on
@@ -369,7 +368,7 @@ __device__ __forceinline__ void dw_row_words(const ConvGeom& g, const int8_t* __
     }
 }
 
-template <int WHAT, bool STRIPS>
+template <int WHAT>
 __global__ __launch_bounds__(256) void k_dwconv_rework(DwArgs p, QuantArgs qa, int nq)
 {
     constexpr bool GRAD = WHAT == ROWS_GRAD;
@@ -383,7 +382,7 @@ __global__ __launch_bounds__(256) void k_dwconv_rework(DwArgs p, QuantArgs qa, i
         if (GRAD) rowf = 2.0f * qa.per_sample[z * qa.st_per_sample + b];
     }
     const int hw = g.Ho * g.Wo, wgroups = g.Wo >> 2;
-    const int pieces = STRIPS ? wgroups * ((g.Ho + DW_STRIP - 1) / DW_STRIP) : (hw + DW_PIX - 1) / DW_PIX;
+    const int pieces = wgroups * ((g.Ho + DW_STRIP - 1) / DW_STRIP);
     const int at = (int)blockIdx.x * 256 + (int)threadIdx.x, piece = at / nq, c0 = 4 * (at - piece * nq);
     const int8_t* __restrict__ ab = p.a + z * p.st_a + (int64_t)b * g.H * g.W * g.cpitch;
     unsigned long long sq = 0;
@@ -408,58 +407,31 @@ __global__ __launch_bounds__(256) void k_dwconv_rework(DwArgs p, QuantArgs qa, i
             if (c0 + e < g.Cin) wr = *(const uint4*)(p.w_q + (int64_t)(c0 + e) * 16);
             w[e][0] = wr.x; w[e][1] = wr.y; w[e][2] = wr.z;
         }
-        if constexpr (STRIPS) {
-            uint32_t wk[4][3];   // three taps of a kernel row, fourth byte zero
+        uint32_t wk[4][3];   // three taps of a kernel row, fourth byte zero
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                wk[e][0] = w[e][0] & 0x00FFFFFFu;
-                wk[e][1] = __builtin_amdgcn_alignbyte(w[e][1], w[e][0], 3u) & 0x00FFFFFFu;
-                wk[e][2] = __builtin_amdgcn_alignbyte(w[e][2], w[e][1], 2u) & 0x00FFFFFFu;
-            }
-            const int hb = piece / wgroups, wo = 4 * (piece - hb * wgroups), h0 = hb * DW_STRIP;
-            uint32_t win[3][4][4];
-            dw_row_words(g, ab, h0 - 1, wo - 1, c0, win[0]);
-            dw_row_words(g, ab, h0, wo - 1, c0, win[1]);
+        for (int e = 0; e < 4; ++e) {
+            wk[e][0] = w[e][0] & 0x00FFFFFFu;
+            wk[e][1] = __builtin_amdgcn_alignbyte(w[e][1], w[e][0], 3u) & 0x00FFFFFFu;
+            wk[e][2] = __builtin_amdgcn_alignbyte(w[e][2], w[e][1], 2u) & 0x00FFFFFFu;
+        }
+        const int hb = piece / wgroups, wo = 4 * (piece - hb * wgroups), h0 = hb * DW_STRIP;
+        uint32_t win[3][4][4];
+        dw_row_words(g, ab, h0 - 1, wo - 1, c0, win[0]);
+        dw_row_words(g, ab, h0, wo - 1, c0, win[1]);
 #pragma unroll
-            for (int r = 0; r < DW_STRIP; ++r) {
-                if (h0 + r >= g.Ho) break;
-                dw_row_words(g, ab, h0 + r + 1, wo - 1, c0, win[(r + 2) % 3]);
+        for (int r = 0; r < DW_STRIP; ++r) {
+            if (h0 + r >= g.Ho) break;
+            dw_row_words(g, ab, h0 + r + 1, wo - 1, c0, win[(r + 2) % 3]);
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    int acc[4];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        acc[e] = 0;
-#pragma unroll
-                        for (int kh = 0; kh < 3; ++kh) acc[e] = __builtin_amdgcn_sdot4((int)win[(r + kh) % 3][e][j], (int)wk[e][kh], acc[e], false);
-                    }
-                    result((h0 + r) * g.Wo + wo + j, acc);
-                }
-            }
-        } else {
-#pragma unroll 2
-            for (int i = 0; i < DW_PIX; ++i) {
-                const int pix = piece * DW_PIX + i;
-                if (pix >= hw) break;
-                const int ho = pix / g.Wo, wo = pix - ho * g.Wo;
-                uint32_t x[9];   // tap words: byte e = channel c0 + e
-#pragma unroll
-                for (int t = 0; t < 9; ++t) {
-                    const int hi = ho * g.stride + t / 3 - g.pad, wi = wo * g.stride + t % 3 - g.pad;
-                    x[t] = (unsigned)hi < (unsigned)g.H && (unsigned)wi < (unsigned)g.W
-                               ? *(const uint32_t*)(ab + ((int64_t)hi * g.W + wi) * g.cpitch + c0) : 0u;
-                }
-                uint32_t lo[4], hi4[4];
-                dw_transpose4x4(x, lo);
-                dw_transpose4x4(x + 4, hi4);
+            for (int j = 0; j < 4; ++j) {
                 int acc[4];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    acc[e] = (int)(int8_t)(x[8] >> (8 * e)) * (int)(int8_t)(w[e][2] & 0xFFu);
-                    acc[e] = __builtin_amdgcn_sdot4((int)lo[e], (int)w[e][0], acc[e], false);
-                    acc[e] = __builtin_amdgcn_sdot4((int)hi4[e], (int)w[e][1], acc[e], false);
+                    acc[e] = 0;
+#pragma unroll
+                    for (int kh = 0; kh < 3; ++kh) acc[e] = __builtin_amdgcn_sdot4((int)win[(r + kh) % 3][e][j], (int)wk[e][kh], acc[e], false);
                 }
-                result(pix, acc);
+                result((h0 + r) * g.Wo + wo + j, acc);
             }
         }
     };
@@ -486,27 +458,40 @@ __global__ __launch_bounds__(256) void k_dwconv_rework(DwArgs p, QuantArgs qa, i
     }
 }
 
+// threads per sample of a launch over nq channel quads
+static int64_t dwconv_rework_threads(const ConvGeom& g, int64_t nq) { return (int64_t)(g.Wo >> 2) * ((g.Ho + DW_STRIP - 1) / DW_STRIP) * nq; }
+
 template <int WHAT>
 static hipError_t launch_dwconv_rework_t(const DwArgs& p, const QuantArgs& q, hipStream_t s)
 {
-    const ConvGeom& g = p.g;
-    const bool strips = g.stride == 1 && (g.Wo & 3) == 0;
     // (codes: quads up to the row pitch, whose pad bytes become zeros)
-    const int nq = (int)((WHAT == ROWS_GOODNESS ? g.Cin : q.ldq) + 3) >> 2;
-    const int64_t pieces = strips ? (int64_t)(g.Wo >> 2) * ((g.Ho + DW_STRIP - 1) / DW_STRIP) : ((int64_t)g.Ho * g.Wo + DW_PIX - 1) / DW_PIX;
-    const int64_t blocks = (pieces * nq + 255) / 256;
+    const int nq = (int)((WHAT == ROWS_GOODNESS ? p.g.Cin : q.ldq) + 3) >> 2;
+    const int64_t blocks = (dwconv_rework_threads(p.g, nq) + 255) / 256;
     if (blocks > (int64_t(1) << 22)) return hipErrorInvalidValue;   // (thread numbers in 32 bits)
-    const dim3 grid((unsigned)blocks, (unsigned)p.B, (unsigned)p.nb);
-    if (strips) hipLaunchKernelGGL((k_dwconv_rework<WHAT, true>), grid, dim3(256), 0, s, p, q, nq);
-    else hipLaunchKernelGGL((k_dwconv_rework<WHAT, false>), grid, dim3(256), 0, s, p, q, nq);
+    hipLaunchKernelGGL(k_dwconv_rework<WHAT>, dim3((unsigned)blocks, (unsigned)p.B, (unsigned)p.nb), dim3(256), 0, s, p, q, nq);
     return hipGetLastError();
+}
+
+// Stride one and rows of whole 4-pixel groups (strips), from 2^23 outputs a pass on, where the stored accumulators no longer stay
+// in the caches, and not where the last workgroup of a sample leaves more than a quarter of its threads idle.  Steps of 1x1, depthwise
+// and 1x1 layers, stored and reworked: 144 channels, 32x32, 64 images (9.4 M outputs) 212 and 201 us, 256 images 601 and 471; 64
+// channels, 128 images (8.4 M) 171.9 and 171.4; 240 channels, 16x16, 256 images (15.7 M) 244 and 219.  Above the line and slower: 64
+// channels, 28x28, 256 images (12.8 M) 213 and 218, 192, 16x16, 256 (12.6 M) 201 and 204.  Below it: 64 channels, 28x28, 128 images (6.4 M) 161
+// and 170, 64, 16x16, 256 (4.2 M) 127 and 143, 240, 16x16, 128 (7.9 M) 171 and 171.  Idle threads: 144 channels, 16x16, 256 images (9.4 M,
+// 288 threads a sample) 187 and 196.  Pixels one by one, each with its nine loads, are slower reworked: stride two, 192 channels, 32x32, 256 images 401
+// and 419, 384 785 and 813; widths of 14, 192 channels, 256 images 252 and 270, of 30 863 and 940.
+bool dwconv_rework_pays(const ConvGeom& g, int64_t B)
+{
+    if (g.stride != 1 || (g.Wo & 3) != 0 || B * g.Ho * g.Wo * g.Cin < (int64_t(1) << 23)) return false;
+    const int64_t threads = dwconv_rework_threads(g, (g.Cin + 3) >> 2);
+    return 4 * threads >= 3 * ((threads + 255) / 256 * 256);
 }
 
 hipError_t launch_dwconv_rework(int what, const DwArgs& p, const QuantArgs& q, hipStream_t s)
 {
     const ConvGeom& g = p.g;
     if (p.B <= 0) return hipSuccess;
-    if (g.ks != 3 || p.B > 65535 || (g.Cin & 3) != 0 || p.nb < 1 || p.nb > 2) return hipErrorInvalidValue;
+    if (g.ks != 3 || g.stride != 1 || (g.Wo & 3) != 0 || p.B > 65535 || (g.Cin & 3) != 0 || p.nb < 1 || p.nb > 2) return hipErrorInvalidValue;
     if (what == ROWS_GOODNESS) return p.gsum && p.vmax ? launch_dwconv_rework_t<ROWS_GOODNESS>(p, q, s) : hipErrorInvalidValue;
     if (q.round_mode != FF_ROUND_STOCHASTIC || q.l2norm || !q.q || q.q_t || q.ldq != g.cpitch || q.cols != g.Cin || q.rows != (int64_t)p.B * g.Ho * g.Wo)
         return hipErrorInvalidValue;

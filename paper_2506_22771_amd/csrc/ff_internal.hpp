@@ -485,6 +485,7 @@ int dwconv_wgrad_splits(const ConvGeom& g, int64_t chunk_b, int problems);
 hipError_t launch_dwconv_forward(const DwArgs& p, hipStream_t s);
 // a pass over a layer whose accumulators are not stored: `what` is a RowsResult, codes row-major either way
 hipError_t launch_dwconv_rework(int what, const DwArgs& p, const QuantArgs& q, hipStream_t s);
+bool dwconv_rework_pays(const ConvGeom& g, int64_t B);
 hipError_t launch_dwconv_wgrad(const DwArgs& p, hipStream_t s);
 
 }  // namespace ffi

@@ -51,3 +51,22 @@ def kernel_nodes(call):
             ok(hip.hipGraphNodeGetDependencies(C.c_void_p(node), deps, C.byref(m)))
         out.append((name(node), [name(d) for d in deps[:m.value]]))
     return [e for e in out if e[0]]
+
+
+def step_kernels(layers, B, mode="auto"):
+    """kernel_nodes of one ff_train_step of a stack, over random weights and inputs."""
+    from paper_2506_22771_amd import schedule
+    g = torch.Generator(device="cuda").manual_seed(3)
+    w = [torch.rand((l.N, l.K), generator=g, device="cuda") * 0.4 - 0.2 for l in layers]
+    x = [torch.randn((B, layers[0].in_elems_per_sample), generator=g, device="cuda") for _ in range(2)]
+    st = schedule.TrainState.from_weights(layers, B, w)
+    net = ff.Net(layers, B, st.w_master, st.w_q, st.s_w, launch_mode=mode)
+    loss, good = torch.empty((len(layers), 2), device="cuda"), torch.empty((len(layers), 2, B), device="cuda")
+    ws = torch.empty(net.workspace_bytes(), dtype=torch.uint8, device="cuda")
+
+    def step():
+        ff.ff_train_step(net, x[0], x[1], 2.0, 0.05, 1e-4, 5, 0, loss, good, ws)
+
+    step()
+    torch.cuda.synchronize()
+    return kernel_nodes(step)

@@ -17,39 +17,30 @@ def ff():
     return m
 
 
-from graph_util import kernel_nodes  # noqa: E402
-
-
-def _kernels(ff, layers, B, mode):
-    from paper_2506_22771_amd import schedule
-    g = torch.Generator(device="cuda").manual_seed(3)
-    w = [torch.rand((l.N, l.K), generator=g, device="cuda") * 0.4 - 0.2 for l in layers]
-    x = [torch.randn((B, layers[0].in_elems_per_sample), generator=g, device="cuda") for _ in range(2)]
-    st = schedule.TrainState.from_weights(layers, B, w)
-    net = ff.Net(layers, B, st.w_master, st.w_q, st.s_w, launch_mode=mode)
-    loss, good = torch.empty((len(layers), 2), device="cuda"), torch.empty((len(layers), 2, B), device="cuda")
-    ws = torch.empty(net.workspace_bytes(), dtype=torch.uint8, device="cuda")
-
-    def step():
-        ff.ff_train_step(net, x[0], x[1], 2.0, 0.05, 1e-4, 5, 0, loss, good, ws)
-
-    step()
-    torch.cuda.synchronize()
-    return [name for name, _ in kernel_nodes(step)]
+from graph_util import step_kernels  # noqa: E402
 
 
 @pytest.mark.parametrize("mode,launches", [("kernels", 3), ("lanes", 0), ("auto", 0)])
 def test_block_outputs_have_launches_of_their_own(ff, mode, launches):
     """Three blocks, maps of 256 and 64 pixels."""
-    names = _kernels(ff, res_stack(16, [(16, 1, 2), (32, 2, 1)], 16, 16), 4, mode)
+    names = [n for n, _ in step_kernels(res_stack(16, [(16, 1, 2), (32, 2, 1)], 16, 16), 4, mode)]
     assert sum("k_residual_act" in n for n in names) == launches
     assert sum("k_goodness_fx" in n for n in names) == max(1, launches)   # (the last block's, in any mode)
 
 
-@pytest.mark.parametrize("mode,launches", [("kernels", 0), ("lanes", 3), ("auto", 3)])
-def test_accumulators_worked_out_again(ff, mode, launches):
-    """Stem, 1x1 expansion, depthwise layer and 1x1 projection: goodness sums, hand-off and local gradient each."""
-    names = _kernels(ff, bottleneck_stack(16, [(2, 24, 1)], 8, 8), 4, mode)
-    assert sum("k_rows_i8" in n for n in names) == max(0, 3 * launches - 1)   # (the last layer hands nothing on)
-    assert sum("k_dwconv_rework" in n for n in names) == launches
-    assert sum("k_dwconv_forward" in n for n in names) == (0 if launches else 1)
+@pytest.mark.parametrize("mode", ["kernels", "lanes", "auto"])
+@pytest.mark.parametrize("B", [64, 256])   # 2^21 and 2^23 outputs of the depthwise layer
+def test_accumulators_worked_out_again(ff, mode, B):
+    """Stem, 1x1 expansion, depthwise layer and 1x1 projection: goodness sums, hand-off (not the last layer's) and local gradient."""
+    names = [n for n, _ in step_kernels(bottleneck_stack(16, [(2, 24, 1)], 32, 32), B, mode)]
+    depthwise = 3 if mode != "kernels" and B == 256 else 0
+    assert sum("k_rows_i8" in n for n in names) == (0 if mode == "kernels" else 8)
+    assert sum("k_dwconv_rework" in n for n in names) == depthwise
+    assert sum("k_dwconv_forward" in n for n in names) == (0 if depthwise else 1)
+
+
+@pytest.mark.parametrize("side,C,stride,reworked", [(32, 64, 1, True), (30, 96, 1, False), (32, 64, 2, False), (16, 144, 1, False)])
+def test_depthwise_layers_worked_out_again(ff, side, C, stride, reworked):
+    """Strips of whole groups of four pixels, and workgroups that are not half empty."""
+    names = [n for n, _ in step_kernels(bottleneck_stack(C, [(1, 16, stride)], side, side), 256, "lanes")]
+    assert any("k_dwconv_rework" in n for n in names) == reworked

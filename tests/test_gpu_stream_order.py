@@ -18,28 +18,13 @@ def ff():
     return m
 
 
-from graph_util import kernel_nodes  # noqa: E402
+from graph_util import step_kernels  # noqa: E402
 
 
 @pytest.mark.parametrize("side,reader", [(12, "k_residual_act"),   # 36 rows a sample: a launch of its own forms the block output
                                          (16, "k_gemm_nt_i8")])    # 64: the contraction does
 def test_projection_runs_beside_the_second_convolution(ff, side, reader):
-    from paper_2506_22771_amd import schedule
-    layers, B = res_stack(16, [(32, 2, 1)], side, side), 5
-    g = torch.Generator(device="cuda").manual_seed(3)
-    w = [torch.rand((l.N, l.K), generator=g, device="cuda") * 0.4 - 0.2 for l in layers]
-    x = [torch.randn((B, layers[0].in_elems_per_sample), generator=g, device="cuda") for _ in range(2)]
-    st = schedule.TrainState.from_weights(layers, B, w)
-    net = ff.Net(layers, B, st.w_master, st.w_q, st.s_w, launch_mode="lanes")
-    loss, good = torch.empty((len(layers), 2), device="cuda"), torch.empty((len(layers), 2, B), device="cuda")
-    ws = torch.empty(net.workspace_bytes(), dtype=torch.uint8, device="cuda")
-
-    def step():
-        ff.ff_train_step(net, x[0], x[1], 2.0, 0.05, 1e-4, 5, 0, loss, good, ws)
-
-    step()
-    torch.cuda.synchronize()
-    nodes = kernel_nodes(step)
+    nodes = step_kernels(res_stack(16, [(32, 2, 1)], side, side), 5, "lanes")
     # in the forward pass one launch waits for two others: the one that reads the projection's accumulators
     joined = [(name, deps) for name, deps in nodes if len(deps) > 1 and not any("k_goodness" in d for d in deps)]
     assert len(joined) == 1 and reader in joined[0][0], nodes
