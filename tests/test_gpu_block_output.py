@@ -41,3 +41,38 @@ def test_residual_step_with_resident_weights(ff):
     """Blocks large enough for the resident-weight contraction."""
     wl = Workload("res", res_stack(64, [(64, 1, 1)], 32, 32), 9, "normal", lam=0.05)
     _run_steps(ff, wl, 1, theta_layer=_matched_thetas(wl))
+
+
+from graph_util import step_kernels  # noqa: E402
+
+
+@pytest.mark.parametrize("H,W,B,stem,stages,blocks", [
+    (31, 29, 11, 20, [(20, 1, 1)], 1),        # one piece a pixel, narrow ragged columns; 899 rows: slices of two samples, a partial last tile
+    (15, 19, 30, 36, [(36, 1, 2)], 2),        # two pieces, wide columns of which 36 exist; 285 rows
+    (32, 30, 36, 16, [(32, 2, 1)], 1),        # a projection; 240 rows
+    (30, 26, 42, 24, [(56, 2, 1)], 1),        # a projection, two pieces; 195 rows, 64 tiles in all
+    (16, 9, 60, 12, [(12, 1, 1)], 1)])        # 144 rows: hardly more than half a tile
+def test_block_output_with_resident_weights(ff, H, W, B, stem, stages, blocks):
+    layers = res_stack(stem, stages, H, W)
+    names = [n for n, _ in step_kernels(layers, B)]
+    assert not any("k_residual_act" in n for n in names)
+    assert sum("k_conv3_i8ILi2E" in n or "k_conv3_i8<2" in n for n in names) == blocks   # (the form that makes the block output)
+    wl = Workload("res", layers, B, "normal", lam=0.05)
+    _run_steps(ff, wl, 1, theta_layer=_matched_thetas(wl))
+
+
+@pytest.mark.parametrize("H,W,B,head,reader", [
+    (7, 7, 38, 0, True),      # 49 rows: several samples in a tile, their sums meet in LDS row by row
+    (5, 6, 513, 20, True),    # a dense reader whose last row of tiles lies beyond the tensor, in the pitch of its transposed copy
+    (8, 8, 2048, 0, True),    # the largest batch whose next layer forms the sums,
+    (8, 8, 2049, 0, False),   # and beyond it
+    (2, 2, 12289, 0, False)])   # goodness layer by layer
+def test_goodness_sums_of_block_outputs(ff, H, W, B, head, reader):
+    layers = res_stack(8, [(8, 1, 1), (12, 1, 1)], H, W)
+    if head:
+        layers = res_stack(8, [(8, 1, 1)], H, W) + (Layer("dense", in_features=H * W * 8, out_features=head),)
+    names = [n for n, _ in step_kernels(layers, B, "lanes")]
+    blocks = 1 if head else 2
+    assert sum("k_goodness_fx" in n for n in names) == (blocks - 1 if reader else blocks)
+    wl = Workload("res", layers, B, "normal", lam=0.05)
+    _run_steps(ff, wl, 1, theta_layer=_matched_thetas(wl), launch_mode="lanes")

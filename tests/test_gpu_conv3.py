@@ -21,6 +21,7 @@ def ff():
 
 
 from gpu_util import dev, empty32, pad8, pad_nhwc, workspace  # noqa: E402
+from graph_util import kernel_nodes  # noqa: E402
 
 
 @pytest.mark.parametrize("B,H,W,Cin,Cout,relu", [
@@ -30,7 +31,7 @@ from gpu_util import dev, empty32, pad8, pad_nhwc, workspace  # noqa: E402
     (5, 33, 31, 40, 228, 1),      # three chunks a pixel of which the last is half pad channels
     (9, 16, 16, 20, 512, 1),      # two chunks, the last a quarter full; eight column blocks
     (16, 12, 11, 64, 512, 1),     # samples of 132 rows
-    (33, 16, 8, 8, 100, 1),       # 128 rows: two samples per tile; eight channels
+    (65, 16, 8, 8, 100, 1),       # 128 rows: two samples per tile; eight channels
     (70, 16, 16, 60, 36, 0)])     # one column block that is half empty
 def test_conv_forward_with_resident_weights(ff, B, H, W, Cin, Cout, relu):
     rng = np.random.default_rng(B * W + Cin)
@@ -45,7 +46,13 @@ def test_conv_forward_with_resident_weights(ff, B, H, W, Cin, Cout, relu):
     gsum = torch.full((B,), 7, dtype=torch.int64, device="cuda")
     vmax = torch.full((B,), 7, dtype=torch.int32, device="cuda")
     ws = workspace(ff.ff_layer_workspace_bytes(desc))
-    ff.ff_layer_forward(desc, dev(pad_nhwc(a_q)), dev(pad8(w_q.reshape(Cout, K))), d_acc, gsum, vmax, ws)
+    d_a, d_w = dev(pad_nhwc(a_q)), dev(pad8(w_q.reshape(Cout, K)))
+
+    def forward():
+        ff.ff_layer_forward(desc, d_a, d_w, d_acc, gsum, vmax, ws)
+
+    assert any("k_conv3_i8" in n for n, _ in kernel_nodes(forward))
+    forward()
     torch.cuda.synchronize()
     np.testing.assert_array_equal(d_acc.cpu().numpy()[:, :Cout], acc)
     np.testing.assert_array_equal(gsum.cpu().numpy().view(np.uint64), gd["g_int"])
