@@ -14,7 +14,7 @@ namespace ffi {
 struct CodeScale {
     float s_y, inv, floor_y;
     uint32_t key;
-    bool fixed, live;   // fixed-point rounding applies (see quantize_tile); the range does not vanish
+    bool fixed, live;   // fixed-point rounding applies: no NaN, infinite only where rectified away (see quantize_tile); the range does not vanish
     float amax;
 };
 

@@ -38,7 +38,7 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v)
 }
 
 // one random word per element: two multiply / xor-shift stages over (low index word ^ key).  sr_head leaves out the last
-// xor-shift; the 24 bits that decide a code are then sr_bits24 of what it returns.
+// xor-shift; the 24 bits that decide a code are then (head ^ head >> 16) >> 8 of what it returns (sr_top).
 __device__ __forceinline__ uint32_t sr_head(uint32_t v)
 {
     v ^= v >> 16;
@@ -47,7 +47,6 @@ __device__ __forceinline__ uint32_t sr_head(uint32_t v)
     v *= 0x846CA68Bu;
     return v;
 }
-__device__ __forceinline__ uint32_t sr_bits24(uint32_t head) { return (head >> 8) ^ (head >> 24); }   // (head ^ head >> 16) >> 8
 __device__ __forceinline__ uint32_t sr_mix(uint32_t v)
 {
     v = sr_head(v);
@@ -82,7 +81,8 @@ __device__ __forceinline__ void sr_head4(uint32_t v, uint32_t w[4])
 // the floating-point form rounds frac(t) = t + 1 to fp32, which (t + 1) - 1 does here.  One clamp, one conversion and one
 // addition instead of floor, two conversions, a compare, a carry and a clamp; the gfx950 VALU issues additions, multiplications and
 // shifts at twice the rate of those.  Quantisers of tensors that fit the caches are bound by that issue.
-// `sr_top` holds -X - 2^24 + k; four of them make a word of codes.  Only for finite t.
+// `sr_top` holds -X - 2^24 + k; four of them make a word of codes.  t may be infinite, where the bounds make it a code as any other
+// t beyond them (activities that are rectified away only here may overflow on their way), but no NaN.
 // ------------------------------------------------------------------------------------------------
 constexpr float SR_MOST = 127.0f * 0x1p24f;
 __device__ __forceinline__ int floor_to_int(float x)   // |x| < 2^31

@@ -408,9 +408,11 @@ __device__ __forceinline__ void quantize_tile(const QuantArgs& a, uint32_t* tile
     // (the smallest nonzero activity is s_y, the largest 2^31 s_y: with these bounds every quotient and remainder is normal)
     const bool plain_range = s_y > 0x1p-40f && s_y < 0x1p40f;
 
-    // fixed-point rounding where every t is finite: a finite range, of activities that cannot have overflowed, and a sign that is known
-    // per row (or taken from t)
-    // (half-size tiles of an fp32 tensor, which has no sign known beforehand, in floating point: 1000 x 784 4.4 us, 4.7 with the fixed form)
+    // fixed-point rounding where no t is a NaN and its sign is known per row (or taken from t): a finite range, of activities that
+    // have not overflowed themselves.  A finite range makes the factors and everything that counts for it finite.  Negative
+    // activities do not count: times a row's factor, over a small norm or times inv they may become infinite, but not NaN (inv is neither
+    // zero nor infinite), and the bound on their side is zero.
+    // (Half-size tiles of an fp32 tensor, which has no sign known beforehand, in floating point: 1000 x 784 4.4 us, 4.7 with the fixed form.)
     constexpr bool MAY_FIX = STOCH && !(SRC == QSRC_F32 && U == 1);
     const bool fixed = MAY_FIX && live && amax < __builtin_inff() && (PLAIN || a.relu) && (F32SRC || s_y < 0x1p80f);
 
