@@ -315,7 +315,7 @@ def other_config(ff, torch, name, steps=10, warmup=3):
     del graph
     out_extra = {"ms_per_step_graph_replay": round(ms_g, 4), "ms_per_step_per_operation_kernels_one_stream": round(ms_k, 4)}
     if not fused:
-        out_extra["launch"] = ("one kernel per operation; update chains of different layers on several streams where "
+        out_extra["launch"] = ("kernels per operation, some shared by several; update chains of different layers on several streams where "
                                "FF_LAUNCH_AUTO chooses so (cfg2, cfg3, cfg4)")
     if fused:
         # phase durations inside the launch (100 MHz stamps of its first workgroup), mean of 20 steps
@@ -369,7 +369,7 @@ def main() -> int:
                     help="stop after the timed steps and print a short line (for rocprofv3 runs: the trace or the counters "
                          "then cover the threshold set-up step, the warm-up and the timed steps only)")
     ap.add_argument("--launch-mode", choices=("auto", "kernels", "fused", "lanes"), default="auto",
-                    help="kernels: one kernel per operation on one stream; lanes: the same, the update chains of "
+                    help="kernels: one kernel per operation on one stream; lanes: kernels as auto, the update chains of "
                          "different layers on up to three streams; fused: the whole step as one persistent launch (small "
                          "dense stacks); auto: fused or lanes where they apply and the layers are small")
     ap.add_argument("--lookahead", choices=("coeff", "chain"), default="coeff",
