@@ -147,6 +147,13 @@ static int64_t wgrad_cols(const Dims& d)
 }
 // Sample chunks of equal size go into one launch as further problems of the batch.
 static bool chunks_together(const Dims& d) { return d.n_chunks > 1 && d.B == d.n_chunks * d.chunk_b; }
+// Splits of a weight gradient's reduction of R rows, nb problems in a launch; *window: the launch reads its input through windows (wgrad3.hip).
+static int wgrad_splits(const Dims& d, int64_t R, int nb, bool* window)
+{
+    const int w3 = d.kind == FF_CONV2D && !wgrad_from_patches(d) ? wgrad3_splits(d.g, d.N, R, nb) : 0;
+    *window = w3 > 0;
+    return w3 > 0 ? w3 : gemm_plan(d.N, wgrad_cols(d), R, nb, true, d.kind != FF_DENSE).splits;
+}
 // Scratch for the partial results of a split weight gradient: [launch][pass][chunk of the launch][split][N, pitch32(K)].
 static size_t wgrad_part_bytes(const Dims& d, int nb)
 {
@@ -156,8 +163,8 @@ static size_t wgrad_part_bytes(const Dims& d, int nb)
     const int problems = nb * (chunks_together(d) ? d.n_chunks : 1);
     const int64_t chunk_rows = min(d.M, d.chunk_b * d.rps), last_rows = d.M - (d.n_chunks - 1) * chunk_rows;
     int splits = 1;   // (the last chunk of a pass may be shorter and cut into other tiles)
-    for (const int64_t rows : {chunk_rows, last_rows})
-        splits = max(splits, gemm_plan(d.N, wgrad_cols(d), rows, problems, true, d.kind != FF_DENSE).splits);
+    bool window;
+    for (const int64_t rows : {chunk_rows, last_rows}) splits = max(splits, wgrad_splits(d, rows, problems, &window));
     if (splits <= 1) return 0;
     return align_up((size_t)(nb * d.n_chunks) * (size_t)splits * (size_t)(d.N * pitch32(d.K)) * sizeof(int32_t), 256);
 }
@@ -756,10 +763,12 @@ static ff_status run_wgrad(const Dims& d, const int8_t* gy_t, int64_t st_gy, con
             g.stride = q.stride; g.pad = q.pad; g.Ho = q.Ho; g.Wo = q.Wo;
             g.p_bytes = (b1 - b0) * q.H * q.W * q.cpitch;
         }
-        g.splits = gemm_plan(g.I, g.J, g.R, g.nb, true, g.conv == 2).splits;
+        bool window;
+        g.splits = wgrad_splits(d, mc, g.nb, &window);
         const int64_t room = part_elems / launches;            // this launch's share of the scratch
         const int64_t fit = room / (elems * g.nb);             // partial results per accumulator it holds
-        if (g.splits > fit) g.splits = split_evenly(g.R, fit < 1 ? 1 : fit);
+        if (g.splits > fit) g.splits = window ? wgrad3_split_evenly(g.R, fit < 1 ? 1 : fit) : split_evenly(g.R, fit < 1 ? 1 : fit);
+        auto contract = [&] { return window ? launch_wgrad3(g, d.g, s) : launch_gemm_nt_i8(g, s); };
         g.clk = g_clock_probe;
         if (g.splits > 1) {
             // problem (pass z, chunk c) keeps its partial results at ((z * together + c) * splits) * elems
@@ -769,7 +778,7 @@ static ff_status run_wgrad(const Dims& d, const int8_t* gy_t, int64_t st_gy, con
             g.st_split = elems;
             g.st_c2 = g.splits * elems;
             g.st_c = together * g.st_c2;
-            HIPCHK_T(FF_K_GEMM_DW, launch_gemm_nt_i8(g, s));
+            HIPCHK_T(FF_K_GEMM_DW, contract());
             if (terms) {
                 for (int c = 0; c < together; ++c) {
                     terms->splits[l + c] = g.splits;
@@ -779,7 +788,7 @@ static ff_status run_wgrad(const Dims& d, const int8_t* gy_t, int64_t st_gy, con
                 HIPCHK_T(FF_K_GEMM_DW, launch_reduce_splits(mine, g.splits, elems, g.st_c2, out, dw_elems, elems, together, s));
             }
         } else {
-            HIPCHK_T(FF_K_GEMM_DW, launch_gemm_nt_i8(g, s));
+            HIPCHK_T(FF_K_GEMM_DW, contract());
         }
     }
     return FF_OK;

@@ -37,6 +37,15 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v)
     return max(max(a, b), max(c, d));
 }
 
+// Waits for this wavefront's LDS operations.  The builtin and not inline assembly: the compiler counts it, where behind an assembly wait
+// it still takes the reads before it for outstanding and, once younger ones are on their way, waits for those as well.
+__device__ __forceinline__ void wait_lds()
+{
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
+    asm volatile("" ::: "memory");
+}
+
 // one random word per element: two multiply / xor-shift stages over (low index word ^ key).  sr_head leaves out the last
 // xor-shift; the 24 bits that decide a code are then (head ^ head >> 16) >> 8 of what it returns (sr_top).
 __device__ __forceinline__ uint32_t sr_head(uint32_t v)

@@ -385,6 +385,20 @@ struct Conv3Geom {   // filled in by the launch: 16-byte chunks of a pixel, of a
 bool conv3_ok(const GemmArgs& a);   // covers this implicit convolution, and there are enough tiles
 hipError_t launch_conv3(const GemmArgs& a, hipStream_t s);
 
+// ---- weight gradient of 3x3 convolutions from one input window per step (wgrad3.hip) --------------------------------------
+struct ConvGeom {
+    int32_t H, W, Cin, cpitch, ks, stride, pad, Ho, Wo;
+};
+struct Wgrad3Geom {   // filled in by the launch: reciprocals of Ho Wo, Wo, W + 1, H + 1; positions of a window; tiles and work items
+    uint32_t div_hw, div_wo, div_wp, div_hp;
+    int32_t window, tiles_c, tiles, items, per_xcd;
+};
+// splits of the reduction of a launch over nb problems of R output pixels each, or 0 where it does not cover the layer (GemmArgs::conv == 2
+// for the rest)
+int wgrad3_splits(const ConvGeom& g, int64_t N, int64_t R, int nb);
+int wgrad3_split_evenly(int64_t R, int64_t splits);   // at most `splits` shares of a reduction of R, none of them empty
+hipError_t launch_wgrad3(const GemmArgs& a, const ConvGeom& g, hipStream_t s);
+
 // ---- contraction of short rows without stored accumulators (rows.hip) ------------------------------------------------
 // Rows P [I, ldp] x Q [J, ldq]^T over R <= ROWS_MAX_R bytes, nb passes (st_p, st_g apart), J a multiple of four.
 constexpr int ROWS_MAX_R = 128;
@@ -446,9 +460,6 @@ struct FusedArgs {
 hipError_t launch_fused_dense_step(const FusedArgs& a, int workgroups, hipStream_t s);
 
 // ---- explicit im2col (conv.hip) ----------------------------------------------------------------------
-struct ConvGeom {
-    int32_t H, W, Cin, cpitch, ks, stride, pad, Ho, Wo;
-};
 struct Im2colArgs {
     const int8_t* a;  // NHWC int8 [B, H, W, cpitch]
     int8_t* out;      // [B*Ho*Wo, ld_out]
