@@ -647,6 +647,10 @@ static ff_status run_forward(const Dims& d, int relu, const int8_t* aq, int64_t 
         HIPCHK_T(FF_K_GEMM_FWD, launch_conv3(g, s));
         return FF_OK;
     }
+    if (conv3_wide_ok(g)) {
+        HIPCHK_T(FF_K_GEMM_FWD, launch_conv3_wide(g, s));
+        return FF_OK;
+    }
     g.clk = g_clock_probe;
     HIPCHK_T(FF_K_GEMM_FWD, launch_gemm_nt_i8(g, s));
     return FF_OK;

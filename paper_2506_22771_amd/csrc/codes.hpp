@@ -174,12 +174,6 @@ __device__ __forceinline__ ResidualScale residual_scale(const ResidualArgs& a, i
     return {a.s_a[z * a.st_s_a] * a.s_w[0],
             a.skip == FF_SKIP_IDENTITY ? a.s_x[z * a.st_s_x] : a.s_ap[z * a.st_s_ap] * a.s_wp[0]};
 }
-__device__ __forceinline__ int4 residual_skip(const ResidualArgs& a, int z, int64_t row, int col)   // (raw: codes or accumulators)
-{
-    if (a.skip != FF_SKIP_IDENTITY) return *(const int4*)(a.accp + z * a.st_accp + row * a.ldaccp + col);
-    const uint32_t x = *(const uint32_t*)(a.xq + z * a.st_xq + row * a.ldx + col);
-    return make_int4((int8_t)x, (int8_t)(x >> 8), (int8_t)(x >> 16), (int8_t)(x >> 24));
-}
 __device__ __forceinline__ float4 residual_value(const ResidualScale& s, int relu, const int c[4], const int4 skip, uint32_t& m)
 {
     const int u[4] = {skip.x, skip.y, skip.z, skip.w};
@@ -187,33 +181,52 @@ __device__ __forceinline__ float4 residual_value(const ResidualScale& s, int rel
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const float t = (float)c[q] * s.s_y;
-        float w = t + (float)u[q] * s.s_u;
-        if (relu) w = fmaxf(w, 0.0f);
-        y[q] = w;
-        m = max(m, __float_as_uint(fabsf(w)));
+        y[q] = t + (float)u[q] * s.s_u;
+    }
+    if (relu) {   // (bits of values that are not negative, or of -0, compared as signed integers: no magnitudes to take)
+        int b[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            y[q] = fmaxf(y[q], 0.0f);
+            b[q] = __float_as_int(y[q]);
+        }
+        m = (uint32_t)max(max(max((int)m, b[0]), b[1]), max(b[2], b[3]));
+    } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) m = max(m, __float_as_uint(fabsf(y[q])));
     }
     return make_float4(y[0], y[1], y[2], y[3]);
 }
-// Rows row0 + rl + r RPI, r < NR, of a wavefront's output, LPR lanes of four columns to a row: value(r) gives the accumulators,
-// `in` says whether the lane has columns at all.  Stores y and each sample's largest magnitude.  The rows belong to one sample or
-// to two (samples have at least NR RPI rows, RESIDUAL_MIN_ROWS): one atomic for each.  All atomics of a launch meet in a few cache
+// Rows row0 + rl + r RPI, r < NR, of a wavefront's output, LPR lanes of four columns to a row.  skip: what residual_load loads for them (codes of the
+// block input as they lie, one word, or the projection's accumulators).
+template <bool CODES> using ResidualSkip = std::conditional_t<CODES, uint32_t, int4>;
+template <bool CODES, int LPR, int NR>
+__device__ __forceinline__ void residual_load(const ResidualArgs& a, int z, int row0, int col, bool in, ResidualSkip<CODES> (&u)[NR])
+{
+    constexpr int RPI = 64 / LPR;
+    const int rl = (int)(threadIdx.x & 63) / LPR;
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+        const int64_t row = row0 + r * RPI + rl;
+        u[r] = {};
+        if (in && row < a.M) {
+            if constexpr (CODES) u[r] = *(const uint32_t*)(a.xq + z * a.st_xq + row * a.ldx + col);
+            else u[r] = *(const int4*)(a.accp + z * a.st_accp + row * a.ldaccp + col);
+        }
+    }
+}
+// value(r) gives the accumulators, `in` says whether the lane has columns at all.  Stores y and each sample's largest magnitude.  The rows belong to one
+// sample or to two (samples have at least NR RPI rows, RESIDUAL_MIN_ROWS): one atomic for each.  All atomics of a launch meet in a few cache
 // lines, where they take 2 to 4 ns each: with one per row of a slice of two samples, the contraction of 128 channels on 14x14 maps of 38 images
 // (two passes) took 29 us, this way 17.
-template <int LPR, int NR, typename F>
-__device__ __forceinline__ void residual_rows(const ResidualArgs& a, const ResidualScale& s, int z, int row0, int col, bool in, F value)
+template <bool CODES, int LPR, int NR, typename F>
+__device__ __forceinline__ void residual_rows(const ResidualArgs& a, const ResidualScale& s, int z, int row0, int col, bool in, const ResidualSkip<CODES> (&u)[NR], F value)
 {
     constexpr int RPI = 64 / LPR;
     static_assert(NR * RPI <= RESIDUAL_MIN_ROWS, "more than two samples");
     const int lane = threadIdx.x & 63, rl = lane / LPR;
     const int M = (int)a.M;
     if (row0 >= M) return;   // (uniform)
-    int4 u[NR];
-#pragma unroll
-    for (int r = 0; r < NR; ++r) {
-        const int row = row0 + r * RPI + rl;
-        u[r] = make_int4(0, 0, 0, 0);
-        if (in && row < M) u[r] = residual_skip(a, z, row, col);
-    }
     const uint32_t rps = (uint32_t)a.rows_per_sample, smp = (uint32_t)row0 / rps;
     const int next = (int)((smp + 1) * rps);   // first row of the sample after it
     uint32_t m[2] = {0, 0};
@@ -223,7 +236,10 @@ __device__ __forceinline__ void residual_rows(const ResidualArgs& a, const Resid
         int c[4];
         value(r, c);
         uint32_t mr = 0;
-        const float4 y = residual_value(s, a.relu, c, u[r], mr);
+        int4 skip;
+        if constexpr (CODES) skip = make_int4((int8_t)u[r], (int8_t)(u[r] >> 8), (int8_t)(u[r] >> 16), (int8_t)(u[r] >> 24));
+        else skip = u[r];
+        const float4 y = residual_value(s, a.relu, c, skip, mr);
         if (in && row < M) *(float4*)(a.y + z * a.st_y + (int64_t)row * a.N + col) = y;
         else mr = 0;
         m[0] = max(m[0], row < next ? mr : 0u);

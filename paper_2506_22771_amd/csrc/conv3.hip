@@ -11,28 +11,12 @@
 //
 // LDS rows: a weight row has an odd number of 16-byte chunks, a pixel one or three, or two or four XOR-swizzled by its address,
 // so that sixteen consecutive rows or pixels fall into sixteen different bank groups at any offset.
-#include "codes.hpp"
+#include "window.hpp"
 
 namespace ffi {
 
-typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v16i __attribute__((ext_vector_type(16)));
-
 constexpr int C3_PIX = 256;        // output pixels of a tile
 constexpr int C3_SLOTS = 7;        // copy instructions of a thread per window, at most
-constexpr int C3_OOB = 0x7FFFFFF0;   // beyond any tensor (they are shorter than 2^30 bytes)
-
-// 16 bytes per lane straight into LDS, tracked by hand with vmcnt (see gemm_i8.hip)
-__device__ __forceinline__ void copy16(__amdgpu_buffer_rsrc_t rsrc, int voffset, unsigned lds_base)
-{
-    asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds_base), "v"(voffset), "s"(rsrc) : "memory", "m0");
-}
-__device__ __forceinline__ void wave_fence()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 // KT: 32-byte pieces of a pixel (C_in <= 32 KT).  A workgroup has four wavefronts of 64 pixels x 32 TJ columns.
 template <int KT, int TJ> struct C3Shape {
@@ -40,18 +24,14 @@ template <int KT, int TJ> struct C3Shape {
     static constexpr int KW = 288 * KT + 16;                // bytes of a weight row
     static constexpr int LDS = 80 * 1024;                   // two workgroups per compute unit
     static constexpr int BUF = (LDS - BN * KW) / 2 / 1024 * 1024;
-    static constexpr int EROW = TJ * 128 + 16, ESLICE = 16 * EROW;   // staging of a wavefront's stores, in the window just read
+    static constexpr int EROWS = 16, ESLICE = EROWS * (TJ * 128 + 16);   // staging of a wavefront's stores, in the window just read
     static_assert(BUF >= 4 * ESLICE, "staging");
 };
 
-// what becomes of the accumulators: stored, stored with the goodness sums, or the output of a residual block
-enum Conv3Result { C3_STORE, C3_STORE_GOODNESS, C3_RESIDUAL };
-
 template <int WHAT, int KT, int TJ>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_conv3_i8(std::conditional_t<WHAT == C3_RESIDUAL, GemmResidualArgs, GemmArgs> a, Conv3Geom c)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_conv3_i8(Conv3Args<WHAT> a, Conv3Geom c)
 {
     using S = C3Shape<KT, TJ>;
-    constexpr bool GOODNESS = WHAT == C3_STORE_GOODNESS, RESIDUAL = WHAT == C3_RESIDUAL;
     constexpr int T = S::T, BN = S::BN, KW = S::KW;
     __shared__ __attribute__((aligned(16))) int8_t lds[S::LDS];
     const int tid = threadIdx.x, lane = tid & 63, lr = lane & 31, lh = lane >> 5;
@@ -78,7 +58,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
         for (int s = 0; s < C3_SLOTS; ++s)
             if (s * T + wave * 64 < c.chunks) {   // (uniform in a wavefront)
                 const int at = (int)((uint32_t)off[s] + (uint32_t)start);   // before or beyond the tensor: zeros
-                copy16(rp, at < 0 ? C3_OOB : at, base + (unsigned)(s * T + wave * 64) * 16u);
+                copy16(rp, at < 0 ? BEYOND : at, base + (unsigned)(s * T + wave * 64) * 16u);
             }
     };
     if (t0 < t1) copy_window(t0, 0);
@@ -97,7 +77,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     __syncthreads();
 
     const int HW = a.H * a.W;
-    const bool whole_lines = (a.ldc & 31) == 0;
     unsigned long long sq = 0;   // goodness sum and maximum of the sample (or block of rows) at hand
     int vm = 0;
     int cur = 0;
@@ -156,70 +135,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
 
-        // sixteen rows at a time through the window that was just read, then whole row segments
-        int8_t* const slice = win + wave * S::ESLICE;
-        int32_t* const C = a.C + z * a.st_c;
-        ResidualScale rs = {};
-        if constexpr (RESIDUAL) rs = residual_scale(a.res, z);
-#pragma unroll
-        for (int ti = 0; ti < 2; ++ti)
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                if ((lr >> 4) == h) {
-#pragma unroll
-                    for (int tj = 0; tj < TJ; ++tj)
-#pragma unroll
-                        for (int g = 0; g < 4; ++g)
-                            *(v4i*)(slice + (lr & 15) * S::EROW + (tj * 32 + 8 * g + 4 * lh) * 4) =
-                                (v4i){acc[ti][tj][4 * g], acc[ti][tj][4 * g + 1], acc[ti][tj][4 * g + 2], acc[ti][tj][4 * g + 3]};
-                }
-                wave_fence();
-                constexpr int LPR = 8 * TJ, RPI = 64 / LPR;   // lanes per row, rows per store instruction
-                const int rl = lane / LPR, cc = 4 * (lane % LPR);
-                if constexpr (RESIDUAL) {
-                    residual_rows<LPR, 16 / RPI>(a.res, rs, z, i0 + 64 * wave + 32 * ti + 16 * h, j0 + cc, j0 + cc < a.J, [&](int r, int c[4]) {
-                        const v4i v = *(const v4i*)(slice + (r * RPI + rl) * S::EROW + cc * 4);
-                        c[0] = v[0]; c[1] = v[1]; c[2] = v[2]; c[3] = v[3];
-                    });
-                    wave_fence();
-                    continue;
-                }
-#pragma unroll
-                for (int r = 0; r < 16 / RPI; ++r) {
-                    const int m = i0 + 64 * wave + 32 * ti + 16 * h + r * RPI + rl;
-                    const v4i v = *(const v4i*)(slice + (r * RPI + rl) * S::EROW + cc * 4);
-                    // not read again before the caches have been streamed over (see gemm_i8.hip); but where a column block starts or ends
-                    // inside a line, its other half has to meet it in L2
-                    if (m < a.I && j0 + cc < a.J) {
-                        if (whole_lines) __builtin_nontemporal_store(v, (v4i*)(C + (int64_t)m * a.ldc + j0 + cc));
-                        else *(v4i*)(C + (int64_t)m * a.ldc + j0 + cc) = v;
-                    }
-                }
-                wave_fence();
-            }
-        if constexpr (GOODNESS) {
-            // one reduction and two atomics per wavefront and run of tiles in which its rows belong to one sample
-            const int r0 = i0 + 64 * wave, smp = r0 < a.I ? one_sample_of(r0, 64, a.I, (uint32_t)HW) : -1;
-#pragma unroll
-            for (int ti = 0; ti < 2; ++ti) {
-#pragma unroll
-                for (int tj = 0; tj < TJ; ++tj) {
-                    int v[16];
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) v[e] = acc[ti][tj][e];
-                    goodness_terms(a.relu, a.rshift, v, 16, sq, vm);
-                }
-                if (smp >= 0) {
-                    if (ti == 0) continue;
-                    if (t + 1 < t1 && r0 + C3_PIX < a.I && one_sample_of(r0 + C3_PIX, 64, a.I, (uint32_t)HW) == smp) continue;
-                    goodness_one(sq, vm, a.gsum + z * a.st_g + smp, a.vmax + z * a.st_g + smp);
-                } else {
-                    goodness_runs(sq, vm, r0 + 32 * ti, a.I, (uint32_t)HW, a.gsum + z * a.st_g, a.vmax + z * a.st_g);
-                }
-                sq = 0;
-                vm = 0;
-            }
-        }
+        // sixteen rows at a time through the window that was just read
+        const int r0 = i0 + 64 * wave;
+        conv3_store<WHAT, TJ, S::EROWS>(a, z, r0, j0, acc, win + wave * S::ESLICE);
+        if constexpr (WHAT == C3_STORE_GOODNESS) conv3_goodness<TJ>(a, z, r0, t + 1 < t1 ? r0 + C3_PIX : -1, acc, sq, vm);
         __builtin_amdgcn_s_barrier();   // (behind the fence of the last exchange; the staging slices lie in the window that the copy after next fills)
     }
 }

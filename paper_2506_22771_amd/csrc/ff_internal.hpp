@@ -385,13 +385,13 @@ struct Conv3Geom {   // filled in by the launch: 16-byte chunks of a pixel, of a
 bool conv3_ok(const GemmArgs& a);   // covers this implicit convolution, and there are enough tiles
 hipError_t launch_conv3(const GemmArgs& a, hipStream_t s);
 
+// ---- 3x3 stride-1 convolutions of more than 64 input channels (conv3_wide.hip) ----------------------------------------------
+bool conv3_wide_ok(const GemmArgs& a);   // covers this implicit convolution, and is the better way
+hipError_t launch_conv3_wide(const GemmArgs& a, hipStream_t s);
+
 // ---- weight gradient of 3x3 convolutions from one input window per step (wgrad3.hip) --------------------------------------
 struct ConvGeom {
     int32_t H, W, Cin, cpitch, ks, stride, pad, Ho, Wo;
-};
-struct Wgrad3Geom {   // filled in by the launch: reciprocals of Ho Wo, Wo, W + 1, H + 1; positions of a window; tiles and work items
-    uint32_t div_hw, div_wo, div_wp, div_hp;
-    int32_t window, tiles_c, tiles, items, per_xcd;
 };
 // splits of the reduction of a launch over nb problems of R output pixels each, or 0 where it does not cover the layer (GemmArgs::conv == 2
 // for the rest)

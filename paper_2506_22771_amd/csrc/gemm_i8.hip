@@ -446,15 +446,53 @@ __global__ __launch_bounds__(WM* WN * 64) __attribute__((amdgpu_waves_per_eu(BKT
     // CONV 2 with channel counts that are no multiple of 16: the columns run over whole 16-channel chunks and the store
     // leaves the channels beyond C_in out
     const bool compact = CONV == 2 && a.cin_out != a.Cin;
-    const bool staged = RES || ((interior || (a.J & 3) == 0) && !compact);
+    const bool staged = (interior || (a.J & 3) == 0) && !compact;
     const bool fast_sq = a.relu && a.rshift == 0;
     ResidualScale res_scale = {};
     if constexpr (RES) res_scale = residual_scale(a.res, z);
     int8_t* const ebase = lds + EOFF + wave * ESLICE;
-    if (wait_copies && !staged) {   // (copies and stores complete in issue order: wait before the first store)
+    if (!RES && wait_copies && !staged) {   // (copies and stores complete in issue order: wait before the first store)
         wait_vmcnt<0>();
         wait_copies = false;
     }
+    if constexpr (RES) {
+        // block outputs: what is added is fetched for 32 rows at a time, ahead of the exchanges
+        constexpr int LPR = WTN / 4, RPI = 64 / LPR, NR = EROWS / RPI, NH = 32 / EROWS;
+        const int rl = lane / LPR, cc = lane - rl * LPR, col = j0 + wn * WTN + cc * 4;
+        auto output = [&](auto codes) {
+            constexpr bool CODES = decltype(codes)::value;
+#pragma unroll
+            for (int ti = 0; ti < TI; ++ti) {
+                const int row0 = i0 + wm * WTM + ti * 32;
+                ResidualSkip<CODES> u[NH][NR];
+#pragma unroll
+                for (int h = 0; h < NH; ++h) residual_load<CODES, LPR, NR>(a.res, z, row0 + h * EROWS, col, col < a.J, u[h]);
+#pragma unroll
+                for (int h = 0; h < NH; ++h) {
+                    if (EROWS == 32 || (lr / EROWS) == h) {
+#pragma unroll
+                        for (int tj = 0; tj < TJ; ++tj)
+#pragma unroll
+                            for (int g = 0; g < 4; ++g)
+                                *(v4i*)(ebase + (lr % EROWS) * EROW + (tj * 32 + 8 * g + 4 * lh) * 4) =
+                                    (v4i){acc[ti][tj][4 * g + 0], acc[ti][tj][4 * g + 1], acc[ti][tj][4 * g + 2], acc[ti][tj][4 * g + 3]};
+                    }
+                    wave_lds_fence();
+                    if (wait_copies) {   // (see below)
+                        wait_vmcnt<0>();
+                        wait_copies = false;
+                    }
+                    residual_rows<CODES, LPR, NR>(a.res, res_scale, z, row0 + h * EROWS, col, col < a.J, u[h], [&](int r, int c[4]) {
+                        const v4i v = *(const v4i*)(ebase + (r * RPI + rl) * EROW + cc * 16);
+                        c[0] = v[0]; c[1] = v[1]; c[2] = v[2]; c[3] = v[3];
+                    });
+                    wave_lds_fence();
+                }
+            }
+        };
+        if (a.res.skip == FF_SKIP_IDENTITY) output(std::true_type{});   // (uniform)
+        else output(std::false_type{});
+    } else
 #pragma unroll
     for (int ti = 0; ti < TI; ++ti) {
         const int i = i0 + wm * WTM + ti * 32 + lr;
@@ -535,15 +573,6 @@ __global__ __launch_bounds__(WM* WN * 64) __attribute__((amdgpu_waves_per_eu(BKT
                 constexpr int RPI = 64 / LPR;         // rows per store instruction
                 const int rl = lane / LPR, cc = lane - rl * LPR;
                 const int row0 = i0 + wm * WTM + ti * 32 + h * EROWS;
-                if constexpr (RES) {
-                    const int col = j0 + wn * WTN + cc * 4;
-                    residual_rows<LPR, EROWS / RPI>(a.res, res_scale, z, row0, col, col < a.J, [&](int r, int c[4]) {
-                        const v4i v = *(const v4i*)(ebase + (r * RPI + rl) * EROW + cc * 16);
-                        c[0] = v[0]; c[1] = v[1]; c[2] = v[2]; c[3] = v[3];
-                    });
-                    wave_lds_fence();
-                    continue;
-                }
                 int32_t* const ctile = C + (int64_t)row0 * a.ldc + j0 + wn * WTN + cc * 4;
 #pragma unroll
                 for (int r = 0; r < EROWS / RPI; ++r) {

@@ -19,13 +19,9 @@
 // implicit loop, 2 x 23 here; a ResNet-18-shaped step 2061 -> 1943 us, 3-64-128-256 at 32x32 898 -> 825.
 #include <math.h>
 
-#include "codes.hpp"
+#include "window.hpp"
 
 namespace ffi {
-
-typedef int v2i __attribute__((ext_vector_type(2)));
-typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v16i __attribute__((ext_vector_type(16)));
 
 constexpr int W3_STEP = 512;                 // output pixels of a step
 constexpr int W3_BN = 64, W3_BC = 32;        // output and input channels of a workgroup
@@ -34,27 +30,20 @@ constexpr int W3_P = W3_BN * W3_STEP;        // bytes of a step's gradient
 constexpr int W3_STAGE = 64 * 1024;          // operands of a step, two of them
 constexpr int W3_TABLE = 2 * W3_STAGE;       // tables of four steps behind them
 constexpr int W3_LDS = W3_TABLE + 8 * 1024;   // (the exchange of the sums at the end takes 12 x 9 KB of it)
-constexpr int W3_OOB = 0x7FFFFFF0;
 
 constexpr int W3_CW = (W3_STAGE - W3_P) / (W3_T * 16);   // copy instructions of a thread for a window, at most
 constexpr int W3_POSITIONS = W3_CW * W3_T / 2;
 static_assert(W3_TABLE + 4 * W3_STEP * 4 <= W3_LDS && 12 * 9 * 1024 <= W3_LDS && W3_LDS <= 160 * 1024, "LDS");
 
-__device__ __forceinline__ void w3_copy16(__amdgpu_buffer_rsrc_t rsrc, int voffset, unsigned lds_base)   // (see gemm_i8.hip)
-{
-    asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds_base), "v"(voffset), "s"(rsrc) : "memory", "m0");
-}
 __device__ __forceinline__ v2i w3_tr_read8(const int8_t* p)   // (see gemm_i8.hip)
 {
     typedef __attribute__((address_space(3))) v2i* lds_ptr;
     return __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_ptr)p);
 }
-__device__ __forceinline__ void w3_barrier()   // this wavefront's LDS operations are done
-{
-    wait_lds();
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-}
+struct Wgrad3Geom {   // filled in by the launch
+    WindowGeom div;
+    int32_t window, tiles_c, tiles, items, per_xcd;   // positions of a window; tiles and work items
+};
 
 // What a wavefront needs to know of its workgroup's share.
 struct W3Item {
@@ -78,13 +67,8 @@ __device__ __forceinline__ void wgrad3_body(const GemmArgs& a, const Wgrad3Geom&
     const int rpad = (a.R + 15) & ~15;
     const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc((void*)it.P, 0, (int)(min(W3_BN, a.I - it.n0) * a.ldp), 0x00020000);
     const __amdgpu_buffer_rsrc_t rq = __builtin_amdgcn_make_buffer_rsrc((void*)it.Q, 0, (int)a.p_bytes, 0x00020000);
-    const int wp = a.W + 1;
 
-    // position of tap (0, 0) of output pixel m
-    auto first_tap = [&](uint32_t m) {
-        const uint32_t b = __umulhi(m, c.div_hw), rem = m - b * (uint32_t)(a.Ho * a.Wo), ho = __umulhi(rem, c.div_wo), wo = rem - ho * (uint32_t)a.Wo;
-        return (int)((b * (uint32_t)(a.H + 1) + ho) * (uint32_t)wp + wo);
-    };
+    auto first_tap = [&](uint32_t m) { return window_first(c.div, a.H, a.W, m); };
     // chunk c of row r lies at c ^ (r & 15): sixteen rows, one chunk, sixteen bank groups
     static_assert(PROWS % 16 == 0, "one pattern for all copies");
     const int col_p = ((tid % CPR) ^ ((tid / CPR) & 15)) << 4;   // pixel of this thread's gradient chunks
@@ -94,19 +78,17 @@ __device__ __forceinline__ void wgrad3_body(const GemmArgs& a, const Wgrad3Geom&
     auto copy = [&](int kt, int stage) {
         const int m0 = __builtin_amdgcn_readfirstlane(kt * W3_STEP);
         const unsigned base = (unsigned)(uintptr_t)(lds + stage * W3_STAGE);
-        const int at_p = m0 + col_p < rpad ? off_p + m0 + col_p : W3_OOB;
+        const int at_p = m0 + col_p < rpad ? off_p + m0 + col_p : BEYOND;
         const int more = PROWS * (int)a.ldp;
 #pragma unroll
         for (int s = 0; s < W3_BN / PROWS; ++s)   // (beyond any buffer stays beyond: unsigned offsets)
-            w3_copy16(rp, (int)((uint32_t)at_p + (uint32_t)(s * more)), base + (unsigned)(s * W3_T + wave * 64) * 16u);
+            copy16(rp, (int)((uint32_t)at_p + (uint32_t)(s * more)), base + (unsigned)(s * W3_T + wave * 64) * 16u);
         const int q0 = __builtin_amdgcn_readfirstlane(first_tap((uint32_t)m0));
 #pragma unroll
         for (int s = 0; s < W3_CW; ++s) {
             if (s * (W3_T / 2) + wave * 32 >= c.window) break;   // (uniform)
-            const uint32_t q = (uint32_t)(q0 + s * (W3_T / 2) + (tid >> 1));
-            const uint32_t row = __umulhi(q, c.div_wp), col = q - row * (uint32_t)wp, b = __umulhi(row, c.div_hp), h = row - b * (uint32_t)(a.H + 1);
-            const int at = (int)(((row - b - 1u) * (uint32_t)a.W + col - 1u) * (uint32_t)a.cpitch) + cq;
-            w3_copy16(rq, have_q && col != 0 && h != 0 ? at : W3_OOB, base + W3_P + (unsigned)(s * W3_T + wave * 64) * 16u);
+            const int at = window_source(c.div, a.H, a.W, a.cpitch, (uint32_t)(q0 + s * (W3_T / 2) + (tid >> 1)));
+            copy16(rq, have_q && at != BEYOND ? at + cq : BEYOND, base + W3_P + (unsigned)(s * W3_T + wave * 64) * 16u);
         }
     };
     auto table = [&](int kt) {   // (one pixel a thread)
@@ -131,7 +113,7 @@ __device__ __forceinline__ void wgrad3_body(const GemmArgs& a, const Wgrad3Geom&
             ent[e] = tbl[(j & 3) * W3_STEP + 32 * SUBS * slice + 32 * (e >> 1) + 16 * lh + 8 * (e & 1) + ((lane & 15) >> 1)];
     };
     const int lane_q = W3_P + 16 * ((lane >> 4) & 1) + 8 * (lane & 1);
-    const int pitch_h = wp * W3_BC;
+    const int pitch_h = (a.W + 1) * W3_BC;
     auto fragments = [&](auto piece, int stage) {
         constexpr int U = decltype(piece)::value, F = U & 1;
         const int8_t* const base = lds + stage * W3_STAGE;
@@ -162,7 +144,7 @@ __device__ __forceinline__ void wgrad3_body(const GemmArgs& a, const Wgrad3Geom&
     for (int j = 0; j < 3; ++j)
         if (j < nk) table(it.kt0 + j);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    w3_barrier();
+    lds_barrier();
     if (1 < nk) copy(it.kt0 + 1, 1);
     entries(0);
     fragments(std::integral_constant<int, 0>{}, 0);
@@ -179,7 +161,7 @@ __device__ __forceinline__ void wgrad3_body(const GemmArgs& a, const Wgrad3Geom&
         // The last fragments of this stage are in registers, and the copies of the next one have landed: behind the barrier that is
         // so for every wavefront.
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        w3_barrier();
+        lds_barrier();
         // (one of the two wavefronts of a SIMD multiplies while the other's copies queue up)
         if (j + 1 < nk) fragments(std::integral_constant<int, 0>{}, cur ^ 1);
         if (T0 == 0 && j + 2 < nk) copy(it.kt0 + j + 2, cur);
@@ -196,7 +178,7 @@ __device__ __forceinline__ void wgrad3_body(const GemmArgs& a, const Wgrad3Geom&
         const int ci = it.ch0 + 8 * M + 4 * lh;
 #pragma unroll
         for (int ti = 0; ti < 2; ++ti) {
-            w3_barrier();   // (every wavefront has read its last fragments, or the sums of the first rows)
+            lds_barrier();   // (every wavefront has read its last fragments, or the sums of the first rows)
 #pragma unroll
             for (int t = 0; t < NT; ++t)
 #pragma unroll
@@ -204,7 +186,7 @@ __device__ __forceinline__ void wgrad3_body(const GemmArgs& a, const Wgrad3Geom&
                     if (g != M)
                         *(v4i*)(lds + (((g * 3 + (M < g ? M : M - 1)) * 9 + T0 + t) * 64 + lane) * 16) =
                             (v4i){acc[ti][t][4 * g], acc[ti][t][4 * g + 1], acc[ti][t][4 * g + 2], acc[ti][t][4 * g + 3]};
-            w3_barrier();
+            lds_barrier();
             const int n = it.n0 + 32 * ti + lr;
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
@@ -268,22 +250,9 @@ __global__ __launch_bounds__(W3_T) __attribute__((amdgpu_waves_per_eu(2, 2))) vo
     }
 }
 
-// Positions between tap (0, 0) of a step's first pixel and the end of tap (2, 2) of its last, at most: every end of a row inside costs two
-// positions, every end of an image a row.
-static int64_t wgrad3_window(const ConvGeom& g)
+static bool wgrad3_fits(const ConvGeom& g, int64_t R, WindowGeom* c)
 {
-    const int64_t wp = g.W + 1, hw = (int64_t)g.H * g.W, rows = (W3_STEP - 1 + g.W - 1) / g.W, images = (W3_STEP - 1 + hw - 1) / hw;
-    return W3_STEP + rows + images * wp + 2 * wp + 2;
-}
-static uint32_t reciprocal(uint32_t d) { return (uint32_t)(((uint64_t(1) << 32) + d - 1) / d); }   // x / d = x * this >> 32 where x * d < 2^32 and d > 1
-
-static bool wgrad3_fits(const ConvGeom& g, int64_t R)
-{
-    if (g.ks != 3 || g.pad != 1 || g.stride != 1 || g.W < 2 || R < 1) return false;
-    const int64_t hw = (int64_t)g.H * g.W, wp = g.W + 1, images = (R + hw - 1) / hw + 1;
-    const int64_t positions = images * (g.H + 1) * wp + 2 * W3_POSITIONS;   // (copies reach beyond the last image)
-    return positions * wp < (int64_t(1) << 32) && positions / wp * (g.H + 1) < (int64_t(1) << 32) && (R + W3_STEP) * hw < (int64_t(1) << 32) &&
-           wgrad3_window(g) <= W3_POSITIONS;
+    return g.ks == 3 && g.pad == 1 && g.stride == 1 && window_geom(g.H, g.W, R, 2 * W3_POSITIONS, c) && window_positions(g.H, g.W, W3_STEP) <= W3_POSITIONS;
 }
 
 int wgrad3_split_evenly(int64_t R, int64_t splits)
@@ -302,7 +271,8 @@ int wgrad3_split_evenly(int64_t R, int64_t splits)
 // 16x16 30.1 and 33.3, 256 -> 512 of 8x8 28.3 and 30.4: they keep the implicit loop.
 int wgrad3_splits(const ConvGeom& g, int64_t N, int64_t R, int nb)
 {
-    if (g.Cin < 16 || !wgrad3_fits(g, R)) return 0;
+    WindowGeom c;
+    if (g.Cin < 16 || !wgrad3_fits(g, R, &c)) return 0;
     const int64_t tiles = ((N + W3_BN - 1) / W3_BN) * ((g.Cin + W3_BC - 1) / W3_BC) * nb, steps = (R + W3_STEP - 1) / W3_STEP;
     if (R < 16384 && tiles * steps < 384) return 0;
     // 512 pixels take about 1.1 us, writing and adding up a workgroup's partial result 0.012: the least of 1.1 R / 512 splits + 0.012 tiles splits,
@@ -317,16 +287,12 @@ hipError_t launch_wgrad3(const GemmArgs& a_in, const ConvGeom& g, hipStream_t s)
     GemmArgs a = a_in;
     if (a.nc < 1) a.nc = 1;
     if (a.I <= 0 || a.nb < 1) return hipSuccess;
-    if (!wgrad3_fits(g, a.R) || a.conv != 2 || !a.C || a.gsum || a.upd_w || a.residual || a.nb % a.nc != 0 || (a.Cin & 15) != 0 || a.Cin > a.cpitch ||
+    Wgrad3Geom c;
+    if (!wgrad3_fits(g, a.R, &c.div) || a.conv != 2 || !a.C || a.gsum || a.upd_w || a.residual || a.nb % a.nc != 0 || (a.Cin & 15) != 0 || a.Cin > a.cpitch ||
         a.cin_out > a.Cin || a.p_bytes >= (int64_t(1) << 31) || a.ldp >= (int64_t(1) << 22) || a.R % (a.Ho * a.Wo) != 0 || a.splits < 1 ||
         wgrad3_split_evenly(a.R, a.splits) != a.splits)
         return hipErrorInvalidValue;
-    Wgrad3Geom c;
-    c.div_hw = reciprocal((uint32_t)(a.Ho * a.Wo));
-    c.div_wo = reciprocal((uint32_t)a.Wo);
-    c.div_wp = reciprocal((uint32_t)(a.W + 1));
-    c.div_hp = reciprocal((uint32_t)(a.H + 1));
-    c.window = (int32_t)wgrad3_window(g);
+    c.window = (int32_t)window_positions(g.H, g.W, W3_STEP);
     c.tiles_c = (a.Cin + W3_BC - 1) / W3_BC;
     c.tiles = (a.I + W3_BN - 1) / W3_BN * c.tiles_c;
     const int64_t items = (int64_t)c.tiles * a.nb * a.splits;

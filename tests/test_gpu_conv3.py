@@ -1,5 +1,6 @@
-"""Forward contraction of 3x3 stride-1 convolutions with resident weights, against the CPU oracle: windows that cross images and
-the ends of the tensor, odd widths, channel counts with half-empty pieces, ragged column blocks, tiles that end inside a pass."""
+"""Forward contraction of 3x3 stride-1 convolutions with resident weights, and with streamed ones beyond 64 input channels: windows that
+cross images and the ends of the tensor, odd widths, channel counts with half-empty pieces, ragged column blocks, tiles that end inside a
+pass."""
 import numpy as np
 import pytest
 
@@ -54,6 +55,48 @@ def test_conv_forward_with_resident_weights(ff, B, H, W, Cin, Cout, relu):
     assert any("k_conv3_i8" in n for n, _ in kernel_nodes(forward))
     forward()
     torch.cuda.synchronize()
+    np.testing.assert_array_equal(d_acc.cpu().numpy()[:, :Cout], acc)
+    np.testing.assert_array_equal(gsum.cpu().numpy().view(np.uint64), gd["g_int"])
+    np.testing.assert_array_equal(vmax.cpu().numpy(), gd["vmax"])
+
+
+@pytest.mark.parametrize("B,H,W,Cin,Cout,relu", [
+    (64, 32, 32, 128, 128, 1),    # whole tiles of 256 pixels, one a workgroup
+    (600, 16, 16, 100, 132, 1),   # two tiles a workgroup; a second group of 36 channels, a second column block of four columns
+    (700, 15, 17, 96, 68, 0),     # several tiles a workgroup, the last not full; plain activations
+    (300, 29, 9, 108, 260, 1),    # channels that are no multiple of eight
+    (1100, 8, 8, 128, 512, 1),    # four samples per tile
+    (160, 13, 43, 192, 72, 1),    # a wide map: seven copies a window
+    (20, 5, 70, 128, 80, 1),      # a wider one: 128-pixel tiles of six copies
+    (3, 12, 11, 100, 68, 1),      # small: 128-pixel tiles, the second of a sample nearly empty
+    (40, 4, 4, 512, 192, 1),      # eight samples per tile
+    (2, 7, 7, 65 * 4, 76, 0),     # one tile that is not full
+    (5, 3, 2, 96, 68, 1)])
+def test_conv_forward_with_streamed_weights(ff, B, H, W, Cin, Cout, relu):
+    rng = np.random.default_rng(B * W + Cin)
+    layer = Layer("conv", H=H, W=W, C_in=Cin, C_out=Cout, ksize=3, stride=1, pad=1, relu=relu)
+    desc = ff.layer_desc(layer, B)
+    M, K = B * H * W, 9 * Cin
+    a_q = rng.integers(-127, 128, (B, H, W, Cin)).astype(np.int8)
+    w_q = rng.integers(-127, 128, (Cout, 3, 3, Cin)).astype(np.int8)
+    d_acc = empty32(M, Cout)
+    gsum = torch.full((B,), 7, dtype=torch.int64, device="cuda")
+    vmax = torch.full((B,), 7, dtype=torch.int32, device="cuda")
+    ws = workspace(ff.ff_layer_workspace_bytes(desc))
+    d_a, d_w = dev(pad_nhwc(a_q)), dev(pad8(w_q.reshape(Cout, K)))
+
+    def forward():
+        ff.ff_layer_forward(desc, d_a, d_w, d_acc, gsum, vmax, ws)
+
+    assert any("k_conv3_wide_i8" in n for n, _ in kernel_nodes(forward))
+    forward()
+    torch.cuda.synchronize()
+    # float64 sums of products below 2^31 are exact
+    x = torch.nn.functional.pad(dev(a_q).double(), (0, 0, 1, 1, 1, 1))
+    w = dev(w_q).double()
+    acc = sum(x[:, kh:kh + H, kw:kw + W].reshape(M, Cin) @ w[:, kh, kw].t().contiguous() for kh in range(3) for kw in range(3))
+    acc = acc.cpu().numpy().astype(np.int32)
+    gd = O.goodness(acc.reshape(B, H * W * Cout), relu, O.goodness_shift(K, layer.terms_per_sample), np.float32(1), np.float32(1))
     np.testing.assert_array_equal(d_acc.cpu().numpy()[:, :Cout], acc)
     np.testing.assert_array_equal(gsum.cpu().numpy().view(np.uint64), gd["g_int"])
     np.testing.assert_array_equal(vmax.cpu().numpy(), gd["vmax"])
