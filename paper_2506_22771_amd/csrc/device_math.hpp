@@ -188,4 +188,13 @@ __device__ __forceinline__ float loss_derivative(float x, int sign, float& xs)
 // softplus; it feeds no quantiser, so any accurate exp / log1p will do
 __device__ __forceinline__ float loss_term(float xs) { return fmaxf(xs, 0.0f) + log1pf(expf(-fabsf(xs))); }
 
+// Lanes of one wavefront exchange data through LDS: the hardware executes a wave's LDS
+// instructions in order, but the compiler reasons per thread and, without a fence, may keep a value it loaded
+// earlier instead of re-reading a location another lane has written since.
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 }  // namespace ffi

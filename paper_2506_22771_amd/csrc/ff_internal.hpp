@@ -388,6 +388,9 @@ hipError_t launch_conv3(const GemmArgs& a, hipStream_t s);
 // ---- 3x3 stride-1 convolutions of more than 64 input channels (conv3_wide.hip) ----------------------------------------------
 bool conv3_wide_ok(const GemmArgs& a);   // covers this implicit convolution, and is the better way
 hipError_t launch_conv3_wide(const GemmArgs& a, hipStream_t s);
+// dense contractions with few outputs (see gemm_few.hip); launch_gemm_nt_i8 has checked the arguments
+bool gemm_few_ok(const GemmArgs& a);
+hipError_t launch_gemm_few(const GemmArgs& a, hipStream_t s);
 
 // ---- weight gradient of 3x3 convolutions from one input window per step (wgrad3.hip) --------------------------------------
 struct ConvGeom {

@@ -63,15 +63,6 @@ __device__ __forceinline__ unsigned long long shfl_xor_u64(unsigned long long v,
     const unsigned lo = (unsigned)__shfl_xor((int)(unsigned)v, d), hi = (unsigned)__shfl_xor((int)(unsigned)(v >> 32), d);
     return ((unsigned long long)hi << 32) | lo;
 }
-// Lanes of one wavefront exchange data through LDS in the epilogues: the hardware executes a wave's LDS
-// instructions in order, but the compiler reasons per thread and, without a fence, may keep a value it loaded
-// earlier instead of re-reading a location another lane has written since.
-__device__ __forceinline__ void wave_lds_fence()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 // Transposing LDS read: each group of 16 lanes reads eight rows of 16 bytes (lanes 2r and 2r + 1 give the halves of row r)
 // and lane j of the group receives byte column j, rows 0 .. 7.
 __device__ __forceinline__ v2i tr_read8(const int8_t* p)
@@ -956,6 +947,7 @@ hipError_t launch_gemm_nt_i8(const GemmArgs& a_in, hipStream_t s)
         while ((1 << sh) < v) ++sh;
         return sh;
     };
+    if (gemm_few_ok(a)) return launch_gemm_few(a, s);
     a.cin_shift = a.conv == 1 ? shift_of(a.Cin) : -1;
     const GemmPlan p = gemm_plan(a.I, a.J, a.R, a.nb, a.splits > 1, a.conv == 2);
     const int bm = p.bm, bn = p.bn;
