@@ -189,8 +189,8 @@ static bool conv3_plan(const GemmArgs& a, Conv3Plan* p)
 // loop against this, forward launches of two passes: 64 -> 64 channels, 8 images of 32x32 (64 tiles) 18.9 and 13.9 us, 64 images
 // 24.5 and 20.4, 256 66 and 37; 64 -> 128, 256 images 100 and 65; 16 -> 64 51 and 31; 48 -> 96, 100 images of 28x28 36 and 26; 64
 // -> 64, 256 images of 16x16 17.2 and 17.3.  Below the line: 64 -> 512, 16 images of 8x8 11.2 and 13.7; 64 -> 64, 200 of 7x7 8.8 and
-// 13.0.  (96 and 128 channels were measured as weights of 64 columns and two windows in the LDS of a whole compute unit, one
-// workgroup each: 128 -> 256 at 32x32 239 and 376 us.  Weights of 32 columns and a single window fit twice up to maps 32 wide: not tried.)
+// 13.0.  (Weights of 96 and 128 channels, 64 columns and two windows, fill the LDS of a
+// compute unit: 128 -> 256 at 32x32 239 us in the implicit loop, 376 that way.  They are streamed instead, see conv3_wide.hip.)
 bool conv3_ok(const GemmArgs& a)
 {
     Conv3Plan p;
