@@ -74,11 +74,11 @@ __global__ __launch_bounds__(CW_T) __attribute__((amdgpu_waves_per_eu(2, 2))) vo
         const int n = (s * CW_T + tid) >> 2;
         off_w[s] = n * (int)a.ldq + 16 * ((tid & 3) ^ ((n >> 2) & 3));
     }
-    auto copy_weights = [&](int tap, int g, int slot) {   // (beyond a row's last channels: the next tap's, against zeros of the window)
-        const int at = tap * a.cin_out + 64 * g;
+    auto copy_weights = [&](int tap, int g, int slot, bool zeros = false) {   // (beyond a row's last channels: the next tap's, against zeros of the window)
+        const uint32_t at = zeros ? (uint32_t)BEYOND : (uint32_t)(tap * a.cin_out + 64 * g);
 #pragma unroll
         for (int s = 0; s < WCH; ++s)
-            copy16(rq, off_w[s] + at, (unsigned)(uintptr_t)(ring + slot * S::WEIGHTS + (s * CW_T + wave * 64) * 16));
+            copy16(rq, (int)((uint32_t)off_w[s] + at), (unsigned)(uintptr_t)(ring + slot * S::WEIGHTS + (s * CW_T + wave * 64) * 16));
     };
 
     int ent[2];   // bytes from the window's start to tap (0, 0) of this lane's pixels
@@ -146,11 +146,18 @@ __global__ __launch_bounds__(CW_T) __attribute__((amdgpu_waves_per_eu(2, 2))) vo
                 // What the next step reads has landed: all but the copies that went out one step ago.
                 if (!(fresh && TAP < 2)) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(WCH + (TAP >= 1 && TAP <= CW ? 1 : 0)) : "memory");
                 lds_barrier();
-                if (TAP == 0 && last) aim(t + slots < tiles ? t + slots : t);   // (after the last tile: its own again, which nothing reads)
+                if (TAP == 0 && last) {
+                    if (t + slots < tiles) {
+                        aim(t + slots);
+                    } else {   // the counted waits want the copies of a next tile all the same: zeros, which cost no memory traffic
+#pragma unroll
+                        for (int s = 0; s < CW; ++s) off[s] = BEYOND;
+                    }
+                }
                 if (TAP == 8 && last && t + slots < tiles) enter(t + slots);
                 fragments(P0, next_, TAP == 8 ? buf ^ 1 : buf, (TAP + 1) % CW_RING);
                 if (TAP < CW) copy_window(TAP, last ? 0 : g + 1, buf ^ 1);
-                copy_weights(AHEAD, TAP + 3 < 9 ? g : (last ? 0 : g + 1), SLOT);
+                copy_weights(AHEAD, TAP + 3 < 9 ? g : (last ? 0 : g + 1), SLOT, TAP + 3 >= 9 && last && t + slots >= tiles);
                 multiply(1);
             };
 #define FFI_TAP(n) step(std::integral_constant<int, n>{}, std::integral_constant<int, (n + 1) % 9>{})
