@@ -27,7 +27,10 @@ template <int WM, int TJ, int CW> struct CwShape {
     static constexpr int WINDOW = CW * CW_T * 16, WEIGHTS = BN * 64;   // bytes of a window, of a step's weights
     static constexpr int EROWS = 8, ESLICE = EROWS * (TJ * 128 + 16);  // staging of a wavefront's stores, in the window that was read last
     static constexpr int LDS = 2 * WINDOW + CW_RING * WEIGHTS;
-    static_assert(LDS <= 80 * 1024 && 4 * ESLICE <= WINDOW && CW <= 8, "LDS");
+    static_assert(LDS <= 80 * 1024 && 4 * ESLICE <= WINDOW, "LDS");
+    // Piece s of the next window goes out in step s, and the wait of a step leaves the copies of the step before it in flight: an eighth piece
+    // might still be on its way when step 8 reads that window.
+    static_assert(CW <= 7, "pieces of a window");
 };
 
 template <int WHAT, int WM, int TJ, int CW>
