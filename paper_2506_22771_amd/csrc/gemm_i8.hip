@@ -447,19 +447,23 @@ __global__ __launch_bounds__(WM* WN * 64) __attribute__((amdgpu_waves_per_eu(BKT
         wait_copies = false;
     }
     if constexpr (RES) {
-        // block outputs: what is added is fetched for 32 rows at a time, ahead of the exchanges
+        // Block outputs: what is added is fetched for 32 rows at a time, ahead of the exchanges; accumulators of a projection beside 64 x 128
+        // a wavefront slice by slice, for lack of registers.  (Ahead they spill 5 to 7 registers: blocks with projections of 136 channels
+        // on 1024 images of 8x8, the step's four forward contractions 195 us, 187 this way; 72 channels 107.5 and 106.5.  All of it slice by slice:
+        // 212 and 114.)
         constexpr int LPR = WTN / 4, RPI = 64 / LPR, NR = EROWS / RPI, NH = 32 / EROWS;
         const int rl = lane / LPR, cc = lane - rl * LPR, col = j0 + wn * WTN + cc * 4;
         auto output = [&](auto codes) {
-            constexpr bool CODES = decltype(codes)::value;
+            constexpr bool CODES = decltype(codes)::value, AHEAD = CODES || TI * TJ < 8;
 #pragma unroll
             for (int ti = 0; ti < TI; ++ti) {
                 const int row0 = i0 + wm * WTM + ti * 32;
                 ResidualSkip<CODES> u[NH][NR];
 #pragma unroll
-                for (int h = 0; h < NH; ++h) residual_load<CODES, LPR, NR>(a.res, z, row0 + h * EROWS, col, col < a.J, u[h]);
+                for (int h = 0; h < (AHEAD ? NH : 0); ++h) residual_load<CODES, LPR, NR>(a.res, z, row0 + h * EROWS, col, col < a.J, u[h]);
 #pragma unroll
                 for (int h = 0; h < NH; ++h) {
+                    if (!AHEAD) residual_load<CODES, LPR, NR>(a.res, z, row0 + h * EROWS, col, col < a.J, u[h]);
                     if (EROWS == 32 || (lr / EROWS) == h) {
 #pragma unroll
                         for (int tj = 0; tj < TJ; ++tj)

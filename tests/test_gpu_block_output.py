@@ -61,6 +61,24 @@ def test_block_output_with_resident_weights(ff, H, W, B, stem, stages, blocks):
     _run_steps(ff, wl, 1, theta_layer=_matched_thetas(wl))
 
 
+@pytest.mark.parametrize("H,W,B,stem,stage,tile", [
+    (15, 14, 313, 72, (72, 1, 1), "256, 128, 4, 1"),      # 210 rows a sample: slices of two, a partial last tile; columns end in the tile
+    (16, 16, 256, 72, (72, 1, 1), "256, 128, 4, 1"),      # whole tiles
+    (31, 33, 250, 24, (72, 2, 1), "256, 128, 4, 1"),      # a projection; 272 rows a sample
+    (15, 14, 160, 136, (136, 1, 1), "128, 256, 2, 2"),
+    (30, 28, 160, 24, (136, 2, 1), "128, 256, 2, 2"),
+    (16, 16, 256, 136, (136, 1, 1), "256, 256, 4, 2"),    # two tiles a workgroup, whose first copies wait for the tile before
+    (31, 33, 250, 24, (136, 2, 1), "256, 256, 4, 2")])
+def test_block_output_of_wide_tiles(ff, H, W, B, stem, stage, tile):
+    """The implicit contraction's tiles with 64 x 128 accumulators a wavefront."""
+    layers = res_stack(stem, [stage], H, W)
+    mangled = "k_gemm_nt_i8I" + "".join(f"Li{v}E" for v in tile.split(", ") + ["4", "1"])
+    names = [n for n, _ in step_kernels(layers, B)]
+    assert sum(mangled in n or f"k_gemm_nt_i8<{tile}, 4, 1" in n for n in names) == 1
+    wl = Workload("res", layers, B, "normal", lam=0.05)
+    _run_steps(ff, wl, 1, theta_layer=_matched_thetas(wl))
+
+
 @pytest.mark.parametrize("H,W,B,head,reader", [
     (7, 7, 38, 0, True),      # 49 rows: several samples in a tile, their sums meet in LDS row by row
     (5, 6, 513, 20, True),    # a dense reader whose last row of tiles lies beyond the tensor, in the pitch of its transposed copy
