@@ -1558,10 +1558,10 @@ static ff_status train_step_impl(const ff_net_desc* net, const ff_net_state* sta
             ra.st_b = B;
             ra.nb = 2;
         }
-        // Implicit contractions form the block output from the accumulators; behind others a launch of its own does, and where samples
-        // have so few rows that most of a wavefront's slices hold several (one atomic per row then: 512 channels on 4x4 maps 87 us
+        // Implicit contractions form the block output from the accumulators; behind others a launch of its own does, and where a
+        // wavefront's rows belong to more than two samples (measured with one atomic per row there: 512 channels on 4x4 maps 87 us
         // against 39 + 10).
-        const bool in_contraction = ra.y && d.implicit && !d.pointwise && d.rps >= 64 && net->launch_mode != FF_LAUNCH_KERNELS;
+        const bool in_contraction = ra.y && d.implicit && !d.pointwise && d.rps >= RESIDUAL_MIN_ROWS && net->launch_mode != FF_LAUNCH_KERNELS;
         // The projection's accumulators are read by whichever launch forms the block output: until then its stream runs beside this one.
         // (At 38 and 237 images with maps of 49 and 16 pixels last, a step takes as long with the wait ahead of every second
         // convolution: 820 and 1780 us.)

@@ -215,21 +215,25 @@ __device__ __forceinline__ void residual_load(const ResidualArgs& a, int z, int 
         }
     }
 }
-// value(r) gives the accumulators, `in` says whether the lane has columns at all.  Stores y and each sample's largest magnitude.  The rows belong to one
-// sample or to two (samples have at least NR RPI rows, RESIDUAL_MIN_ROWS): one atomic for each.  All atomics of a launch meet in a few cache
-// lines, where they take 2 to 4 ns each: with one per row of a slice of two samples, the contraction of 128 channels on 14x14 maps of 38 images
-// (two passes) took 29 us, this way 17.
+// A lane's largest magnitudes of a wavefront's rows, which belong to one sample or to two (samples have RESIDUAL_MIN_ROWS rows at least): of `sample`, and
+// of the one after it, whose rows start at `next`.
+struct ResidualMax {
+    uint32_t m[2], sample;
+    int next;
+};
+__device__ __forceinline__ ResidualMax residual_max_of(const ResidualArgs& a, int row0)
+{
+    const uint32_t rps = (uint32_t)a.rows_per_sample, sample = (uint32_t)row0 / rps;
+    return {{0, 0}, sample, (int)((sample + 1) * rps)};
+}
+// value(r) gives the accumulators, `in` says whether the lane has columns at all.  Stores y and takes its largest magnitudes into x.
 template <bool CODES, int LPR, int NR, typename F>
-__device__ __forceinline__ void residual_rows(const ResidualArgs& a, const ResidualScale& s, int z, int row0, int col, bool in, const ResidualSkip<CODES> (&u)[NR], F value)
+__device__ __forceinline__ void residual_rows(const ResidualArgs& a, const ResidualScale& s, int z, int row0, int col, bool in, const ResidualSkip<CODES> (&u)[NR], ResidualMax& x, F value)
 {
     constexpr int RPI = 64 / LPR;
-    static_assert(NR * RPI <= RESIDUAL_MIN_ROWS, "more than two samples");
-    const int lane = threadIdx.x & 63, rl = lane / LPR;
+    const int rl = (int)(threadIdx.x & 63) / LPR;
     const int M = (int)a.M;
     if (row0 >= M) return;   // (uniform)
-    const uint32_t rps = (uint32_t)a.rows_per_sample, smp = (uint32_t)row0 / rps;
-    const int next = (int)((smp + 1) * rps);   // first row of the sample after it
-    uint32_t m[2] = {0, 0};
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
         const int row = row0 + r * RPI + rl;
@@ -242,15 +246,25 @@ __device__ __forceinline__ void residual_rows(const ResidualArgs& a, const Resid
         const float4 y = residual_value(s, a.relu, c, skip, mr);
         if (in && row < M) *(float4*)(a.y + z * a.st_y + (int64_t)row * a.N + col) = y;
         else mr = 0;
-        m[0] = max(m[0], row < next ? mr : 0u);
-        m[1] = max(m[1], row < next ? 0u : mr);
+        x.m[0] = max(x.m[0], row < x.next ? mr : 0u);
+        x.m[1] = max(x.m[1], row < x.next ? 0u : mr);
     }
-    uint32_t* const ymax = a.ymax_bits + z * a.st_b + smp;
-    m[0] = wave_max_u32(m[0]);
-    if (lane == 0 && m[0]) atomicMax(ymax, m[0]);
-    if (next < min(row0 + NR * RPI, M)) {   // (uniform)
-        m[1] = wave_max_u32(m[1]);
-        if (lane == 0 && m[1]) atomicMax(ymax + 1, m[1]);
+}
+// One atomic per sample for all ROWS rows of a wavefront from row0 on.  All atomics of a launch meet in a few cache lines, where they take 2 to 4 ns
+// each: with one per slice of 8 rows, the forward contractions of a step with a 24-128 projection block on 16 images of 28x28 took
+// 119 us, 85 this way; with one per row of a slice, 128 channels on 14x14 maps of 38 images (two passes) 29 instead of 17.
+template <int ROWS>
+__device__ __forceinline__ void residual_max_store(const ResidualArgs& a, int z, int row0, ResidualMax& x)
+{
+    static_assert(ROWS <= RESIDUAL_MIN_ROWS, "more than two samples");
+    if (row0 >= (int)a.M) return;   // (uniform)
+    uint32_t* const ymax = a.ymax_bits + z * a.st_b + x.sample;
+    const int lane = threadIdx.x & 63;
+    x.m[0] = wave_max_u32(x.m[0]);
+    if (lane == 0 && x.m[0]) atomicMax(ymax, x.m[0]);
+    if (x.next < min(row0 + ROWS, (int)a.M)) {   // (uniform)
+        x.m[1] = wave_max_u32(x.m[1]);
+        if (lane == 0 && x.m[1]) atomicMax(ymax + 1, x.m[1]);
     }
 }
 

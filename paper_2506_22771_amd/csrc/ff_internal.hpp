@@ -225,7 +225,7 @@ struct ResidualArgs {
     int32_t nb;
 };
 hipError_t launch_residual_act(const ResidualArgs& a, hipStream_t s);
-constexpr int RESIDUAL_MIN_ROWS = 32;   // rows of a sample, where a contraction forms the block output (residual_rows)
+constexpr int RESIDUAL_MIN_ROWS = 64;   // rows of a sample, where a contraction forms the block output (residual_max_store)
 
 struct GoodnessFxArgs {
     const float* y;      // [M, N] contiguous

@@ -453,11 +453,13 @@ __global__ __launch_bounds__(WM* WN * 64) __attribute__((amdgpu_waves_per_eu(BKT
         // 212 and 114.)
         constexpr int LPR = WTN / 4, RPI = 64 / LPR, NR = EROWS / RPI, NH = 32 / EROWS;
         const int rl = lane / LPR, cc = lane - rl * LPR, col = j0 + wn * WTN + cc * 4;
+        const int first = i0 + wm * WTM;
+        ResidualMax x = residual_max_of(a.res, first);
         auto output = [&](auto codes) {
             constexpr bool CODES = decltype(codes)::value, AHEAD = CODES || TI * TJ < 8;
 #pragma unroll
             for (int ti = 0; ti < TI; ++ti) {
-                const int row0 = i0 + wm * WTM + ti * 32;
+                const int row0 = first + ti * 32;
                 ResidualSkip<CODES> u[NH][NR];
 #pragma unroll
                 for (int h = 0; h < (AHEAD ? NH : 0); ++h) residual_load<CODES, LPR, NR>(a.res, z, row0 + h * EROWS, col, col < a.J, u[h]);
@@ -477,7 +479,7 @@ __global__ __launch_bounds__(WM* WN * 64) __attribute__((amdgpu_waves_per_eu(BKT
                         wait_vmcnt<0>();
                         wait_copies = false;
                     }
-                    residual_rows<CODES, LPR, NR>(a.res, res_scale, z, row0 + h * EROWS, col, col < a.J, u[h], [&](int r, int c[4]) {
+                    residual_rows<CODES, LPR, NR>(a.res, res_scale, z, row0 + h * EROWS, col, col < a.J, u[h], x, [&](int r, int c[4]) {
                         const v4i v = *(const v4i*)(ebase + (r * RPI + rl) * EROW + cc * 16);
                         c[0] = v[0]; c[1] = v[1]; c[2] = v[2]; c[3] = v[3];
                     });
@@ -487,6 +489,7 @@ __global__ __launch_bounds__(WM* WN * 64) __attribute__((amdgpu_waves_per_eu(BKT
         };
         if (a.res.skip == FF_SKIP_IDENTITY) output(std::true_type{});   // (uniform)
         else output(std::false_type{});
+        residual_max_store<WTM>(a.res, z, first, x);
     } else
 #pragma unroll
     for (int ti = 0; ti < TI; ++ti) {

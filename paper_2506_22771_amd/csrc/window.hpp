@@ -100,6 +100,7 @@ __device__ __forceinline__ void conv3_store(const Conv3Args<WHAT>& a, int z, int
     const bool in = col < a.J;
     if constexpr (WHAT == C3_RESIDUAL) {
         const ResidualScale rs = residual_scale(a.res, z);
+        ResidualMax x = residual_max_of(a.res, r0);
         // What is added to the accumulators is fetched ahead of the exchanges: all of it where registers are left (64 -> 64 channels on 256 images of
         // 32x32, two passes: 67 us with the loads of each slice behind the stores of the one before, 54 this way), else one slice ahead.
         auto output = [&](auto codes) {
@@ -112,7 +113,7 @@ __device__ __forceinline__ void conv3_store(const Conv3Args<WHAT>& a, int z, int
             for (int b = 0; b < 2 * NH; ++b) {
                 if (DEPTH == 2 && b + 1 < 2 * NH) residual_load<CODES, LPR, NR>(a.res, z, r0 + EROWS * (b + 1), col, in, u[(b + 1) % DEPTH]);
                 conv3_exchange<TJ, EROWS>(acc, b / NH, b % NH, slice, [&](auto row) {
-                    residual_rows<CODES, LPR, NR>(a.res, rs, z, r0 + EROWS * b, col, in, u[b % DEPTH], [&](int r, int v[4]) {
+                    residual_rows<CODES, LPR, NR>(a.res, rs, z, r0 + EROWS * b, col, in, u[b % DEPTH], x, [&](int r, int v[4]) {
                         const v4i w = row(r);
                         v[0] = w[0]; v[1] = w[1]; v[2] = w[2]; v[3] = w[3];
                     });
@@ -121,6 +122,7 @@ __device__ __forceinline__ void conv3_store(const Conv3Args<WHAT>& a, int z, int
         };
         if (a.res.skip == FF_SKIP_IDENTITY) output(std::true_type{});   // (uniform)
         else output(std::false_type{});
+        residual_max_store<64>(a.res, z, r0, x);
     } else {
         const bool whole_lines = (a.ldc & 31) == 0;
         int32_t* const C = a.C + z * a.st_c;

@@ -79,6 +79,25 @@ def test_block_output_of_wide_tiles(ff, H, W, B, stem, stage, tile):
     _run_steps(ff, wl, 1, theta_layer=_matched_thetas(wl))
 
 
+@pytest.mark.parametrize("H,W,B,stem,stage", [
+    (8, 8, 9, 324, (324, 1, 1)),        # 64 rows a sample, the fewest; columns end behind four of a block
+    (5, 13, 7, 300, (300, 1, 1)),       # 65 rows: nearly every wavefront has two samples
+    (22, 12, 9, 24, (324, 2, 1)),       # 66 rows, a projection
+    (14, 14, 30, 100, (100, 1, 1)),     # 196 rows, a second group of 36 channels and as many columns
+    (15, 17, 20, 128, (128, 1, 1)),     # 255 rows
+    (28, 28, 86, 24, (192, 2, 1)),      # tiles of 256 x 128, the last of a pass not full, half of the second column block; a projection
+    (14, 14, 86, 192, (192, 1, 1)),
+    (15, 17, 300, 128, (128, 1, 1)),    # two tiles a workgroup, the second in the other pass behind one that is not full
+    (5, 66, 60, 128, (128, 1, 1)),      # a wide map: tiles of 128 x 64, two a workgroup
+    (8, 56, 74, 128, (128, 1, 1))])     # windows of seven copies
+def test_block_output_with_streamed_weights(ff, H, W, B, stem, stage):
+    layers = res_stack(stem, [stage], H, W)
+    names = [n for n, _ in step_kernels(layers, B)]
+    assert sum("k_conv3_wide_i8ILi2E" in n or "k_conv3_wide_i8<2" in n for n in names) == 1   # (the form that makes the block output)
+    wl = Workload("res", layers, B, "normal", lam=0.05)
+    _run_steps(ff, wl, 1, theta_layer=_matched_thetas(wl))
+
+
 @pytest.mark.parametrize("H,W,B,head,reader", [
     (7, 7, 38, 0, True),      # 49 rows: several samples in a tile, their sums meet in LDS row by row
     (5, 6, 513, 20, True),    # a dense reader whose last row of tiles lies beyond the tensor, in the pitch of its transposed copy
