@@ -185,15 +185,19 @@ __global__ __launch_bounds__(CW_T) __attribute__((amdgpu_waves_per_eu(2, 2))) vo
     }
 }
 
+// Workgroups for a column block at once (two for each compute unit in all), and how many tiles of a block each of them goes through at most.
+static int64_t conv3_wide_slots(int ncb) { return max(1, num_cus() / 8 * 2 / ncb) * 8; }
+static int64_t conv3_wide_rounds(int64_t tiles, int ncb) { return (tiles + conv3_wide_slots(ncb) - 1) / conv3_wide_slots(ncb); }
+
 template <int WM, int TJ, int CW>
 static hipError_t launch_conv3_wide_cfg(const GemmArgs& a, const WindowGeom& c, hipStream_t s)
 {
     using S = CwShape<WM, TJ, CW>;
-    const int ncb = (a.J + S::BN - 1) / S::BN, per_xcd = num_cus() / 8 * 2;
+    static_assert(S::BN == 128, "conv3_wide_ok");
+    const int ncb = (a.J + S::BN - 1) / S::BN;
     const int64_t tiles = ((int64_t)a.I + S::BM - 1) / S::BM * a.nb;
     // as many workgroups per column block as give each the same number of tiles
-    const int64_t most = max(1, per_xcd / ncb) * 8, rounds = (tiles + most - 1) / most;
-    const int64_t slots = ((tiles + rounds - 1) / rounds + 7) / 8 * 8;
+    const int64_t rounds = conv3_wide_rounds(tiles, ncb), slots = ((tiles + rounds - 1) / rounds + 7) / 8 * 8;
     const dim3 grid((unsigned)(slots * ncb));
     if (a.residual) hipLaunchKernelGGL((k_conv3_wide_i8<C3_RESIDUAL, WM, TJ, CW>), grid, dim3(CW_T), 0, s, GemmResidualArgs{a, *a.residual}, c, ncb);
     else if (a.gsum) hipLaunchKernelGGL((k_conv3_wide_i8<C3_STORE_GOODNESS, WM, TJ, CW>), grid, dim3(CW_T), 0, s, a, c, ncb);
@@ -212,16 +216,43 @@ static bool conv3_wide_fits(const GemmArgs& a, WindowGeom* c)
            (a.J + 63) / 64 <= num_cus() / 4 && window_geom(a.H, a.W, a.I, 4096, c) && conv3_wide_copies(a, 128) <= 6;
 }
 
-// Forward launches of one pass, the implicit loop against this, us: 128 -> 256 channels, 64 images of 32x32 46.4 and 36.8, 256 images 122 and 104; 128 ->
-// 128, 128 of 32x32 42.4 and 37.1, 512 131 and 112; 256 -> 256, 256 of 32x32 185 and 170; 96 -> 96, 256 of 28x28 56.7 and 51.9; 160 -> 200, 64 of
-// 20x20 36.1 and 26.9; 128 -> 256, 512 of 16x16 58.3 and 55.8; 512 -> 512, 512 of 4x4 30.0 and 27.9; 128 -> 128, 512 of 16x16 32.5 and 32.9; 256 -> 256,
-// 512 of 8x8 28.8 and 29.4, 474 of 7x7 23.7 and 25.3.  Not where a quarter of the groups' channels is padding (72 -> 64, 512 of 32x32 76 and 99), not for
-// up to 64 columns (96 -> 64, 256 of 32x32 42.4 and 47.3), and not beyond 3 x 2^25 outputs, more than the memory-side cache: 128 -> 256, 512 of 32x32
-// (134 M) 241 and 248, in a step 215 and 230.
+// Tiles of 256 x 128, or of 128 x 128 in launches of fewer than one such tile per compute unit and for maps whose windows of 256 pixels do not fit.
+static bool conv3_wide_large(const GemmArgs& a)
+{
+    return conv3_wide_copies(a, 256) <= 7 && ((int64_t)a.I + 255) / 256 * a.nb * ((a.J + 127) / 128) >= num_cus();
+}
+
+// Where this is faster than the implicit loop, whose tiles are finer and which starts 2 us sooner: short launches of few channel groups stay with it, and on
+// small maps, whose windows hold more zeros, the two are close.  ff_layer_forward of one pass, the implicit loop and this, us:
+//  - Channel groups at least three quarters full (72 -> 128, 256 images of 32x32 61 and 67), more than 64 columns (96 -> 64, 256 of 32x32 45 and 52).
+//  - Up to 3 x 2^25 outputs: 128 -> 256, 305 of 32x32 (80 M) 161 and 141, 512 (134 M) 231 and 244, 6103 of 8x8 (100 M) 166 and 170.  (From 256
+//    channels on it stays 2 to 7 % ahead beyond.)
+//  - Maps without windows of 256 pixels up to 5 x 2^22 outputs (128 -> 256 on 24x82, 33 images 99 and 65, 133 images 141 and 157), from three groups
+//    on up to twice that (256 -> 256, 66 images 127 and 122, 133 images 201 and 218).
+//  - Five groups and more everywhere: 320 -> 320, 56 of 3x3 19.2 and 18.2; 512 -> 512, 32 of 28x28 118 and 74.
+//  - Three and four on maps from 16x16 on (192 -> 200, 1 of 20x30 15.1 and 14.3); below from 3 x 2^16 outputs on (256 -> 128, 5 of 10x10 (64 K) 15.5 and 16.0,
+//    192 -> 68, 14 of 14x14 (187 K) 15.3 and 14.3), below 8x8 with more than one tile for every second compute unit (256 -> 128, 1024 of 4x4 17.7 and 17.9, 6272
+//    of 4x4 49.7 and 43.5).
+//  - Two from 2^19 outputs on: 128 -> 128, 2 of 28x28 (201 K) 12.2 and 12.8, 7 (702 K) 15.5 and 14.3; maps below 16x16 from 2^20 on: 96 -> 96, 10 of 14x14
+//    11.4 and 12.4, 128 -> 128, 64 of 14x14 15.2 and 14.7.  Maps from 4x4 to below 14x14 in rounds that are three quarters full, or from the third on, with tiles of
+//    256 x 128 only from 97 channels on: 128 -> 128, 512 of 8x8 15.9 and 15.6, 784 of 8x8 24.2 and 20.7, 128 -> 256, 549 of 6x6 18.0 and 20.2; 96 -> 96, 8192 of 4x4
+//    30.0 and 31.7, 128 -> 128 34.3 and 33.6; 112 -> 320, 867 of 5x5, whose 3 x 170 tiles make two rounds, 23.0 and 32.0; 96 -> 96, 227 of 3x3 10.8 and 13.1.
+//  - Not one large tile per compute unit in one column block: 128 -> 128, 1024 of 8x8 20.4 and 23.2.
 bool conv3_wide_ok(const GemmArgs& a)
 {
     WindowGeom c;
-    return a.Cin > 64 && 4 * a.cin_out >= 192 * ((a.Cin + 63) / 64) && a.J > 64 && (int64_t)a.I * a.J * a.nb <= (int64_t(3) << 25) && conv3_wide_fits(a, &c);
+    const int groups = (a.Cin + 63) / 64, pixels = a.H * a.W;
+    const int64_t outputs = (int64_t)a.I * a.J * a.nb;
+    if (a.Cin <= 64 || 4 * a.cin_out < 192 * groups || a.J <= 64 || outputs > (int64_t(3) << 25) || !conv3_wide_fits(a, &c)) return false;
+    if (conv3_wide_copies(a, 256) > 7 && outputs > (int64_t(5) << (groups == 2 || pixels < 16 ? 22 : 23))) return false;
+    if (groups >= 5) return true;
+    const bool large = conv3_wide_large(a);
+    const int bm = large ? 256 : 128, ncb = (a.J + 127) / 128;
+    const int64_t tiles = ((int64_t)a.I + bm - 1) / bm * a.nb, rounds = conv3_wide_rounds(tiles, ncb);   // of a column block
+    if (large && pixels < 256 && ncb == 1 && tiles <= num_cus()) return false;
+    if (groups > 2) return pixels >= 256 || (pixels < 64 ? 2 * tiles * ncb > num_cus() : outputs >= 3 << 16);
+    if (pixels >= 196) return outputs >= 1 << (pixels < 256 ? 20 : 19);
+    return pixels >= 16 && (rounds > 2 || 4 * tiles >= 3 * rounds * conv3_wide_slots(ncb)) && (!large || a.cin_out > 96);
 }
 
 hipError_t launch_conv3_wide(const GemmArgs& a, hipStream_t s)
@@ -230,9 +261,7 @@ hipError_t launch_conv3_wide(const GemmArgs& a, hipStream_t s)
     if (a.I <= 0 || a.J <= 0) return hipSuccess;
     if (!conv3_wide_fits(a, &c) || (!a.C && !a.residual) || (a.gsum && (a.residual || !a.vmax))) return hipErrorInvalidValue;
     if (a.residual && (a.residual->M != a.I || a.residual->N != a.J || a.residual->rows_per_sample < RESIDUAL_MIN_ROWS)) return hipErrorInvalidValue;
-    const int copies = conv3_wide_copies(a, 256);
-    const int64_t tiles = ((int64_t)a.I + 255) / 256 * a.nb * ((a.J + 127) / 128);
-    if (copies <= 7 && tiles >= num_cus()) return copies <= 6 ? launch_conv3_wide_cfg<4, 4, 6>(a, c, s) : launch_conv3_wide_cfg<4, 4, 7>(a, c, s);
+    if (conv3_wide_large(a)) return conv3_wide_copies(a, 256) <= 6 ? launch_conv3_wide_cfg<4, 4, 6>(a, c, s) : launch_conv3_wide_cfg<4, 4, 7>(a, c, s);
     return conv3_wide_copies(a, 128) <= 4 ? launch_conv3_wide_cfg<2, 2, 4>(a, c, s) : launch_conv3_wide_cfg<2, 2, 6>(a, c, s);
 }
 

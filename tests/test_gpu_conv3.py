@@ -60,19 +60,29 @@ def test_conv_forward_with_resident_weights(ff, B, H, W, Cin, Cout, relu):
     np.testing.assert_array_equal(vmax.cpu().numpy(), gd["vmax"])
 
 
-@pytest.mark.parametrize("B,H,W,Cin,Cout,relu", [
-    (64, 32, 32, 128, 128, 1),    # whole tiles of 256 pixels, one a workgroup
-    (600, 16, 16, 100, 132, 1),   # two tiles a workgroup; a second group of 36 channels, a second column block of four columns
-    (700, 15, 17, 96, 68, 0),     # several tiles a workgroup, the last not full; plain activations
-    (300, 29, 9, 108, 260, 1),    # channels that are no multiple of eight
-    (1100, 8, 8, 128, 512, 1),    # four samples per tile
-    (160, 13, 43, 192, 72, 1),    # a wide map: seven copies a window
-    (20, 5, 70, 128, 80, 1),      # a wider one: 128-pixel tiles of six copies
-    (3, 12, 11, 100, 68, 1),      # small: 128-pixel tiles, the second of a sample nearly empty
-    (40, 4, 4, 512, 192, 1),      # eight samples per tile
-    (2, 7, 7, 65 * 4, 76, 0),     # one tile that is not full
-    (5, 3, 2, 96, 68, 1)])
-def test_conv_forward_with_streamed_weights(ff, B, H, W, Cin, Cout, relu):
+@pytest.mark.parametrize("B,H,W,Cin,Cout,relu,streamed", [
+    (64, 32, 32, 128, 128, 1, True),    # whole tiles of 256 pixels, one a workgroup
+    (600, 16, 16, 100, 132, 1, True),   # two tiles a workgroup; a second group of 36 channels, a second column block of four columns
+    (700, 15, 17, 96, 68, 0, True),     # several tiles a workgroup, the last not full; plain activations
+    (300, 29, 9, 108, 260, 1, True),    # channels that are no multiple of eight
+    (1100, 8, 8, 128, 512, 1, True),    # four samples per tile
+    (160, 13, 43, 192, 72, 1, True),    # a wide map: seven copies a window
+    (20, 5, 70, 128, 80, 1, True),      # a wider one: 128-pixel tiles of six copies
+    (3, 12, 11, 300, 68, 1, True),      # small: 128-pixel tiles, the second of a sample nearly empty
+    (40, 4, 4, 512, 192, 1, True),      # eight samples per tile
+    (2, 7, 7, 65 * 4, 76, 0, True),     # one tile that is not full
+    (5, 3, 2, 288, 68, 1, True),
+    # the limits of the rule: few channels and outputs, small maps, rounds that are not full, windows that do not fit
+    (3, 12, 11, 100, 68, 1, False), (5, 3, 2, 96, 68, 1, False),
+    (9, 18, 16, 128, 200, 0, False), (10, 18, 16, 128, 200, 0, True),
+    (33, 14, 14, 96, 160, 1, False), (35, 14, 14, 96, 160, 1, True),
+    (14, 8, 8, 256, 204, 1, False), (16, 8, 8, 256, 204, 1, True),
+    (330, 7, 7, 192, 128, 1, False), (340, 7, 7, 192, 128, 1, True),
+    (760, 8, 8, 128, 128, 1, False), (770, 8, 8, 128, 128, 1, True),
+    (1030, 9, 12, 96, 128, 1, False), (1030, 9, 12, 100, 128, 1, True),
+    (867, 5, 5, 112, 320, 1, False), (2, 9, 30, 192, 200, 1, True),
+    (159, 5, 80, 128, 328, 1, True), (160, 5, 80, 128, 328, 1, False)])
+def test_conv_forward_with_streamed_weights(ff, B, H, W, Cin, Cout, relu, streamed):
     rng = np.random.default_rng(B * W + Cin)
     layer = Layer("conv", H=H, W=W, C_in=Cin, C_out=Cout, ksize=3, stride=1, pad=1, relu=relu)
     desc = ff.layer_desc(layer, B)
@@ -88,7 +98,7 @@ def test_conv_forward_with_streamed_weights(ff, B, H, W, Cin, Cout, relu):
     def forward():
         ff.ff_layer_forward(desc, d_a, d_w, d_acc, gsum, vmax, ws)
 
-    assert any("k_conv3_wide_i8" in n for n, _ in kernel_nodes(forward))
+    assert any("k_conv3_wide_i8" in n for n, _ in kernel_nodes(forward)) == streamed
     forward()
     torch.cuda.synchronize()
     # float64 sums of products below 2^31 are exact
