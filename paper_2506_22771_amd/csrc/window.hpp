@@ -17,12 +17,6 @@ __device__ __forceinline__ void copy16(__amdgpu_buffer_rsrc_t rsrc, int voffset,
 {
     asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds_base), "v"(voffset), "s"(rsrc) : "memory", "m0");
 }
-__device__ __forceinline__ void wave_fence()   // lanes of a wavefront exchange data through LDS (see gemm_i8.hip)
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 __device__ __forceinline__ void lds_barrier()   // this wavefront's LDS operations are done, and so are the others'
 {
     wait_lds();
@@ -49,7 +43,7 @@ __device__ __forceinline__ int window_source(const WindowGeom& c, int H, int W, 
     return col != 0 && h != 0 ? (int)(((row - b - 1u) * (uint32_t)W + col - 1u) * (uint32_t)cpitch) : BEYOND;
 }
 // [host] positions between tap (0, 0) of the first of n consecutive pixels and the end of tap (2, 2) of the last, at most: every end of a row
-// inside costs two positions, every end of an image a row more
+// inside costs one position, every end of an image W + 1 more; taps reach 2 (W + 1) + 2 positions further (some maps do reach this)
 static inline int64_t window_positions(int64_t H, int64_t W, int64_t n)
 {
     const int64_t wp = W + 1, hw = H * W, rows = (n - 1 + W - 1) / W, images = (n - 1 + hw - 1) / hw;
@@ -88,9 +82,9 @@ __device__ __forceinline__ void conv3_exchange(const v16i (&acc)[2][TJ], int ti,
                 *(v4i*)(slice + (lr % EROWS) * EROW + (tj * 32 + 8 * g + 4 * lh) * 4) =
                     (v4i){acc[ti][tj][4 * g], acc[ti][tj][4 * g + 1], acc[ti][tj][4 * g + 2], acc[ti][tj][4 * g + 3]};
     }
-    wave_fence();
+    wave_lds_fence();
     store([&](int r) { return *(const v4i*)(slice + (r * RPI + lane / LPR) * EROW + 16 * (lane % LPR)); });   // four columns of row r RPI + lane / LPR
-    wave_fence();
+    wave_lds_fence();
 }
 template <int WHAT, int TJ, int EROWS>
 __device__ __forceinline__ void conv3_store(const Conv3Args<WHAT>& a, int z, int r0, int j0, const v16i (&acc)[2][TJ], int8_t* slice)
