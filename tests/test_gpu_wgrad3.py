@@ -60,7 +60,10 @@ def test_conv_weight_gradient_from_windows(ff, B, H, W, Cin, Cout):
     # float64 sums of products below 2^31 are exact
     x = torch.nn.functional.pad(dev(a_q).double(), (0, 0, 1, 1, 1, 1))
     g = dev(gq_ref).double().t().contiguous()
-    ref = torch.stack([g @ x[:, kh:kh + H, kw:kw + W].reshape(M, Cin)
-                       for kh in range(3) for kw in range(3)], dim=1).reshape(Cout, K)
-    got = dw.cpu().numpy()[:, :, :K].astype(np.int64).sum(axis=0)
-    np.testing.assert_array_equal(got, ref.cpu().numpy().astype(np.int64))
+    per = B if n_chunks == 1 else 1 << ((133144 // (H * W)).bit_length() - 1)   # samples of a chunk
+    assert (B + per - 1) // per == n_chunks
+    for c in range(n_chunks):
+        rows = slice(c * per * H * W, min(B, (c + 1) * per) * H * W)
+        ref = torch.stack([g[:, rows].contiguous() @ x[:, kh:kh + H, kw:kw + W].reshape(M, Cin)[rows]
+                           for kh in range(3) for kw in range(3)], dim=1).reshape(Cout, K)
+        np.testing.assert_array_equal(dw[c, :, :K].cpu().numpy(), ref.cpu().numpy().astype(np.int64), err_msg=f"chunk {c}")
