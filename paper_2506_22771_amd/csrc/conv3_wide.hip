@@ -7,10 +7,11 @@
 // first steps, and on across the tiles of a workgroup: a launch waits for memory once, at its beginning.  Two workgroups share a compute unit, so
 // that one's stores run under the other's multiplies.
 //
-// What bounds it: the int32 accumulators, which leave at 5.2 TB/s while hardly anything else happens (two workgroups of a compute unit start
-// together), then the multiplies: a tile of 256 x 128 of 128 channels takes 22 thousand clocks of main loop beside another (18.4 of multiplies), 8 of goodness
-// sums and 16 to 23 of stores.  A wave priority that lets one of the two run ahead changed nothing, stores without the streaming hint were slower (the single
-// operations of 128 -> 256 on 256 images of 16x16 70.8 instead of 69.1 us; 73.6 with the implicit loop).
+// What bounds it: a tile of 256 x 128 of 128 channels takes 22 thousand clocks of main loop beside another (18.4 of multiplies), 8 of goodness sums (a 64-bit
+// multiply-add and a maximum per accumulator) and 16 to 23 of stores (the accumulators leave at 5.2 TB/s). The two workgroups of a compute unit start together and
+// stay in step, so that little of the three overlaps: 128 -> 256 on 256 images of 16x16 takes 33 us, 13 of stores and 11 of multiplies.  A wave priority that
+// lets one of the two run ahead changed nothing, stores without the streaming hint were slower (that layer's single operations 70.8 instead of 69.1 us; 73.6 with
+// the implicit loop).
 //
 // LDS: 16-byte chunks of a position or a weight row are XOR-swizzled by its number / 4, so that sixteen consecutive ones put a chunk into sixteen
 // different bank groups, at any offset.
